@@ -384,3 +384,93 @@ def tolerance(case):
     if case["kind"] == "stack":
         return {"rel": 5e-4, "max": 0.3, "differ": 0.002}
     return {"rel": 1e-5, "max": 2e-3}
+
+
+# the same in 64 bits ---------------------------------------------------------------------------------------------
+
+def _exponent64(x, bits):
+    """The smallest e with max |x| <= (2^(bits-1) - 1) 2^e."""
+    top, qmax, e = float(x.abs().max()), 2 ** (bits - 1) - 1, -64
+    while top > qmax * 2.0 ** e:
+        e += 1
+    return e
+
+
+def _linear64(x, e, bits, zp, wq, scale):
+    """2^e scale[n] sum_k (q - zp) w with Eq.2's codes q of fp16 x."""
+    lo, hi = (0, 2 ** bits - 1) if zp else (-2 ** (bits - 1), 2 ** (bits - 1) - 1)
+    q = (x.double() * 2.0 ** -e).round_().add_(zp).clamp_(lo, hi).sub_(zp)
+    return torch.mm(q, wq.double().t().contiguous()) * (scale.double() * 2.0 ** e)
+
+
+def _exact_groups(g, M, d, F, bits, zp):
+    out = []
+    for K, widths in _groups(d, F):
+        x = _activation(g, M, K, _outliers(K, M))
+        e = _exponent64(x, bits)
+        for N in widths:
+            out.append(_linear64(x, e, bits, zp, *_weight(g, N, K)))
+    return out
+
+
+def _log2_weights(t, qmax, above):
+    """2^(qmax - c) of Eq.3's codes c = clip(round(t)), t = -log2 p; 0 above the diagonal."""
+    w = torch.exp2(qmax - t.round_().clamp_(0, qmax))
+    return w if above is None else w.masked_fill_(above, 0.0)
+
+
+def _exact_attn_probs(g, case):
+    H, S, D, qmax = case["H"], case["S"], case["D"], case["qmax"]
+    above = torch.ones(S, S, dtype=torch.bool, device=DEVICE).triu_(1) if case["causal"] else None
+    weights, score = [], torch.zeros(S, dtype=torch.float64, device=DEVICE)
+    for h in range(H):
+        q, k = torch.randn(S, D, generator=g, device=DEVICE), torch.randn(S, D, generator=g, device=DEVICE)
+        logits = torch.mm(q, k.t().contiguous()) / math.sqrt(D)
+        logits[:, 0] += 4.0 + 2.0 * torch.randn(S, generator=g, device=DEVICE)
+        if above is not None:
+            logits.masked_fill_(above, float("-inf"))
+        p = torch.softmax(logits, dim=1).to(torch.float16)
+        score += p[:, 0].double() * 2.0 ** 24
+        weights.append(_log2_weights(-torch.log2(p.double()), qmax, above).half())     # powers of two: exact
+    v = torch.randn(H * S, D, generator=g, device=DEVICE).to(torch.float16)
+    e_v = _exponent64(v, 8)
+    vq = (v.double() * 2.0 ** -e_v).round_().clamp_(-128, 127).view(H, S, D)
+    o = torch.cat([torch.mm(w.double(), vq[h]) for h, w in enumerate(weights)], dim=1) * 2.0 ** (e_v - qmax)
+    d, F = H * D, case["F"]
+    o16 = o.to(torch.float16)                          # the entry points hand fp16 tensors on
+    w_o, s_o = _weight(g, d, d)
+    e_o = _exponent64(o16, 8)
+    all_o = _linear64(o16, e_o, 8, 0, w_o, s_o).to(torch.float16)
+    idx = torch.sort(torch.sort(score, descending=True, stable=True)[1][:case["keep"]])[0]
+    y_o = _linear64(o16[idx], e_o, 8, 0, w_o, s_o)
+    y_f = _linear64(y_o.to(torch.float16), _exponent64(all_o, 8), 8, 0, *_weight(g, F, d))
+    return dict(o=o, score=None, idx=None, y_o=y_o, y_f=y_f)
+
+
+def _exact_attn_qk(g, case):
+    state, H, S, D, qmax = _prepare_attn_qk(g, case), case["H"], case["S"], case["D"], case["qmax"]
+    above = torch.ones(S, S, dtype=torch.bool, device=DEVICE).triu_(1) if case["causal"] else None
+    parts = []
+    for h in range(H):
+        logits = torch.mm(state["q"][h].double(), state["k"][h].double().t().contiguous()) * (2.0 ** -10 / math.sqrt(D))
+        if above is not None:
+            logits.masked_fill_(above, float("-inf"))
+        t = torch.log_softmax(logits, dim=1) / -math.log(2.0)
+        parts.append(torch.mm(_log2_weights(t, qmax, above), state["v"][h].double()))
+    return dict(o=torch.cat(parts, dim=1) * 2.0 ** (-5 - qmax), score=None)
+
+
+def exact(case, seed):
+    """run()'s floating outputs in 64 bits.  None where the way there has no such value: factors that a search picks, and
+    blocks, in which a rounding to fp16 decides codes and the tokens that are kept."""
+    g, kind = _generator(seed), case["kind"]
+    if kind == "linear":
+        x = _activation(g, case["M"], case["K"], _outliers(case["K"], case["M"]))
+        return _linear64(x, _exponent64(x, case["bits"]), case["bits"], case["zp"], *_weight(g, case["N"], case["K"]))
+    if kind == "decode":
+        return [y for _ in range(case["layers"]) for y in _exact_groups(g, case["M"], case["d"], case["F"], case["bits"], 0)]
+    if kind == "layer":
+        return None if case["trip"] else _exact_groups(g, case["M"], case["d"], case["F"], case["bits"], case["zp"])
+    if kind == "attn_probs":
+        return _exact_attn_probs(g, case)
+    return _exact_attn_qk(g, case) if kind == "attn_qk" else None
