@@ -108,6 +108,15 @@ __device__ __forceinline__ __half agq_dequant(int acc, float g) {
     return __float2half_rn((float)acc * g);
 }
 
+// The same for two accumulators (already as float): both products rounded to fp16 once (the compiler turns the single
+// form above into this instruction too), in the two halves of a word.
+__device__ __forceinline__ uint32_t agq_dequant2(float acc0, float g0, float acc1, float g1) {
+    uint32_t d;
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(d) : "v"(acc0), "v"(g0));
+    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(d) : "v"(acc1), "v"(g1));
+    return d;
+}
+
 // Direct global-to-LDS copy: lane i's 16 bytes land at lds_chunk + 16 i (the LDS
 // address is wave-uniform and travels in M0).  Issued as inline assembly on
 // purpose: the compiler, seeing such a copy, drains every outstanding load

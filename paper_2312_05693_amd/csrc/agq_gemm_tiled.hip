@@ -24,7 +24,7 @@
 //     of a 32-row MFMA: low nibbles feed k-block t, high nibbles k-block t + 2.
 //   No load in the main loop returns to registers, so the only waits on vector
 //   memory are the ones written here: loads return in order, every step issues
-//   four per wavefront, and a step waits until at most the four of the step two
+//   as many per wavefront, and a step waits until at most those of the step two
 //   ahead are still in flight (copies start three steps ahead; the fragments of the
 //   step being multiplied are already in registers, so three stages suffice).
 //
@@ -36,6 +36,8 @@
 #include "agq_device.h"
 #include "agq_internal.h"
 
+#include <type_traits>
+
 typedef unsigned int agq_u4 __attribute__((ext_vector_type(4)));
 typedef int agq_v16i __attribute__((ext_vector_type(16)));
 
@@ -44,12 +46,8 @@ namespace {
 constexpr int BM = 128, BN = 128, BK = 128;
 constexpr int kThreads = 256;
 constexpr int kBand = 4;                  // token tiles per band of the tile walk
-constexpr int kAChunks = (BM / 32) * 4;   // 16 chunks of 1 KiB per stage
 constexpr int kBChunks = BN / 16;         // 8 chunks of 1 KiB per stage
-constexpr int kABytes = kAChunks * 1024;
-constexpr int kStageBytes = (kAChunks + kBChunks) * 1024;   // 24 KiB
 constexpr int kStages = 3;
-constexpr int kCopies = (kAChunks + kBChunks) * 64 / kThreads;   // 6 copies per wavefront and step
 constexpr int kOutStride = 144;           // bytes per row of a wavefront's 64 x 64 fp16 output tile in LDS
 
 constexpr int kMaxProj = 4;   // == AGQ_MAX_PROJ of the public header
@@ -57,19 +55,20 @@ constexpr int kMaxProj = 4;   // == AGQ_MAX_PROJ of the public header
 // Up to four projections of the same activation share a launch (q/k/v, gate/up): one
 // grid covers the tiles of all of them, which fills the chip where a single projection
 // has too few tiles and saves the gaps between launches.
+struct TiledProj {
+    const agq_u4 *blob;
+    const __half *sw;
+    __half *y;
+    int32_t *acc;
+    const int32_t *wsum;    // per-channel weight sums (end of every blob)
+    int64_t ldy;
+    int N, tiles_n, start;  // start: first tile of the projection
+};
 struct TiledArgs {
+    TiledProj proj[kMaxProj];   // projections past the last one repeat it, with no tile left for them
     const agq_u4 *xt;    // activation codes in operand order (pre-pass output)
     int M, K, KT;
     int tiles_m;
-    int tile_start[kMaxProj + 1];   // first workgroup of every projection; [count..] = the grid size
-    int N4[kMaxProj];
-    int tiles_n4[kMaxProj];
-    const agq_u4 *blob4[kMaxProj];
-    const __half *sw4[kMaxProj];
-    __half *y4[kMaxProj];
-    int64_t ldy4[kMaxProj];
-    int32_t *acc4[kMaxProj];
-    const int32_t *wsum4[kMaxProj];   // per-channel weight sums (end of every blob)
     float scale_e;
     int corr;               // unsigned activation grid: acc += corr * wsum[n]; 0 on the signed grid
     // TRIP blob: the first n_extra steps are the extra chunks of the channels with a factor;
@@ -82,6 +81,31 @@ struct TiledArgs {
     int32_t *part;       // [tile][split][16][256 threads][4]
 };
 
+// The projection a workgroup serves is read from the argument record where it lies, in constant memory: an index
+// into the by-value parameter would copy all of it to memory, and selects over its four entries took the kernel
+// 160 spilled scalar registers and several hundred instructions before its first copy.
+typedef const __attribute__((address_space(4))) TiledArgs TiledArgsC;
+typedef const __attribute__((address_space(4))) TiledProj TiledProjC;
+__device__ __forceinline__ TiledProjC *tiled_proj(const TiledArgs &a, int tile) {
+    const int pj = (tile >= a.proj[1].start) + (tile >= a.proj[2].start) + (tile >= a.proj[3].start);
+    return ((TiledArgsC *)__builtin_amdgcn_kernarg_segment_ptr())->proj + pj;
+}
+
+template <int N>
+struct Int {
+    static constexpr int value = N;
+};
+
+// Global-to-LDS copy with a scalar base address: lane l's 16 bytes at sbase + voff(l) + G go to lds_addr + L + G + 16 l
+// (see lds_dma16 in agq_device.h for why this is inline assembly).
+template <int L, int G>
+__device__ __forceinline__ void lds_dma16_s(uint32_t voff, const void *sbase, uint32_t lds_addr) {
+    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%4"
+                 :
+                 : "v"(voff), "s"(sbase), "s"(lds_addr), "n"(L), "n"(G)
+                 : "memory", "m0", "scc");
+}
+
 // TRIP: the blob and the activation stages carry extra steps in front, ordered by
 // descending factor; after the last step of a factor the accumulators are shifted
 // left by the difference to the next factor (Horner), so that at the end every
@@ -92,9 +116,7 @@ struct TiledArgs {
 // split_reduce_kernel, launched behind it, adds the partial tiles up and runs the epilogue.  (One
 // kernel in which the last workgroup to arrive at a tile adds the others' partial tiles was measured
 // slower than no split at all: it has to read them in dependent rounds through device-scope loads,
-// or with cache-wide write-backs and invalidations around them.  A lone workgroup on a CU is not
-// short of copies in flight either: six stages instead of three changed nothing, its sixteen
-// MFMAs per wavefront and step, about 60 cycles apart in this loop, are the step time.)  An int32 sum does not depend on
+// or with cache-wide write-backs and invalidations around them.)  An int32 sum does not depend on
 // its order, so the result is the unsplit kernel's bit for bit.
 //
 // NI: 32-token MFMA tiles per wavefront.  2: the 128-token workgroup tile described above.  1: a 64-token
@@ -105,13 +127,11 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
     static_assert(NI == 2 || (NI == 1 && !SPLIT), "the partial tiles of a K split are laid out for 128 tokens");
     constexpr int BMT = NI * 64;                 // tokens per workgroup tile
     constexpr int kAChunksT = NI * 8;            // activation chunks of 1 KiB per stage
-    constexpr int kABytesT = kAChunksT * 1024;
-    constexpr int kStageT = kABytesT + kBChunks * 1024;      // 24 KiB (16 KiB for NI == 1)
+    constexpr int kStageT = (kAChunksT + kBChunks) * 1024;   // 24 KiB (16 KiB for NI == 1)
     constexpr int kNA = NI * 2;                  // activation copies per wavefront and step
     constexpr int kCopiesT = kNA + 2;
     // Three pipeline stages; the epilogue reuses the first 36 KiB.
     __shared__ __align__(16) unsigned char lds[kStages * kStageT];
-    unsigned char *const stage0 = lds, *const stage1 = lds + kStageT, *const stage2 = lds + 2 * kStageT;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -128,19 +148,15 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
     const int split = SPLIT ? bid / a.tiles_all : 0;
     if (SPLIT) bid -= split * a.tiles_all;
     const int tile_id = bid;
-    // which projection this workgroup serves: scalar compares and selects (an index into the
-    // argument record would move it to memory)
-    const int pj = (bid >= a.tile_start[1]) + (bid >= a.tile_start[2]) + (bid >= a.tile_start[3]);
-    auto pick = [pj](auto v0, auto v1, auto v2, auto v3) { return pj == 0 ? v0 : (pj == 1 ? v1 : (pj == 2 ? v2 : v3)); };
-    bid -= pick(0, a.tile_start[1], a.tile_start[2], a.tile_start[3]);
-    const int pN = pick(a.N4[0], a.N4[1], a.N4[2], a.N4[3]);
-    const int ptiles_n = pick(a.tiles_n4[0], a.tiles_n4[1], a.tiles_n4[2], a.tiles_n4[3]);
-    const agq_u4 *const pblob = pick(a.blob4[0], a.blob4[1], a.blob4[2], a.blob4[3]);
-    const __half *const psw = pick(a.sw4[0], a.sw4[1], a.sw4[2], a.sw4[3]);
-    __half *const py = pick(a.y4[0], a.y4[1], a.y4[2], a.y4[3]);
-    const int64_t pldy = pick(a.ldy4[0], a.ldy4[1], a.ldy4[2], a.ldy4[3]);
-    int32_t *const pacc = pick(a.acc4[0], a.acc4[1], a.acc4[2], a.acc4[3]);
-    const int32_t *const pwsum = pick(a.wsum4[0], a.wsum4[1], a.wsum4[2], a.wsum4[3]);
+    TiledProjC *const pr = tiled_proj(a, bid);
+    bid -= pr->start;
+    const int pN = pr->N, ptiles_n = pr->tiles_n;
+    const agq_u4 *const pblob = pr->blob;
+    const __half *const psw = pr->sw;
+    __half *const py = pr->y;
+    const int64_t pldy = pr->ldy;
+    int32_t *const pacc = pr->acc;
+    const int32_t *const pwsum = pr->wsum;
     const int band = bid / (kBand * ptiles_n);
     const int rows = min(kBand, a.tiles_m - band * kBand);
     const int within = bid - band * kBand * ptiles_n;
@@ -158,28 +174,47 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
     // (2 t + (l >> 5)) * 16 + (l & 15).
     // (NI == 1: the 64-token tile tm is half tm & 1 of the 128-token tile tm >> 1 of the pre-pass: eight
     // consecutive chunks of every stage, two per wavefront)
-    const agq_u4 *asrc = a.xt + (((int64_t)(NI == 2 ? tm : tm >> 1) * KTfull + kbeg) * 16 + (NI == 2 ? 0 : (tm & 1) * 8) + wave * kNA) * 64 + lane;
-    const agq_u4 *bsrc[2];
+    const uint32_t wave_u = __builtin_amdgcn_readfirstlane((uint32_t)wave);
+    const int atile = NI == 2 ? tm : tm >> 1, achunk = (NI == 2 ? 0 : (tm & 1) * 8) + (int)wave_u * kNA;
+    const char *abase = reinterpret_cast<const char *>(a.xt) + (((int64_t)atile * KTfull + kbeg) * 16 + achunk) * 1024;
+    const char *bbase = reinterpret_cast<const char *>(pblob) + ((int64_t)(n0 / 16) * KTfull + kbeg) * 1024;
+    const uint32_t avoff = (uint32_t)lane * 16;
+    uint32_t bvoff[2];
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
         const int c = wave * 2 + p, grp = c >> 2, j = (c >> 1) & 1, t = c & 1;
-        const int chunk_row = n0 / 16 + grp * 4 + j * 2 + ((lane & 31) >> 4);
-        bsrc[p] = pblob + ((int64_t)chunk_row * KTfull + kbeg) * 64 + (2 * t + (lane >> 5)) * 16 + (lane & 15);
+        const int chunk_row = grp * 4 + j * 2 + ((lane & 31) >> 4);
+        bvoff[p] = (uint32_t)chunk_row * (uint32_t)KTfull * 1024u + (uint32_t)((2 * t + (lane >> 5)) * 16 + (lane & 15)) * 16u;
     }
     // LDS byte address (wave-uniform, kept in a scalar register) of this
     // wavefront's first activation chunk in stage 0
     const uint32_t lds_base = __builtin_amdgcn_readfirstlane(
         (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char *)lds);
-    const uint32_t wave_u = __builtin_amdgcn_readfirstlane((uint32_t)wave);
-    auto copy_piece = [&](int p, int kt, unsigned char *st) {
-        if (kt >= KT) return;               // nothing to fetch past the last step (uniform)
-        const int k = kt;
-        const uint32_t dst = lds_base + (uint32_t)(st - lds);
-        if (p < kNA)
-            lds_dma16(asrc + ((int64_t)k * 16 + p) * 64, dst + (wave_u * kNA + p) * 1024);
-        else
-            lds_dma16(bsrc[p - kNA] + (int64_t)k * 64, dst + kABytesT + (wave_u * 2 + (p - kNA)) * 1024);
+    const uint32_t lds_a = lds_base + wave_u * (kNA * 1024), lds_b = lds_base + kAChunksT * 1024 + wave_u * 2048;
+    // copy p of a step into the stage that starts `st` bytes into lds, from the step's source addresses (the
+    // activation pieces of a wavefront are contiguous on both sides: one base, the piece in the offset)
+    auto copy_piece = [&](auto p_tag, uint32_t st, const char *ap, const char *bp) {
+        constexpr int p = decltype(p_tag)::value;
+        if constexpr (p < kNA) lds_dma16_s<0, p * 1024>(avoff, ap, lds_a + st);
+        else lds_dma16_s<(p - kNA) * 1024, 0>(bvoff[p - kNA], bp, lds_b + st);
     };
+    auto copy_a = [&](uint32_t st, const char *ap) {
+        copy_piece(Int<0>{}, st, ap, nullptr);
+        copy_piece(Int<1>{}, st, ap, nullptr);
+        if constexpr (kNA == 4) {
+            copy_piece(Int<2>{}, st, ap, nullptr);
+            copy_piece(Int<3>{}, st, ap, nullptr);
+        }
+    };
+    auto copy_b = [&](uint32_t st, const char *bp) {
+        copy_piece(Int<kNA>{}, st, nullptr, bp);
+        copy_piece(Int<kNA + 1>{}, st, nullptr, bp);
+    };
+    // The first three steps.  (A tile of fewer copies its last step again, into stages nobody reads.)
+    const int k1 = min(1, KT - 1), k2 = min(2, KT - 1);
+    copy_a(0, abase);
+    copy_a(kStageT, abase + k1 * 16384);
+    copy_a(2 * kStageT, abase + k2 * 16384);
 
     // per-channel scales of this lane's output columns, fetched early
     // (accumulator register 4 q + r of tile j: channel 32 j + 8 q + 4 (lane >> 5) + r)
@@ -209,44 +244,73 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
 
-    // Fragments of a whole step live in registers: eight activation fragments
+    // Fragments of a whole step live in registers: NI * 4 activation fragments
     // (index i * 4 + t: 32-token tile i, k-block t) and four packed weight pieces.
     // Two such sets alternate: while one is multiplied, the other is filled from
     // the next step's LDS stage, so no MFMA ever waits for an LDS read it issued
     // a few instructions earlier.
     agq_u4 xa0[NI * 4], b0[4], xa1[NI * 4], b1[4];
 
-    // One K step, software-pipelined by hand.  A wavefront issues in order and an
-    // MFMA blocks the next MFMA while the matrix core is busy, but LDS reads,
-    // copies and bit operations slip in between: every pair of MFMAs is followed
-    // by LDS reads for the next step (twelve per step), and the six copies of the
-    // step three ahead are spread over the step.
-    auto step = [&](int kt, const unsigned char *nxt, unsigned char *fill, const agq_u4 (&xc)[NI * 4], const agq_u4 (&bc)[4],
-                    agq_u4 (&xn)[NI * 4], agq_u4 (&bn)[4]) {
-        const agq_u4 *sn = reinterpret_cast<const agq_u4 *>(nxt) + lane;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            agq_v4i wb[2];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const agq_u4 p = bc[j * 2 + (t & 1)];
-                const agq_u4 w = t < 2 ? ((p << 4) & 0xF0F0F0F0u) : (p & 0xF0F0F0F0u);
-                wb[j] = __builtin_bit_cast(agq_v4i, w);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < NI; ++i) {
-                const agq_v4i x = __builtin_bit_cast(agq_v4i, xc[i * 4 + t]);
-                acc[i][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wb[0], x, acc[i][0], 0, 0, 0);
-                acc[i][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wb[1], x, acc[i][1], 0, 0, 0);
+    // One K step, software-pipelined by hand.  A wavefront issues in order, one
+    // instruction every four cycles, and an MFMA waits at issue until the matrix
+    // core is done with the one before it: what follows an MFMA is hidden by it up to
+    // about seven instructions, and anything beyond that leaves the matrix core
+    // idle.  So the other work of a step is dealt out one MFMA at a time: after each of
+    // the 8 NI MFMAs at most one LDS read for the next step, one copy of the step
+    // three ahead, and 4 / NI words of the weights of the next k-block widened (the first
+    // k-block of the next step included, so that a step starts with an MFMA).  Nothing
+    // in the steady loop branches (a branch around each copy costs more than the copies).
+    // Measured against the same work in bunches behind every second MFMA (1024 tokens, one
+    // workgroup per CU): 0.58 -> 0.48 us per step.  What is left is not latency: six stages instead of
+    // three change nothing, while the loop without its copies takes 0.36 us and with its MFMAs alone
+    // 0.31 us, at 1.6-1.75 GHz: under this load the chip runs at its power limit, so every byte moved costs time.
+    const char *anext = abase + 3 * 16384, *bnext = bbase + 3 * 1024;   // sources of the step three ahead
+    uint32_t rd = kStageT, fill = 0;                     // stage read from (next step), stage refilled
+    constexpr int kSlots = 8 * NI;                       // MFMAs of a step
+    constexpr int kReads = 4 * NI + 4;
+    const agq_u4 *const rda = reinterpret_cast<const agq_u4 *>(lds) + lane + wm * (NI * 4 * 64);
+    const agq_u4 *const rdb = reinterpret_cast<const agq_u4 *>(lds) + lane + (kAChunksT + wn * 4) * 64;
+    agq_v4i wb[2][2];                                    // widened weights of this k-block and the next
+    auto widen1 = [&](const agq_u4 (&bc)[4], int t, int d) {   // dword d (0..7) of k-block t
+        const uint32_t p = bc[(d >> 2) * 2 + (t & 1)][d & 3];
+        wb[t & 1][d >> 2][d & 3] = (int)(t < 2 ? ((p << 4) & 0xF0F0F0F0u) : (p & 0xF0F0F0F0u));
+    };
+    auto step = [&](auto copy_tag, auto next_tag, const agq_u4 (&xc)[NI * 4], const agq_u4 (&bc)[4], agq_u4 (&xn)[NI * 4], agq_u4 (&bn)[4]) {
+        constexpr bool COPY = decltype(copy_tag)::value, NEXT = decltype(next_tag)::value;
+        const agq_u4 *const sa = rda + rd / 16, *const sb = rdb + rd / 16;
+        auto slot = [&](auto slot_tag) {
+            constexpr int sl = decltype(slot_tag)::value, t = sl / (2 * NI), i = (sl - t * 2 * NI) / 2, j = sl & 1;
+            if constexpr (sl < kSlots) {
+                acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wb[t & 1][j], __builtin_bit_cast(agq_v4i, xc[i * 4 + t]), acc[i][j], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
-                const int mi = wm * NI + i;   // 32-token tile of the stage
-                xn[i * 4 + t] = sn[(mi * 4 + t) * 64];
-                if (i == NI - 1) bn[t] = sn[(kAChunksT + wn * 4 + t) * 64];
-                if (NI * t + i < kCopiesT) copy_piece(NI * t + i, kt + 3, fill);
+                if constexpr (NEXT && sl < kReads) {     // b0 b2 x.0 b1 b3 x.1 x.2 x.3
+                    constexpr int h = sl / (NI + 2), q = sl - h * (NI + 2);
+                    if constexpr (h < 2 && q < 2) bn[q * 2 + h] = sb[(q * 2 + h) * 64];
+                    else {
+                        constexpr int m = h < 2 ? h * NI + q - 2 : sl - 4;
+                        xn[(m % NI) * 4 + m / NI] = sa[((m % NI) * 4 + m / NI) * 64];
+                    }
+                }
+                constexpr int cs = NI == 2 ? sl - 3 : sl - 1;
+                if constexpr (COPY && cs >= 0 && (cs & 1) == 0 && cs / 2 < kCopiesT) copy_piece(Int<cs / 2>{}, fill, anext, bnext);
+                constexpr int wd = 4 / NI;               // dwords widened per slot
+                constexpr int w0 = (sl - t * 2 * NI) * wd;
+#pragma unroll
+                for (int d = w0; d < w0 + wd; ++d) {
+                    if constexpr (t < 3) widen1(bc, t + 1, d);
+                    else if constexpr (NEXT) widen1(bn, 0, d);
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
+        };
+        slot(Int<0>{}); slot(Int<1>{}); slot(Int<2>{}); slot(Int<3>{}); slot(Int<4>{}); slot(Int<5>{}); slot(Int<6>{}); slot(Int<7>{});
+        slot(Int<8>{}); slot(Int<9>{}); slot(Int<10>{}); slot(Int<11>{}); slot(Int<12>{}); slot(Int<13>{}); slot(Int<14>{}); slot(Int<15>{});
+        if (COPY) {
+            anext += 16384;
+            bnext += 1024;
+            fill = fill == 2 * kStageT ? 0 : fill + kStageT;
         }
+        rd = rd == 2 * kStageT ? 0 : rd + kStageT;
     };
 
     auto shift_acc = [&](int sh) {          // uniform
@@ -259,22 +323,17 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
                 for (int r = 0; r < 16; ++r) acc[i][j][r] <<= sh;
     };
 
-#pragma unroll
-    for (int p = 0; p < kCopiesT; ++p) copy_piece(p, 0, stage0);
-#pragma unroll
-    for (int p = 0; p < kCopiesT; ++p) copy_piece(p, 1, stage1);
-#pragma unroll
-    for (int p = 0; p < kCopiesT; ++p) copy_piece(p, 2, stage2);
-    static_assert(kCopiesT == 6 || kCopiesT == 4, "the vmcnt immediates below count the copies of one and two steps");
-    if (KT < 3)
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    else if (kCopiesT == 6)
-        asm volatile("s_waitcnt vmcnt(12)" ::: "memory");   // step 0 has landed
-    else
-        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-    __syncthreads();
+    copy_b(0, bbase);
+    copy_b(kStageT, bbase + k1 * 1024);
+    copy_b(2 * kStageT, bbase + k2 * 1024);
+    // vmcnt(n) lgkmcnt(0): bits 3:0 and 15:14 = vmcnt, 6:4 = 7 (no wait), 11:8 = lgkmcnt
+#define AGQ_WAIT(VM) __builtin_amdgcn_s_waitcnt(((VM) & 15) | (((VM) >> 4) << 14) | 0x70)
+    AGQ_WAIT(2);        // steps 0 and 1 have landed (the weights of step 2 are the last two copies)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
     {
-        const agq_u4 *s0 = reinterpret_cast<const agq_u4 *>(stage0) + lane;
+        const agq_u4 *s0 = reinterpret_cast<const agq_u4 *>(lds) + lane;
 #pragma unroll
         for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -282,32 +341,62 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
 #pragma unroll
         for (int j = 0; j < 4; ++j) b0[j] = s0[(kAChunksT + wn * 4 + j) * 64];
     }
-    // Every step kt: wait until this wavefront's copies of step kt+1 have landed
-    // (loads return in order, each step issues kCopiesT, so only those of step
-    // kt+2, if there is one, may still fly), meet the others (everybody's copies of step kt+1 are
-    // in LDS, and everybody has read step kt's fragments out of the stage that is
-    // refilled next), then multiply step kt while copying step kt+3.
-#define AGQ_STEP(KT_, NXT, FILL, XC, BC, XN, BN)                             \
-    if ((KT_) < KT) {                                                        \
-        if ((KT_) + 2 >= KT)                                                 \
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 \
-        else if (kCopiesT == 6)                                              \
-            asm volatile("s_waitcnt vmcnt(6)" ::: "memory");                 \
-        else                                                                 \
-            asm volatile("s_waitcnt vmcnt(4)" ::: "memory");                 \
-        __syncthreads();                                                     \
-        step((KT_), NXT, FILL, XC, BC, XN, BN);                              \
-        if (TRIP && split == 0 && (KT_) < a.n_extra) shift_acc(a.trip_shift[(KT_)]); \
+    // Between two steps: this wavefront's copies of the next step have landed (at most VM newer ones may fly: loads
+    // return in order) and its reads of the stage that is refilled next have returned; then meet the others.  (Not
+    // __syncthreads(), in front of which the compiler may wait for more.)
+#define AGQ_MEET(VM)                              \
+    asm volatile("" ::: "memory");                \
+    __builtin_amdgcn_sched_barrier(0);            \
+    AGQ_WAIT(VM);                                 \
+    __builtin_amdgcn_s_barrier();                 \
+    asm volatile("" ::: "memory");                \
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int d = 0; d < 8; ++d) widen1(b0, 0, d);
+#define AGQ_SHIFT(KT_) if (TRIP && split == 0 && (KT_) < a.n_extra) shift_acc(a.trip_shift[KT_]);
+    // stages rotate through three, the register sets through two; the copies of the step two ahead stay in flight
+    int kt = 0;
+    for (; kt + 4 < KT; kt += 2) {
+        AGQ_MEET(kCopiesT)
+        step(std::true_type{}, std::true_type{}, xa0, b0, xa1, b1);
+        AGQ_SHIFT(kt)
+        AGQ_MEET(kCopiesT)
+        step(std::true_type{}, std::true_type{}, xa1, b1, xa0, b0);
+        AGQ_SHIFT(kt + 1)
     }
-    for (int kt = 0; kt < KT; kt += 6) {      // stage of step kt is kt % 3, register set kt % 2
-        AGQ_STEP(kt, stage1, stage0, xa0, b0, xa1, b1)
-        AGQ_STEP(kt + 1, stage2, stage1, xa1, b1, xa0, b0)
-        AGQ_STEP(kt + 2, stage0, stage2, xa0, b0, xa1, b1)
-        AGQ_STEP(kt + 3, stage1, stage0, xa1, b1, xa0, b0)
-        AGQ_STEP(kt + 4, stage2, stage1, xa0, b0, xa1, b1)
-        AGQ_STEP(kt + 5, stage0, stage2, xa1, b1, xa0, b0)
+    if (kt + 3 < KT) {                                   // four steps are left, or up to three
+        AGQ_MEET(kCopiesT)
+        step(std::true_type{}, std::true_type{}, xa0, b0, xa1, b1);
+        AGQ_SHIFT(kt)
+        ++kt;
+#pragma unroll
+        for (int i = 0; i < NI * 4; ++i) xa0[i] = xa1[i];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b0[i] = b1[i];
     }
-#undef AGQ_STEP
+    if (kt + 1 < KT) {
+        AGQ_MEET(kCopiesT)
+        step(std::false_type{}, std::true_type{}, xa0, b0, xa1, b1);
+        AGQ_SHIFT(kt)
+        ++kt;
+        if (kt + 1 < KT) {
+            AGQ_MEET(0)
+            step(std::false_type{}, std::true_type{}, xa1, b1, xa0, b0);
+            AGQ_SHIFT(kt)
+            ++kt;
+        } else {
+#pragma unroll
+            for (int i = 0; i < NI * 4; ++i) xa0[i] = xa1[i];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) b0[i] = b1[i];
+        }
+    }
+    AGQ_MEET(0)
+    step(std::false_type{}, std::false_type{}, xa0, b0, xa1, b1);
+    AGQ_SHIFT(kt)
+#undef AGQ_SHIFT
+#undef AGQ_MEET
+#undef AGQ_WAIT
     __syncthreads();                                   // every wavefront is done with the stages
 
     if (SPLIT) {
@@ -315,7 +404,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
         int4 *const mine = reinterpret_cast<int4 *>(a.part) + ((int64_t)tile_id * a.splits + split) * (16 * kThreads) + threadIdx.x;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-            if (m0 + wm * 64 + i * 32 >= a.M) continue;   // no token in these 32 rows: nobody reads them (uniform)
+            if (m0 + wm * (NI * 32) + i * 32 >= a.M) continue;   // no token in these 32 rows: nobody reads them (uniform)
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -326,8 +415,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
         return;
     }
 
-    // Fused epilogue.  Drop the factor 16 of the widened weights, dequantize with
-    // 2^e * sw[n] in registers, then transpose through LDS: a lane holds four
+    // Fused epilogue.  Dequantize with 2^e * sw[n] / 16 in registers (16: the widened weights), then transpose through LDS: a lane holds four
     // consecutive channels of one token (8 bytes), the store wants eight lanes
     // per 128-byte row.  Each wavefront uses a private 64 x 144-byte region.
     const int mrow = m0 + wm * (NI * 32) + (lane & 31);
@@ -359,24 +447,23 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
                     if (m < a.M && n < pN) pacc[(int64_t)m * pN + n] = acc[i][j][r] >> AGQ_W_SHIFT;
                 }
     }
-    unsigned char *obuf = lds + wave * (64 * kOutStride);   // 9 KiB per wavefront, 36 KiB in all
+    const float scale16 = a.scale_e * (1.0f / (1 << AGQ_W_SHIFT));   // the factor 16 goes with the scale: exact
+    unsigned char *obuf = lds + wave * (NI * 32 * kOutStride);   // 4.5 NI KiB per wavefront
 #pragma unroll
     for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const float g0 = a.scale_e * __half2float(__ushort_as_half((unsigned short)(swp[j][q].x & 0xFFFF)));
-                const float g1 = a.scale_e * __half2float(__ushort_as_half((unsigned short)(swp[j][q].x >> 16)));
-                const float g2 = a.scale_e * __half2float(__ushort_as_half((unsigned short)(swp[j][q].y & 0xFFFF)));
-                const float g3 = a.scale_e * __half2float(__ushort_as_half((unsigned short)(swp[j][q].y >> 16)));
-                const __half h0 = agq_dequant(acc[i][j][4 * q] >> AGQ_W_SHIFT, g0);
-                const __half h1 = agq_dequant(acc[i][j][4 * q + 1] >> AGQ_W_SHIFT, g1);
-                const __half h2 = agq_dequant(acc[i][j][4 * q + 2] >> AGQ_W_SHIFT, g2);
-                const __half h3 = agq_dequant(acc[i][j][4 * q + 3] >> AGQ_W_SHIFT, g3);
+                float g[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const uint32_t pair = r < 2 ? swp[j][q].x : swp[j][q].y;
+                    g[r] = scale16 * __half2float(__ushort_as_half((unsigned short)((r & 1) ? pair >> 16 : pair & 0xFFFF)));
+                }
                 uint2 pk;
-                pk.x = (uint32_t)__half_as_ushort(h0) | ((uint32_t)__half_as_ushort(h1) << 16);
-                pk.y = (uint32_t)__half_as_ushort(h2) | ((uint32_t)__half_as_ushort(h3) << 16);
+                pk.x = agq_dequant2((float)acc[i][j][4 * q], g[0], (float)acc[i][j][4 * q + 1], g[1]);
+                pk.y = agq_dequant2((float)acc[i][j][4 * q + 2], g[2], (float)acc[i][j][4 * q + 3], g[3]);
                 const int row = i * 32 + (lane & 31), col = j * 32 + q * 8 + (lane >> 5) * 4;
                 *reinterpret_cast<uint2 *>(obuf + row * kOutStride + col * 2) = pk;
             }
@@ -411,16 +498,14 @@ __global__ __launch_bounds__(kThreads) void split_reduce_kernel(const TiledArgs 
     const int tile_id = blockIdx.x >> 4, c = blockIdx.x & 15;
     const int i = c >> 3, j = (c >> 2) & 1, q = c & 3;
     int bid = tile_id;
-    const int pj = (bid >= a.tile_start[1]) + (bid >= a.tile_start[2]) + (bid >= a.tile_start[3]);
-    auto pick = [pj](auto v0, auto v1, auto v2, auto v3) { return pj == 0 ? v0 : (pj == 1 ? v1 : (pj == 2 ? v2 : v3)); };
-    bid -= pick(0, a.tile_start[1], a.tile_start[2], a.tile_start[3]);
-    const int pN = pick(a.N4[0], a.N4[1], a.N4[2], a.N4[3]);
-    const int ptiles_n = pick(a.tiles_n4[0], a.tiles_n4[1], a.tiles_n4[2], a.tiles_n4[3]);
-    const uint16_t *const psw = reinterpret_cast<const uint16_t *>(pick(a.sw4[0], a.sw4[1], a.sw4[2], a.sw4[3]));
-    __half *const py = pick(a.y4[0], a.y4[1], a.y4[2], a.y4[3]);
-    const int64_t pldy = pick(a.ldy4[0], a.ldy4[1], a.ldy4[2], a.ldy4[3]);
-    int32_t *const pacc = pick(a.acc4[0], a.acc4[1], a.acc4[2], a.acc4[3]);
-    const int32_t *const pwsum = pick(a.wsum4[0], a.wsum4[1], a.wsum4[2], a.wsum4[3]);
+    TiledProjC *const pr = tiled_proj(a, bid);
+    bid -= pr->start;
+    const int pN = pr->N, ptiles_n = pr->tiles_n;
+    const uint16_t *const psw = reinterpret_cast<const uint16_t *>(pr->sw);
+    __half *const py = pr->y;
+    const int64_t pldy = pr->ldy;
+    int32_t *const pacc = pr->acc;
+    const int32_t *const pwsum = pr->wsum;
     const int band = bid / (kBand * ptiles_n);
     const int rows = min(kBand, a.tiles_m - band * kBand);
     const int within = bid - band * kBand * ptiles_n;
@@ -474,19 +559,19 @@ int agq_launch_gemm_tiled(const void *x_tiles, int64_t M, int64_t K, int e, int 
     int tiles = 0;
     for (int p = 0; p < kMaxProj; ++p) {
         const agq_proj &pr = projs[p < count ? p : count - 1];
-        a.tile_start[p] = tiles;
-        a.N4[p] = (int)pr.N;
-        a.tiles_n4[p] = (int)((pr.N + BN - 1) / BN);
-        if (p < count) tiles += a.tiles_m * a.tiles_n4[p];
-        a.blob4[p] = (const agq_u4 *)pr.w_packed;
-        a.sw4[p] = (const __half *)pr.w_scale_f16;
-        a.y4[p] = (__half *)pr.y_f16;
-        a.ldy4[p] = pr.ldy;
-        a.acc4[p] = pr.acc_out;
-        a.wsum4[p] = n_extra >= 0 ? (const int32_t *)((const char *)pr.w_packed + agq_trip_layout(pr.N, K, n_extra).wsum_off)
-                                  : agq_blob_wsum(pr.w_packed, pr.N, K);
+        TiledProj &t = a.proj[p];
+        t.start = tiles;
+        t.N = (int)pr.N;
+        t.tiles_n = (int)((pr.N + BN - 1) / BN);
+        if (p < count) tiles += a.tiles_m * t.tiles_n;
+        t.blob = (const agq_u4 *)pr.w_packed;
+        t.sw = (const __half *)pr.w_scale_f16;
+        t.y = (__half *)pr.y_f16;
+        t.ldy = pr.ldy;
+        t.acc = pr.acc_out;
+        t.wsum = n_extra >= 0 ? (const int32_t *)((const char *)pr.w_packed + agq_trip_layout(pr.N, K, n_extra).wsum_off)
+                              : agq_blob_wsum(pr.w_packed, pr.N, K);
     }
-    for (int p = count; p <= kMaxProj; ++p) a.tile_start[p] = tiles;
     const unsigned grid = (unsigned)tiles;
     hipStream_t st = (hipStream_t)stream;
     if (n_extra >= 0) {
@@ -524,3 +609,4 @@ int agq_launch_gemm_tiled(const void *x_tiles, int64_t M, int64_t K, int e, int 
     }
     return (int)hipGetLastError();
 }
+

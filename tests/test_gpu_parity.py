@@ -1296,3 +1296,25 @@ def test_qk_attention_longest_sequence(agq, oracle):
         _, want_o = oracle.attn_v_from_codes(live, vq[:, :i + 1], e_v, qmax, causal=False)
         assert np.array_equal(o_h[i:i + 1].view(np.uint16), want_o.view(np.uint16)), i
         assert score_h[i] == 1 << (qmax - int(live[0, 0, 0]))
+
+
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 6, 7, 8, 11])
+@pytest.mark.parametrize("M,N", [(300, 40), (1100, 2000)])          # 64-token tiles; 128-token tiles
+def test_tiled_every_pipeline_tail(agq, oracle, M, N, steps):
+    """The tiled kernel's K loop: fewer steps than its three stages, and every number of steps behind the steady loop."""
+    x, wq, sw = make_case(M, 128 * steps, N, 90 + steps)
+    rows = sorted({0, 31, 32, 63, 64, 127, 128, M // 2, M - 1})
+    e = oracle.calibrate_act_exp(x, 8)
+    acc_want, y_want = oracle.linear_w4(x[rows], 8, e, 0, wq, sw)
+    acc = torch.full((M, N), -12345, dtype=torch.int32, device="cuda")
+    y = agq.gemm_w4a8(dev(x), e, agq.pack_w4(dev(wq)), dev(sw), N, 128 * steps, acc_out=acc)
+    assert np.array_equal(host(acc)[rows].astype(np.int64), acc_want)
+    assert_f16_close(host(y)[rows], y_want, "y")
+
+
+def test_trip_split_slice_of_extra_steps_only(agq, oracle):
+    """A K split whose first slice is the 16 extra steps and nothing else: its last step is followed by a shift."""
+    M, N, K = 300, 300, 2048
+    x, wq, sw, e = trip_case(M, K, N, 95, K // 100, 4, 8, oracle)
+    run_trip_linear(agq, oracle, x, wq, sw, 8, e, np.ones(K, dtype=np.int8))
+    run_trip_linear(agq, oracle, x, wq, sw, 8, e, random_alpha(np.random.default_rng(44), K, (700, 600, 300, 256)))
