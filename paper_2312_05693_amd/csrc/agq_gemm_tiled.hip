@@ -470,8 +470,31 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (pldy & 7) {
+        // Rows that do not start on 16 bytes: 32 lanes a row, four bytes a lane and two rows an instruction, from the row's
+        // first word boundary on; a row that starts inside a word has single values at both ends.  (2000 tokens,
+        // 4096 -> 4100, pre-pass included: 57 us; with eight channels a lane and two bytes a store 69 us; 4096 -> 4096: 40 us.)
+        const int nw = n0 + wn * 64, half = lane >> 5;
+#pragma unroll 4
+        for (int it = 0; it < NI * 16; ++it) {
+            const int row = it * 2 + half, m = m0 + wm * (NI * 32) + row;
+            if (m >= a.M) break;
+            const int odd = (int)((int64_t)m * pldy) & 1;
+            const int c0 = 2 * (lane & 31) + odd, c1 = c0 + 1 < 64 ? c0 + 1 : 0;       // the last lane of an odd row: both ends
+            const uint16_t *const op = reinterpret_cast<const uint16_t *>(obuf + row * kOutStride);
+            const uint32_t v0 = op[c0], v1 = op[c1];
+            __half *const yp = py + (int64_t)m * pldy + nw;
+            if (c1 && nw + c1 < pN) {
+                *reinterpret_cast<uint32_t *>(yp + c0) = v0 | (v1 << 16);
+            } else {
+                if (nw + c0 < pN) yp[c0] = __ushort_as_half((unsigned short)v0);
+                if (c1 == 0 && nw < pN) yp[0] = __ushort_as_half((unsigned short)v1);
+            }
+        }
+        return;
+    }
     const int nbase = n0 + wn * 64 + (lane & 7) * 8;          // eight channels per lane
-    const bool vec_ok = (pldy & 7) == 0 && nbase + 7 < pN;
+    const bool vec_ok = nbase + 7 < pN;
 #pragma unroll
     for (int it = 0; it < NI * 4; ++it) {
         const int row = it * 8 + (lane >> 3);

@@ -1318,3 +1318,18 @@ def test_trip_split_slice_of_extra_steps_only(agq, oracle):
     x, wq, sw, e = trip_case(M, K, N, 95, K // 100, 4, 8, oracle)
     run_trip_linear(agq, oracle, x, wq, sw, 8, e, np.ones(K, dtype=np.int8))
     run_trip_linear(agq, oracle, x, wq, sw, 8, e, random_alpha(np.random.default_rng(44), K, (700, 600, 300, 256)))
+
+
+@pytest.mark.parametrize("M,N,pitch", [(300, 130, 131), (300, 129, 130), (300, 63, 63), (1100, 2001, 2001), (1100, 2050, 2052),
+                                       (1100, 1985, 1988)])
+def test_tiled_output_rows_off_the_16_byte_grid(agq, oracle, M, N, pitch):
+    """Output pitches that are no multiple of eight: odd and even, the width on both sides of a 64-channel tile's edge."""
+    x, wq, sw = make_case(M, 256, N, seed=500 + N)
+    e = oracle.calibrate_act_exp(x, 8)
+    rows = sorted({0, 1, 30, 31, 32, 63, 64, 127, 128, M - 2, M - 1})
+    _, y_want = oracle.linear_w4(x[rows], 8, e, 0, wq, sw)
+    ybuf = torch.full((M + 1, pitch), -5.0, dtype=torch.float16, device="cuda")
+    agq.gemm_w4a8(dev(x), e, agq.pack_w4(dev(wq)), dev(sw), N, 256, y=ybuf[:M, :N])
+    yh = host(ybuf)
+    assert_f16_close(yh[rows][:, :N], y_want, "y")
+    assert np.all(yh[:M, N:] == np.float16(-5.0)) and np.all(yh[M] == np.float16(-5.0)), "wrote past a row"
