@@ -62,17 +62,16 @@ int agq_gemm_w4_run(int bits, const void *x, int x_kind, int64_t M, int64_t K, i
     }
     AgqSplitPlan plan = agq_tiled_split_plan(M, tiles_n, K / 128, true);
     if (workspace_bytes < need + plan.bytes) plan = agq_tiled_split_plan(M, tiles_n, K / 128, false);
-    const bool half_tiles = agq_tiled_half_tiles(M, tiles_n, K / 128, plan.cost_ns);
-    const int64_t tiled_ns = half_tiles ? K / 128 * 370 : plan.cost_ns;
-    if (M <= AGQ_DECODE_MAX_M || agq_decode_row_groups(x_kind, M, K, n_sum, wg_pairs, tiled_ns))
+    const AgqTiledChoice choice = agq_tiled_choose(M, tiles_n, K / 128, plan);
+    if (M <= AGQ_DECODE_MAX_M || agq_decode_row_groups(x_kind, M, K, n_sum, wg_pairs, choice.cost_ns))
         return hip_status(agq_launch_gemm_decode(x, x_kind, bits, M, K, ldx, e, zp, projs, count, -1, stream));
 
     // many tokens: lay the codes out in MFMA operand order once (quantizing on the
     // way when x is fp16), then run the tiled kernel for all projections on that copy
-    void *const split_ws = plan.splits > 1 && !half_tiles ? static_cast<char *>(workspace) + codes_bytes(M, K) : nullptr;
+    void *const split_ws = static_cast<char *>(workspace) + codes_bytes(M, K);
     if (agq_launch_prepack_act(x, x_kind, bits, M, K, ldx, e, zp, workspace, stream)) return AGQ_EHIP;
     return hip_status(
-        agq_launch_gemm_tiled(workspace, M, K, e, agq_zp_corr(bits, zp), projs, count, -1, split_ws, half_tiles, stream));
+        agq_launch_gemm_tiled(workspace, M, K, e, agq_zp_corr(bits, zp), projs, count, -1, choice.variant, plan, split_ws, stream));
 }
 
 namespace {
@@ -130,10 +129,9 @@ int gemm_w4_trip_multi(int bits, const void *x, int64_t M, int64_t K, int64_t ld
     for (int p = 0; p < count; ++p) tiles_n += (projs[p].N + 127) / 128;
     AgqSplitPlan plan = agq_tiled_split_plan(M, tiles_n, K / 128 + n_extra, true, n_extra);
     if (workspace_bytes < need + plan.bytes) plan = agq_tiled_split_plan(M, tiles_n, K / 128 + n_extra, false);
-    const bool half_tiles = agq_tiled_half_tiles(M, tiles_n, K / 128 + n_extra, plan.cost_ns);
-    void *const split_ws = plan.splits > 1 && !half_tiles ? static_cast<char *>(workspace) + need : nullptr;
-    return hip_status(agq_launch_gemm_tiled(workspace, M, K, e, agq_zp_corr(bits, zp), projs, count, n_extra, split_ws,
-                                            half_tiles, stream));
+    const AgqTiledChoice choice = agq_tiled_choose(M, tiles_n, K / 128 + n_extra, plan, n_extra);
+    return hip_status(agq_launch_gemm_tiled(workspace, M, K, e, agq_zp_corr(bits, zp), projs, count, n_extra, choice.variant, plan,
+                                            static_cast<char *>(workspace) + need, stream));
 }
 
 int gemm_w4_trip(int bits, const void *x, int64_t M, int64_t K, int64_t ldx, int e, int zp, const void *w_packed,

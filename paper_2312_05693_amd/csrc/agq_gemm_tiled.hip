@@ -122,28 +122,37 @@ __device__ __forceinline__ void lds_dma16_s(uint32_t voff, const void *sbase, ui
 // NI: 32-token MFMA tiles per wavefront.  2: the 128-token workgroup tile described above.  1: a 64-token
 // tile (each wavefront 32 x 64, half of the MFMAs per step for two thirds of the operand bytes), for grids
 // whose 128-token tiles would leave the last round of workgroups mostly empty.
-template <bool TRIP, bool SPLIT, int NI = 2>
-__global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs a) {
+//
+// KG: groups of four wavefronts that share the K steps of the workgroup's tile, each with stages of its own; they meet at
+// the same barriers, and at the end group 1 hands its sums to group 0 through LDS.  With one workgroup on a CU a single
+// wavefront per SIMD waits at every barrier with the matrix core idle (64-token tiles, K = 11008, 100 tokens: 0.24 us a
+// step, of which the MFMAs are 0.12; 0.36 with the weights from HBM); two groups take 0.36 (0.52) us for two steps.
+// 128-token tiles gain nothing from it (0.29 against 0.26 us a step), nor does either from more than three stages.
+template <bool TRIP, bool SPLIT, int NI, int KG>
+__global__ __launch_bounds__(kThreads * KG, 2) void gemm_tiled_kernel(const TiledArgs a) {
     static_assert(NI == 2 || (NI == 1 && !SPLIT), "the partial tiles of a K split are laid out for 128 tokens");
+    static_assert(KG == 1 || (KG == 2 && !SPLIT), "one kind of K split at a time");
     constexpr int BMT = NI * 64;                 // tokens per workgroup tile
     constexpr int kAChunksT = NI * 8;            // activation chunks of 1 KiB per stage
     constexpr int kStageT = (kAChunksT + kBChunks) * 1024;   // 24 KiB (16 KiB for NI == 1)
     constexpr int kNA = NI * 2;                  // activation copies per wavefront and step
     constexpr int kCopiesT = kNA + 2;
-    // Three pipeline stages; the epilogue reuses the first 36 KiB.
-    __shared__ __align__(16) unsigned char lds[kStages * kStageT];
+    // Three pipeline stages per K group; the epilogue reuses the first 18 NI KiB.
+    __shared__ __align__(16) unsigned char lds[KG * kStages * kStageT];
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = (threadIdx.x >> 6) & 3;
+    const int grp = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    const int tid = threadIdx.x & (kThreads - 1);        // in the K group
     const int wm = wave >> 1, wn = wave & 1;
 
     // XCD-aware tile order.  Consecutive workgroup ids land on different XCDs
     // (round-robin over 8), each with its own L2, so first give every XCD a
-    // contiguous run of logical tile ids; then walk the tile grid in bands of
+    // contiguous run of logical tile ids (the first nblk % 8 of them one more); then walk the tile grid in bands of
     // kBand token tiles, column by column, so that a run covers a compact
     // rectangle and re-reads as little of either operand as possible.
     const int nblk = gridDim.x;
     int bid = blockIdx.x;
-    if ((nblk & 7) == 0) bid = (bid & 7) * (nblk >> 3) + (bid >> 3);
+    bid = (bid & 7) * (nblk >> 3) + min(bid & 7, nblk & 7) + (bid >> 3);
     // SPLIT: workgroups with the same K slice are neighbours (they share activation stages)
     const int split = SPLIT ? bid / a.tiles_all : 0;
     if (SPLIT) bid -= split * a.tiles_all;
@@ -163,8 +172,14 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
     const int tn = within / rows, tm = band * kBand + within - tn * rows;
     const int m0 = tm * BMT, n0 = tn * BN;
     const int KTfull = a.KT;
-    const int kbeg = SPLIT ? split * a.steps_per_split : 0;
-    const int KT = SPLIT ? min(a.steps_per_split, KTfull - kbeg) : KTfull;   // steps of this workgroup
+    const int kwg = SPLIT ? split * a.steps_per_split : 0;
+    const int KTwg = SPLIT ? min(a.steps_per_split, KTfull - kwg) : KTfull;  // steps of this workgroup
+    // KG == 2: the first half for group 0 (the extra steps, whose shifts apply to what came before them, stay together),
+    // the rest for group 1.  A group with nothing to do takes a step whose result is dropped.
+    const int khalf = KG == 1 ? KTwg : max((KTwg + 1) >> 1, TRIP && split == 0 ? a.n_extra : 0);
+    const bool idle = KG == 2 && grp == 1 && khalf >= KTwg;
+    const int kbeg = kwg + (grp == 1 && !idle ? khalf : 0);
+    const int KT = KG == 1 ? KTwg : (grp == 0 ? khalf : (idle ? 1 : KTwg - khalf));   // steps of this group
 
     // Copies of this wavefront per step: activation chunks 4 wave .. 4 wave + 3 of
     // the 16 KiB stage, and weight chunks 2 wave, 2 wave + 1.  Weight chunk c
@@ -189,7 +204,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
     // LDS byte address (wave-uniform, kept in a scalar register) of this
     // wavefront's first activation chunk in stage 0
     const uint32_t lds_base = __builtin_amdgcn_readfirstlane(
-        (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char *)lds);
+        (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char *)lds) + grp * (kStages * kStageT);
     const uint32_t lds_a = lds_base + wave_u * (kNA * 1024), lds_b = lds_base + kAChunksT * 1024 + wave_u * 2048;
     // copy p of a step into the stage that starts `st` bytes into lds, from the step's source addresses (the
     // activation pieces of a wavefront are contiguous on both sides: one base, the piece in the offset)
@@ -268,8 +283,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
     uint32_t rd = kStageT, fill = 0;                     // stage read from (next step), stage refilled
     constexpr int kSlots = 8 * NI;                       // MFMAs of a step
     constexpr int kReads = 4 * NI + 4;
-    const agq_u4 *const rda = reinterpret_cast<const agq_u4 *>(lds) + lane + wm * (NI * 4 * 64);
-    const agq_u4 *const rdb = reinterpret_cast<const agq_u4 *>(lds) + lane + (kAChunksT + wn * 4) * 64;
+    const agq_u4 *const rda = reinterpret_cast<const agq_u4 *>(lds + grp * (kStages * kStageT)) + lane + wm * (NI * 4 * 64);
+    const agq_u4 *const rdb = reinterpret_cast<const agq_u4 *>(lds + grp * (kStages * kStageT)) + lane + (kAChunksT + wn * 4) * 64;
     agq_v4i wb[2][2];                                    // widened weights of this k-block and the next
     auto widen1 = [&](const agq_u4 (&bc)[4], int t, int d) {   // dword d (0..7) of k-block t
         const uint32_t p = bc[(d >> 2) * 2 + (t & 1)][d & 3];
@@ -333,7 +348,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     {
-        const agq_u4 *s0 = reinterpret_cast<const agq_u4 *>(lds) + lane;
+        const agq_u4 *s0 = reinterpret_cast<const agq_u4 *>(lds + grp * (kStages * kStageT)) + lane;
 #pragma unroll
         for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -353,7 +368,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int d = 0; d < 8; ++d) widen1(b0, 0, d);
-#define AGQ_SHIFT(KT_) if (TRIP && split == 0 && (KT_) < a.n_extra) shift_acc(a.trip_shift[KT_]);
+#define AGQ_SHIFT(KT_) if (TRIP && split == 0 && grp == 0 && (KT_) < a.n_extra) shift_acc(a.trip_shift[KT_]);
     // stages rotate through three, the register sets through two; the copies of the step two ahead stay in flight
     int kt = 0;
     for (; kt + 4 < KT; kt += 2) {
@@ -397,11 +412,45 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_tiled_kernel(const TiledArgs
 #undef AGQ_SHIFT
 #undef AGQ_MEET
 #undef AGQ_WAIT
+    if (KG == 2) {
+        // the groups meet once per step and once before the first one: the shorter one catches up
+        for (int more = (grp == 0 ? max(KTwg - khalf, 1) : khalf) - KT; more > 0; --more) __builtin_amdgcn_s_barrier();
+    }
     __syncthreads();                                   // every wavefront is done with the stages
+    if constexpr (KG == 2) {
+        // group 1 hands its sums over through its stages: piece c of thread t at [c][t]
+        int4 *const ex = reinterpret_cast<int4 *>(lds + kStages * kStageT) + tid;
+        static_assert(NI * 8 * kThreads * 16 <= kStages * kStageT, "the sums of a group fit its stages");
+        if (grp == 1) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        ex[((i * 2 + j) * 4 + q) * kThreads] =
+                            idle ? make_int4(0, 0, 0, 0)
+                                 : make_int4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+        }
+        __syncthreads();
+        if (grp == 1) return;
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int4 v = ex[((i * 2 + j) * 4 + q) * kThreads];
+                    acc[i][j][4 * q] += v.x;
+                    acc[i][j][4 * q + 1] += v.y;
+                    acc[i][j][4 * q + 2] += v.z;
+                    acc[i][j][4 * q + 3] += v.w;
+                }
+    }
 
     if (SPLIT) {
         // accumulator piece c = (i * 2 + j) * 4 + q of thread t at [c][t]: 16 bytes per lane, contiguous
-        int4 *const mine = reinterpret_cast<int4 *>(a.part) + ((int64_t)tile_id * a.splits + split) * (16 * kThreads) + threadIdx.x;
+        int4 *const mine = reinterpret_cast<int4 *>(a.part) + ((int64_t)tile_id * a.splits + split) * (16 * kThreads) + tid;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             if (m0 + wm * (NI * 32) + i * 32 >= a.M) continue;   // no token in these 32 rows: nobody reads them (uniform)
@@ -567,14 +616,14 @@ __global__ __launch_bounds__(kThreads) void split_reduce_kernel(const TiledArgs 
 }  // namespace
 
 int agq_launch_gemm_tiled(const void *x_tiles, int64_t M, int64_t K, int e, int corr, const struct agq_proj *projs, int count,
-                          int n_extra, void *split_ws, bool half_tiles, void *stream) {
+                          int n_extra, AgqTiledVariant variant, const AgqSplitPlan &plan, void *split_ws, void *stream) {
     TiledArgs a = {};
     a.xt = (const agq_u4 *)x_tiles;
     a.M = (int)M;
     a.K = (int)K;
     a.KT = (int)agq_k_tiles(K);
     a.tiles_m = (int)((M + BM - 1) / BM);
-    if (half_tiles) a.tiles_m = (int)((M + 63) / 64);
+    if (variant == TILED_64 || variant == TILED_64X2) a.tiles_m = (int)((M + 63) / 64);
     a.scale_e = ldexpf(1.0f, e);
     a.corr = corr;
     a.n_extra = 0;
@@ -604,31 +653,24 @@ int agq_launch_gemm_tiled(const void *x_tiles, int64_t M, int64_t K, int e, int 
         a.n_extra = n_extra;
         a.trip_shift = (const int32_t *)((const char *)projs[0].w_packed + L.meta_off) + 16;
     }
-    if (split_ws && !half_tiles) {
-        // the extra steps and their shifts stay together in the first slice
-        const AgqSplitPlan plan = agq_tiled_split_plan(M, tiles / a.tiles_m, a.KT, true, n_extra >= 0 ? n_extra : 0);
-        if (plan.splits > 1) {
-            a.splits = plan.splits;
-            a.steps_per_split = plan.steps;
-            a.tiles_all = tiles;
-            a.part = (int32_t *)split_ws;
-            if (n_extra >= 0)
-                gemm_tiled_kernel<true, true><<<grid * (unsigned)plan.splits, kThreads, 0, st>>>(a);
-            else
-                gemm_tiled_kernel<false, true><<<grid * (unsigned)plan.splits, kThreads, 0, st>>>(a);
-            split_reduce_kernel<<<grid * 16, kThreads, 0, st>>>(a);
-            return (int)hipGetLastError();
-        }
-    }
-    if (half_tiles) {
-        if (n_extra >= 0)
-            gemm_tiled_kernel<true, false, 1><<<grid, kThreads, 0, st>>>(a);
-        else
-            gemm_tiled_kernel<false, false, 1><<<grid, kThreads, 0, st>>>(a);
-    } else if (n_extra >= 0) {
-        gemm_tiled_kernel<true, false><<<grid, kThreads, 0, st>>>(a);
+    const bool trip = n_extra >= 0;
+    if (variant == TILED_SPLIT) {
+        a.splits = plan.splits;                          // TRIP: the extra steps and their shifts stay in the first slice
+        a.steps_per_split = plan.steps;
+        a.tiles_all = tiles;
+        a.part = (int32_t *)split_ws;
+        if (trip) gemm_tiled_kernel<true, true, 2, 1><<<grid * (unsigned)plan.splits, kThreads, 0, st>>>(a);
+        else gemm_tiled_kernel<false, true, 2, 1><<<grid * (unsigned)plan.splits, kThreads, 0, st>>>(a);
+        split_reduce_kernel<<<grid * 16, kThreads, 0, st>>>(a);
+    } else if (variant == TILED_64X2) {
+        if (trip) gemm_tiled_kernel<true, false, 1, 2><<<grid, 2 * kThreads, 0, st>>>(a);
+        else gemm_tiled_kernel<false, false, 1, 2><<<grid, 2 * kThreads, 0, st>>>(a);
+    } else if (variant == TILED_64) {
+        if (trip) gemm_tiled_kernel<true, false, 1, 1><<<grid, kThreads, 0, st>>>(a);
+        else gemm_tiled_kernel<false, false, 1, 1><<<grid, kThreads, 0, st>>>(a);
     } else {
-        gemm_tiled_kernel<false, false><<<grid, kThreads, 0, st>>>(a);
+        if (trip) gemm_tiled_kernel<true, false, 2, 1><<<grid, kThreads, 0, st>>>(a);
+        else gemm_tiled_kernel<false, false, 2, 1><<<grid, kThreads, 0, st>>>(a);
     }
     return (int)hipGetLastError();
 }

@@ -79,24 +79,55 @@ static inline AgqSplitPlan agq_tiled_split_plan(int64_t M, int64_t tiles_n, int6
     return p;
 }
 
-// 64-token tiles instead of 128-token ones in the tiled kernel: twice the workgroups, each with half of the MFMAs
-// per K step for two thirds of the operand bytes.  At full load that is 15-20 % slower (measured), but while the
-// 128-token tiles number 128 or fewer every workgroup still has a CU to itself, and its step takes about 370 ns
-// instead of 470: used when that beats the plan above (4096 x 4096 at 256..512 rows: 19.4..21.6 against
-// 23.0..25.2 us; with a long K the split wins: 11008 -> 4096 at 128 rows 22.7 against 43.1 us).
-static inline bool agq_tiled_half_tiles(int64_t M, int64_t tiles_n, int64_t KT, int64_t plan_cost_ns) {
-    return ((M + 127) / 128) * tiles_n <= 128 && KT * 370 < plan_cost_ns;
+// The tiled kernel's variants and the choice between them: the one with the smallest time under a model of the launch,
+// a fixed part and a time per K step that depends on how many workgroups share the chip (KT steps, w workgroups).
+//   TILED_128     128-token tiles, at most two workgroups on a CU
+//   TILED_SPLIT   the same with the K split above
+//   TILED_64      64-token tiles, at most three on a CU: half of the MFMAs per step for two thirds of the operand bytes, so
+//                 about 15 % dearer where the chip is full, but finer to deal out
+//   TILED_64X2    64-token tiles with the K steps of a tile shared by two groups of four wavefronts of one workgroup: at
+//                 most one workgroup per CU, whose two wavefronts per SIMD hide each other's waits
+// Measured (us, the GEMM launch alone, other weights from HBM at every launch, as a model's layers have it;
+// 128 / split / 64 / 64x2):
+//   4096 -> 4096     100 tokens 16.4 / 13.9 / 14.2 / 12.2, 300 tokens 16.7 / - / 14.7 / 12.5, 512 tokens 17.1 / - / 15.4 / 13.9
+//   11008 -> 4096    100 tokens 39.3 / 19.7 / 35.1 / 27.3, 213 tokens 39.1 / 23.6 / 35.2 / 27.4, 300 tokens 39.2 / 30.0 / 35.6 / 28.2
+//   4096 -> 12288    100 tokens 17.4 / - / 15.6 / 13.7, 213 tokens 19.1 / - / 20.8 / -, 300 tokens 27.9 / - / 23.4 / -
+//   4096 -> 22016    100 tokens 20.0 / - / 22.3 / 25.7, 213 tokens 31.3 / - / 33.0 / -, 300 tokens 42.2 / - / 41.5 / -
+//   5120 -> 5120     333 tokens 21.5 / - / 19.5 / 16.6, 1024 tokens 35.9 / - / 37.0 / -
+//   4096 -> 22016    1000 tokens 89 / - / 101 / -, 2048 tokens 157 / - / 186 / -
+// which the model reproduces to about 10 %.  (The split's own price above was fitted to resident weights and decides only
+// how many slices it would have.)
+enum AgqTiledVariant { TILED_128, TILED_SPLIT, TILED_64, TILED_64X2 };
+struct AgqTiledChoice {
+    AgqTiledVariant variant;
+    int64_t cost_ns;
+};
+static inline AgqTiledChoice agq_tiled_choose(int64_t M, int64_t tiles_n, int64_t KT, const AgqSplitPlan &plan, int n_extra = 0) {
+    const int64_t w = ((M + 127) / 128) * tiles_n, w64 = ((M + 63) / 64) * tiles_n;
+    auto at_least = [](int64_t a, int64_t b) { return a > b ? a : b; };
+    const int64_t step = w <= 256 ? 360 + w * 11 / 20 : (w <= 512 ? 700 + (w - 256) * 8 / 5 : at_least(1300, w * 187 / 100));
+    AgqTiledChoice c = {TILED_128, 4500 + KT * step};
+    auto offer = [&c](AgqTiledVariant v, int64_t cost) {
+        if (cost < c.cost_ns) c = {v, cost};
+    };
+    if (plan.splits > 1) {
+        const int64_t part_bytes = ((M + 31) / 32) * 32 * tiles_n * 512;
+        offer(TILED_SPLIT, 6500 + plan.steps * (360 + w * plan.splits * 11 / 20) + part_bytes * plan.splits * 450 / 1000000);
+    }
+    const int64_t step64 = w64 <= 256 ? 300 + w64 * 7 / 20 : (w64 <= 768 ? 460 + (w64 - 256) * 21 / 20 : at_least(1360, w64 * 127 / 100));
+    offer(TILED_64, 4000 + KT * step64);
+    if (w64 <= 256) offer(TILED_64X2, 4800 + at_least((KT + 1) / 2, n_extra) * (430 + w64 * 3 / 4));
+    return c;
 }
 
 // Between 17 and 256 rows of fp16 input the weight-streaming kernel can run with sixteen rows and two channel
 // tiles per workgroup (grid.y row groups): every row group reads the weights again (from L2 after the first),
 // about 3 us + 0.24 us per MB read in all, more when the workgroups fill the last round of 256 CUs badly.  The
-// other path is the layout pre-pass plus the tiled kernel: about 8 us around the plan's time above.  Measured
-// (row groups against tiles): 4096 x 4096 at 32 / 64 / 96 / 128 rows 6.4 / 11.0 / 15.6 / 19.6 against 13.4 /
-// 14.7 / 16.2 / 17.5 us; 4096 -> 11008 at 48 / 64 rows 18.3 / 21.7 against 19.8 / 19.9 us; 768 x 768 at 128
-// rows 4.1 against 8.2 us.  wg_pairs: tile pairs (32 channels) of all projections; tiled_ns: the cost of the
-// plan the call would run instead.  (Four tiles per workgroup instead of two were measured too: the same at best,
-// and 50 % slower on the widest layer, where the registers no longer hold the weight chunks.)
+// other path is the layout pre-pass (about 3 us with the gap behind it) plus the tiled kernel (above).  Measured
+// (row groups against pre-pass and tiles): 4096 x 4096 at 32 / 64 / 100 rows 6.4 / 11.0 / 18.1 against about 13 us at
+// any of them; 768 x 768 at 128 rows 4.1 against 8.2 us.  wg_pairs: tile pairs (32 channels) of all projections;
+// tiled_ns: the cost of the variant the call would run instead.  (Four tiles per workgroup instead of two were measured
+// too: the same at best, and 50 % slower on the widest layer, where the registers no longer hold the weight chunks.)
 #define AGQ_ROW_GROUP_MAX_M 256
 static inline bool agq_decode_row_groups(int x_kind, int64_t M, int64_t K, int64_t n_sum, int64_t wg_pairs,
                                          int64_t tiled_ns) {
@@ -104,7 +135,7 @@ static inline bool agq_decode_row_groups(int x_kind, int64_t M, int64_t K, int64
     const int64_t groups = (M + 15) / 16, wgs = groups * wg_pairs;
     int64_t read_ns = groups * (K * n_sum / 2) * 240 / 1000000;
     if (wgs < 768) read_ns = read_ns * ((wgs + 255) / 256 * 256) / wgs;   // a short last round costs a whole one
-    return 3000 + read_ns <= 8000 + tiled_ns;
+    return read_ns <= tiled_ns;
 }
 
 int agq_launch_calibrate(const void *x, int64_t M, int64_t K, int64_t ldx, int bits, int32_t *e_dev, void *stream);
@@ -125,10 +156,9 @@ int agq_launch_gemm_decode(const void *x, int x_kind, int bits, int64_t M, int64
                            const struct agq_proj *projs, int count, int n_extra, void *stream);
 // K counts the main chunks only; with TRIP blobs (all packed with the same factors) x_tiles and the blobs hold
 // n_extra more steps in front.  The `count` projections of the activation run as one launch.
-// split_ws != NULL: room for the partial tiles agq_tiled_split_plan describes for this call's tiles (the call
-// is split).  half_tiles: 64-token tiles (never together with split_ws).
+// TILED_SPLIT: split_ws has room for the partial tiles that `plan` describes.
 int agq_launch_gemm_tiled(const void *x_tiles, int64_t M, int64_t K, int e, int corr, const struct agq_proj *projs, int count,
-                          int n_extra, void *split_ws, bool half_tiles, void *stream);
+                          int n_extra, AgqTiledVariant variant, const AgqSplitPlan &plan, void *split_ws, void *stream);
 int agq_launch_trip_search(const void *x, int64_t M, int64_t K, int64_t ldx, int bits, int e, int zp, int kmax,
                            int8_t *alpha, void *stream);
 int agq_trip_count_extra(const int8_t *alpha_host, int64_t K);   // number of extra chunks, -1 = bad factors or too many

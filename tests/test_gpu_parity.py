@@ -1314,10 +1314,24 @@ def test_tiled_every_pipeline_tail(agq, oracle, M, N, steps):
 
 def test_trip_split_slice_of_extra_steps_only(agq, oracle):
     """A K split whose first slice is the 16 extra steps and nothing else: its last step is followed by a shift."""
-    M, N, K = 300, 300, 2048
+    M, N, K = 100, 300, 10240
     x, wq, sw, e = trip_case(M, K, N, 95, K // 100, 4, 8, oracle)
-    run_trip_linear(agq, oracle, x, wq, sw, 8, e, np.ones(K, dtype=np.int8))
-    run_trip_linear(agq, oracle, x, wq, sw, 8, e, random_alpha(np.random.default_rng(44), K, (700, 600, 300, 256)))
+    run_trip_linear(agq, oracle, x, wq, sw, 8, e, random_alpha(np.random.default_rng(44), K, (2048, 0, 0, 0)))
+    run_trip_linear(agq, oracle, x, wq, sw, 8, e, random_alpha(np.random.default_rng(45), K, (700, 600, 300, 256)))
+
+
+@pytest.mark.parametrize("steps", [15, 16, 17, 21])
+@pytest.mark.parametrize("M,N", [(258, 40), (320, 700)])
+def test_tiled_k_shared_by_two_groups(agq, oracle, M, N, steps):
+    """64-token tiles whose K steps two groups of wavefronts share: even and odd step counts."""
+    run_linear(agq, oracle, *make_case(M, 128 * steps, N, 600 + steps), 8)
+
+
+@pytest.mark.parametrize("K,counts", [(1664, (780, 130, 260, 390)), (2048, (700, 600, 300, 256)), (2048, (3, 0, 0, 20))])
+def test_trip_k_shared_by_two_groups(agq, oracle, K, counts):
+    """The same with extra steps: more than half of all steps (they stay together in the first group), as many, a few."""
+    x, wq, sw, e = trip_case(300, K, 300, 97, K // 100, 4, 8, oracle)
+    run_trip_linear(agq, oracle, x, wq, sw, 8, e, random_alpha(np.random.default_rng(46), K, counts))
 
 
 @pytest.mark.parametrize("M,N,pitch", [(300, 130, 131), (300, 129, 130), (300, 63, 63), (1100, 2001, 2001), (1100, 2050, 2052),
