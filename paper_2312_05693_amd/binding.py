@@ -129,7 +129,8 @@ def _ptr(t):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    # the handle alone: torch.cuda.current_stream() builds a Stream object around it, which takes longer than the call it is for
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ok(status: int, where: str):
@@ -181,16 +182,30 @@ def gemm_workspace_bytes(M: int, N: int, K: int) -> int:
     return lib().agq_gemm_workspace_bytes(M, N, K)
 
 
+def _scratch(nbytes: int, device):
+    return torch.empty(nbytes, dtype=torch.uint8, device=device) if nbytes else None
+
+
+def _projections(M, projs, device):
+    """(the list of y, struct agq_proj[]) of projs = [(w_packed, w_scale, N, y or None, acc_out or None), ...]; the structs
+    as one array of 8-byte values (for three projections 4 us on the host; as AgqProj objects 7)."""
+    ys, flat = [], []
+    for packed, scale, N, y, acc in projs:
+        if y is None:
+            y = torch.empty((M, N), dtype=torch.float16, device=device)
+        ys.append(y)
+        flat += [_ptr(packed) or 0, _ptr(scale) or 0, N, y.data_ptr(), y.stride(0) if M else N, _ptr(acc) or 0]
+    return ys, (_i64 * len(flat))(*flat)
+
+
 def _gemm(fn_name, x, x_kind, M, K, ldx, e, zp, w_packed, w_scale, N, y, acc_out, workspace):
     if y is None:
         y = torch.empty((M, N), dtype=torch.float16, device=w_packed.device)
-    need = gemm_workspace_bytes(M, N, K)
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=w_packed.device)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    if workspace is None:
+        workspace = _scratch(gemm_workspace_bytes(M, N, K), w_packed.device)
     fn = getattr(lib(), fn_name)
     _ok(fn(_ptr(x), x_kind, M, K, ldx, e, zp, _ptr(w_packed), _ptr(w_scale), N, _ptr(y), y.stride(0) if M else N,
-           _ptr(acc_out), _ptr(workspace), ws_bytes, _stream()), fn_name)
+           _ptr(acc_out), _ptr(workspace), 0 if workspace is None else workspace.nbytes, _stream()), fn_name)
     return y
 
 
@@ -219,19 +234,12 @@ def gemm_w4a4(x, e, w_packed, w_scale, N, K, x_kind=AGQ_X_F16, y=None, acc_out=N
 def _gemm_multi(fn_name, x, x_kind, M, K, ldx, e, zp, projs, workspace):
     """projs: list of (w_packed, w_scale, N, y or None, acc_out or None); returns the list of y."""
     dev = projs[0][0].device
-    ys, arr = [], (AgqProj * len(projs))()
-    for i, (packed, scale, N, y, acc) in enumerate(projs):
-        if y is None:
-            y = torch.empty((M, N), dtype=torch.float16, device=dev)
-        ys.append(y)
-        arr[i] = AgqProj(_ptr(packed), _ptr(scale), N, _ptr(y), y.stride(0) if M else N, _ptr(acc))
-    need = gemm_workspace_bytes(M, sum(p[2] for p in projs), K)
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ys, arr = _projections(M, projs, dev)
+    if workspace is None:
+        workspace = _scratch(gemm_workspace_bytes(M, sum(p[2] for p in projs), K), dev)
     fn = getattr(lib(), fn_name)
-    _ok(fn(_ptr(x), x_kind, M, K, ldx, e, zp, ctypes.cast(arr, _vp), len(projs), _ptr(workspace), ws_bytes,
-           _stream()), fn_name)
+    _ok(fn(_ptr(x), x_kind, M, K, ldx, e, zp, arr, len(projs), _ptr(workspace),
+           0 if workspace is None else workspace.nbytes, _stream()), fn_name)
     return ys
 
 
@@ -352,9 +360,8 @@ def gemm_trip(x, bits, e, w_packed, n_extra, w_scale, N, K, y=None, acc_out=None
     M = x.shape[0]
     if y is None:
         y = torch.empty((M, N), dtype=torch.float16, device=x.device)
-    need = lib().agq_gemm_trip_workspace_bytes(M, N, K, n_extra)
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
+    if workspace is None:
+        workspace = _scratch(lib().agq_gemm_trip_workspace_bytes(M, N, K, n_extra), x.device)
     fn = lib().agq_gemm_w4a8_trip if bits == 8 else lib().agq_gemm_w4a4_trip
     _ok(fn(_ptr(x), M, K, x.stride(0) if M else K, e, zp, _ptr(w_packed), n_extra, _ptr(w_scale), N, _ptr(y),
            y.stride(0) if M else N, _ptr(acc_out), _ptr(workspace), workspace.numel() if workspace is not None else 0,
@@ -366,17 +373,11 @@ def gemm_trip_multi(x, bits, e, projs, n_extra, K, workspace=None, zp=0):
     """The TRIP layer for several projections of one activation: projs = [(blob, w_scale, N, y|None, acc_out|None), ...],
     every blob packed with the same factors.  Returns the list of y."""
     M = x.shape[0]
-    ys, arr = [], (AgqProj * len(projs))()
-    for i, (packed, scale, N, y, acc) in enumerate(projs):
-        if y is None:
-            y = torch.empty((M, N), dtype=torch.float16, device=x.device)
-        ys.append(y)
-        arr[i] = AgqProj(_ptr(packed), _ptr(scale), N, _ptr(y), y.stride(0) if M else N, _ptr(acc))
-    need = lib().agq_gemm_trip_workspace_bytes(M, sum(p[2] for p in projs), K, n_extra)
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
+    ys, arr = _projections(M, projs, x.device)
+    if workspace is None:
+        workspace = _scratch(lib().agq_gemm_trip_workspace_bytes(M, sum(p[2] for p in projs), K, n_extra), x.device)
     fn = lib().agq_gemm_w4a8_trip_multi if bits == 8 else lib().agq_gemm_w4a4_trip_multi
-    _ok(fn(_ptr(x), M, K, x.stride(0) if M else K, e, zp, ctypes.cast(arr, _vp), len(projs), n_extra, _ptr(workspace),
+    _ok(fn(_ptr(x), M, K, x.stride(0) if M else K, e, zp, arr, len(projs), n_extra, _ptr(workspace),
            workspace.numel() if workspace is not None else 0, _stream()), "agq_gemm_w4a%d_trip_multi" % bits)
     return ys
 
