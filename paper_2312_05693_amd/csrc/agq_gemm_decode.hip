@@ -839,12 +839,25 @@ int agq_launch_gemm_decode(const void *x, int x_kind, int bits, int64_t M, int64
     a.scale_e = ldexpf(1.0f, e);
     a.n_extra = n_extra > 0 ? n_extra : 0;
     const bool trip = n_extra >= 0;
+    int singles = 0, doubles = 0;                            // channel tiles, pairs of them
+    for (int p = 0; p < count; ++p) {
+        singles += (int)((projs[p].N + 15) / 16);
+        doubles += (int)((projs[p].N + 31) / 32);
+    }
+    // A workgroup serves a pair of tiles in row groups (more than sixteen rows), and from five rows on with a K beyond the
+    // K-sliced kernel's when that saves a round: a workgroup of sixteen wavefronts then has its CU to itself, and every
+    // round loads and quantizes the whole activation again.  One tile against a pair per workgroup, K = 13824:
+    // N = 5120 (320 tiles) 16 rows 22.1 -> 15.4 us, 9 rows 18.9 -> 13.4, 8 rows 15.6 -> 13.1, 5 rows 14.3 -> 12.6;
+    // N = 8192 16 rows 24.7 -> 18.6; K = 28672, N = 8192, 16 rows 47.8 -> 34.1; three times 9216 -> 4096 26.2 -> 21.9.
+    // Where one round holds all tiles the pair is the slower form (half of the CUs idle), and below five rows a
+    // workgroup is small enough for two on a CU.
+    const bool pairs = M > AGQ_DECODE_MAX_M || (x_kind == 0 && !trip && M > 4 && a.KT > kSliceMaxKT &&
+                                                (doubles + 255) / 256 < (singles + 255) / 256);
     int tiles = 0;
     for (int p = 0; p < kMaxProj; ++p) {
         const agq_proj &pr = projs[p < count ? p : count - 1];
         a.tile_start[p] = tiles;
-        // row groups (more than sixteen rows): a workgroup serves a pair of tiles
-        if (p < count) tiles += M > AGQ_DECODE_MAX_M ? (int)((pr.N + 31) / 32) : (int)((pr.N + 15) / 16);
+        if (p < count) tiles += pairs ? (int)((pr.N + 31) / 32) : (int)((pr.N + 15) / 16);
         a.blob4[p] = (const uint4 *)pr.w_packed;
         a.sw4[p] = (const __half *)pr.w_scale_f16;
         a.N4[p] = (int)pr.N;
@@ -871,8 +884,8 @@ int agq_launch_gemm_decode(const void *x, int x_kind, int bits, int64_t M, int64
         waves = (a.KT + kpw - 1) / kpw;
         if (waves > 16) waves = 16;
     }
-    if (M > AGQ_DECODE_MAX_M && kpw == 8) {
-        // row groups keep two tiles' weight chunks in registers: four chunks per wavefront at most
+    if (pairs && kpw == 8) {
+        // two tiles' weight chunks are kept in registers: four chunks per wavefront at most
         kpw = 4;
         waves = (a.KT + kpw - 1) / kpw;
         if (waves > 16) waves = 16;
@@ -890,15 +903,15 @@ int agq_launch_gemm_decode(const void *x, int x_kind, int bits, int64_t M, int64
     const unsigned grid = (unsigned)tiles;
     a.waves = waves;
     // staging: per wavefront HB chunks x (8 x 4 MP) 16-byte pieces (see the kernel)
-    const int mp = M <= 4 ? 1 : (M <= 8 ? 2 : 4);
+    const int mp = pairs ? 4 : (M <= 4 ? 1 : (M <= 8 ? 2 : 4));
     const int hb = x_kind != 0 ? kpw : (8 / mp < kpw ? 8 / mp : kpw);
     const size_t per_wave = x_kind != 0 ? 0 : (size_t)hb * 8 * 4 * mp * 16;
     // behind the staging regions: one KiB of partial sums per wavefront and channel tile
-    const size_t lds = (size_t)waves * (per_wave + (M > AGQ_DECODE_MAX_M ? 2048 : 1024));
+    const size_t lds = (size_t)waves * (per_wave + (pairs ? 2048 : 1024));
     hipStream_t st = (hipStream_t)stream;
     if (x_kind == AGQ_X_F16_DOT)   // the caller's choice (checked there: one row, signed grid, plain blobs)
         return bits == 8 ? launch_dot<8>(a, kpw, grid, waves, st) : launch_dot<4>(a, kpw, grid, waves, st);
-    if (M > AGQ_DECODE_MAX_M) {   // row groups (the caller has checked: fp16 input, plain blobs)
+    if (pairs) {   // (more than sixteen rows: the caller has checked for fp16 input and plain blobs)
         const unsigned groups = (unsigned)((M + 15) / 16);
         if (zp) return launch_rg<XK_F16_Z>(a, kpw, grid, groups, waves, lds, st);
         return launch_rg<XK_F16>(a, kpw, grid, groups, waves, lds, st);

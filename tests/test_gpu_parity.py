@@ -1347,3 +1347,23 @@ def test_tiled_output_rows_off_the_16_byte_grid(agq, oracle, M, N, pitch):
     yh = host(ybuf)
     assert_f16_close(yh[rows][:, :N], y_want, "y")
     assert np.all(yh[:M, N:] == np.float16(-5.0)) and np.all(yh[M] == np.float16(-5.0)), "wrote past a row"
+
+
+@pytest.mark.parametrize("M,K,Ns,bits,zp", [(5, 8320, [4112], 8, 0), (8, 8320, [4100], 4, 9), (9, 9216, [4097], 8, 131),
+                                            (16, 8320, [2000, 2008, 300], 8, 0), (13, 13824, [4128], 4, 0)])
+def test_decode_tile_pairs_on_long_k(agq, oracle, M, K, Ns, bits, zp):
+    """Five to sixteen rows, K beyond 8192 and more than 256 channel tiles: two tiles per workgroup.  Odd tile counts, widths
+    that end inside a tile, several projections."""
+    x = synth.make_activation(M, K, 4, 700 + M)
+    e = oracle.calibrate_act_exp(x, bits) + (1 if zp else 0)
+    cols = lambda N: sorted({0, 15, 16, 31, 32, N // 2, N - 17, N - 2, N - 1})  # noqa: E731
+    ws = [synth.make_weight_q4(N, K, 700 + N) for N in Ns]
+    accs = [torch.full((M, N), -7, dtype=torch.int32, device="cuda") for N in Ns]
+    fn = agq.gemm_w4a8_multi if bits == 8 else agq.gemm_w4a4_multi
+    ys = fn(dev(x), e, [(agq.pack_w4(dev(wq)), dev(sw), N, None, acc) for (wq, sw), N, acc in zip(ws, Ns, accs)], K, zp=zp)
+    for (wq, sw), N, acc, y in zip(ws, Ns, accs, ys):
+        c = cols(N)
+        acc_w, y_w = oracle.linear_w4(x, bits, e, zp, wq[c], sw[c])
+        assert np.array_equal(host(acc)[:, c].astype(np.int64), acc_w)
+        assert_f16_close(host(y)[:, c], y_w, "y")
+        assert not (host(acc) == -7).all(axis=0).any()       # every column was written
