@@ -19,6 +19,34 @@ inline size_t codes_bytes(int64_t M, int64_t K) { return (size_t)((M + 127) / 12
 
 }  // namespace
 
+namespace {
+
+// Which kernel a call of plain blobs takes: tiles of the tiled kernel in one of its variants, or the weight-streaming kernel.
+struct Route {
+    bool tiles;
+    AgqSplitPlan plan;
+    AgqTiledChoice choice;
+};
+
+Route route(int x_kind, int64_t M, int64_t K, const agq_proj *projs, int count, size_t workspace_bytes) {
+    // With few tiles and a long K the tiled kernel splits the tiles' K steps over workgroups, if the
+    // caller's workspace has the room for the partial tiles behind the codes.
+    int64_t tiles_n = 0, wg_pairs = 0, n_sum = 0;
+    for (int p = 0; p < count; ++p) {
+        tiles_n += (projs[p].N + 127) / 128;
+        wg_pairs += (projs[p].N + 31) / 32;
+        n_sum += projs[p].N;
+    }
+    Route r = {false, agq_tiled_split_plan(M, tiles_n, K / 128, true), {}};
+    if (workspace_bytes < codes_bytes(M, K) + r.plan.bytes) r.plan = agq_tiled_split_plan(M, tiles_n, K / 128, false);
+    r.choice = agq_tiled_choose(M, tiles_n, K / 128, r.plan);
+    r.tiles = M > AGQ_DECODE_MAX_M && !agq_decode_row_groups(x_kind, M, K, n_sum, wg_pairs, r.choice.cost_ns);
+    return r;
+}
+
+}  // namespace
+
+
 // The linear layer behind every agq_gemm_w4a* call.  check_only: run the argument checks (host only) and return.
 int agq_gemm_w4_run(int bits, const void *x, int x_kind, int64_t M, int64_t K, int64_t ldx, int e, int zp,
                     const agq_proj *projs, int count, void *workspace, size_t workspace_bytes, void *stream,
@@ -53,25 +81,26 @@ int agq_gemm_w4_run(int bits, const void *x, int x_kind, int64_t M, int64_t K, i
         if (workspace_bytes < need) return AGQ_ESIZE;
     }
     if (check_only) return AGQ_OK;
-    // With few tiles and a long K the tiled kernel splits the tiles' K steps over workgroups, if the
-    // caller's workspace has the room for the partial tiles behind the codes.
-    int64_t tiles_n = 0, wg_pairs = 0;
-    for (int p = 0; p < count; ++p) {
-        tiles_n += (projs[p].N + 127) / 128;
-        wg_pairs += (projs[p].N + 31) / 32;
-    }
-    AgqSplitPlan plan = agq_tiled_split_plan(M, tiles_n, K / 128, true);
-    if (workspace_bytes < need + plan.bytes) plan = agq_tiled_split_plan(M, tiles_n, K / 128, false);
-    const AgqTiledChoice choice = agq_tiled_choose(M, tiles_n, K / 128, plan);
-    if (M <= AGQ_DECODE_MAX_M || agq_decode_row_groups(x_kind, M, K, n_sum, wg_pairs, choice.cost_ns))
+    const Route r = route(x_kind, M, K, projs, count, workspace_bytes);
+    if (!r.tiles)
         return hip_status(agq_launch_gemm_decode(x, x_kind, bits, M, K, ldx, e, zp, projs, count, -1, stream));
 
     // many tokens: lay the codes out in MFMA operand order once (quantizing on the
     // way when x is fp16), then run the tiled kernel for all projections on that copy
-    void *const split_ws = static_cast<char *>(workspace) + codes_bytes(M, K);
     if (agq_launch_prepack_act(x, x_kind, bits, M, K, ldx, e, zp, workspace, stream)) return AGQ_EHIP;
-    return hip_status(
-        agq_launch_gemm_tiled(workspace, M, K, e, agq_zp_corr(bits, zp), projs, count, -1, choice.variant, plan, split_ws, stream));
+    return hip_status(agq_launch_gemm_tiled(workspace, M, K, e, agq_zp_corr(bits, zp), projs, count, -1, r.choice.variant, r.plan,
+                                            static_cast<char *>(workspace) + codes_bytes(M, K), stream));
+}
+
+bool agq_gemm_takes_tiles(int64_t M, int64_t K, const struct agq_proj *projs, int count, size_t workspace_bytes) {
+    return workspace_bytes >= codes_bytes(M, K) && route(AGQ_X_F16, M, K, projs, count, workspace_bytes).tiles;
+}
+
+int agq_gemm_w4_tiles(int64_t M, int64_t K, int e, const struct agq_proj *projs, int count, void *workspace,
+                      size_t workspace_bytes, void *stream) {
+    const Route r = route(AGQ_X_F16, M, K, projs, count, workspace_bytes);
+    return hip_status(agq_launch_gemm_tiled(workspace, M, K, e, 0, projs, count, -1, r.choice.variant, r.plan,
+                                            static_cast<char *>(workspace) + codes_bytes(M, K), stream));
 }
 
 namespace {
@@ -332,7 +361,7 @@ int agq_prune_tokens(const int32_t *score, int64_t S, int64_t n_keep, const void
     if (!score || !x_f16) return AGQ_EINVAL;
     if (n_keep == 0) return AGQ_OK;
     if (!idx_out || !x_out_f16 || !aligned16(x_f16) || !aligned16(x_out_f16)) return AGQ_EINVAL;
-    return hip_status(agq_launch_prune(score, S, n_keep, x_f16, d, idx_out, x_out_f16, stream));
+    return hip_status(agq_launch_prune(score, S, n_keep, x_f16, d, idx_out, x_out_f16, AgqCodes(), stream));
 }
 
 }  // extern "C"

@@ -15,6 +15,8 @@
 #include "agq_device.h"
 #include "agq_internal.h"
 
+AgqQuant agq_make_quant_signed(int bits, int e, int zp);   // agq_quant.hip
+
 #include <type_traits>
 
 typedef _Float16 agq_v8h __attribute__((ext_vector_type(8)));
@@ -427,6 +429,17 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint4 *__restric
     for (int64_t c = threadIdx.x; c < d8; c += blockDim.x) out[(int64_t)blockIdx.x * d8 + c] = x[src * d8 + c];
 }
 
+// the same, and the rows' Eq.2 codes in the operand order of the tiled GEMM
+__global__ __launch_bounds__(256) void gather_codes_kernel(const uint4 *__restrict__ x, const int32_t *__restrict__ idx,
+                                                            int d8, uint4 *__restrict__ out, const AgqQuant q, char *__restrict__ tiles) {
+    const int r = blockIdx.x, src = idx[r];
+    for (int c = threadIdx.x; c < d8; c += 256) {
+        const uint4 v = x[(int64_t)src * d8 + c];
+        out[(int64_t)r * d8 + c] = v;
+        *reinterpret_cast<uint2 *>(tiles + agq_code_offset(r, c, d8 >> 4)) = agq_quant8<true>(v, q);
+    }
+}
+
 }  // namespace
 
 int agq_launch_log2_attn(const void *p, int64_t H, int64_t S, int64_t D, int causal, int qmax, const int8_t *vq,
@@ -466,9 +479,13 @@ int agq_launch_log2_attn(const void *p, int64_t H, int64_t S, int64_t D, int cau
 }
 
 int agq_launch_prune(const int32_t *score, int64_t S, int64_t n_keep, const void *x, int64_t d, int32_t *idx,
-                     void *x_out, void *stream) {
+                     void *x_out, const AgqCodes &codes, void *stream) {
     hipStream_t st = (hipStream_t)stream;
     prune_select_kernel<<<1, kSelThreads, 0, st>>>(score, (int)S, (int)n_keep, idx);
-    gather_rows_kernel<<<(unsigned)n_keep, 256, 0, st>>>((const uint4 *)x, idx, d / 8, (uint4 *)x_out);
+    if (codes.tiles)
+        gather_codes_kernel<<<(unsigned)n_keep, 256, 0, st>>>((const uint4 *)x, idx, (int)(d / 8), (uint4 *)x_out,
+                                                              agq_make_quant_signed(codes.bits, codes.e, 0), (char *)codes.tiles);
+    else
+        gather_rows_kernel<<<(unsigned)n_keep, 256, 0, st>>>((const uint4 *)x, idx, d / 8, (uint4 *)x_out);
     return (int)hipGetLastError();
 }

@@ -9,6 +9,8 @@
 #include "agq_device.h"
 #include "agq_internal.h"
 
+AgqQuant agq_make_quant_signed(int bits, int e, int zp);   // agq_quant.hip
+
 namespace {
 
 // float64 -> fp16, round to nearest even in ONE step.  The hardware converts
@@ -42,12 +44,14 @@ constexpr int kNormCache = 4;   // rows up to 4 * 256 * 8 = 8192 elements stay i
 // y[r,:] = x1[r,:] * g / sqrt(mean(x1[r,:]^2) + eps), x1 = x (ADD == false) or
 // fp16(res[idx[r],:] + x[r,:]) (ADD == true, x1 also written out, with the positions
 // of the surviving rows).
-template <bool ADD>
+// CODES: the Eq.2 codes of y as well, in the operand order of the tiled GEMM (q, tiles).
+template <bool ADD, bool CODES>
 __global__ __launch_bounds__(kNormThreads) void rmsnorm_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ res,
                                                               const int32_t *__restrict__ idx, const uint16_t *__restrict__ g,
                                                               uint16_t *__restrict__ x1_out, uint16_t *__restrict__ y, int d,
                                                               double eps, const int32_t *__restrict__ pos,
-                                                              int32_t *__restrict__ pos_out, int32_t *__restrict__ idx_out) {
+                                                              int32_t *__restrict__ pos_out, int32_t *__restrict__ idx_out,
+                                                              const AgqQuant q, char *__restrict__ tiles) {
     const int r = blockIdx.x, tid = threadIdx.x;
     const int src = (ADD && idx) ? idx[r] : r;
     const uint16_t *xr = x + (size_t)r * d;
@@ -111,6 +115,8 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_kernel(const uint16_t *_
 #pragma unroll
             for (int i = 0; i < 8; ++i) o.v[i] = d2h((h2d(cache[it].v[i]) * h2d(gg.v[i])) * inv);
             store8(y + (size_t)r * d + c * 8, o);
+            if (CODES)
+                *reinterpret_cast<uint2 *>(tiles + agq_code_offset(r, c, d >> 7)) = agq_quant8<true>(__builtin_bit_cast(uint4, o), q);
         }
     }
     for (int c = tid + kNormCache * kNormThreads; c < nchunk; c += kNormThreads) {
@@ -119,6 +125,8 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_kernel(const uint16_t *_
 #pragma unroll
         for (int i = 0; i < 8; ++i) o.v[i] = d2h((h2d(h.v[i]) * h2d(gg.v[i])) * inv);
         store8(y + (size_t)r * d + c * 8, o);
+        if (CODES)
+            *reinterpret_cast<uint2 *>(tiles + agq_code_offset(r, c, d >> 7)) = agq_quant8<true>(__builtin_bit_cast(uint4, o), q);
     }
 }
 
@@ -214,6 +222,25 @@ __global__ __launch_bounds__(256) void swiglu_kernel(const uint16_t *__restrict_
     store8(out + c * 8, o);
 }
 
+// the same over rows of F8 chunks (grid: chunks of a row, rows), with the rows' Eq.2 codes in the operand order of the
+// tiled GEMM
+__global__ __launch_bounds__(256) void swiglu_codes_kernel(const uint16_t *__restrict__ gate, const uint16_t *__restrict__ up,
+                                                           uint16_t *__restrict__ out, int F8, const AgqQuant q,
+                                                           char *__restrict__ tiles) {
+    const int c = blockIdx.x * 256 + threadIdx.x, r = blockIdx.y;
+    if (c >= F8) return;
+    const size_t at = ((size_t)r * F8 + c) * 8;
+    const Half8 g = load8(gate + at), u = load8(up + at);
+    Half8 o;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const double z = h2d(g.v[i]);
+        o.v[i] = d2h(z / (1.0 + exp(-z)) * h2d(u.v[i]));
+    }
+    store8(out + at, o);
+    *reinterpret_cast<uint2 *>(tiles + agq_code_offset(r, c, F8 >> 4)) = agq_quant8<true>(__builtin_bit_cast(uint4, o), q);
+}
+
 __global__ __launch_bounds__(256) void add_kernel(const uint16_t *__restrict__ a, const uint16_t *__restrict__ b,
                                                   uint16_t *__restrict__ out, size_t nchunk) {
     const size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
@@ -228,17 +255,16 @@ __global__ __launch_bounds__(256) void add_kernel(const uint16_t *__restrict__ a
 }  // namespace
 
 int agq_launch_rmsnorm(const void *x, const void *res, const int32_t *idx, const void *g, void *x1_out, void *y, int64_t rows,
-                       int64_t d, double eps, const int32_t *pos, int32_t *pos_out, int32_t *idx_out, void *stream) {
+                       int64_t d, double eps, const int32_t *pos, int32_t *pos_out, int32_t *idx_out, const AgqCodes &codes,
+                       void *stream) {
     if (rows == 0) return 0;
     hipStream_t st = (hipStream_t)stream;
-    if (res)
-        rmsnorm_kernel<true><<<(unsigned)rows, kNormThreads, 0, st>>>((const uint16_t *)x, (const uint16_t *)res, idx,
-                                                                      (const uint16_t *)g, (uint16_t *)x1_out, (uint16_t *)y,
-                                                                      (int)d, eps, pos, pos_out, idx_out);
-    else
-        rmsnorm_kernel<false><<<(unsigned)rows, kNormThreads, 0, st>>>((const uint16_t *)x, nullptr, nullptr, (const uint16_t *)g,
-                                                                       nullptr, (uint16_t *)y, (int)d, eps, nullptr, nullptr,
-                                                                       nullptr);
+    const AgqQuant q = codes.tiles ? agq_make_quant_signed(codes.bits, codes.e, 0) : AgqQuant{};
+    const auto kernel = res ? (codes.tiles ? rmsnorm_kernel<true, true> : rmsnorm_kernel<true, false>)
+                            : (codes.tiles ? rmsnorm_kernel<false, true> : rmsnorm_kernel<false, false>);
+    kernel<<<(unsigned)rows, kNormThreads, 0, st>>>((const uint16_t *)x, (const uint16_t *)res, idx, (const uint16_t *)g,
+                                                    (uint16_t *)x1_out, (uint16_t *)y, (int)d, eps, pos, pos_out, idx_out, q,
+                                                    (char *)codes.tiles);
     return (int)hipGetLastError();
 }
 
@@ -267,6 +293,14 @@ int agq_launch_swiglu(const void *gate, const void *up, void *out, int64_t n, vo
     const size_t nchunk = (size_t)n / 8;
     swiglu_kernel<<<(unsigned)((nchunk + 255) / 256), 256, 0, (hipStream_t)stream>>>((const uint16_t *)gate, (const uint16_t *)up,
                                                                                    (uint16_t *)out, nchunk);
+    return (int)hipGetLastError();
+}
+
+int agq_launch_swiglu_rows(const void *gate, const void *up, void *out, int64_t rows, int64_t F, const AgqCodes &codes, void *stream) {
+    const int F8 = (int)(F / 8);
+    swiglu_codes_kernel<<<dim3((unsigned)((F8 + 255) / 256), (unsigned)rows), 256, 0, (hipStream_t)stream>>>(
+        (const uint16_t *)gate, (const uint16_t *)up, (uint16_t *)out, F8, agq_make_quant_signed(codes.bits, codes.e, 0),
+        (char *)codes.tiles);
     return (int)hipGetLastError();
 }
 

@@ -11,6 +11,11 @@ namespace {
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 constexpr int64_t kMaxTokens = 8192;        // agq_prune_tokens' limit (calls that prune)
+// Up to this many rows the operator in front of a projection (RMSNorm, SwiGLU, the gather of the surviving rows) writes the
+// tiled GEMM's codes itself and the pre-pass, a launch of 3 to 5 us at these sizes, is left out.  Two blocks of 512 tokens
+// 357 -> 347 us, four of 300 tokens 564 -> 540, four narrow ones of 212 tokens 277 -> 257, one of 1024 tokens 284 -> 280; at
+// 2048 tokens the operators' scattered 8-byte stores cost more than the pre-pass's own trip through memory (750 -> 758).
+constexpr int64_t kFuseRows = 1536;
 constexpr int64_t kMaxAttnTokens = 32768;   // the attention call's limit (calls that keep every token)
 constexpr int64_t kMaxWidth = 65536;   // the GEMMs' limit on K
 constexpr int64_t kMaxTripWidth = 32768;   // and with TRIP blobs
@@ -133,14 +138,32 @@ int run(const agq_block *b, int *exps, bool calibrate, const void *x, const int3
         return AGQ_OK;
     };
 
+    // A projection site behind an operator of few rows: the operator writes the codes, in the order the tiled kernel wants
+    // them, into that kernel's workspace, and the pre-pass is left out (see kFuseRows).
+    auto codes_for = [&](int bits, int which, int n_extra, int64_t M, int64_t K, const agq_proj *projs, int count) {
+        AgqCodes c;
+        if (!calibrate && n_extra < 0 && M <= kFuseRows && agq_gemm_takes_tiles(M, K, projs, count, gws_bytes)) {
+            c.tiles = gws;
+            c.bits = bits;
+            c.e = exps[which];
+        }
+        return c;
+    };
+    auto project = [&](const AgqCodes &c, int bits, const void *act, int64_t M, int64_t K, int which, int n_extra,
+                       const agq_proj *projs, int count) -> int {
+        if (c.tiles) return agq_gemm_w4_tiles(M, K, exps[which], projs, count, gws, gws_bytes, stream);
+        return site_gemm(bits, act, M, K, exps[which], n_extra, projs, count, gws, gws_bytes, stream);
+    };
+
     // attention half
-    AGQ_TRY_HIP(agq_launch_rmsnorm(x, nullptr, nullptr, b->g_attn_f16, nullptr, at(L.h1), S, d, b->rms_eps, nullptr, nullptr,
-                                   nullptr, stream));
-    AGQ_TRY(exp_for(E_ATTN_IN, at(L.h1), S, d, 8));
     const agq_proj qkv[3] = {{b->w_q, b->s_q, d, at(L.q), d, nullptr},
                              {b->w_k, b->s_k, d, at(L.k), d, nullptr},
                              {b->w_v, b->s_v, d, at(L.v), d, nullptr}};
-    AGQ_TRY(site_gemm(8, at(L.h1), S, d, exps[E_ATTN_IN], b->trip_attn_in, qkv, 3, gws, gws_bytes, stream));
+    const AgqCodes h1_codes = codes_for(8, E_ATTN_IN, b->trip_attn_in, S, d, qkv, 3);
+    AGQ_TRY_HIP(agq_launch_rmsnorm(x, nullptr, nullptr, b->g_attn_f16, nullptr, at(L.h1), S, d, b->rms_eps, nullptr, nullptr,
+                                   nullptr, h1_codes, stream));
+    AGQ_TRY(exp_for(E_ATTN_IN, at(L.h1), S, d, 8));
+    AGQ_TRY(project(h1_codes, 8, at(L.h1), S, d, E_ATTN_IN, b->trip_attn_in, qkv, 3));
     if (calibrate) {
         AGQ_TRY_HIP(agq_launch_rope(at(L.q), at(L.k), at(L.v), S, L.S_pad, H, D, pos, cos_t, sin_t, P, 0, 0, 0, nullptr,
                                     nullptr, nullptr, at(L.q_rot), at(L.k_rot), nullptr, stream));
@@ -159,22 +182,28 @@ int run(const agq_block *b, int *exps, bool calibrate, const void *x, const int3
     // pruning (Eq.4) and the projection after attention on the surviving rows
     int32_t *idx = static_cast<int32_t *>(at(L.idx));
     const bool pruned = n_keep < S;
-    if (pruned) AGQ_TRY(agq_prune_tokens(score, S, n_keep, at(L.o), d, idx, at(L.o_kept), stream));
-    AGQ_TRY(exp_for(E_ATTN_OUT, at(L.o_kept), n_keep, d, b->bits_attn_out));
     const agq_proj op = {b->w_o, b->s_o, d, at(L.attn_out), d, nullptr};
-    AGQ_TRY(site_gemm(b->bits_attn_out, at(L.o_kept), n_keep, d, exps[E_ATTN_OUT], b->trip_attn_out, &op, 1, gws, gws_bytes,
-                      stream));
+    AgqCodes o_codes;
+    if (pruned) {
+        o_codes = codes_for(b->bits_attn_out, E_ATTN_OUT, b->trip_attn_out, n_keep, d, &op, 1);
+        AGQ_TRY_HIP(agq_launch_prune(score, S, n_keep, at(L.o), d, idx, at(L.o_kept), o_codes, stream));
+    }
+    AGQ_TRY(exp_for(E_ATTN_OUT, at(L.o_kept), n_keep, d, b->bits_attn_out));
+    AGQ_TRY(project(o_codes, b->bits_attn_out, at(L.o_kept), n_keep, d, E_ATTN_OUT, b->trip_attn_out, &op, 1));
 
     // MLP half: x1 = x[idx] + attn_out, h2 = RMSNorm(x1)
-    AGQ_TRY_HIP(agq_launch_rmsnorm(at(L.attn_out), x, pruned ? idx : nullptr, b->g_mlp_f16, at(L.x1), at(L.h2), n_keep, d,
-                                   b->rms_eps, pos, pos_out, pruned ? nullptr : idx, stream));
-    AGQ_TRY(exp_for(E_MLP_IN, at(L.h2), n_keep, d, 8));
     const agq_proj gu[2] = {{b->w_gate, b->s_gate, F, at(L.gate), F, nullptr}, {b->w_up, b->s_up, F, at(L.up), F, nullptr}};
-    AGQ_TRY(site_gemm(8, at(L.h2), n_keep, d, exps[E_MLP_IN], b->trip_mlp_in, gu, 2, gws, gws_bytes, stream));
-    AGQ_TRY_HIP(agq_launch_swiglu(at(L.gate), at(L.up), at(L.act), n_keep * F, stream));
-    AGQ_TRY(exp_for(E_MLP_ACT, at(L.act), n_keep, F, 8));
+    const AgqCodes h2_codes = codes_for(8, E_MLP_IN, b->trip_mlp_in, n_keep, d, gu, 2);
+    AGQ_TRY_HIP(agq_launch_rmsnorm(at(L.attn_out), x, pruned ? idx : nullptr, b->g_mlp_f16, at(L.x1), at(L.h2), n_keep, d,
+                                   b->rms_eps, pos, pos_out, pruned ? nullptr : idx, h2_codes, stream));
+    AGQ_TRY(exp_for(E_MLP_IN, at(L.h2), n_keep, d, 8));
+    AGQ_TRY(project(h2_codes, 8, at(L.h2), n_keep, d, E_MLP_IN, b->trip_mlp_in, gu, 2));
     const agq_proj dp = {b->w_down, b->s_down, d, at(L.down), d, nullptr};
-    AGQ_TRY(site_gemm(8, at(L.act), n_keep, F, exps[E_MLP_ACT], b->trip_mlp_act, &dp, 1, gws, gws_bytes, stream));
+    const AgqCodes act_codes = codes_for(8, E_MLP_ACT, b->trip_mlp_act, n_keep, F, &dp, 1);
+    if (act_codes.tiles) AGQ_TRY_HIP(agq_launch_swiglu_rows(at(L.gate), at(L.up), at(L.act), n_keep, F, act_codes, stream));
+    else AGQ_TRY_HIP(agq_launch_swiglu(at(L.gate), at(L.up), at(L.act), n_keep * F, stream));
+    AGQ_TRY(exp_for(E_MLP_ACT, at(L.act), n_keep, F, 8));
+    AGQ_TRY(project(act_codes, 8, at(L.act), n_keep, F, E_MLP_ACT, b->trip_mlp_act, &dp, 1));
     AGQ_TRY_HIP(agq_launch_add(at(L.x1), at(L.down), x_out, n_keep * d, stream));
     return AGQ_OK;
 }
@@ -192,7 +221,7 @@ int agq_rmsnorm(const void *x_f16, const void *res_f16, const int32_t *idx, cons
     if (!aligned16(x_f16) || !aligned16(g_f16) || !aligned16(y_f16) || !aligned16(res_f16) || !aligned16(sum_out_f16))
         return AGQ_EINVAL;
     return agq_launch_rmsnorm(x_f16, res_f16, idx, g_f16, sum_out_f16, y_f16, rows, d, eps, nullptr, nullptr, nullptr,
-                              stream) ? AGQ_EHIP : AGQ_OK;
+                              AgqCodes(), stream) ? AGQ_EHIP : AGQ_OK;
 }
 
 int agq_rope_quantize(const void *q_f16, const void *k_f16, const void *v_f16, int64_t S, int64_t H, int64_t D,

@@ -89,6 +89,13 @@ __device__ __forceinline__ uint2 agq_quant8(const uint4 &h, const AgqQuant &q) {
     return out;
 }
 
+// Where the eight codes of values 8 c .. 8 c + 7 of token row r lie in the tiled kernel's operand order (byte offset;
+// KT = K / 128): stage (r / 128, step), 32-token tile, k-block of 32, lane 32 (k-half) + token, 16 bytes per lane.
+__device__ __forceinline__ size_t agq_code_offset(int r, int c, int KT) {
+    const int seg = (c & 15) >> 1;                       // sixteen values wide
+    return ((((size_t)(r >> 7) * KT + (c >> 4)) * 16 + ((r >> 5) & 3) * 4 + (seg >> 1)) * 64 + (seg & 1) * 32 + (r & 31)) * 16 + (c & 1) * 8;
+}
+
 // A word of the packed weight blob holds eight 4-bit weights: the low nibbles of
 // its four bytes belong to MFMA step 0, the high nibbles to step 1.  Moving a
 // nibble into the top half of its byte yields the weight times 16 as an int8

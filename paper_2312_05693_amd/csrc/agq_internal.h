@@ -151,6 +151,11 @@ struct agq_proj;
 int agq_gemm_w4_run(int bits, const void *x, int x_kind, int64_t M, int64_t K, int64_t ldx, int e, int zp,
                     const struct agq_proj *projs, int count, void *workspace, size_t workspace_bytes, void *stream,
                     bool check_only);
+// The same in two halves, for a producer that writes the tiled kernel's codes itself (fp16 values through Eq.2, signed
+// grid): whether the call would take that kernel, and the call on codes that lie in the workspace already.
+bool agq_gemm_takes_tiles(int64_t M, int64_t K, const struct agq_proj *projs, int count, size_t workspace_bytes);
+int agq_gemm_w4_tiles(int64_t M, int64_t K, int e, const struct agq_proj *projs, int count, void *workspace,
+                      size_t workspace_bytes, void *stream);
 // n_extra >= 0 with TRIP blobs (all packed with the same factors, fp16 input); -1 for plain blobs
 int agq_launch_gemm_decode(const void *x, int x_kind, int bits, int64_t M, int64_t K, int64_t ldx, int e, int zp,
                            const struct agq_proj *projs, int count, int n_extra, void *stream);
@@ -174,19 +179,27 @@ int agq_launch_log2_attn(const void *p, int64_t H, int64_t S, int64_t D, int cau
                          const int8_t *vq, int e_v, void *o, void *codes, int32_t *score, void *stream);
 int agq_launch_qk_log2_attn(const int8_t *q, const int8_t *k, const int8_t *v, int64_t H, int64_t S, int64_t D, int causal,
                             int qmax, int e_q, int e_k, int e_v, void *o, void *codes, int32_t *score, void *stream);
+// codes (optional): where Eq.2's codes of every value go as well, in the operand order of the tiled GEMM
+struct AgqCodes {
+    void *tiles = nullptr;
+    int bits = 8, e = 0;
+};
 int agq_launch_prune(const int32_t *score, int64_t S, int64_t n_keep, const void *x, int64_t d,
-                     int32_t *idx, void *x_out, void *stream);
+                     int32_t *idx, void *x_out, const AgqCodes &codes, void *stream);
 
 // ---- fp16 operators of a block (agq_block.hip)
 // res != NULL: x1 = fp16(res[idx ? idx[r] : r] + x[r]) is written to x1_out and normalised; pos_out / idx_out
 // (optional) receive pos[...] and the source row of every output row
 int agq_launch_rmsnorm(const void *x, const void *res, const int32_t *idx, const void *g, void *x1_out, void *y, int64_t rows,
-                       int64_t d, double eps, const int32_t *pos, int32_t *pos_out, int32_t *idx_out, void *stream);
+                       int64_t d, double eps, const int32_t *pos, int32_t *pos_out, int32_t *idx_out, const AgqCodes &codes,
+                       void *stream);
 // q_q != NULL: rotate q and k, Eq.2 on q, k, v, int8 [H,S_pad,D] out (and zero[0..S_pad) = 0 when given);
 // q_q == NULL: rotated fp16 q, k to q_rot, k_rot
 int agq_launch_rope(const void *q, const void *k, const void *v, int64_t S, int64_t S_pad, int64_t H, int64_t D,
                     const int32_t *pos, const float *cos_t, const float *sin_t, int64_t P, int e_q, int e_k, int e_v,
                     int8_t *q_q, int8_t *k_q, int8_t *v_q, void *q_rot, void *k_rot, int32_t *zero, void *stream);
 int agq_launch_swiglu(const void *gate, const void *up, void *out, int64_t n, void *stream);
+// the same for rows of F values, with codes
+int agq_launch_swiglu_rows(const void *gate, const void *up, void *out, int64_t rows, int64_t F, const AgqCodes &codes, void *stream);
 int agq_launch_add(const void *a, const void *b, void *out, int64_t n, void *stream);
 int agq_read_i32(const int32_t *dev, int32_t *host, int n, void *stream);

@@ -417,3 +417,11 @@ def test_block_longest_sequences(agq, oracle, blk_oracle):
     (here 8200, padded to 8320 for the attention call), on a narrow block."""
     check_block_sampled(agq, oracle, blk_oracle, 8192, 128, 2, 128, 5000, seed=14)
     check_block_sampled(agq, oracle, blk_oracle, 8200, 128, 2, 128, 8200, seed=15)
+
+
+@pytest.mark.parametrize("S,d,H,F,keep,qmax,bits_o", [(400, 512, 4, 1152, 300, 15, 4), (700, 256, 2, 2176, 259, 15, 8),
+                                                      (290, 384, 3, 640, 290, 15, 4)])
+def test_block_with_codes_from_the_operators(agq, oracle, blk_oracle, S, d, H, F, keep, qmax, bits_o):
+    """More than 256 rows in front of every projection, so each goes to the tiled GEMM: RMSNorm, SwiGLU and (with pruning) the
+    gather write its codes.  Row counts that end inside a 32-token tile, widths of 2 to 17 K steps."""
+    test_block_stage_by_stage(agq, oracle, blk_oracle, S, d, H, F, keep, qmax, bits_o)
