@@ -45,9 +45,9 @@ PREFILL_M = 2048
 # source has changed since, the figure is reported as null (stale) instead of a number that no longer holds.
 #   name: (bytes per launch, profiles/ file, source file, first 12 hex digits of the source's sha256)
 MEASURED_TRAFFIC = {
-    "decode": (26.3e6, "profiles/gemm_decode_llama7b_sweep.md", "agq_gemm_decode.hip", "24fa7e62b535"),
-    "attn": (252.3e6, "profiles/log2_attn_llama13b_block.md", "agq_attn.hip", "e6b7cee61965"),
-    "tiled": (169.2e6, "profiles/gemm_decode_llama7b_sweep.md", "agq_gemm_tiled.hip", "11177da4338a"),
+    "decode": (26.3e6, "profiles/gemm_decode_llama7b_sweep.md", "agq_gemm_decode.hip", "daa8f56b4336"),
+    "attn": (252.6e6, "profiles/log2_attn_llama13b_block.md", "agq_attn.hip", "93d0e33be0e8"),
+    "tiled": (187.5e6, "profiles/gemm_decode_llama7b_sweep.md", "agq_gemm_tiled.hip", "9316c4b6d7f9"),
 }
 
 
