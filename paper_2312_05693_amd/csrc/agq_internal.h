@@ -46,10 +46,10 @@ static inline AgqTripLayout agq_trip_layout(int64_t N, int64_t K, int E) {
 
 // tokens up to which the weight-streaming kernel is used
 #define AGQ_DECODE_MAX_M 16
-// K split of the tiled kernel.  A workgroup that has its CU (or its half of one) to itself takes about 470 ns per
-// K step (twice the time of its MFMAs: a single wavefront per SIMD cannot cover its own waits), however few
-// workgroups the launch has: with few 128 x 128 tiles and a long K most CUs idle while a few walk K.  Then `splits` workgroups share a tile's K steps (at least four each,
-// at most one workgroup per CU in all) and leave int32 partial tiles behind the activation codes in the workspace,
+// K split of the tiled kernel.  A K step of a workgroup takes about as long however few workgroups the launch has (the
+// plan counts 470 ns: a single wavefront per SIMD cannot cover its own waits): with few 128 x 128 tiles and a long K
+// most CUs idle while a few walk K.  Then `splits` workgroups share a tile's K steps (at least four each, at most one
+// workgroup per CU in all) and leave int32 partial tiles behind the activation codes in the workspace,
 // which a second kernel adds up.  That costs about 2 us for the launch and 0.45 us per MB of partial tiles
 // (written, read back); the plan is the split count with the smallest sum under this model (all measured on
 // MI355X).  M tokens, tiles_n = 128-wide column tiles of all projections of the call, KT = K steps (TRIP
@@ -95,8 +95,8 @@ static inline AgqSplitPlan agq_tiled_split_plan(int64_t M, int64_t tiles_n, int6
 //   4096 -> 22016    100 tokens 20.0 / - / 22.3 / 25.7, 213 tokens 31.3 / - / 33.0 / -, 300 tokens 42.2 / - / 41.5 / -
 //   5120 -> 5120     333 tokens 21.5 / - / 19.5 / 16.6, 1024 tokens 35.9 / - / 37.0 / -
 //   4096 -> 22016    1000 tokens 89 / - / 101 / -, 2048 tokens 157 / - / 186 / -
-// which the model reproduces to about 10 %.  (The split's own price above was fitted to resident weights and decides only
-// how many slices it would have.)
+// which the model reproduces to about 10 %.  (The 470 ns of the plan above are from an earlier schedule of the loop and
+// from resident weights; they decide how many slices a split would have and its room, not whether it is taken.)
 enum AgqTiledVariant { TILED_128, TILED_SPLIT, TILED_64, TILED_64X2 };
 struct AgqTiledChoice {
     AgqTiledVariant variant;
