@@ -452,7 +452,7 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // TL: tiles a workgroup holds at a time (its tiles are blockIdx.x + gridDim.x j, j = 0, 1, ...);
 // MULTI: more than TL tiles per workgroup, in rounds of TL: a slot is requested again, for the next round,
 // as soon as it has been multiplied, and the workgroup meets twice per round (the operands stay in registers).
-constexpr int kSliceMaxKT = 64;
+constexpr int kSliceMaxKT = AGQ_SLICE_MAX_KT;
 
 template <int KPW, int MP, int TL, bool ZP, bool MULTI>
 __global__ __launch_bounds__(1024) void gemm_decode_slice_kernel(const DecodeArgs a, int total_tiles) {
@@ -844,15 +844,8 @@ int agq_launch_gemm_decode(const void *x, int x_kind, int bits, int64_t M, int64
         singles += (int)((projs[p].N + 15) / 16);
         doubles += (int)((projs[p].N + 31) / 32);
     }
-    // A workgroup serves a pair of tiles in row groups (more than sixteen rows), and from five rows on with a K beyond the
-    // K-sliced kernel's when that saves a round: a workgroup of sixteen wavefronts then has its CU to itself, and every
-    // round loads and quantizes the whole activation again.  One tile against a pair per workgroup, K = 13824:
-    // N = 5120 (320 tiles) 16 rows 22.1 -> 15.4 us, 9 rows 18.9 -> 13.4, 8 rows 15.6 -> 13.1, 5 rows 14.3 -> 12.6;
-    // N = 8192 16 rows 24.7 -> 18.6; K = 28672, N = 8192, 16 rows 47.8 -> 34.1; three times 9216 -> 4096 26.2 -> 21.9.
-    // Where one round holds all tiles the pair is the slower form (half of the CUs idle), and below five rows a
-    // workgroup is small enough for two on a CU.
-    const bool pairs = M > AGQ_DECODE_MAX_M || (x_kind == 0 && !trip && M > 4 && a.KT > kSliceMaxKT &&
-                                                (doubles + 255) / 256 < (singles + 255) / 256);
+    // A workgroup serves a pair of tiles in row groups (more than sixteen rows), and where that saves time below
+    const bool pairs = M > AGQ_DECODE_MAX_M || agq_decode_pairs(x_kind, trip, M, a.KT, singles, doubles);
     int tiles = 0;
     for (int p = 0; p < kMaxProj; ++p) {
         const agq_proj &pr = projs[p < count ? p : count - 1];

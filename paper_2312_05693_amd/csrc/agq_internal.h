@@ -138,6 +138,25 @@ static inline bool agq_decode_row_groups(int x_kind, int64_t M, int64_t K, int64
     return read_ns <= tiled_ns;
 }
 
+// K steps up to which a launch of five to sixteen rows with several channel tiles per CU takes the K-sliced kernel
+#define AGQ_SLICE_MAX_KT 64
+// Whether a workgroup of the per-tile kernel serves a pair of channel tiles for five to sixteen rows (fp16 input, plain
+// blobs, a K beyond the K-sliced kernel's; more than sixteen rows always run in pairs).  The pair quantizes the activation
+// once for both tiles; with 256 CUs its tiles come in `pairs` rounds, single tiles in `ones`.
+// From nine rows on a workgroup of single tiles has its CU to itself, so every round saved counts: K = 11008, 16 rows,
+// N = 5120 (2 rounds -> 1) 19.1 -> 13.4 us, 9600 (3 -> 2) 28.1 -> 24.6, 16384 (4 -> 2) 39.3 -> 29.0, 16500 (5 -> 3) 45.1 ->
+// 36.0; 9 rows 24.8 -> 21.9 at 9600.  With five to eight rows two workgroups of single tiles share a CU, so one round of
+// pairs takes as long as two of them: pairs have to halve the rounds (K = 11008, 8 rows, N = 6000 13.6 -> 12.1 us, 16384
+// 28.0 -> 25.5, but 9600 19.3 -> 21.6 and 16500 30.2 -> 31.7), and at five and six rows, beyond one round of them, to do so
+// with the last two rounds of single tiles nearly full (5 rows, 16384 26.7 -> 25.8, 14000 24.0 -> 24.8).  Where one round
+// holds all single tiles the pair leaves half of the CUs idle.
+static inline bool agq_decode_pairs(int x_kind, bool trip, int64_t M, int64_t KT, int64_t tiles, int64_t tile_pairs) {
+    if (x_kind != 0 || trip || M <= 4 || M > AGQ_DECODE_MAX_M || KT <= AGQ_SLICE_MAX_KT) return false;
+    const int64_t ones = (tiles + 255) / 256, pairs = (tile_pairs + 255) / 256;
+    if (M > 8) return pairs < ones;
+    return 2 * pairs == ones && (pairs == 1 || M > 6 || tiles > ones * 256 - 128);
+}
+
 int agq_launch_calibrate(const void *x, int64_t M, int64_t K, int64_t ldx, int bits, int32_t *e_dev, void *stream);
 int agq_launch_quantize(const void *x, int64_t M, int64_t K, int64_t ldx, int bits, int e, int zp,
                         void *out, int64_t ld_out_bytes, int out_bits, void *stream);

@@ -1,10 +1,12 @@
-// Measurement aid for bench.py, built as its own small library (libagq_probe.so): not part of the product and
-// not linked into libagq.so.  Two kernels that bound what one launch of a weight-streaming kernel can reach on
+// Measurement aid for bench.py and the tests' view of the library's dispatch rules, built as its own small library
+// (libagq_probe.so): not part of the product and not linked into libagq.so.  Two kernels that bound what one launch of a weight-streaming kernel can reach on
 // the device at hand: a plain read of a buffer with the access pattern of the decode kernels (one coalesced
 // 16-byte load per lane and KiB, every load of a workgroup requested before the first is used), and an empty
 // kernel (the cost of a launch inside a replayed graph).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include "agq_internal.h"
 
 namespace {
 
@@ -89,4 +91,15 @@ extern "C" int agq_probe_mfma_i8(const void *a, const void *b, int workgroups, i
     probe_mfma_kernel<<<(unsigned)workgroups, 256, 0, (hipStream_t)stream>>>((const probe_v4i *)a, (const probe_v4i *)b,
                                                                             reps, (uint32_t *)sink);
     return hipGetLastError() == hipSuccess ? 0 : -3;
+}
+
+// Host only: whether 5 to 16 rows of fp16 input on plain blobs [N[p], K] run with two channel tiles per workgroup of the
+// per-tile kernel (1 / 0).
+extern "C" int agq_probe_decode_pairs(int64_t M, int64_t K, const int64_t *N, int count) {
+    int64_t tiles = 0, tile_pairs = 0;
+    for (int p = 0; p < count; ++p) {
+        tiles += (N[p] + 15) / 16;
+        tile_pairs += (N[p] + 31) / 32;
+    }
+    return agq_decode_pairs(0, false, M, agq_k_tiles(K), tiles, tile_pairs);
 }

@@ -346,3 +346,22 @@ def test_chain_argument_errors_need_no_gpu(lib):
     assert lib.agq_gemm_chain_run(None, None) == EINVAL and lib.agq_gemm_chain_run(4100, None) == EINVAL
     assert lib.agq_gemm_chain_status(None, None) == EINVAL
     assert lib.agq_status_string(-4) == b"a wait inside the kernel timed out"
+
+
+@pytest.fixture(scope="module")
+def probe(lib):
+    from paper_2312_05693_amd import build
+    return ctypes.CDLL(build.PROBE_LIB)
+
+
+@pytest.mark.parametrize("M,K,Ns,pairs", [
+    # more than 256 tiles of 16 channels, K beyond 8192; the measured winner on either side of every switch
+    (4, 11008, [5120], 0), (5, 11008, [4096], 0), (5, 11008, [5120], 1), (8, 20480, [4112], 1),
+    (5, 9216, [8208], 0), (8, 9216, [9000], 0), (8, 9216, [4096] * 3, 0), (9, 9216, [9000], 1), (16, 9216, [4096] * 3, 1),
+    (5, 9216, [16384], 1), (6, 11008, [14000], 0), (5, 11008, [12400], 0), (7, 11008, [12400], 1), (8, 14336, [14000], 1),
+    (8, 9216, [16500], 0), (5, 8448, [20000], 0), (16, 8448, [16500], 1), (5, 9216, [24576], 1), (8, 9216, [28000], 0),
+    (16, 8192, [5120], 0), (17, 9216, [9000], 0)])
+def test_rule_for_tile_pairs(probe, M, K, Ns, pairs):
+    """Five to eight rows: two workgroups of single tiles share a CU, so a pair per workgroup has to halve the rounds (three
+    rounds of single tiles against two of pairs were up to 19 % slower in pairs); from nine rows on any round saved counts."""
+    assert probe.agq_probe_decode_pairs(ctypes.c_int64(M), ctypes.c_int64(K), (ctypes.c_int64 * len(Ns))(*Ns), len(Ns)) == pairs

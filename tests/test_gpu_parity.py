@@ -1350,10 +1350,12 @@ def test_tiled_output_rows_off_the_16_byte_grid(agq, oracle, M, N, pitch):
 
 
 @pytest.mark.parametrize("M,K,Ns,bits,zp", [(5, 8320, [4112], 8, 0), (8, 8320, [4100], 4, 9), (9, 9216, [4097], 8, 131),
-                                            (16, 8320, [2000, 2008, 300], 8, 0), (13, 13824, [4128], 4, 0)])
+                                            (16, 8320, [2000, 2008, 300], 8, 0), (13, 13824, [4128], 4, 0),
+                                            (8, 8320, [8208], 8, 0), (9, 8320, [8200], 4, 5), (7, 8320, [12400], 8, 0)])
 def test_decode_tile_pairs_on_long_k(agq, oracle, M, K, Ns, bits, zp):
-    """Five to sixteen rows, K beyond 8192 and more than 256 channel tiles: two tiles per workgroup.  Odd tile counts, widths
-    that end inside a tile, several projections."""
+    """Five to sixteen rows, K beyond 8192 and more than 256 channel tiles: two tiles per workgroup where that saves time
+    ((8, 8320, 8208): three rounds of single tiles, which stay).  Odd tile counts, widths that end inside a tile, several
+    projections."""
     x = synth.make_activation(M, K, 4, 700 + M)
     e = oracle.calibrate_act_exp(x, bits) + (1 if zp else 0)
     cols = lambda N: sorted({0, 15, 16, 31, 32, N // 2, N - 17, N - 2, N - 1})  # noqa: E731
