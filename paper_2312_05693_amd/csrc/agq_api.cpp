@@ -14,38 +14,13 @@ inline int hip_status(int err) { return err == 0 ? AGQ_OK : AGQ_EHIP; }
 constexpr int64_t kMaxDim = (int64_t)1 << 30;
 constexpr int64_t kMaxAttnS = 32768;   // one head of P stays below 4 GiB: 32-bit offsets inside the kernel
 
-// int8 codes in operand order, tokens padded to the 128-row tile (a multiple of 16 KiB)
-inline size_t codes_bytes(int64_t M, int64_t K) { return (size_t)((M + 127) / 128) * 128 * (size_t)K; }
-
-}  // namespace
-
-namespace {
-
-// Which kernel a call of plain blobs takes: tiles of the tiled kernel in one of its variants, or the weight-streaming kernel.
-struct Route {
-    bool tiles;
-    AgqSplitPlan plan;
-    AgqTiledChoice choice;
-};
-
-Route route(int x_kind, int64_t M, int64_t K, const agq_proj *projs, int count, size_t workspace_bytes) {
-    // With few tiles and a long K the tiled kernel splits the tiles' K steps over workgroups, if the
-    // caller's workspace has the room for the partial tiles behind the codes.
-    int64_t tiles_n = 0, wg_pairs = 0, n_sum = 0;
-    for (int p = 0; p < count; ++p) {
-        tiles_n += (projs[p].N + 127) / 128;
-        wg_pairs += (projs[p].N + 31) / 32;
-        n_sum += projs[p].N;
-    }
-    Route r = {false, agq_tiled_split_plan(M, tiles_n, K / 128, true), {}};
-    if (workspace_bytes < codes_bytes(M, K) + r.plan.bytes) r.plan = agq_tiled_split_plan(M, tiles_n, K / 128, false);
-    r.choice = agq_tiled_choose(M, tiles_n, K / 128, r.plan);
-    r.tiles = M > AGQ_DECODE_MAX_M && !agq_decode_row_groups(x_kind, M, K, n_sum, wg_pairs, r.choice.cost_ns);
-    return r;
+AgqRoute route_of(int x_kind, int64_t M, int64_t K, const agq_proj *projs, int count, int n_extra, size_t workspace_bytes) {
+    int64_t N[AGQ_MAX_PROJ] = {};
+    for (int p = 0; p < count; ++p) N[p] = projs[p].N;
+    return agq_gemm_route(x_kind, M, K, N, count, n_extra, workspace_bytes);
 }
 
 }  // namespace
-
 
 // The linear layer behind every agq_gemm_w4a* call.  check_only: run the argument checks (host only) and return.
 int agq_gemm_w4_run(int bits, const void *x, int x_kind, int64_t M, int64_t K, int64_t ldx, int e, int zp,
@@ -75,13 +50,13 @@ int agq_gemm_w4_run(int bits, const void *x, int x_kind, int64_t M, int64_t K, i
         if (!aligned16(projs[p].w_packed) || !aligned16(projs[p].w_scale_f16) || !aligned16(projs[p].y_f16))
             return AGQ_EINVAL;
     }
-    const size_t need = M <= AGQ_DECODE_MAX_M ? 0 : codes_bytes(M, K);
+    const size_t need = M <= AGQ_DECODE_MAX_M ? 0 : agq_codes_bytes(M, K);
     if (need > 0) {
         if (!workspace || !aligned16(workspace)) return AGQ_EINVAL;
         if (workspace_bytes < need) return AGQ_ESIZE;
     }
     if (check_only) return AGQ_OK;
-    const Route r = route(x_kind, M, K, projs, count, workspace_bytes);
+    const AgqRoute r = route_of(x_kind, M, K, projs, count, -1, workspace_bytes);
     if (!r.tiles)
         return hip_status(agq_launch_gemm_decode(x, x_kind, bits, M, K, ldx, e, zp, projs, count, -1, stream));
 
@@ -89,18 +64,18 @@ int agq_gemm_w4_run(int bits, const void *x, int x_kind, int64_t M, int64_t K, i
     // way when x is fp16), then run the tiled kernel for all projections on that copy
     if (agq_launch_prepack_act(x, x_kind, bits, M, K, ldx, e, zp, workspace, stream)) return AGQ_EHIP;
     return hip_status(agq_launch_gemm_tiled(workspace, M, K, e, agq_zp_corr(bits, zp), projs, count, -1, r.choice.variant, r.plan,
-                                            static_cast<char *>(workspace) + codes_bytes(M, K), stream));
+                                            static_cast<char *>(workspace) + agq_codes_bytes(M, K), stream));
 }
 
 bool agq_gemm_takes_tiles(int64_t M, int64_t K, const struct agq_proj *projs, int count, size_t workspace_bytes) {
-    return workspace_bytes >= codes_bytes(M, K) && route(AGQ_X_F16, M, K, projs, count, workspace_bytes).tiles;
+    return workspace_bytes >= agq_codes_bytes(M, K) && route_of(AGQ_X_F16, M, K, projs, count, -1, workspace_bytes).tiles;
 }
 
 int agq_gemm_w4_tiles(int64_t M, int64_t K, int e, const struct agq_proj *projs, int count, void *workspace,
                       size_t workspace_bytes, void *stream) {
-    const Route r = route(AGQ_X_F16, M, K, projs, count, workspace_bytes);
+    const AgqRoute r = route_of(AGQ_X_F16, M, K, projs, count, -1, workspace_bytes);
     return hip_status(agq_launch_gemm_tiled(workspace, M, K, e, 0, projs, count, -1, r.choice.variant, r.plan,
-                                            static_cast<char *>(workspace) + codes_bytes(M, K), stream));
+                                            static_cast<char *>(workspace) + agq_codes_bytes(M, K), stream));
 }
 
 namespace {
@@ -144,7 +119,7 @@ int gemm_w4_trip_multi(int bits, const void *x, int64_t M, int64_t K, int64_t ld
         if (!aligned16(projs[p].w_packed) || !aligned16(projs[p].w_scale_f16) || !aligned16(projs[p].y_f16))
             return AGQ_EINVAL;
     }
-    const size_t need = M <= AGQ_DECODE_MAX_M ? 0 : codes_bytes(M, K + 128 * (int64_t)n_extra);
+    const size_t need = M <= AGQ_DECODE_MAX_M ? 0 : agq_codes_bytes(M, K + 128 * (int64_t)n_extra);
     if (need > 0) {
         if (!workspace || !aligned16(workspace)) return AGQ_EINVAL;
         if (workspace_bytes < need) return AGQ_ESIZE;
@@ -153,13 +128,8 @@ int gemm_w4_trip_multi(int bits, const void *x, int64_t M, int64_t K, int64_t ld
         return hip_status(agq_launch_gemm_decode(x, AGQ_X_F16, bits, M, K, ldx, e, zp, projs, count, n_extra, stream));
     if (agq_launch_prepack_trip(x, bits, M, K, ldx, e, zp, projs[0].w_packed, projs[0].N, n_extra, workspace, stream))
         return AGQ_EHIP;
-    // few tiles and a long K: K split over workgroups when the workspace has the room (as for plain blobs)
-    int64_t tiles_n = 0;
-    for (int p = 0; p < count; ++p) tiles_n += (projs[p].N + 127) / 128;
-    AgqSplitPlan plan = agq_tiled_split_plan(M, tiles_n, K / 128 + n_extra, true, n_extra);
-    if (workspace_bytes < need + plan.bytes) plan = agq_tiled_split_plan(M, tiles_n, K / 128 + n_extra, false);
-    const AgqTiledChoice choice = agq_tiled_choose(M, tiles_n, K / 128 + n_extra, plan, n_extra);
-    return hip_status(agq_launch_gemm_tiled(workspace, M, K, e, agq_zp_corr(bits, zp), projs, count, n_extra, choice.variant, plan,
+    const AgqRoute r = route_of(AGQ_X_F16, M, K, projs, count, n_extra, workspace_bytes);
+    return hip_status(agq_launch_gemm_tiled(workspace, M, K, e, agq_zp_corr(bits, zp), projs, count, n_extra, r.choice.variant, r.plan,
                                             static_cast<char *>(workspace) + need, stream));
 }
 
@@ -233,7 +203,7 @@ size_t agq_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
         const AgqSplitPlan plan = agq_tiled_split_plan(M, t, K / 128, true);
         if (plan.bytes > split) split = plan.bytes;
     }
-    return codes_bytes(M, K) + split;
+    return agq_codes_bytes(M, K) + split;
 }
 
 int agq_trip_search(const void *x_f16, int64_t M, int64_t K, int64_t ldx, int bits, int e, int zp, int kmax,
@@ -278,7 +248,7 @@ size_t agq_gemm_trip_workspace_bytes(int64_t M, int64_t N, int64_t K, int n_extr
         const AgqSplitPlan plan = agq_tiled_split_plan(M, t, K / 128 + n_extra, true, n_extra);
         if (plan.bytes > split) split = plan.bytes;
     }
-    return codes_bytes(M, K + 128 * (int64_t)n_extra) + split;
+    return agq_codes_bytes(M, K + 128 * (int64_t)n_extra) + split;
 }
 
 int agq_gemm_w4a8_trip(const void *x_f16, int64_t M, int64_t K, int64_t ldx, int e, int zp, const void *w_packed,

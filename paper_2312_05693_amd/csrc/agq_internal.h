@@ -138,6 +138,35 @@ static inline bool agq_decode_row_groups(int x_kind, int64_t M, int64_t K, int64
     return read_ns <= tiled_ns;
 }
 
+// int8 codes in operand order, tokens padded to the 128-row tile (a multiple of 16 KiB); K: extra steps included
+static inline size_t agq_codes_bytes(int64_t M, int64_t K) { return (size_t)((M + 127) / 128) * 128 * (size_t)K; }
+
+// Which kernel a linear layer takes: the tiled kernel (`tiles`) in one of its variants, or the weight-streaming kernel.
+// n_extra >= 0: TRIP blobs with that many extra steps; -1: plain blobs.
+struct AgqRoute {
+    bool tiles;
+    AgqSplitPlan plan;
+    AgqTiledChoice choice;
+};
+static inline AgqRoute agq_gemm_route(int x_kind, int64_t M, int64_t K, const int64_t *N, int count, int n_extra,
+                                      size_t workspace_bytes) {
+    int64_t tiles_n = 0, wg_pairs = 0, n_sum = 0;
+    for (int p = 0; p < count; ++p) {
+        tiles_n += (N[p] + 127) / 128;
+        wg_pairs += (N[p] + 31) / 32;
+        n_sum += N[p];
+    }
+    // With few tiles and a long K the tiled kernel splits the tiles' K steps over workgroups, if the
+    // caller's workspace has the room for the partial tiles behind the codes.
+    const int extra = n_extra > 0 ? n_extra : 0;
+    const int64_t KT = agq_k_tiles(K) + extra;
+    AgqRoute r = {false, agq_tiled_split_plan(M, tiles_n, KT, true, extra), {}};
+    if (workspace_bytes < agq_codes_bytes(M, KT * 128) + r.plan.bytes) r.plan = agq_tiled_split_plan(M, tiles_n, KT, false);
+    r.choice = agq_tiled_choose(M, tiles_n, KT, r.plan, extra);
+    r.tiles = M > AGQ_DECODE_MAX_M && (n_extra >= 0 || !agq_decode_row_groups(x_kind, M, K, n_sum, wg_pairs, r.choice.cost_ns));
+    return r;
+}
+
 // K steps up to which a launch of five to sixteen rows with several channel tiles per CU takes the K-sliced kernel
 #define AGQ_SLICE_MAX_KT 64
 // Whether a workgroup of the per-tile kernel serves a pair of channel tiles for five to sixteen rows (fp16 input, plain

@@ -93,6 +93,13 @@ extern "C" int agq_probe_mfma_i8(const void *a, const void *b, int workgroups, i
     return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
+// Host only: the kernel that a linear layer of x [M,K] and blobs [N[p], K] takes with a workspace of that size: an
+// AgqTiledVariant (agq_internal.h), or -1 for the weight-streaming kernel.  n_extra: -1 for plain blobs.
+extern "C" int agq_probe_gemm_route(int x_kind, int64_t M, int64_t K, const int64_t *N, int count, int n_extra, size_t workspace_bytes) {
+    const AgqRoute r = agq_gemm_route(x_kind, M, K, N, count, n_extra, workspace_bytes);
+    return r.tiles ? (int)r.choice.variant : -1;
+}
+
 // Host only: whether 5 to 16 rows of fp16 input on plain blobs [N[p], K] run with two channel tiles per workgroup of the
 // per-tile kernel (1 / 0).
 extern "C" int agq_probe_decode_pairs(int64_t M, int64_t K, const int64_t *N, int count) {

@@ -421,7 +421,15 @@ def test_block_longest_sequences(agq, oracle, blk_oracle):
 
 @pytest.mark.parametrize("S,d,H,F,keep,qmax,bits_o", [(400, 512, 4, 1152, 300, 15, 4), (700, 256, 2, 2176, 259, 15, 8),
                                                       (290, 384, 3, 640, 290, 15, 4)])
-def test_block_with_codes_from_the_operators(agq, oracle, blk_oracle, S, d, H, F, keep, qmax, bits_o):
+def test_block_with_codes_from_the_operators(agq, oracle, blk_oracle, gemm_route, S, d, H, F, keep, qmax, bits_o):
     """More than 256 rows in front of every projection, so each goes to the tiled GEMM: RMSNorm, SwiGLU and (with pruning) the
     gather write its codes.  Row counts that end inside a 32-token tile, widths of 2 to 17 K steps."""
+    assert "stream" not in {gemm_route(M, K, Ns) for M, K, Ns in ((S, d, [d] * 3), (keep, d, [d]), (keep, d, [F] * 2), (keep, F, [d]))}
     test_block_stage_by_stage(agq, oracle, blk_oracle, S, d, H, F, keep, qmax, bits_o)
+
+
+def test_block_with_codes_for_large_tiles_and_a_split(agq, oracle, blk_oracle, gemm_route):
+    """The operators' codes read by 128-token tiles (gate/up) and by a K split (down)."""
+    S, d, H, F, keep = 1100, 512, 4, 8192, 1050
+    assert (gemm_route(keep, d, [F] * 2), gemm_route(keep, F, [d])) == ("128", "split")
+    check_block_sampled(agq, oracle, blk_oracle, S, d, H, F, keep, seed=16)

@@ -1,7 +1,7 @@
 """GPU parity: the HIP path, called through the C ABI, against the CPU oracle on
 the same seeded inputs.  Integer results (codes, packed bytes, accumulators,
 indices) must be bit-exact; fp16 outputs must agree within 1e-3 relative (plus
-one fp16 subnormal step absolute), the tolerance of the benchmark spec - the
+one fp16 subnormal step absolute), the tolerance for one rounding to fp16 - the
 kernel's float(acc) * g is rounded to fp32 and then to fp16, the oracle rounds
 the exact product once, so they differ by at most one fp16 ulp, rarely."""
 from __future__ import annotations
@@ -136,7 +136,7 @@ def test_calibrate(agq, oracle):
 
 # ------------------------------------------------------------------ the linear layer
 
-def run_linear(agq, oracle, x, wq, sw, bits, x_kind="f16", e=None, check_y=True, zp=0):
+def run_linear(agq, oracle, x, wq, sw, bits, x_kind="f16", e=None, check_y=True, zp=0, workspace=None):
     M, K = x.shape
     N = wq.shape[0]
     if e is None:
@@ -151,7 +151,7 @@ def run_linear(agq, oracle, x, wq, sw, bits, x_kind="f16", e=None, check_y=True,
         xin, kind = dev(x), agq.AGQ_X_F16_DOT
     else:
         xin, kind = agq.quantize_act(dev(x), bits, e, zp), agq.AGQ_X_Q
-    y = fn(xin, e, packed, dev(sw), N, K, x_kind=kind, acc_out=acc, zp=zp)
+    y = fn(xin, e, packed, dev(sw), N, K, x_kind=kind, acc_out=acc, zp=zp, workspace=workspace)
     assert np.array_equal(host(acc).astype(np.int64), acc_want), "accumulators differ"
     if check_y:
         assert_f16_close(host(y), y_want, "y")
@@ -213,14 +213,16 @@ def test_tiled_small(agq, oracle, M, K, N):
     run_linear(agq, oracle, x, wq, sw, 8)
 
 
-@pytest.mark.parametrize("M,K,N,bits,zp", [(17, 4096, 4096, 8, 0), (64, 4096, 4096, 8, 0), (80, 4096, 4096, 8, 0),
-                                             (32, 4096, 11008, 8, 0), (48, 4096, 11008, 8, 0), (64, 11008, 4096, 8, 0),
-                                             (250, 2048, 512, 4, 0), (256, 768, 768, 8, 131), (100, 1408, 272, 4, 9),
-                                             (31, 13824, 48, 8, 0)])
-def test_row_groups_and_the_switch_to_tiles(agq, oracle, M, K, N, bits, zp):
+@pytest.mark.parametrize("M,K,N,bits,zp,variant", [
+    (17, 4096, 4096, 8, 0, "stream"), (64, 4096, 4096, 8, 0, "stream"), (80, 4096, 4096, 8, 0, "stream"),
+    (32, 4096, 11008, 8, 0, "stream"), (48, 4096, 11008, 8, 0, "64x2"), (64, 11008, 4096, 8, 0, "split"),
+    (250, 2048, 512, 4, 0, "stream"), (256, 768, 768, 8, 131, "stream"), (100, 1408, 272, 4, 9, "stream"),
+    (31, 13824, 48, 8, 0, "split")])
+def test_row_groups_and_the_switch_to_tiles(agq, oracle, gemm_route, M, K, N, bits, zp, variant):
     """17..256 rows: sixteen rows per workgroup of the weight-streaming kernel while the weights re-read per row
     group stay cheap, else the tiled path; shapes on both sides of the switch, both grids, ragged last groups.
     The accumulators are compared on sampled rows where the full product would take the oracle too long."""
+    assert gemm_route(M, K, [N]) == variant
     x, wq, sw = make_case(M, K, N, seed=400 + M + N, n_out=6)
     e = oracle.calibrate_act_exp(x, bits) + (1 if zp else 0)
     acc = torch.full((M, N), -3, dtype=torch.int32, device="cuda")
@@ -241,19 +243,25 @@ def test_row_groups_and_the_switch_to_tiles(agq, oracle, M, K, N, bits, zp):
     assert np.array_equal(a2[M // 2], a1[0])
 
 
-@pytest.mark.parametrize("M,K,N,bits,zp,x_kind", [(300, 2048, 384, 8, 0, "f16"), (290, 2048, 500, 4, 0, "f16"),
-                                                    (700, 2816, 272, 8, 131, "f16"), (260, 2560, 130, 8, 0, "q"),
-                                                    (128, 4096, 4096, 8, 0, "f16"), (257, 4096, 4096, 4, 9, "f16"),
-                                                    (400, 11008, 4096, 8, 0, "f16"), (300, 13824, 640, 8, 0, "q")])
-def test_tiled_split_k(agq, oracle, M, K, N, bits, zp, x_kind):
-    """Few 128 x 128 tiles and a long K: the K steps of a tile are shared out over several workgroups, whose int32
-    partial tiles a second kernel adds up.  Against the oracle (sampled rows at the large sizes), against the
-    same call with a workspace that only has room for the activation (no split), and call after call into the same
-    workspace."""
+@pytest.mark.parametrize("M,K,N,bits,zp,x_kind,variant", [
+    (300, 2048, 384, 8, 0, "f16", "64x2"), (290, 2048, 500, 4, 0, "f16", "64x2"), (700, 2816, 272, 8, 131, "f16", "64x2"),
+    (260, 2560, 130, 8, 0, "q", "split"), (128, 4096, 4096, 8, 0, "f16", "64x2"), (257, 4096, 4096, 4, 9, "f16", "64x2"),
+    (400, 11008, 4096, 8, 0, "f16", "64x2"), (300, 13824, 640, 8, 0, "q", "split"),
+    (300, 8192, 384, 8, 0, "f16", "split"), (290, 8192, 500, 4, 0, "f16", "split"), (700, 11008, 272, 8, 131, "f16", "split"),
+    (260, 6144, 272, 8, 0, "q", "split"), (257, 6144, 130, 4, 9, "f16", "split")])
+def test_tiled_split_k(agq, oracle, gemm_route, M, K, N, bits, zp, x_kind, variant):
+    """Few 128 x 128 tiles and a long K, for which the workspace has room for partial tiles.  "split": the K steps of a
+    tile are shared out over several workgroups, whose int32 partial tiles a second kernel adds up; "64x2": two groups of
+    wavefronts of one workgroup share them, which is faster while K is not that long.  Against the oracle (sampled rows
+    at the large sizes), against the same call with a workspace that only has room for the activation (never a split), and
+    call after call into the same workspace."""
     x, wq, sw = make_case(M, K, N, seed=900 + M + N, n_out=6)
     e = oracle.calibrate_act_exp(x, bits) + (1 if zp else 0)
     full, small = agq.gemm_workspace_bytes(M, N, K), agq.gemm_workspace_bytes(M, 0, K)
-    assert full > small == -(-M // 128) * 128 * K       # these shapes are split
+    assert full > small == -(-M // 128) * 128 * K
+    kind = agq.AGQ_X_Q if x_kind == "q" else agq.AGQ_X_F16
+    assert gemm_route(M, K, [N], kind, workspace_bytes=full) == variant
+    assert gemm_route(M, K, [N], kind, workspace_bytes=small) == "64x2"
     fn = agq.gemm_w4a8 if bits == 8 else agq.gemm_w4a4
     if x_kind == "f16":
         xin, kind = dev(x), agq.AGQ_X_F16
@@ -279,11 +287,24 @@ def test_tiled_split_k(agq, oracle, M, K, N, bits, zp, x_kind):
     assert_f16_close(outs[0][1][rows], y_w, "y")
 
 
-@pytest.mark.parametrize("M,K,N,bits,zp,x_kind", [(448, 4096, 1000, 8, 0, "f16"), (300, 1024, 2100, 4, 9, "f16"),
-                                                    (512, 4096, 4096, 8, 0, "q"), (321, 512, 5000, 8, 131, "f16")])
-def test_tiled_64_token_tiles(agq, oracle, M, K, N, bits, zp, x_kind):
-    """At most 128 tiles of 128 x 128 and no K split that pays: the tiled kernel runs 64-token tiles (twice the
-    workgroups).  Token counts that end inside the first and inside the second half of a 128-token tile."""
+@pytest.mark.parametrize("M,K,N,bits,zp,x_kind,variant", [
+    (448, 4096, 1000, 8, 0, "f16", "64x2"), (300, 1024, 2100, 4, 9, "f16", "64"), (512, 4096, 4096, 8, 0, "q", "64x2"),
+    (321, 512, 5000, 8, 131, "f16", "64"), (448, 512, 1000, 8, 0, "f16", "64"), (1200, 1280, 4100, 4, 0, "q", "64")])
+def test_tiled_64_token_tiles(agq, oracle, gemm_route, M, K, N, bits, zp, x_kind, variant):
+    """Grids that 64-token tiles (twice the workgroups) fill better than 128-token ones, with the K steps of a tile in one
+    group of wavefronts or shared by two.  Token counts that end inside the first and inside the second half of a 128-token
+    tile."""
+    run_tiled_variant(agq, oracle, gemm_route, M, K, N, bits, zp, x_kind, variant)
+
+
+@pytest.mark.parametrize("M,K,N,bits,zp,x_kind", [(1100, 384, 6000, 8, 131, "f16"), (1030, 256, 6100, 4, 9, "q"),
+                                                    (1100, 640, 6040, 4, 0, "f16"), (1000, 128, 12008, 8, 1, "q")])
+def test_tiled_128_token_tiles(agq, oracle, gemm_route, M, K, N, bits, zp, x_kind):
+    """Grids of many 128-token tiles, unsplit: ragged token counts and widths, both grids, zero points, both inputs."""
+    run_tiled_variant(agq, oracle, gemm_route, M, K, N, bits, zp, x_kind, "128")
+
+
+def run_tiled_variant(agq, oracle, gemm_route, M, K, N, bits, zp, x_kind, variant):
     x, wq, sw = make_case(M, K, N, seed=950 + M + N, n_out=6)
     e = oracle.calibrate_act_exp(x, bits) + (1 if zp else 0)
     fn = agq.gemm_w4a8 if bits == 8 else agq.gemm_w4a4
@@ -293,6 +314,7 @@ def test_tiled_64_token_tiles(agq, oracle, M, K, N, bits, zp, x_kind):
         xin, kind = dev(x), agq.AGQ_X_F16_DOT
     else:
         xin, kind = agq.quantize_act(dev(x), bits, e, zp), agq.AGQ_X_Q
+    assert gemm_route(M, K, [N], kind) == variant
     acc = torch.full((M, N), -3, dtype=torch.int32, device="cuda")
     ybuf = torch.full((M, N + 8), 5.0, dtype=torch.float16, device="cuda")
     fn(xin, e, agq.pack_w4(dev(wq)), dev(sw), N, K, x_kind=kind, acc_out=acc, zp=zp, y=ybuf[:, :N])
@@ -304,29 +326,32 @@ def test_tiled_64_token_tiles(agq, oracle, M, K, N, bits, zp, x_kind):
     assert (got[:, N:] == 5.0).all() and not (host(acc) == -3).all(axis=1).any()     # every row written, nothing beyond
 
 
-def test_tiled_split_k_multi_and_graph(agq, oracle):
-    # q/k/v-style call whose tiles together are still few: one split launch over all projections; replayed as a graph
-    M, K, Ns, bits = 300, 2048, [256, 100, 384], 8
+@pytest.mark.parametrize("K,zp,variant", [(2048, 0, "64x2"), (4096, 0, "split"), (6144, 131, "split")])
+def test_tiled_split_k_multi_and_graph(agq, oracle, gemm_route, K, zp, variant):
+    # q/k/v-style call whose tiles together are still few: one launch over all projections, split from K = 4096 on;
+    # replayed as a graph
+    M, Ns, bits = 300, [256, 100, 384], 8
     x = synth.make_activation(M, K, 4, seed=910)
-    e = oracle.calibrate_act_exp(x, bits)
+    e = oracle.calibrate_act_exp(x, bits) + (1 if zp else 0)
     xd = dev(x)
     projs, wants = [], []
     for i, N in enumerate(Ns):
         wq, sw = synth.make_weight_q4(N, K, seed=920 + i)
         projs.append((agq.pack_w4(dev(wq)), dev(sw), N, torch.empty((M, N), dtype=torch.float16, device="cuda"),
                       torch.empty((M, N), dtype=torch.int32, device="cuda")))
-        wants.append(oracle.linear_w4(x, bits, e, 0, wq, sw))
+        wants.append(oracle.linear_w4(x, bits, e, zp, wq, sw))
     full = agq.gemm_workspace_bytes(M, sum(Ns), K)
     assert full > agq.gemm_workspace_bytes(M, 0, K)
+    assert gemm_route(M, K, Ns, workspace_bytes=full) == variant
     ws = torch.empty(full, dtype=torch.uint8, device="cuda")
-    agq.gemm_w4a8_multi(xd, e, projs, K, workspace=ws)
+    agq.gemm_w4a8_multi(xd, e, projs, K, workspace=ws, zp=zp)
     for (acc_w, y_w), p in zip(wants, projs):
         assert np.array_equal(host(p[4]).astype(np.int64), acc_w)
         assert_f16_close(host(p[3]), y_w, "multi split")
     eager = [host(p[3]).copy() for p in projs]
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
-        agq.gemm_w4a8_multi(xd, e, projs, K, workspace=ws)
+        agq.gemm_w4a8_multi(xd, e, projs, K, workspace=ws, zp=zp)
     for rep in range(3):
         for p in projs:
             p[3].zero_()
@@ -959,7 +984,7 @@ def test_trip_linear_tiled(agq, oracle, M, K, N, bits):
 
 
 @pytest.mark.parametrize("M,K,N,bits,zp", [(300, 4096, 300, 8, 0), (140, 8192, 700, 4, 9)])
-def test_trip_tiled_split_k(agq, oracle, M, K, N, bits, zp):
+def test_trip_tiled_split_k(agq, oracle, gemm_route, M, K, N, bits, zp):
     """TRIP blobs with few tiles and a long K: the K split keeps the extra steps and their shifts in the first slice.
     Against the oracle and, bit for bit, against the call with a workspace too small for a split."""
     rng = np.random.default_rng(43)
@@ -972,6 +997,8 @@ def test_trip_tiled_split_k(agq, oracle, M, K, N, bits, zp):
     full = agq.lib().agq_gemm_trip_workspace_bytes(M, N, K, n_extra)
     small = agq.lib().agq_gemm_trip_workspace_bytes(M, 0, K, n_extra)
     assert full > small == -(-M // 128) * 128 * (K + 128 * n_extra)
+    assert gemm_route(M, K, [N], n_extra=n_extra, workspace_bytes=full) == "split"
+    assert gemm_route(M, K, [N], n_extra=n_extra, workspace_bytes=small) == "64x2"
     res = []
     for nbytes in (full, small, full):
         ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda").fill_(0x5A)
@@ -1299,9 +1326,12 @@ def test_qk_attention_longest_sequence(agq, oracle):
 
 
 @pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 6, 7, 8, 11])
-@pytest.mark.parametrize("M,N", [(300, 40), (1100, 2000)])          # 64-token tiles; 128-token tiles
-def test_tiled_every_pipeline_tail(agq, oracle, M, N, steps):
+@pytest.mark.parametrize("M,N,variant", [(300, 40, "64"), (1100, 2000, "64"), (1000, 12000, "128")])
+def test_tiled_every_pipeline_tail(agq, oracle, gemm_route, M, N, variant, steps):
     """The tiled kernel's K loop: fewer steps than its three stages, and every number of steps behind the steady loop."""
+    if (N, steps) == (2000, 11):
+        variant = "128"                                  # the longest of these takes the larger tiles
+    assert gemm_route(M, 128 * steps, [N]) == variant
     x, wq, sw = make_case(M, 128 * steps, N, 90 + steps)
     rows = sorted({0, 31, 32, 63, 64, 127, 128, M // 2, M - 1})
     e = oracle.calibrate_act_exp(x, 8)
@@ -1312,9 +1342,11 @@ def test_tiled_every_pipeline_tail(agq, oracle, M, N, steps):
     assert_f16_close(host(y)[rows], y_want, "y")
 
 
-def test_trip_split_slice_of_extra_steps_only(agq, oracle):
+def test_trip_split_slice_of_extra_steps_only(agq, oracle, gemm_route):
     """A K split whose first slice is the 16 extra steps and nothing else: its last step is followed by a shift."""
     M, N, K = 100, 300, 10240
+    full = agq.lib().agq_gemm_trip_workspace_bytes(M, N, K, 16)
+    assert gemm_route(M, K, [N], n_extra=16, workspace_bytes=full) == "split"
     x, wq, sw, e = trip_case(M, K, N, 95, K // 100, 4, 8, oracle)
     run_trip_linear(agq, oracle, x, wq, sw, 8, e, random_alpha(np.random.default_rng(44), K, (2048, 0, 0, 0)))
     run_trip_linear(agq, oracle, x, wq, sw, 8, e, random_alpha(np.random.default_rng(45), K, (700, 600, 300, 256)))
@@ -1322,22 +1354,31 @@ def test_trip_split_slice_of_extra_steps_only(agq, oracle):
 
 @pytest.mark.parametrize("steps", [15, 16, 17, 21])
 @pytest.mark.parametrize("M,N", [(258, 40), (320, 700)])
-def test_tiled_k_shared_by_two_groups(agq, oracle, M, N, steps):
-    """64-token tiles whose K steps two groups of wavefronts share: even and odd step counts."""
-    run_linear(agq, oracle, *make_case(M, 128 * steps, N, 600 + steps), 8)
+def test_tiled_k_shared_by_two_groups(agq, oracle, gemm_route, M, N, steps):
+    """64-token tiles whose K steps two groups of wavefronts share: even and odd step counts.  (The workspace holds the
+    activation alone; with room for partial tiles the narrow layer would be split over workgroups from 16 steps on.)"""
+    codes_only = agq.gemm_workspace_bytes(M, 0, 128 * steps)
+    assert gemm_route(M, 128 * steps, [N], workspace_bytes=codes_only) == "64x2"
+    run_linear(agq, oracle, *make_case(M, 128 * steps, N, 600 + steps), 8,
+               workspace=torch.empty(codes_only, dtype=torch.uint8, device="cuda"))
 
 
 @pytest.mark.parametrize("K,counts", [(1664, (780, 130, 260, 390)), (2048, (700, 600, 300, 256)), (2048, (3, 0, 0, 20))])
-def test_trip_k_shared_by_two_groups(agq, oracle, K, counts):
+def test_trip_k_shared_by_two_groups(agq, oracle, gemm_route, K, counts):
     """The same with extra steps: more than half of all steps (they stay together in the first group), as many, a few."""
+    n_extra = sum(-(-c // 128) for c in counts)
+    assert gemm_route(300, K, [300], n_extra=n_extra, workspace_bytes=agq.lib().agq_gemm_trip_workspace_bytes(300, 300, K, n_extra)) == "64x2"
     x, wq, sw, e = trip_case(300, K, 300, 97, K // 100, 4, 8, oracle)
     run_trip_linear(agq, oracle, x, wq, sw, 8, e, random_alpha(np.random.default_rng(46), K, counts))
 
 
-@pytest.mark.parametrize("M,N,pitch", [(300, 130, 131), (300, 129, 130), (300, 63, 63), (1100, 2001, 2001), (1100, 2050, 2052),
-                                       (1100, 1985, 1988)])
-def test_tiled_output_rows_off_the_16_byte_grid(agq, oracle, M, N, pitch):
+@pytest.mark.parametrize("M,N,pitch,variant", [(300, 130, 131, "64"), (300, 129, 130, "64"), (300, 63, 63, "64"),
+                                               (1100, 2001, 2001, "64"), (1100, 2050, 2052, "64"), (1100, 1985, 1988, "64"),
+                                               (1100, 6001, 6001, "128"), (1100, 6018, 6020, "128"), (1100, 5953, 5956, "128"),
+                                               (1000, 7999, 7999, "128")])
+def test_tiled_output_rows_off_the_16_byte_grid(agq, oracle, gemm_route, M, N, pitch, variant):
     """Output pitches that are no multiple of eight: odd and even, the width on both sides of a 64-channel tile's edge."""
+    assert gemm_route(M, 256, [N]) == variant
     x, wq, sw = make_case(M, 256, N, seed=500 + N)
     e = oracle.calibrate_act_exp(x, 8)
     rows = sorted({0, 1, 30, 31, 32, 63, 64, 127, 128, M - 2, M - 1})

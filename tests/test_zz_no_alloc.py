@@ -26,18 +26,20 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
-def test_static_workspace_two_calls_in_a_row(agq, oracle):
-    # (M, K, N): a K split with partial tiles behind the codes, then a smaller call that leaves stale bytes of the
-    # first in the array, then a weight-streaming call (no workspace at all) and a many-tile call without a split
-    cases = [(600, 2048, 384, 31), (300, 2048, 256, 32), (5, 512, 48, 33), (1000, 768, 1024, 34)]
+def test_static_workspace_two_calls_in_a_row(agq, oracle, gemm_route):
+    # (M, K, N): a K split with partial tiles behind the codes, then smaller calls that leave stale bytes of the
+    # first in the array, split and not, then a weight-streaming call (no workspace at all) and a many-tile call
+    cases = [(600, 8192, 384, 35), (300, 8192, 256, 36), (600, 2048, 384, 31), (300, 2048, 256, 32), (5, 512, 48, 33),
+             (1000, 768, 1024, 34)]
+    static_bytes = 32 << 20
+    assert [gemm_route(M, K, [N], workspace_bytes=static_bytes) for M, K, N, _ in cases] == ["split", "split", "64x2", "64x2", "stream", "64"]
     inputs = []
     for (M, K, N, seed) in cases:
         x = synth.make_activation(M, K, 4, seed)
         wq, sw = synth.make_weight_q4(N, K, seed)
         e = oracle.calibrate_act_exp(x, 8)
         inputs.append((dev(x), e, agq.pack_w4(dev(wq)), dev(sw), oracle.linear_w4(x, 8, e, 0, wq, sw)))
-    # the first two cases do split K when given the room (that is what puts partial tiles into the array)
-    for (M, K, N, _) in cases[:2]:
+    for (M, K, N, _) in cases[:4]:                       # room for partial tiles is asked for, and the array has it
         assert agq.gemm_workspace_bytes(M, N, K) > agq.gemm_workspace_bytes(M, 0, K)
         assert agq.gemm_workspace_bytes(M, N, K) <= agq.lib().agq_gemm_workspace_bytes(2048, 0, 11008)
     outs = []
