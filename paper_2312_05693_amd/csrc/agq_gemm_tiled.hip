@@ -175,11 +175,10 @@ __global__ __launch_bounds__(kThreads * KG, 2) void gemm_tiled_kernel(const Tile
     const int kwg = SPLIT ? split * a.steps_per_split : 0;
     const int KTwg = SPLIT ? min(a.steps_per_split, KTfull - kwg) : KTfull;  // steps of this workgroup
     // KG == 2: the first half for group 0 (the extra steps, whose shifts apply to what came before them, stay together),
-    // the rest for group 1.  A group with nothing to do takes a step whose result is dropped.
-    const int khalf = KG == 1 ? KTwg : max((KTwg + 1) >> 1, TRIP && split == 0 ? a.n_extra : 0);
-    const bool idle = KG == 2 && grp == 1 && khalf >= KTwg;
-    const int kbeg = kwg + (grp == 1 && !idle ? khalf : 0);
-    const int KT = KG == 1 ? KTwg : (grp == 0 ? khalf : (idle ? 1 : KTwg - khalf));   // steps of this group
+    // the rest for group 1.  (Two steps at least, and the extra steps are never all of them: neither group is empty.)
+    const int khalf = KG == 1 ? KTwg : max((KTwg + 1) >> 1, TRIP ? a.n_extra : 0);
+    const int kbeg = kwg + (grp == 1 ? khalf : 0);
+    const int KT = grp == 1 ? KTwg - khalf : khalf;      // steps of this group
 
     // Copies of this wavefront per step: activation chunks 4 wave .. 4 wave + 3 of
     // the 16 KiB stage, and weight chunks 2 wave, 2 wave + 1.  Weight chunk c
@@ -414,7 +413,7 @@ __global__ __launch_bounds__(kThreads * KG, 2) void gemm_tiled_kernel(const Tile
 #undef AGQ_WAIT
     if (KG == 2) {
         // the groups meet once per step and once before the first one: the shorter one catches up
-        for (int more = (grp == 0 ? max(KTwg - khalf, 1) : khalf) - KT; more > 0; --more) __builtin_amdgcn_s_barrier();
+        for (int more = KTwg - 2 * KT; more > 0; --more) __builtin_amdgcn_s_barrier();
     }
     __syncthreads();                                   // every wavefront is done with the stages
     if constexpr (KG == 2) {
@@ -429,8 +428,7 @@ __global__ __launch_bounds__(kThreads * KG, 2) void gemm_tiled_kernel(const Tile
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
                         ex[((i * 2 + j) * 4 + q) * kThreads] =
-                            idle ? make_int4(0, 0, 0, 0)
-                                 : make_int4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+                            make_int4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
         }
         __syncthreads();
         if (grp == 1) return;

@@ -116,7 +116,7 @@ static inline AgqTiledChoice agq_tiled_choose(int64_t M, int64_t tiles_n, int64_
     }
     const int64_t step64 = w64 <= 256 ? 300 + w64 * 7 / 20 : (w64 <= 768 ? 460 + (w64 - 256) * 21 / 20 : at_least(1360, w64 * 127 / 100));
     offer(TILED_64, 4000 + KT * step64);
-    if (w64 <= 256) offer(TILED_64X2, 4800 + at_least((KT + 1) / 2, n_extra) * (430 + w64 * 3 / 4));
+    if (w64 <= 256 && KT > 1) offer(TILED_64X2, 4800 + at_least((KT + 1) / 2, n_extra) * (430 + w64 * 3 / 4));
     return c;
 }
 

@@ -365,3 +365,12 @@ def test_rule_for_tile_pairs(probe, M, K, Ns, pairs):
     """Five to eight rows: two workgroups of single tiles share a CU, so a pair per workgroup has to halve the rounds (three
     rounds of single tiles against two of pairs were up to 19 % slower in pairs); from nine rows on any round saved counts."""
     assert probe.agq_probe_decode_pairs(ctypes.c_int64(M), ctypes.c_int64(K), (ctypes.c_int64 * len(Ns))(*Ns), len(Ns)) == pairs
+
+
+def test_two_groups_have_a_step_each(gemm_route):
+    """The kernel whose two wavefront groups share a tile's K steps is never chosen for a tile of a single step."""
+    for M in (17, 64, 100, 257, 300, 700, 2000):
+        for N in (16, 300, 1000, 4096, 30000):
+            for n_extra in (-1, 0):
+                assert gemm_route(M, 128, [N], x_kind=1, n_extra=n_extra) != "64x2", (M, N)
+    assert gemm_route(100, 128 * 12, [1000], x_kind=1) == "64x2"
