@@ -128,9 +128,15 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# The stream's handle alone: torch.cuda.current_stream() builds a Stream object around it, which takes longer than the call it
+# is for.  torch does not promise to keep this name, so the public call is what remains without it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    # the handle alone: torch.cuda.current_stream() builds a Stream object around it, which takes longer than the call it is for
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ok(status: int, where: str):

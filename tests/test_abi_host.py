@@ -374,3 +374,18 @@ def test_two_groups_have_a_step_each(gemm_route):
             for n_extra in (-1, 0):
                 assert gemm_route(M, 128, [N], x_kind=1, n_extra=n_extra) != "64x2", (M, N)
     assert gemm_route(100, 128 * 12, [1000], x_kind=1) == "64x2"
+
+
+def test_binding_without_the_private_stream_call(monkeypatch):
+    """A torch that no longer has the private call for the stream's handle: the public one is used."""
+    import importlib.util
+    import types
+    import torch
+    from paper_2312_05693_amd import binding
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1234))
+    spec = importlib.util.spec_from_file_location("binding_copy", binding.__file__)
+    copy = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(copy)
+    assert copy._stream() == 0x1234

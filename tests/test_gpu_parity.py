@@ -1410,3 +1410,12 @@ def test_decode_tile_pairs_on_long_k(agq, oracle, M, K, Ns, bits, zp):
         assert np.array_equal(host(acc)[:, c].astype(np.int64), acc_w)
         assert_f16_close(host(y)[:, c], y_w, "y")
         assert not (host(acc) == -7).all(axis=0).any()       # every column was written
+
+
+def test_calls_go_to_the_current_stream(agq):
+    """The handle the binding passes on is the current stream's, on the default stream and on others."""
+    side = torch.cuda.Stream()
+    assert agq._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert agq._stream() == side.cuda_stream
+    assert agq._stream() != side.cuda_stream
