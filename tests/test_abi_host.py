@@ -389,3 +389,18 @@ def test_binding_without_the_private_stream_call(monkeypatch):
     copy = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(copy)
     assert copy._stream() == 0x1234
+
+
+def test_projection_array_has_the_layout_of_the_struct():
+    """The calls for several projections get struct agq_proj[] as plain 8-byte values in the order of its fields."""
+    import torch
+    from paper_2312_05693_amd import binding
+    names = ["w_packed", "w_scale_f16", "N", "y_f16", "ldy", "acc_out"]
+    assert [n for n, _ in binding.AgqProj._fields_] == names
+    assert [getattr(binding.AgqProj, n).offset for n in names] == [0, 8, 16, 24, 32, 40] and ctypes.sizeof(binding.AgqProj) == 48
+    w, sc, acc = torch.empty(64, dtype=torch.uint8), torch.empty(32, dtype=torch.float16), torch.empty(4, 32, dtype=torch.int32)
+    y = torch.empty(4, 40, dtype=torch.float16)[:, :32]
+    ys, arr = binding._projections(4, [(w, sc, 32, y, acc), (w, sc, 16, None, None)], "cpu")
+    want = (binding.AgqProj * 2)(binding.AgqProj(w.data_ptr(), sc.data_ptr(), 32, y.data_ptr(), 40, acc.data_ptr()),
+                                 binding.AgqProj(w.data_ptr(), sc.data_ptr(), 16, ys[1].data_ptr(), 16, None))
+    assert ys[0] is y and bytes(arr) == bytes(want)
