@@ -116,8 +116,9 @@ int agq_unpack_w4(const void *packed, int64_t N, int64_t K, int8_t *wq_out,
  * workspace: agq_gemm_workspace_bytes(M,N,K) bytes, 16-byte aligned, may be
  *            NULL when that is 0.  Holds the quantized activation when M is
  *            large enough for the tiled kernel, and behind it, when the call
- *            has few output tiles and a long K, the int32 partial tiles of a
- *            split of K over workgroups; contents are scratch.  A workspace of
+ *            has few output tiles and a long K, room for the int32 partial tiles
+ *            of a split of K over workgroups (taken when the split is the fastest
+ *            way for the call's sizes); contents are scratch.  A workspace of
  *            agq_gemm_workspace_bytes(M,0,K) bytes (the activation only) is
  *            accepted too: K is then not split, which costs time where it
  *            applies and changes no result; a smaller one is AGQ_ESIZE.

@@ -13,8 +13,11 @@ inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 constexpr int64_t kMaxTokens = 8192;        // agq_prune_tokens' limit (calls that prune)
 // Up to this many rows the operator in front of a projection (RMSNorm, SwiGLU, the gather of the surviving rows) writes the
 // tiled GEMM's codes itself and the pre-pass, a launch of 3 to 5 us at these sizes, is left out.  Two blocks of 512 tokens
-// 357 -> 347 us, four of 300 tokens 564 -> 540, four narrow ones of 212 tokens 277 -> 257, one of 1024 tokens 284 -> 280; at
-// 2048 tokens the operators' scattered 8-byte stores cost more than the pre-pass's own trip through memory (750 -> 758).
+// 357 -> 347 us, four of 300 tokens 564 -> 540, four narrow ones of 212 tokens 277 -> 257, one of 1024 tokens 284 -> 280.  What
+// the operators' scattered 8-byte stores cost grows with rows times width, so the line is where the widest layers break even
+// (unpruned blocks, 1024 / 1280 / 1408 / 1536 tokens; F = 13824: 449 -> 443, 529 -> 520, 573 -> 570, 613 -> 610; F = 11008:
+// 313 -> 305, 390 -> 384, 425 -> 423, 448 -> 448; F = 2816: 106 -> 102 .. 140 -> 135); at 2048 tokens of F = 13824 they lose
+// (750 -> 758).  Narrow layers gain up to the line, and would beyond it.
 constexpr int64_t kFuseRows = 1536;
 constexpr int64_t kMaxAttnTokens = 32768;   // the attention call's limit (calls that keep every token)
 constexpr int64_t kMaxWidth = 65536;   // the GEMMs' limit on K

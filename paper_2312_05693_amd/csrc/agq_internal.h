@@ -51,26 +51,29 @@ static inline AgqTripLayout agq_trip_layout(int64_t N, int64_t K, int E) {
 // most CUs idle while a few walk K.  Then `splits` workgroups share a tile's K steps (at least four each, at most one
 // workgroup per CU in all) and leave int32 partial tiles behind the activation codes in the workspace,
 // which a second kernel adds up.  That costs about 2 us for the launch and 0.45 us per MB of partial tiles
-// (written, read back); the plan is the split count with the smallest sum under this model (all measured on
-// MI355X).  M tokens, tiles_n = 128-wide column tiles of all projections of the call, KT = K steps (TRIP
+// (written, read back); the plan is the split count with the smallest sum under this model (measured on
+// MI355X with an earlier schedule of the loop and resident weights).  Its count is the one that agq_tiled_choose below
+// weighs against the other variants with the constants of the present loop, and a plan of one slice is never offered there;
+// the sizes that callers reserve (agq_gemm_workspace_bytes) hold the plan's partial tiles whether or not the choice then
+// takes the split.  M tokens, tiles_n = 128-wide column tiles of all projections of the call, KT = K steps (TRIP
 // blobs: the extra steps in front included, all of which stay in the first slice: min_steps of them).
 // splits == 1: no split, bytes == 0.
 struct AgqSplitPlan {
     int splits, steps;
     size_t bytes;
-    int64_t cost_ns;   // the model's time for the chosen plan (GEMM launches only)
 };
 static inline AgqSplitPlan agq_tiled_split_plan(int64_t M, int64_t tiles_n, int64_t KT, bool may_split, int min_steps = 0) {
     const int64_t tiles = ((M + 127) / 128) * tiles_n;
-    AgqSplitPlan p = {1, (int)KT, 0, KT * 470 * (tiles > 256 ? (tiles + 255) / 256 : 1)};
+    AgqSplitPlan p = {1, (int)KT, 0};
     if (!may_split || tiles < 1 || tiles * 2 > 256 || KT < 8) return p;
     const int64_t part_bytes = ((M + 31) / 32) * 32 * tiles_n * 512;   // per split: rows that hold tokens x columns x 4
+    int64_t least = KT * 470;
     for (int64_t s = 2; s <= KT / 4 && s * tiles <= 256; ++s) {
         const int64_t steps = (KT + s - 1) / s;
         if ((KT + steps - 1) / steps != s || steps < min_steps) continue;   // the same steps with fewer workgroups exist
         const int64_t cost = steps * 470 + 2000 + part_bytes * s * 450 / 1000000;
-        if (cost < p.cost_ns) {
-            p.cost_ns = cost;
+        if (cost < least) {
+            least = cost;
             p.splits = (int)s;
             p.steps = (int)steps;
         }
@@ -95,8 +98,9 @@ static inline AgqSplitPlan agq_tiled_split_plan(int64_t M, int64_t tiles_n, int6
 //   4096 -> 22016    100 tokens 20.0 / - / 22.3 / 25.7, 213 tokens 31.3 / - / 33.0 / -, 300 tokens 42.2 / - / 41.5 / -
 //   5120 -> 5120     333 tokens 21.5 / - / 19.5 / 16.6, 1024 tokens 35.9 / - / 37.0 / -
 //   4096 -> 22016    1000 tokens 89 / - / 101 / -, 2048 tokens 157 / - / 186 / -
-// which the model reproduces to about 10 %.  (The 470 ns of the plan above are from an earlier schedule of the loop and
-// from resident weights; they decide how many slices a split would have and its room, not whether it is taken.)
+// The model is within 10 % of these for 128-token, split and two-group tiles.  For 64-token tiles it is up to 15 % high
+// where two or three of them share a CU and 22 % high at 2048 tokens: of the calls above, 4096 -> 22016 at 300 tokens
+// goes to 128-token tiles for it, 2 % slower than 64-token ones.
 enum AgqTiledVariant { TILED_128, TILED_SPLIT, TILED_64, TILED_64X2 };
 struct AgqTiledChoice {
     AgqTiledVariant variant;
@@ -125,7 +129,9 @@ static inline AgqTiledChoice agq_tiled_choose(int64_t M, int64_t tiles_n, int64_
 // about 3 us + 0.24 us per MB read in all, more when the workgroups fill the last round of 256 CUs badly.  The
 // other path is the layout pre-pass (about 3 us with the gap behind it) plus the tiled kernel (above).  Measured
 // (row groups against pre-pass and tiles): 4096 x 4096 at 32 / 64 / 100 rows 6.4 / 11.0 / 18.1 against about 13 us at
-// any of them; 768 x 768 at 128 rows 4.1 against 8.2 us.  wg_pairs: tile pairs (32 channels) of all projections;
+// any of them; 768 x 768 at 128 rows 4.1 against 8.2 us.  (The two 3 us cancel in the rule.  Inside a block the operator in
+// front writes the codes and there is no pre-pass; the same rule is asked there, so between 17 and about 100 rows a block
+// may keep row groups, or tiles, a few rows too long.)  wg_pairs: tile pairs (32 channels) of all projections;
 // tiled_ns: the cost of the variant the call would run instead.  (Four tiles per workgroup instead of two were measured
 // too: the same at best, and 50 % slower on the widest layer, where the registers no longer hold the weight chunks.)
 #define AGQ_ROW_GROUP_MAX_M 256
