@@ -23,6 +23,20 @@
 // in that order (slot 8 g + 4 q' + r of step u <-> key 16 u + 8 q' + 4 g + r).  The
 // V tile in LDS is written in that slot order, so no shuffle is needed between
 // the two products.
+//
+// What bounds it: the vector ALU and the matrix cores of a SIMD, which two wavefronts of different
+// workgroups keep busy in turn.  Measured: a wavefront by itself issues an instruction every 4.5 cycles, and every
+// eight where it needs the one before; conversions, permutes and packed fp16 take the ALU 4.4 cycles, plain
+// fp32 2.5, the exponential 8.5, an MFMA eight of the ALU's and 33 of the matrix core's.  So the work of a step is
+// dealt out one MFMA at a time, the scores of the next sub-tile beside the arithmetic of this one; scores become floats
+// by a subtraction; a conversion to bytes rounds and packs the weights' exponents; V is widened by one
+// packed multiply-add.  Against a kernel with nothing dealt out and three workgroups on a CU (the same results bit for
+// bit): 40 x 2048 x 128 causal 67 -> 62 us, 40 x 2048 x 64 57 -> 43 (half of the output blocks were empty there),
+// 32 x 384 x 128 14.4 -> 13.4.  What is left of a large causal call is the chain of its longest row blocks (32 tiles
+// take 46 us alone on a CU).  Not kept: a reference score in place of the running maximum, with differences to it straight from
+// the accumulators (58 us, and three times fewer codes off, but other codes than before); one block on eight
+// wavefronts, the key tiles shared by two groups of four (72 us then: both wavefronts of a SIMD want the same unit at
+// the same time); V tiles straight into registers (no difference).
 #include "agq_device.h"
 #include "agq_internal.h"
 
@@ -40,7 +54,7 @@ namespace {
 
 constexpr int kQRows = 128;     // query rows per workgroup (32 per wavefront)
 constexpr int kKeys = 64;       // keys per tile: two 32-key sub-tiles
-constexpr int kVRow = 144;      // bytes per channel row of the V tile: 64 key slots in fp16 + 16 of padding
+constexpr int kRing = 4;        // K tiles in LDS
 
 struct QkArgs {
     const int8_t *q, *k, *v;   // [H,S,D] each
@@ -50,17 +64,37 @@ struct QkArgs {
     int H, S;
     int causal, qmax;
     float kappa;               // 2^(e_q+e_k) log2(e) / sqrt(D)
-    float out_scale;           // 2^(e_v - qmax)
+    float out_scale;           // 2^(e_v - qmax + 9)
     int ncu;
 };
 
+template <int N>
+struct Int {
+    static constexpr int value = N;
+};
+
+// Between two tiles: at most VM of this wavefront's loads may still fly (they return in order), its LDS reads and writes
+// are done; then meet the others.
+template <int VM>
+__device__ __forceinline__ void meet() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | 0x70);   // vmcnt(VM) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // DT = D / 32: int8 MFMA steps per score tile and 32-channel blocks of the output
 template <int DT, bool CODES>
-__global__ __launch_bounds__(256, 3) void qk_log2_attn_kernel(const QkArgs a) {
-    constexpr int D = DT * 32, DQ = D / 4;
-    constexpr int kKRow = D + 16;                                // bytes per key row of the K tile (padded)
-    __shared__ __align__(16) uint8_t kt[kKeys * kKRow];          // one K tile: three workgroups fit a CU
-    __shared__ __align__(16) uint8_t vt[2][D * kVRow];
+__global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
+    constexpr int D = DT * 32;
+    constexpr int kKTile = kKeys * D;                            // bytes of a K tile
+    constexpr int kVTile = D * kKeys * 2;                        // bytes of a V tile, fp16 [channel][slot]
+    constexpr int kKC = kKTile / 4096;                           // copies of a K tile per wavefront
+    __shared__ __align__(16) uint8_t kt[kRing * kKTile];
+    __shared__ __align__(16) uint8_t vt[2 * kVTile];
+    __shared__ __align__(16) uint8_t vq[2 * kKTile];                // V tiles as they come
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int S = a.S, H = a.H;
     const int nb = S / kQRows;
@@ -75,12 +109,12 @@ __global__ __launch_bounds__(256, 3) void qk_log2_attn_kernel(const QkArgs a) {
     const int h = rank % H;
     const int b = a.causal ? nb - 1 - rank / H : rank / H;
     const int q0 = b * kQRows;
-    const int r0 = q0 + wave * 32;
+    const int r0 = __builtin_amdgcn_readfirstlane(q0 + wave * 32);
     const int row = r0 + (lane & 31);                            // this lane's query
-    const int g = lane >> 5;
+    const int c = lane & 31, g = lane >> 5;
     const int nt = (a.causal ? q0 + kQRows : S) / kKeys;         // key tiles of the block
-    const int wave_last = a.causal ? r0 + 31 : S - 1;            // tiles starting past this are dead for the wavefront
-    const int wave_lim = a.causal ? r0 : S - 1;                  // a sub-tile reaching past this needs the mask
+    const int n_main = a.causal ? nt - 2 : nt;                   // tiles that are live for every row of the block
+    const int last_sub = a.causal ? r0 >> 5 : 2 * nt - 1;        // last sub-tile with a live key for this wavefront
 
     const int8_t *qh = a.q + (int64_t)h * S * D;
     const int8_t *kh = a.k + (int64_t)h * S * D;
@@ -91,77 +125,92 @@ __global__ __launch_bounds__(256, 3) void qk_log2_attn_kernel(const QkArgs a) {
 #pragma unroll
     for (int s = 0; s < DT; ++s) qf[s] = *reinterpret_cast<const agq_v4i *>(qh + (int64_t)row * D + 32 * s + 16 * g);
 
-    // K tile: 64 keys x D bytes; thread = (key tid >> 2, quarter tid & 3 of the row)
-    constexpr int KL = D / 64;                                   // 16-byte loads per thread
-    agq_u4 kraw[KL];
-    const int kkey = threadIdx.x >> 2, kpart = threadIdx.x & 3;
-    auto load_k = [&](int t) {
+    // K tiles: copied straight into a ring of four in LDS, for both passes in one sequence (tile T of the sequence is key
+    // tile T, or T - nt in pass 2).  Sixteen lanes read LDS at a time, 256 bytes; the sixteen-byte pieces of a key's row
+    // are permuted by the key so that a fragment read (one piece of sixteen keys) meets every bank once: piece i of
+    // row r lies at i ^ (r >> 1 & 7) where two rows fill the banks (D = 128), at i ^ (r >> 2 & 3) where four do.  A row stays
+    // inside its own cache line on the way.
+    constexpr int kPieces = D / 16;
+    const int kr = lane / kPieces;                               // row among those that a copy holds: eight or sixteen
+    uint32_t k_src[kKC];
 #pragma unroll
-        for (int i = 0; i < KL; ++i)
-            kraw[i] = *reinterpret_cast<const agq_u4 *>(kh + (int64_t)(t * kKeys + kkey) * D + (kpart * KL + i) * 16);
+    for (int i = 0; i < kKC; ++i) {
+        const int sw = kPieces == 8 ? (4 * i + (kr >> 1)) & 7 : (kr >> 2) & 3;
+        k_src[i] = (uint32_t)(kr * D + (((lane & (kPieces - 1)) ^ sw) << 4));
+    }
+    const uint32_t wave_u = __builtin_amdgcn_readfirstlane((uint32_t)wave);
+    const uint32_t k_lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t *)kt) + wave_u * (kKC * 1024);
+    auto copy_k = [&](int T) {                                   // past the end: the last tile again, into a slot nobody reads
+        const int t = T < nt ? T : min(T, 2 * nt - 1) - nt;
+        const int8_t *const src = kh + (int64_t)t * kKTile + wave_u * (kKC * 1024);
+        const uint32_t dst = k_lds + (uint32_t)(T & (kRing - 1)) * kKTile;
+        lds_dma16_s<0, 0>(k_src[0], src, dst);
+        if constexpr (kKC == 2) lds_dma16_s<0, 1024>(k_src[kKC - 1], src, dst);
     };
-    auto store_k = [&](uint8_t *buf) {
+    uint32_t k_rd[DT];                                           // operand reads: sixteen d of k-group g of step s, key l & 31
+    const int swz = kPieces == 8 ? (c >> 1) & 7 : (c >> 2) & 3;
 #pragma unroll
-        for (int i = 0; i < KL; ++i) *reinterpret_cast<agq_u4 *>(buf + kkey * kKRow + (kpart * KL + i) * 16) = kraw[i];
+    for (int s = 0; s < DT; ++s) k_rd[s] = (uint32_t)(c * D + (((2 * s + g) ^ swz) << 4));
+    agq_v4i kf[DT];
+    auto read_k = [&](int s, const uint8_t *tile, int sub) { kf[s] = *reinterpret_cast<const agq_v4i *>(tile + k_rd[s] + sub * (32 * D)); };
+
+    // score tile of 32 keys, transposed: register 4 q + r = key 8 q + 4 g + r, this lane's query
+    agq_v16i acc0, acc1, acc2, acc3, cinit;
+    auto mfma_s = [&](int s, agq_v16i &acc) {
+        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf[s], qf[s], s == 0 ? cinit : acc, 0, 0, 0);
     };
 
-    // V tile: int8 [key][d] -> fp16 [d][slot] in LDS.  A thread unit is (chunk of eight
-    // slots, four channels); the eight slots of chunk ch = 4 sub + 2 u + g' hold the keys
-    // 32 sub + 16 u + 8 (i >> 2) + 4 g' + (i & 3), i = 0..7 (see the header).
-    uint32_t vraw[8];
-    const bool vu_ok = (int)threadIdx.x < 8 * DQ;
-    const int vu_c = threadIdx.x % DQ, vu_ch = vu_ok ? threadIdx.x / DQ : 0;
-    auto load_v = [&](int t) {
+    // V tiles: copied as they are into one of two buffers, then int8 [key][d] -> fp16 [d][slot].  A thread's unit is (chunk of
+    // eight slots, NB channels); the eight slots of chunk ch = 4 sub + 2 u + g' hold the keys
+    // 32 sub + 16 u + 8 (i >> 2) + 4 g' + (i & 3), i = 0..7 (see the header).  Channel NB c + n is column c of output block
+    // n, row 32 n + c of the tile; chunk ch of a row lies at place ch ^ (row >> 1 & 7), for the same reason as K's
+    // pieces.      constexpr int NB = DT;
+    const uint32_t vq_lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t *)vq) + wave_u * (kKC * 1024);
+    auto copy_v = [&](int t) {                                   // past the end: the last tile again
+        const int8_t *const src = vh + (int64_t)min(t, nt - 1) * kKTile + wave_u * (kKC * 1024);
+        const uint32_t dst = vq_lds + (uint32_t)(t & 1) * kKTile;
+        lds_dma16_s<0, 0>((uint32_t)lane * 16, src, dst);
+        if constexpr (kKC == 2) lds_dma16_s<0, 1024>((uint32_t)lane * 16, src, dst);
+    };
+    const int vu_c = threadIdx.x & 31, vu_ch = threadIdx.x >> 5;
+    const uint8_t *const v_src = vq + (32 * (vu_ch >> 2) + 16 * ((vu_ch >> 1) & 1) + 4 * (vu_ch & 1)) * D + NB * vu_c;
+    uint8_t *const v_dst = vt + vu_c * 128 + ((vu_ch ^ ((vu_c >> 1) & 7)) << 4);
+    uint32_t vx[8];
+    auto read_v = [&](int t) {                                   // bytes v + 128
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int key = t * kKeys + 32 * (vu_ch >> 2) + 16 * ((vu_ch >> 1) & 1) + 8 * (i >> 2) + 4 * (vu_ch & 1) + (i & 3);
-            vraw[i] = *reinterpret_cast<const uint32_t *>(vh + (int64_t)key * D + 4 * vu_c);
+            const uint8_t *const p = v_src + (t & 1) * kKTile + (8 * (i >> 2) + (i & 3)) * D;
+            vx[i] = (NB == 4 ? *reinterpret_cast<const uint32_t *>(p) : *reinterpret_cast<const uint16_t *>(p)) ^ 0x80808080u;
         }
     };
-    auto store_v = [&](uint8_t *buf) {
-        const agq_v2h bias = {(_Float16)1152.0f, (_Float16)1152.0f};
-        uint32_t x[8];
+    // as the low byte of a half, v + 128 is the number (v + 128) 2^-24, and one fused multiply-add makes it v 2^-9
+    auto store_v = [&](int t, auto bb_tag) {
+        constexpr int bb = decltype(bb_tag)::value;
+        agq_u4 out;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = vraw[i] ^ 0x80808080u;            // bytes v + 128
-#pragma unroll
-        for (int bb = 0; bb < 4; ++bb) {
-            // halves 0x64uu = 1024 + (v + 128) of slots 2 i and 2 i + 1 of channel 4 c + bb
-            const uint32_t sel = 0x0C000C00u | (uint32_t)bb | ((uint32_t)(4 + bb) << 16);
-            agq_u4 out;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t w = __builtin_amdgcn_perm(x[2 * i + 1], x[2 * i], sel) | 0x64006400u;
-                out[i] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(agq_v2h, w) - bias);
-            }
-            if (vu_ok) *reinterpret_cast<agq_u4 *>(buf + (bb * DQ + vu_c) * kVRow + (vu_ch << 4)) = out;
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t w = __builtin_amdgcn_perm(vx[2 * i + 1], vx[2 * i], 0x0C000C00u | (uint32_t)bb | ((uint32_t)(4 + bb) << 16));
+            out[i] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(agq_v2h, w), agq_v2h{(_Float16)32768.0f, (_Float16)32768.0f},
+                                                                            agq_v2h{(_Float16)-0.25f, (_Float16)-0.25f}));
         }
+        *reinterpret_cast<agq_u4 *>(v_dst + (t & 1) * kVTile + bb * (32 * 128)) = out;
     };
 
-    // scores of a 32-key sub-tile, transposed: register 4 q + r = key 8 q + 4 g + r, this lane's query
-    auto scores = [&](const uint8_t *kbuf, int sub) {
-        agq_v16i acc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0;
-#pragma unroll
-        for (int s = 0; s < DT; ++s) {
-            const agq_v4i kf = *reinterpret_cast<const agq_v4i *>(kbuf + (32 * sub + (lane & 31)) * kKRow + 32 * s + 16 * g);
-            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf, qf[s], acc, 0, 0, 0);
-        }
-        return acc;
-    };
+    copy_k(0);
+    copy_k(1);
+    meet<0>();                                                   // K tiles 0 and 1 and Q have landed
+    copy_k(2);
+    copy_v(0);
+    copy_v(1);
 
-    // both sub-tiles of a tile at once: two independent accumulation chains
-    auto scores2 = [&](const uint8_t *kbuf, agq_v16i &acc0, agq_v16i &acc1) {
+    // The accumulators start at the bit pattern of 1.5 * 2^23: read as floats they are 1.5 * 2^23 + s, and a subtraction
+    // makes that (float)s for half the time of a conversion.  As integers they order like the scores.
+    constexpr int kBias = 0x4B400000;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc0[r] = acc1[r] = 0;
-#pragma unroll
-        for (int s = 0; s < DT; ++s) {
-            const agq_v4i k0f = *reinterpret_cast<const agq_v4i *>(kbuf + (lane & 31) * kKRow + 32 * s + 16 * g);
-            const agq_v4i k1f = *reinterpret_cast<const agq_v4i *>(kbuf + (32 + (lane & 31)) * kKRow + 32 * s + 16 * g);
-            acc0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(k0f, qf[s], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(k1f, qf[s], acc1, 0, 0, 0);
-        }
-    };
+    for (int r = 0; r < 16; ++r) cinit[r] = kBias;
+    float kappa = a.kappa;                                       // in a vector register: a product of three of those is the faster one
+    asm("" : "+v"(kappa));
+    auto score_of = [&](int bits) { return __int_as_float(bits) - AGQ_MAGIC; };
 
     // ---- pass 1: per row the maximum score M (an integer) and sum_j 2^(kappa (s_j - M)).
     // Differences of scores are exact integers, so the only roundings are the product
@@ -169,180 +218,358 @@ __global__ __launch_bounds__(256, 3) void qk_log2_attn_kernel(const QkArgs a) {
     constexpr int kMasked = -(1 << 30);                          // stands for -infinity (|s| < 2^23)
     int run_m = kMasked;
     float run_s = 0.f;
-    auto stats = [&](agq_v16i acc, int kb, auto masked_tag) {
-        constexpr bool MASKED = decltype(masked_tag)::value;
-        if (MASKED) {                                            // diagonal sub-tile: keys past the query do not count
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                if (kb + 8 * (r >> 2) + 4 * g + (r & 3) > row) acc[r] = kMasked;
-        }
-        int mx = acc[0];
+    for (int s = 0; s < DT; ++s) read_k(s, kt, 0);
 #pragma unroll
-        for (int r = 1; r < 16; ++r) mx = max(mx, acc[r]);
+    for (int s = 0; s < DT; ++s) mfma_s(s, acc0);
+#pragma unroll
+    for (int s = 0; s < DT; ++s) read_k(s, kt, 1);
+#pragma unroll
+    for (int s = 0; s < DT; ++s) mfma_s(s, acc1);
+    // a sub-tile at the diagonal
+    auto stats = [&](const agq_v16i &acc, int sub, bool masked) {
+        auto dead = [&](int r) { return masked && 32 * sub + 8 * (r >> 2) + 4 * g + (r & 3) > row; };   // keys past the query do not count
+        int mx = kMasked;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = max(mx, dead(r) ? kMasked : acc[r] - kBias);
         const int nm = max(run_m, mx);
         float add = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const float term = __builtin_amdgcn_exp2f(a.kappa * (float)(acc[r] - nm));
-            add += (MASKED && acc[r] == kMasked) ? 0.f : term;
+            const float term = __builtin_amdgcn_exp2f(kappa * (float)(acc[r] - kBias - nm));
+            add += dead(r) ? 0.f : term;
         }
         // nothing counted so far (run_m == kMasked) means run_s == 0: the factor does not matter
-        run_s = run_s * __builtin_amdgcn_exp2f(a.kappa * (float)(run_m - nm)) + add;
+        run_s = run_s * __builtin_amdgcn_exp2f(kappa * (float)(run_m - nm)) + add;
         run_m = nm;
     };
-    load_k(0);
-    for (int t = 0; t < nt; ++t) {
-        uint8_t *kbuf = (t & 1) ? vt[0] : kt;                    // the V buffers are idle in this pass: two K tiles, one barrier
-        store_k(kbuf);
-        if (t + 1 < nt) load_k(t + 1);
-        __syncthreads();
-        const int k0 = t * kKeys;
-        if (k0 > wave_last) continue;                            // wave-uniform; the barrier above was joined
-        if (k0 + kKeys - 1 <= wave_lim) {
-            // whole tile live for every row of the wavefront: 32 scores per lane, one rescale
-            agq_v16i acc0, acc1;
-            scores2(kbuf, acc0, acc1);
-            int mx = max(acc0[0], acc1[0]);
+    auto tile_stats = [&](const agq_v16i &cur0, const agq_v16i &cur1) {   // a whole live tile
+        int mx = run_m + kBias;
 #pragma unroll
-            for (int r = 1; r < 16; ++r) mx = max(mx, max(acc0[r], acc1[r]));
-            const int nm = max(run_m, mx);
-            // kappa s - kappa M with one rounding of the product (|kappa s| stays far below 2^10,
-            // so the difference is good to ~1e-5: enough for a sum of 2^x)
-            const float nmf = -a.kappa * (float)nm;
-            float add0 = 0.f, add1 = 0.f;
+        for (int r = 0; r < 16; ++r) mx = max(mx, max(cur0[r], cur1[r]));
+        const int nm = mx - kBias;
+        const float nmf = -kappa * (float)nm;
+        float add0 = 0.f, add1 = 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                add0 += __builtin_amdgcn_exp2f(fmaf(a.kappa, (float)acc0[r], nmf));
-                add1 += __builtin_amdgcn_exp2f(fmaf(a.kappa, (float)acc1[r], nmf));
+        for (int r = 0; r < 16; ++r) {
+            add0 += __builtin_amdgcn_exp2f(fmaf(kappa, score_of(cur0[r]), nmf));
+            add1 += __builtin_amdgcn_exp2f(fmaf(kappa, score_of(cur1[r]), nmf));
+        }
+        run_s = run_s * __builtin_amdgcn_exp2f(kappa * (float)(run_m - nm)) + (add0 + add1);
+        run_m = nm;
+    };
+    // A tile that is live for every row of the wavefront, from cur0 and cur1, and the scores of the next tile.  An
+    // instruction that needs the result of the one before it waits twice as long as any other: four scores at a time go
+    // through difference, product and exponential, and a slot later into the sums.
+    auto pass1_tile = [&](int T, const agq_v16i &cur0, const agq_v16i &cur1, agq_v16i &nxt0, agq_v16i &nxt1) {
+        const uint8_t *const ahead = kt + ((T + 1) & (kRing - 1)) * kKTile;
+        copy_k(T + 3);
+#pragma unroll
+        for (int s = 0; s < DT; ++s) read_k(s, ahead, 0);
+        int mx[4] = {run_m + kBias, cur0[0], cur1[0], cur0[1]};
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx[r & 3] = max(mx[r & 3], max(cur0[r], cur1[r]));
+        const int nm = max(max(mx[0], mx[1]), max(mx[2], mx[3])) - kBias;
+        // kappa s - kappa M with one rounding of the product (|kappa s| stays far below 2^10,
+        // so the difference is good to ~1e-5: enough for a sum of 2^x)
+        const float nmf = -kappa * (float)nm;
+        const float keep = __builtin_amdgcn_exp2f(kappa * (float)(run_m - nm));
+        float add0 = 0.f, add1 = 0.f;
+        constexpr int R = 16 / DT;                               // scores of a slot: R / 2 of either sub-tile
+        float e[R];
+        auto slot = [&](auto k_tag) {
+            constexpr int k = decltype(k_tag)::value, s = k % DT;
+            if constexpr (k < 2 * DT) {
+                mfma_s(s, k < DT ? nxt0 : nxt1);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (k < DT) read_k(s, ahead, 1);
+                float x[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) x[r] = score_of(r & 1 ? cur1[k * (R / 2) + r / 2] : cur0[k * (R / 2) + r / 2]);
+                __builtin_amdgcn_sched_barrier(0);
+                if (k > 0) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) (r & 1 ? add1 : add0) += e[r];
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r) x[r] = fmaf(kappa, x[r], nmf);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = 0; r < R; ++r) e[r] = __builtin_amdgcn_exp2f(x[r]);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            run_s = run_s * __builtin_amdgcn_exp2f(a.kappa * (float)(run_m - nm)) + (add0 + add1);
-            run_m = nm;
-            continue;
-        }
+        };
+        slot(Int<0>{}); slot(Int<1>{}); slot(Int<2>{}); slot(Int<3>{}); slot(Int<4>{}); slot(Int<5>{}); slot(Int<6>{}); slot(Int<7>{});
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-            const int kb = k0 + 32 * sub;
-            if (kb > wave_last) continue;
-            const agq_v16i acc = scores(kbuf, sub);
-            if (kb + 31 > wave_lim) stats(acc, kb, std::true_type{});
-            else stats(acc, kb, std::false_type{});
+        for (int r = 0; r < R; ++r) (r & 1 ? add1 : add0) += e[r];
+        run_s = run_s * keep + (add0 + add1);
+        run_m = nm;
+        meet<kKC>();                                             // the tile after the next one has landed
+    };
+    int T = 0;
+    for (; T + 2 <= n_main; T += 2) {
+        pass1_tile(T, acc0, acc1, acc2, acc3);
+        pass1_tile(T + 1, acc2, acc3, acc0, acc1);
+    }
+    auto last_tile = [&](int T, const agq_v16i &cur0, const agq_v16i &cur1) {
+        const int sub = 2 * T;
+        if (sub + 1 < last_sub) {
+            tile_stats(cur0, cur1);
+        } else {
+            if (sub <= last_sub) stats(cur0, sub, sub == last_sub);
+            if (sub + 1 <= last_sub) stats(cur1, sub + 1, true);
         }
+    };
+    if (a.causal) {                                              // the two tiles at the diagonal
+        const uint8_t *const ahead = kt + ((T + 1) & (kRing - 1)) * kKTile;
+        copy_k(T + 3);
+#pragma unroll
+        for (int s = 0; s < DT; ++s) read_k(s, ahead, 0);
+#pragma unroll
+        for (int s = 0; s < DT; ++s) mfma_s(s, acc2);
+#pragma unroll
+        for (int s = 0; s < DT; ++s) read_k(s, ahead, 1);
+#pragma unroll
+        for (int s = 0; s < DT; ++s) mfma_s(s, acc3);
+        last_tile(T, acc0, acc1);
+        meet<kKC>();
+        copy_k(T + 4);
+        last_tile(T + 1, acc2, acc3);
+        meet<kKC>();
     }
     // the two lanes of a query (k-groups 0 and 1) join their halves; every row has its own key, so M is a real score
     const int om = __shfl_xor(run_m, 32);
     const float os = __shfl_xor(run_s, 32);
     const int M = max(run_m, om);
     // (a half with nothing counted has sum 0, whatever its factor)
-    const float tot = run_s * __builtin_amdgcn_exp2f(a.kappa * (float)(run_m - M)) +
-                      os * __builtin_amdgcn_exp2f(a.kappa * (float)(om - M));
+    const float tot = run_s * __builtin_amdgcn_exp2f(kappa * (float)(run_m - M)) +
+                      os * __builtin_amdgcn_exp2f(kappa * (float)(om - M));
     // -log2 p = t = kappa (M - s) + log2(tot).  The weight 2^(qmax - c) has the fp16 exponent field
-    // 15 + qmax - c = round(15 + qmax - t) clamped to [15, 15 + qmax]: one fused multiply-add gives
-    // 15 + qmax - t, adding 1.5 * 2^23 rounds it to an integer (ties to even: a tie has measure
-    // zero and lies inside the evaluation error anyway) that sits in the low bits of the pattern.
-    const float c2 = (float)(15 + a.qmax) - __builtin_amdgcn_logf(tot) - a.kappa * (float)M;   // v_log_f32: base 2
+    // 15 + qmax - c = round(15 + qmax - t) clamped to [15, 15 + qmax]: one fused multiply-add gives 15 + qmax - t, and
+    // after the clamp a conversion to a byte rounds it (to even: a tie has measure zero and lies inside the
+    // evaluation error anyway).
+    const float c2 = (float)(15 + a.qmax) - __builtin_amdgcn_logf(tot) - kappa * (float)M;   // v_log_f32: base 2
+    float elo = 15.0f, ehi = (float)(15 + a.qmax);
+    asm("" : "+v"(elo), "+v"(ehi));
 
     // ---- pass 2: codes, weights, product with V
-    // four accumulators: block n holds the channels 4 c + n (c = column l & 31 < D / 4)
-    agq_v16f acc_o[4];
+    agq_v16f acc_o[NB];
 #pragma unroll
-    for (int n = 0; n < 4; ++n)
+    for (int n = 0; n < NB; ++n)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc_o[n][r] = 0.f;
-    const int bslot = min(lane & 31, DQ - 1);
-    const uint32_t wtop = 15u + (uint32_t)a.qmax;                // exponent field of the weight of code 0
-    const float elo = AGQ_MAGIC + 15.0f, ehi = AGQ_MAGIC + (float)(15 + a.qmax);
+    uint32_t v_rd[4];                                            // operand reads: chunk 4 sub + 2 u + g of row c
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v_rd[i] = (uint32_t)(c * 128 + (((2 * i + g) ^ ((c >> 1) & 7)) << 4));
+    agq_v8h vf[NB];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) vf[n] = agq_v8h{};
+    uint32_t f0 = 0, f1 = 0;                                     // exponents of a half sub-tile's eight weights, a byte each
+    agq_u4 w;
 
-    auto weights = [&](const agq_v16i &acc, int kb, const uint8_t *vbuf, int sub, auto masked_tag) {
+    read_v(0);
+    store_v(0, Int<0>{});
+    store_v(0, Int<1>{});
+    if constexpr (NB == 4) {
+        store_v(0, Int<2>{});
+        store_v(0, Int<3>{});
+    }
+    {
+        const uint8_t *const first = kt + (nt & (kRing - 1)) * kKTile;
+#pragma unroll
+        for (int s = 0; s < DT; ++s) read_k(s, first, 0);
+#pragma unroll
+        for (int s = 0; s < DT; ++s) mfma_s(s, acc0);
+#pragma unroll
+        for (int s = 0; s < DT; ++s) read_k(s, first, 1);
+    }
+    // importance on the quantized map: the weight of the first key (always live)
+    if (a.score && g == 0)
+        atomicAdd(&a.score[row], 1 << (__builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(fmaf(kappa, score_of(acc0[0]), c2), elo, ehi), 0, 0) - 15));
+    meet<63>();                                                  // V tile 0 is in LDS
+
+    // the weights of half sub-tile `hs` (keys 16 hs ..) from their exponents
+    auto exponents = [&] {                                       // upper bytes of the fp16 patterns
+        f0 <<= 2;
+        f1 <<= 2;
+    };
+    auto weights = [&](int hs, auto masked_tag) {
         constexpr bool MASKED = decltype(masked_tag)::value;
-        uint32_t ex[16];       // bit patterns whose low byte is the exponent field of the weight (0 = weight 0)
-        uint32_t cw[4] = {0, 0, 0, 0};                           // codes of keys 8 q + 4 g + r, r = 0..3, as nibbles
+        w[0] = __builtin_amdgcn_perm(f0, f0, 0x010C000Cu);
+        w[1] = __builtin_amdgcn_perm(f0, f0, 0x030C020Cu);
+        w[2] = __builtin_amdgcn_perm(f1, f1, 0x010C000Cu);
+        w[3] = __builtin_amdgcn_perm(f1, f1, 0x030C020Cu);
+        if (MASKED) {
+            const int left = row - (16 * hs + 4 * g);            // key i of a lane's four is live if i <= left
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const float ef = __builtin_amdgcn_fmed3f(fmaf(a.kappa, (float)acc[r], c2) + AGQ_MAGIC, elo, ehi);
-            uint32_t e = __float_as_uint(ef);                    // 0x4B400000 + exponent field
-            if (MASKED && kb + 8 * (r >> 2) + 4 * g + (r & 3) > row) e = 0;
-            ex[r] = e;
-            if (CODES) cw[r >> 2] |= ((e & 0xFFu) ? wtop - (e & 0xFFu) : (uint32_t)a.qmax) << (4 * (r & 3));
-            // importance on the quantized map: the weight of the first key (always live)
-            if (r == 0 && a.score && kb == 0 && g == 0) atomicAdd(&a.score[row], 1 << ((int)(e & 0xFFu) - 15));
-        }
-        if (CODES) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<uint16_t *>(a.codes + ((int64_t)h * S + row) * (S >> 1) + ((kb + 8 * q + 4 * g) >> 1)) =
-                    (uint16_t)cw[q];
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            // first operand: slots 8 g .. 8 g + 7 of step u = registers 8 u .. 8 u + 7, as fp16 bit patterns
-            agq_u4 wq;
-#pragma unroll
-            for (int j = 0; j < 4; ++j)   // the shifts drop everything above the low byte's five bits
-                wq[j] = ((ex[8 * u + 2 * j + 1] << 16) | ex[8 * u + 2 * j]) << 10;
-            const agq_v8h af = __builtin_bit_cast(agq_v8h, wq);
-            const int chunk = 4 * sub + 2 * u + g;
-#pragma unroll
-            for (int n = 0; n < 4; ++n) {
-                const agq_v8h bf = *reinterpret_cast<const agq_v8h *>(vbuf + (n * DQ + bslot) * kVRow + (chunk << 4));
-                acc_o[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af, bf, acc_o[n], 0, 0, 0);
+            for (int i = 0; i < 4; ++i) {
+                const int key = 8 * (i >> 1) + 2 * (i & 1);
+                w[i] &= (key <= left ? 0xFFFFu : 0u) | (key + 1 <= left ? 0xFFFF0000u : 0u);
             }
         }
     };
-
-    __syncthreads();                                             // pass 1 is done with the K tile
-    load_k(0);
-    load_v(0);
-    for (int t = 0; t < nt; ++t) {
-        uint8_t *vbuf = vt[t & 1];
-        if (t > 0) __syncthreads();                              // everyone is done with the previous K tile
-        store_k(kt);
-        store_v(vbuf);
-        if (t + 1 < nt) {
-            load_k(t + 1);
-            load_v(t + 1);
-        }
-        __syncthreads();
-        const int k0 = t * kKeys;
-        if (k0 > wave_last) continue;                            // wave-uniform; the barriers above were joined
-        if (k0 + kKeys - 1 <= wave_lim) {                        // whole tile live: both sub-tiles' scores first
-            agq_v16i acc0, acc1;
-            scores2(kt, acc0, acc1);
-            weights(acc0, k0, vbuf, 0, std::false_type{});
-            weights(acc1, k0 + 32, vbuf, 1, std::false_type{});
-            continue;
-        }
+    auto codes = [&](int hs, uint32_t f, int q, auto masked_tag) {   // keys 16 hs + 8 q + 4 g .. + 3
+        const int key = 16 * hs + 8 * q + 4 * g;
+        uint32_t cw = 0;
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-            const int kb = k0 + 32 * sub;
-            if (kb > wave_last) continue;
-            const agq_v16i acc = scores(kt, sub);
-            if (kb + 31 > wave_lim) weights(acc, kb, vbuf, sub, std::true_type{});
-            else weights(acc, kb, vbuf, sub, std::false_type{});
+        for (int r = 0; r < 4; ++r)
+            cw |= ((decltype(masked_tag)::value && key + r > row) ? (uint32_t)a.qmax : 15u + (uint32_t)a.qmax - ((f >> (8 * r)) & 255u)) << (4 * r);
+        *reinterpret_cast<uint16_t *>(a.codes + ((int64_t)h * S + row) * (S >> 1) + (key >> 1)) = (uint16_t)cw;
+    };
+    // Half a sub-tile (16 keys: registers 8 u .. 8 u + 7 of the scores): the exponents of its weights, the product of the half
+    // before it with V, and half of the scores of the next sub-tile, dealt out one MFMA at a time.  The eight scores go
+    // through conversion, product and rounding in pairs, a slot for each, so that no instruction needs the result of
+    // one right before it.  `other` is run in the slots.
+    auto half = [&](const agq_v16i &cur, agq_v16i &nxt, int sub, auto u_tag, const uint8_t *vtile, const uint8_t *ahead, auto masked_tag, auto other) {
+        constexpr int u = decltype(u_tag)::value;
+        const int vi = 2 * (sub & 1) + u, hs = 2 * sub + u;
+        float x[8];
+        uint32_t n0 = 0, n1 = 0;
+        auto cvt = [&](auto i_tag) {                             // pair i: registers i and i + 4
+            constexpr int i = decltype(i_tag)::value;
+            x[i] = score_of(cur[8 * u + i]);
+            x[i + 4] = score_of(cur[8 * u + i + 4]);
+        };
+        auto mul = [&](auto i_tag) {
+            constexpr int i = decltype(i_tag)::value;
+            x[i] = fmaf(kappa, x[i], c2);
+            x[i + 4] = fmaf(kappa, x[i + 4], c2);
+        };
+        auto rnd = [&](auto i_tag) {
+            constexpr int i = decltype(i_tag)::value;
+            n0 = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(x[i], elo, ehi), i, n0);
+            n1 = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(x[i + 4], elo, ehi), i, n1);
+        };
+        auto pv = [&](auto n_tag) {
+            constexpr int n = decltype(n_tag)::value;
+            acc_o[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(agq_v8h, w), vf[n], acc_o[n], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            vf[n] = *reinterpret_cast<const agq_v8h *>(vtile + v_rd[vi] + n * (32 * 128));
+        };
+        auto qk = [&](auto s_tag) {
+            constexpr int s = decltype(s_tag)::value;
+            mfma_s(s, nxt);
+            __builtin_amdgcn_sched_barrier(0);
+            read_k(s, ahead, sub & 1);
+        };
+        auto end_slot = [&](auto k_tag) {
+            other(k_tag);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        constexpr Int<0> i0; constexpr Int<1> i1; constexpr Int<2> i2; constexpr Int<3> i3; constexpr Int<4> i4; constexpr Int<5> i5;
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (NB == 4) {
+            qk(Int<2 * u>{});
+            exponents(); cvt(i0); weights(hs - 1, masked_tag);
+            end_slot(i0);
+            pv(i0);
+            cvt(i1); mul(i0);
+            end_slot(i1);
+            pv(i1);
+            cvt(i2); mul(i1); rnd(i0);
+            end_slot(i2);
+            qk(Int<2 * u + 1>{});
+            cvt(i3); mul(i2); rnd(i1);
+            end_slot(i3);
+            pv(i2);
+            mul(i3); rnd(i2);
+            end_slot(i4);
+            pv(i3);
+            rnd(i3);
+            end_slot(i5);
+        } else {
+            qk(Int<u>{});
+            exponents(); cvt(i0); cvt(i1); weights(hs - 1, masked_tag);
+            end_slot(i0);
+            pv(i0);
+            cvt(i2); cvt(i3); mul(i0); mul(i1); rnd(i0);
+            end_slot(i1);
+            pv(i1);
+            mul(i2); mul(i3); rnd(i1); rnd(i2); rnd(i3);
+            end_slot(i2);
         }
+        f0 = n0;
+        f1 = n1;
+        if (CODES) {
+            codes(hs, f0, 0, masked_tag);
+            codes(hs, f1, 1, masked_tag);
+        }
+    };
+    auto pass2_tile = [&](int t, auto masked_tag) {
+        constexpr bool MASKED = decltype(masked_tag)::value;
+        const uint8_t *const vtile = vt + (t & 1) * kVTile;
+        const uint8_t *const ahead = kt + ((nt + t + 1) & (kRing - 1)) * kKTile;
+        auto none = [](auto) {};
+        auto stage = [&](auto part_tag) {                        // the V tile t + 1, a part of its rows
+            constexpr int part = decltype(part_tag)::value;
+            if constexpr (NB == 4) store_v(t + 1, part_tag);
+            else if constexpr ((part & 1) == 0) store_v(t + 1, Int<part / 2>{});
+        };
+        constexpr int kAt = NB == 4 ? 4 : 2;                     // slot that does it
+#define AGQ_STAGE(P)                                                     \
+    [&](auto k) {                                                        \
+        if constexpr (decltype(k)::value == kAt) stage(Int<P>{});        \
+        if constexpr (decltype(k)::value == 1 && P == 1) copy_v(t + 2);  \
+        if constexpr (decltype(k)::value == 1 && P == 2) copy_k(nt + t + 3); \
     }
+        read_v(t + 1);
+        if constexpr (!MASKED) {
+            half(acc0, acc1, 2 * t, Int<0>{}, vtile, ahead, masked_tag, AGQ_STAGE(0));
+            half(acc0, acc1, 2 * t, Int<1>{}, vtile, ahead, masked_tag, AGQ_STAGE(1));
+            half(acc1, acc0, 2 * t + 1, Int<0>{}, vtile, ahead, masked_tag, AGQ_STAGE(2));
+            half(acc1, acc0, 2 * t + 1, Int<1>{}, vtile, ahead, masked_tag, AGQ_STAGE(3));
+        } else {
+            copy_v(t + 2);
+            copy_k(nt + t + 3);
+            stage(Int<0>{});
+            stage(Int<1>{});
+            stage(Int<2>{});
+            stage(Int<3>{});
+            if (2 * t <= last_sub) {
+                half(acc0, acc1, 2 * t, Int<0>{}, vtile, ahead, masked_tag, none);
+                half(acc0, acc1, 2 * t, Int<1>{}, vtile, ahead, masked_tag, none);
+            }
+            if (2 * t + 1 <= last_sub) {
+                half(acc1, acc0, 2 * t + 1, Int<0>{}, vtile, ahead, masked_tag, none);
+                half(acc1, acc0, 2 * t + 1, Int<1>{}, vtile, ahead, masked_tag, none);
+            }
+        }
+#undef AGQ_STAGE
+        meet<kKC>();                                             // V tile t + 2 and K tile nt + t + 2 have landed
+    };
+    int t = 0;
+    for (; t < n_main; ++t) pass2_tile(t, std::false_type{});
+    for (; t < nt; ++t) pass2_tile(t, std::true_type{});
+    exponents();
+    if (a.causal) weights(2 * last_sub + 1, std::true_type{});
+    else weights(0, std::false_type{});
+#pragma unroll
+    for (int n = 0; n < NB; ++n) acc_o[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(agq_v8h, w), vf[n], acc_o[n], 0, 0, 0);
 
     // code map right of the last sub-tile this wavefront multiplied: all qmax
     if (CODES && a.causal) {
         const uint32_t fill = 0x11111111u * (uint32_t)a.qmax;
         uint8_t *dst = a.codes + ((int64_t)h * S + row) * (S >> 1);
-        const int done = (wave_last / 32 + 1) * 32;             // first key past the wavefront's last sub-tile
-        for (int k = done + g * 8; k < S; k += 16) *reinterpret_cast<uint32_t *>(dst + (k >> 1)) = fill;
+        for (int k = (last_sub + 1) * 32 + g * 8; k < S; k += 16) *reinterpret_cast<uint32_t *>(dst + (k >> 1)) = fill;
     }
 
+    __builtin_amdgcn_s_waitcnt(0x70);                            // the last copies into LDS have landed before it is given back
+
     // accumulator register 4 q + r holds query row 8 q + 4 g + r of the wavefront,
-    // channel 4 c + n in block n: four consecutive channels per lane and row
-    const int c = lane & 31;
+    // channel NB c + n in block n: NB consecutive channels per lane and row
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int orow = r0 + 8 * q + 4 * g + r;
-            __half hv[4];
+            uint32_t hv[NB / 2];
 #pragma unroll
-            for (int n = 0; n < 4; ++n) hv[n] = __float2half_rn(acc_o[n][4 * q + r] * a.out_scale);
-            if (c < DQ)
-                *reinterpret_cast<uint2 *>(a.o + (int64_t)orow * ((int64_t)H * D) + (int64_t)h * D + 4 * c) =
-                    *reinterpret_cast<const uint2 *>(hv);
+            for (int n = 0; n < NB; n += 2)
+                hv[n / 2] = __half_as_ushort(__float2half_rn(acc_o[n][4 * q + r] * a.out_scale)) |
+                            (uint32_t)__half_as_ushort(__float2half_rn(acc_o[n + 1][4 * q + r] * a.out_scale)) << 16;
+            uint32_t *const dst = reinterpret_cast<uint32_t *>(a.o + (int64_t)orow * ((int64_t)H * D) + (int64_t)h * D + NB * c);
+            if constexpr (NB == 4) *reinterpret_cast<uint2 *>(dst) = make_uint2(hv[0], hv[1]);
+            else *dst = hv[0];
         }
 }
 
@@ -362,7 +589,7 @@ int agq_launch_qk_log2_attn(const int8_t *q, const int8_t *k, const int8_t *v, i
     a.causal = causal;
     a.qmax = qmax;
     a.kappa = (float)(ldexp(1.0, e_q + e_k) * 1.4426950408889634 / sqrt((double)D));
-    a.out_scale = ldexpf(1.0f, e_v - qmax);
+    a.out_scale = ldexpf(1.0f, e_v - qmax + 9);
     static int ncu_of[64] = {0};
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) return (int)hipGetLastError();

@@ -136,3 +136,13 @@ __device__ __forceinline__ void lds_dma16(const void *gsrc, uint32_t lds_addr) {
                  : "v"(gsrc), "s"(lds_addr)
                  : "memory", "m0");
 }
+
+// Global-to-LDS copy with a scalar base address: lane l's 16 bytes at sbase + voff(l) + G go to lds_addr + L + G + 16 l
+// (inline assembly for the same reason).
+template <int L, int G>
+__device__ __forceinline__ void lds_dma16_s(uint32_t voff, const void *sbase, uint32_t lds_addr) {
+    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%4"
+                 :
+                 : "v"(voff), "s"(sbase), "s"(lds_addr), "n"(L), "n"(G)
+                 : "memory", "m0", "scc");
+}

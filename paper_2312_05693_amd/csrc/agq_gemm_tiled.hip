@@ -97,16 +97,6 @@ struct Int {
     static constexpr int value = N;
 };
 
-// Global-to-LDS copy with a scalar base address: lane l's 16 bytes at sbase + voff(l) + G go to lds_addr + L + G + 16 l
-// (see lds_dma16 in agq_device.h for why this is inline assembly).
-template <int L, int G>
-__device__ __forceinline__ void lds_dma16_s(uint32_t voff, const void *sbase, uint32_t lds_addr) {
-    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%4"
-                 :
-                 : "v"(voff), "s"(sbase), "s"(lds_addr), "n"(L), "n"(G)
-                 : "memory", "m0", "scc");
-}
-
 // TRIP: the blob and the activation stages carry extra steps in front, ordered by
 // descending factor; after the last step of a factor the accumulators are shifted
 // left by the difference to the next factor (Horner), so that at the end every

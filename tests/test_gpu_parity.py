@@ -1186,6 +1186,31 @@ def test_qk_attention_scale_and_argument_errors(agq, oracle):
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("e_q,causal,qmax", [(-3, True, 15), (-7, False, 7), (-5, True, 15), (-40, False, 15)])
+def test_qk_attention_whole_code_range(agq, oracle, D, e_q, causal, qmax):
+    """Scores that grow along the keys over the whole range of the codes, so that the maximum of a row moves in every tile
+    and on the diagonal, rows that fall instead, and rows of equal scores; from a softmax that one key decides to a flat one."""
+    H, S, e_v = 3, 384, -4
+    e_k = e_q if e_q == -40 else -5
+    rng = np.random.default_rng([77, D, e_q & 63])
+    ramp = np.clip(np.round(-128 + 255 * np.arange(S) / (S - 1)), -128, 127)
+    kq = np.stack([np.repeat(ramp[:, None], D, 1), np.repeat(ramp[::-1, None], D, 1), rng.integers(-128, 128, (S, D))]).astype(np.int8)
+    qq = rng.integers(-128, 128, (H, S, D)).astype(np.int8)
+    qq[:, ::4] = 127
+    qq[:, 1::4] = -128
+    qq[:, 2::8] = 0
+    vq = rng.integers(-128, 128, (H, S, D)).astype(np.int8)
+    o, codes, score = agq.qk_log2_softmax(dev(qq), dev(kq), dev(vq), e_q, e_k, e_v, qmax=qmax, causal=causal, want_codes=True)
+    got_c = unpack_codes(host(codes), S)
+    want_c, margin = oracle.qk_log2_codes(qq, kq, e_q, e_k, qmax, causal)
+    sure = margin > CODE_MARGIN
+    assert np.array_equal(got_c[sure], want_c[sure]) and np.abs(got_c - want_c).max() <= 1
+    _, want_o = oracle.attn_v_from_codes(got_c, vq, e_v, qmax, causal)
+    assert np.array_equal(host(o).view(np.uint16), want_o.view(np.uint16))
+    assert np.array_equal(host(score).astype(np.int64), oracle.start_token_score_codes(got_c, qmax))
+
+
 def test_qk_attention_llama13b_full_size(agq, oracle):
     """The benchmark's configuration (H = 40, S = 2048, D = 128, causal); the oracle checks two
     whole heads, and the exact integer relations behind the codes are checked for every head."""
