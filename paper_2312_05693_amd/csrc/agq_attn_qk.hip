@@ -164,7 +164,8 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
     // eight slots, NB channels); the eight slots of chunk ch = 4 sub + 2 u + g' hold the keys
     // 32 sub + 16 u + 8 (i >> 2) + 4 g' + (i & 3), i = 0..7 (see the header).  Channel NB c + n is column c of output block
     // n, row 32 n + c of the tile; chunk ch of a row lies at place ch ^ (row >> 1 & 7), for the same reason as K's
-    // pieces.      constexpr int NB = DT;
+    // pieces.
+    constexpr int NB = DT;
     const uint32_t vq_lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t *)vq) + wave_u * (kKC * 1024);
     auto copy_v = [&](int t) {                                   // past the end: the last tile again
         const int8_t *const src = vh + (int64_t)min(t, nt - 1) * kKTile + wave_u * (kKC * 1024);
