@@ -5,7 +5,12 @@
 // returns fp16 (or Eq.2 codes); the arithmetic in between is float64 with one
 // rounding to fp16 at the end, so that a result does not depend on the order of a
 // reduction or on the exponential's implementation beyond the last bit of a double.
-// All of them stream their operands once: they are bound by HBM.
+// SwiGLU's float64 exponential, quotient and rounding take longer than its bytes (1024 x 13824: 28 us for 85 MB).  Most values
+// do not need them: an fp32 evaluation with a proven error bound tells the fp16 result wherever both ends of its interval
+// round to the same one, and only the others, one in several hundred, take the float64 path; the results are float64's in
+// every case (17.7 us; 300 x 11008 8.8 -> 6.6).  The others stream their operands once: they are bound by HBM, or by
+// latency where rows are few.  (The same for RMSNorm's and the rotary embedding's results, a product and a rounding
+// there: 5-20 % slower than float64.)
 #include "agq_device.h"
 #include "agq_internal.h"
 
@@ -38,6 +43,95 @@ static_assert(sizeof(Half8) == 16, "eight fp16 are one 16-byte access");
 __device__ __forceinline__ Half8 load8(const void *p) { return __builtin_bit_cast(Half8, *reinterpret_cast<const uint4 *>(p)); }
 __device__ __forceinline__ void store8(void *p, const Half8 &h) { *reinterpret_cast<uint4 *>(p) = __builtin_bit_cast(uint4, h); }
 
+// Eight values as the four words of their access; value i by selects (i may differ from lane to lane).
+__device__ __forceinline__ uint16_t pick8(const uint4 &v, int i) {
+    const uint32_t lo = (i & 2) ? v.y : v.x, hi = (i & 2) ? v.w : v.z;
+    return (uint16_t)(((i & 4) ? hi : lo) >> (16 * (i & 1)));
+}
+__device__ __forceinline__ void put8(uint4 &v, int i, uint16_t h) {
+    const uint32_t sh = 16 * (i & 1), keep = 0xFFFF0000u >> sh, bits = (uint32_t)h << sh;
+    if ((i >> 1) == 0) v.x = (v.x & keep) | bits;
+    if ((i >> 1) == 1) v.y = (v.y & keep) | bits;
+    if ((i >> 1) == 2) v.z = (v.z & keep) | bits;
+    if ((i >> 1) == 3) v.w = (v.w & keep) | bits;
+}
+
+// The results of an operator on eight values as intervals: both ends of each as fp16 in the halves of a word, the larger
+// magnitude in the upper half.  Where the ends are the same finite number, that is the result (rounding is monotonic);
+// the check costs four instructions a value and one branch.
+struct Ends8 {
+    uint32_t w[8], differ = 0, largest = 0;
+    __device__ __forceinline__ void set(int i, uint32_t ends) {
+        w[i] = ends;
+        differ |= ends ^ __builtin_amdgcn_alignbit(ends, ends, 16);
+        largest = max(largest, ends & 0x7FFFFFFFu);
+    }
+    __device__ __forceinline__ bool open() const { return differ != 0 || largest >= 0x7C000000u; }
+    __device__ __forceinline__ uint32_t open_mask() const {
+        uint32_t m = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            m |= (w[i] != __builtin_amdgcn_alignbit(w[i], w[i], 16) || (w[i] & 0x7C00u) == 0x7C00u) ? 1u << i : 0u;
+        return m;
+    }
+    __device__ __forceinline__ uint4 values() const;
+};
+// p lo and p hi rounded to fp16 once, in the halves of a word (adding -0 keeps the sign of a zero)
+__device__ __forceinline__ uint32_t scaled_ends(float p, float lo, float hi) {
+    uint32_t d;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3" : "=v"(d) : "v"(p), "v"(lo), "v"(-0.0f));
+    asm("v_fma_mixhi_f16 %0, %1, %2, %3" : "+v"(d) : "v"(p), "v"(hi), "v"(-0.0f));
+    return d;
+}
+__device__ __forceinline__ uint4 Ends8::values() const {      // the low halves
+    auto low2 = [](uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); };
+    return make_uint4(low2(w[0], w[1]), low2(w[2], w[3]), low2(w[4], w[5]), low2(w[6], w[7]));
+}
+
+// silu(z) u in eight values, rounded once.  In fp32: e = 2^(-z log2 e) with the exponent in two parts, 1 + e and its
+// reciprocal: off by 2^-22.8 at most, over all fp16 z (all of them compared with float64); the product z u is exact.  With the
+// rounding of an end itself (2^-24) that is 2^-22.3: the interval is 2^-22 to either side.
+__device__ __forceinline__ uint16_t swiglu1(uint16_t g, uint16_t u) {
+    const double z = h2d(g);
+    return d2h(z / (1.0 + exp(-z)) * h2d(u));
+}
+template <bool F32>
+__device__ __forceinline__ Half8 swiglu8(const Half8 &g, const Half8 &u) {
+    if constexpr (!F32) {
+        Half8 o;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o.v[i] = swiglu1(g.v[i], u.v[i]);
+        return o;
+    }
+    Ends8 ends;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float z = __half2float(__ushort_as_half(g.v[i])), p = z * __half2float(__ushort_as_half(u.v[i]));
+        const float zc = __builtin_amdgcn_fmed3f(z, -64.0f, 64.0f);    // beyond: 1 / (1 + e) is 1, or the result is 0
+        const float t = zc * -0x1.715p0f;                              // thirteen bits of log2(e): exact
+        const float k = rintf(t);
+        const float f = fmaf(zc, -0x1.1d94aep-14f, t - k);             // the rest of log2(e)
+        const float e = __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(f), (int)k);
+        const float sg = __builtin_amdgcn_rcpf(1.0f + e);
+        ends.set(i, scaled_ends(p, sg * (1.0f - 0x1p-22f), sg * (1.0f + 0x1p-22f)));
+    }
+    uint4 o = ends.values();
+    if (ends.open()) {
+        const uint4 gw = __builtin_bit_cast(uint4, g), uw = __builtin_bit_cast(uint4, u);
+        for (uint32_t open = ends.open_mask(); open; open &= open - 1) {
+            const int i = __ffs((int)open) - 1;
+            put8(o, i, swiglu1(pick8(gw, i), pick8(uw, i)));
+        }
+    }
+    return __builtin_bit_cast(Half8, o);
+}
+
+// a + b of eight values: fp16 addition rounds the exact sum once
+__device__ __forceinline__ Half8 add8(const Half8 &a, const Half8 &b) {
+    typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+    return __builtin_bit_cast(Half8, __builtin_bit_cast(h8, a) + __builtin_bit_cast(h8, b));
+}
+
 constexpr int kNormThreads = 256;
 constexpr int kNormCache = 4;   // rows up to 4 * 256 * 8 = 8192 elements stay in registers between the two passes
 
@@ -69,9 +163,7 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_kernel(const uint16_t *_
         if (c < nchunk) {
             Half8 h = load8(xr + c * 8);
             if (ADD) {
-                const Half8 b = load8(rr + c * 8);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) h.v[i] = d2h(h2d(b.v[i]) + h2d(h.v[i]));
+                h = add8(load8(rr + c * 8), h);
                 store8(x1_out + (size_t)r * d + c * 8, h);
             }
             cache[it] = h;
@@ -85,9 +177,7 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_kernel(const uint16_t *_
     for (int c = tid + kNormCache * kNormThreads; c < nchunk; c += kNormThreads) {   // rows wider than the cache
         Half8 h = load8(xr + c * 8);
         if (ADD) {
-            const Half8 b = load8(rr + c * 8);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) h.v[i] = d2h(h2d(b.v[i]) + h2d(h.v[i]));
+            h = add8(load8(rr + c * 8), h);
             store8(x1_out + (size_t)r * d + c * 8, h);
         }
 #pragma unroll
@@ -207,36 +297,30 @@ __global__ __launch_bounds__(256) void rope_kernel(const RopeArgs a) {
     }
 }
 
+// From how many values on SwiGLU evaluates in fp32 first.  With fewer there is at most one workgroup on a CU, whose
+// latency the float64 path behind the fp32 one lengthens: 8192 to 400000 values 0.2-0.35 us slower, 600000 and 800000 0.06
+// faster, 1.2 million 4.5 -> 4.1 us, 2.5 million 6.8 -> 5.5.
+constexpr int64_t kSwigluF32 = 256 * 256 * 8;
+
 // a = silu(gate) * up, eight values per thread
+template <bool F32>
 __global__ __launch_bounds__(256) void swiglu_kernel(const uint16_t *__restrict__ gate, const uint16_t *__restrict__ up,
                                                      uint16_t *__restrict__ out, size_t nchunk) {
     const size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (c >= nchunk) return;
-    const Half8 g = load8(gate + c * 8), u = load8(up + c * 8);
-    Half8 o;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const double z = h2d(g.v[i]);
-        o.v[i] = d2h(z / (1.0 + exp(-z)) * h2d(u.v[i]));
-    }
-    store8(out + c * 8, o);
+    store8(out + c * 8, swiglu8<F32>(load8(gate + c * 8), load8(up + c * 8)));
 }
 
 // the same over rows of F8 chunks (grid: chunks of a row, rows), with the rows' Eq.2 codes in the operand order of the
 // tiled GEMM
+template <bool F32>
 __global__ __launch_bounds__(256) void swiglu_codes_kernel(const uint16_t *__restrict__ gate, const uint16_t *__restrict__ up,
                                                            uint16_t *__restrict__ out, int F8, const AgqQuant q,
                                                            char *__restrict__ tiles) {
     const int c = blockIdx.x * 256 + threadIdx.x, r = blockIdx.y;
     if (c >= F8) return;
     const size_t at = ((size_t)r * F8 + c) * 8;
-    const Half8 g = load8(gate + at), u = load8(up + at);
-    Half8 o;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const double z = h2d(g.v[i]);
-        o.v[i] = d2h(z / (1.0 + exp(-z)) * h2d(u.v[i]));
-    }
+    const Half8 o = swiglu8<F32>(load8(gate + at), load8(up + at));
     store8(out + at, o);
     *reinterpret_cast<uint2 *>(tiles + agq_code_offset(r, c, F8 >> 4)) = agq_quant8<true>(__builtin_bit_cast(uint4, o), q);
 }
@@ -245,11 +329,7 @@ __global__ __launch_bounds__(256) void add_kernel(const uint16_t *__restrict__ a
                                                   uint16_t *__restrict__ out, size_t nchunk) {
     const size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (c >= nchunk) return;
-    const Half8 x = load8(a + c * 8), y = load8(b + c * 8);
-    Half8 o;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) o.v[i] = d2h(h2d(x.v[i]) + h2d(y.v[i]));
-    store8(out + c * 8, o);
+    store8(out + c * 8, add8(load8(a + c * 8), load8(b + c * 8)));
 }
 
 }  // namespace
@@ -291,14 +371,14 @@ int agq_launch_rope(const void *q, const void *k, const void *v, int64_t S, int6
 int agq_launch_swiglu(const void *gate, const void *up, void *out, int64_t n, void *stream) {
     if (n == 0) return 0;
     const size_t nchunk = (size_t)n / 8;
-    swiglu_kernel<<<(unsigned)((nchunk + 255) / 256), 256, 0, (hipStream_t)stream>>>((const uint16_t *)gate, (const uint16_t *)up,
+    (n >= kSwigluF32 ? swiglu_kernel<true> : swiglu_kernel<false>)<<<(unsigned)((nchunk + 255) / 256), 256, 0, (hipStream_t)stream>>>((const uint16_t *)gate, (const uint16_t *)up,
                                                                                    (uint16_t *)out, nchunk);
     return (int)hipGetLastError();
 }
 
 int agq_launch_swiglu_rows(const void *gate, const void *up, void *out, int64_t rows, int64_t F, const AgqCodes &codes, void *stream) {
     const int F8 = (int)(F / 8);
-    swiglu_codes_kernel<<<dim3((unsigned)((F8 + 255) / 256), (unsigned)rows), 256, 0, (hipStream_t)stream>>>(
+    (rows * F >= kSwigluF32 ? swiglu_codes_kernel<true> : swiglu_codes_kernel<false>)<<<dim3((unsigned)((F8 + 255) / 256), (unsigned)rows), 256, 0, (hipStream_t)stream>>>(
         (const uint16_t *)gate, (const uint16_t *)up, (uint16_t *)out, F8, agq_make_quant_signed(codes.bits, codes.e, 0),
         (char *)codes.tiles);
     return (int)hipGetLastError();

@@ -308,6 +308,23 @@ def test_elementwise_operators_on_special_values(agq, blk_oracle):
     assert L.agq_residual_add(None, None, None, 0, None) == agq.AGQ_OK
 
 
+@pytest.mark.parametrize("n", [256 * 256 * 8 - 8, 256 * 256 * 8 + 24])
+def test_swiglu_on_every_gate_value(agq, blk_oracle, n):
+    """Every finite fp16 gate value with factors of all magnitudes, specials among them, where the float64 path takes all values
+    and where it takes those that fp32 leaves open."""
+    gate = np.arange(65536, dtype=np.uint32).astype(np.uint16).view(np.float16)
+    gate = np.resize(gate[np.isfinite(gate)], n)
+    rng = np.random.default_rng(n)
+    up = (rng.standard_normal(n) * np.exp(rng.uniform(-10, 8, n))).astype(np.float16)
+    up[:: 37] = np.resize(SPECIAL, up[:: 37].size)
+    up[5], gate[6], up[7], gate[8] = np.inf, np.inf, -np.inf, -np.inf
+    with np.errstate(over="ignore", invalid="ignore"):
+        want = blk_oracle.swiglu(gate, up)
+    got = host(agq.swiglu(dev(gate), dev(up)))
+    nan = np.isnan(want)
+    assert np.array_equal(nan, np.isnan(got)) and same(got[~nan], want[~nan])
+
+
 @pytest.mark.parametrize("rows,d", [(5, 8), (3, 128), (7, 5120), (2, 8200), (2, 16384)])
 def test_rmsnorm_operator(agq, blk_oracle, rows, d):
     rng = np.random.default_rng(d)
