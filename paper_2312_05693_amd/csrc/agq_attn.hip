@@ -322,121 +322,175 @@ __global__ __launch_bounds__(256, CB == 1 ? 3 : 1) void log2_attn_kernel(const A
 
 // ------------------------------------------------------------------ pruning
 
-constexpr int kSelThreads = 1024;
 constexpr int kSelMaxS = 8192;
-constexpr int kSelPer = kSelMaxS / kSelThreads;   // tokens per thread, kept in registers
+constexpr int kSelChunks = kSelMaxS / 64;
 
-// Survivors of Eq.4: the n_keep tokens with the largest score, equal scores to
-// the lower index, written in ascending order.  One workgroup, no sort:
-//   1. radix select (four 8-bit digits, LDS histograms) finds the score T of the
-//      n_keep-th largest token and how many tokens with exactly that score
-//      still fit (`need`);
-//   2. a token survives if its score is above T, or equals T and fewer than
-//      `need` equal-scored tokens precede it;
-//   3. wavefront-shuffle prefix sums give the tie ordinals and output positions.
-// Thread t owns the contiguous tokens [t * per, t * per + per).
-__global__ __launch_bounds__(kSelThreads) void prune_select_kernel(const int32_t *__restrict__ score, int S, int n_keep,
-                                                                    int32_t *__restrict__ idx_out) {
-    __shared__ int hist[256];
-    __shared__ int wave_tot[kSelThreads / 64];
-    __shared__ unsigned sel_prefix;
-    __shared__ int sel_k;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int per = (S + kSelThreads - 1) / kSelThreads;
-    const int lo = threadIdx.x * per;
-    unsigned key[kSelPer];     // order-preserving unsigned image of the signed score
-#pragma unroll
-    for (int e = 0; e < kSelPer; ++e)
-        key[e] = (e < per && lo + e < S) ? ((unsigned)score[lo + e] ^ 0x80000000u) : 0u;
-    auto live = [&](int e) { return e < per && lo + e < S; };
+// One cross-lane step in the data path of the vector ALU; lanes without a source contribute 0.
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ uint32_t dpp0(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t wave_or(uint32_t v) {          // uniform
+    v |= dpp0<0xB1>(v);                                            // quads, halves of eight, of sixteen
+    v |= dpp0<0x4E>(v);
+    v |= dpp0<0x141>(v);
+    v |= dpp0<0x140>(v);
+    return __builtin_amdgcn_readlane(v, 0) | __builtin_amdgcn_readlane(v, 16) | __builtin_amdgcn_readlane(v, 32) | __builtin_amdgcn_readlane(v, 48);
+}
+__device__ __forceinline__ int wave_scan(int x) {                  // inclusive sum over lanes
+    uint32_t v = (uint32_t)x;
+    v += dpp0<0x111>(v);                                           // shifted right by 1, 2, 4, 8 within sixteen lanes
+    v += dpp0<0x112>(v);
+    v += dpp0<0x114>(v);
+    v += dpp0<0x118>(v);
+    v += dpp0<0x142, 0xA>(v);                                      // lane 15 to the second and fourth sixteen
+    v += dpp0<0x143, 0xC>(v);                                      // lane 31 to the upper half
+    return (int)v;
+}
 
-    unsigned prefix = 0, himask = 0;
-    int k = n_keep;            // the k-th largest among the tokens matching `prefix`
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        if (threadIdx.x < 256) hist[threadIdx.x] = 0;
-        __syncthreads();
+// Survivors of Eq.4, the n_keep tokens with the largest score, equal scores to the lower index, in ascending order, and
+// their rows: out[p] = x[idx[p]], with CODES also the rows' Eq.2 codes in the operand order of the tiled GEMM.
+//
+// Every workgroup selects for itself, then copies its few rows: a selection by one workgroup in front of the copies is a
+// launch more, and its time is latency whoever does it.  No sort:
+//   1. the bits in which scores differ at all, then a radix select of the n_keep-th largest over those (digits of eight
+//      bits, histograms in LDS; every wavefront reads the histogram and scans it by itself, with cross-lane
+//      operations of the vector ALU, so a digit takes one barrier);
+//   2. ballots mark, 64 tokens a word, those above that score and those equal to it, and a second scan over the words
+//      gives every word its survivors and their place;
+//   3. the token of output row p is then found by a ballot over the words and a search for a set bit.
+// Thread t of wavefront w holds the tokens 64 (WAVES e + w) + t.  Against a launch for the selection (one
+// workgroup of sixteen wavefronts, four digits always, cross-lane steps through LDS) and one for the rows: 2048 tokens, 1024
+// kept, rows of 5120 11.8 -> 8.4 us (14.0 -> 8.8 where scores crowd at one end), 300 tokens, 213 rows of 4096 8.7 -> 4.6,
+// 8192 tokens, 4096 rows of 4096 24.0 -> 22.4.  What is left of it: about 2.5 us of latency from the scores to the rows,
+// more where a wavefront holds more tokens (code for sixteen tokens a thread alone took 2 us), and the rows.
+// WAVES: wavefronts of a workgroup; PER: tokens per thread, in registers
+template <int WAVES, int PER, bool CODES>
+__global__ __launch_bounds__(WAVES * 64) void prune_rows_kernel(const int32_t *__restrict__ score, int S, int n_keep, int rows_per_wg,
+                                                                 const uint4 *__restrict__ x, int d8, int32_t *__restrict__ idx_out,
+                                                                 uint4 *__restrict__ out, const AgqQuant q, char *__restrict__ tiles) {
+    constexpr int kThreads = WAVES * 64;
+    __shared__ __align__(16) int hist[4][256];
+    __shared__ __align__(16) uint32_t differ[WAVES][2];
+    __shared__ __align__(16) uint64_t above_m[kSelChunks], equal_m[kSelChunks];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint32_t key[PER];         // order-preserving unsigned image of the signed score
+    uint32_t ones = 0, zeros = 0;
+    auto live = [&](int e) { return e * kThreads + tid < S; };
 #pragma unroll
-        for (int e = 0; e < kSelPer; ++e)
-            if (live(e) && (key[e] & himask) == prefix) atomicAdd(&hist[(key[e] >> shift) & 255], 1);
-        __syncthreads();
-        if (wave == 0) {
-            // lane l owns digits 4l .. 4l+3; suffix sums from the top digit down
-            const int c0 = hist[4 * lane], c1 = hist[4 * lane + 1], c2 = hist[4 * lane + 2], c3 = hist[4 * lane + 3];
-            const int mine4 = c0 + c1 + c2 + c3;
-            int above = mine4;                       // inclusive suffix sum over lanes >= l
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int v = __shfl_down(above, off);
-                if (lane + off < 64) above += v;
-            }
-            const int higher = above - mine4;        // tokens in digits owned by higher lanes
-            if (higher < k && k <= above) {          // the k-th largest falls into this lane's digits
-                int rem = k - higher, d = 3;
-                const int c[4] = {c0, c1, c2, c3};
-                while (rem > c[d]) {
-                    rem -= c[d];
-                    --d;
-                }
-                sel_prefix = prefix | ((unsigned)(4 * lane + d) << shift);
-                sel_k = rem;
-            }
-        }
-        __syncthreads();
-        prefix = sel_prefix;
-        k = sel_k;
-        himask |= 0xFFu << shift;
+    for (int e = 0; e < PER; ++e) {
+        key[e] = live(e) ? (uint32_t)score[e * kThreads + tid] ^ 0x80000000u : 0u;
+        ones |= key[e];
+        zeros |= live(e) ? ~key[e] : 0u;
     }
-    // prefix = image of T; k = number of tokens with score T that survive
-    int ties = 0;
+    for (int i = tid; i < 4 * 256 / 4; i += kThreads) reinterpret_cast<int4 *>(hist)[i] = make_int4(0, 0, 0, 0);
+    if (tid < kSelChunks) above_m[tid] = equal_m[tid] = 0;
+    ones = wave_or(ones);
+    zeros = wave_or(zeros);
+    if (lane == 0) {
+        differ[wave][0] = ones;
+        differ[wave][1] = zeros;
+    }
+    __syncthreads();
+    ones = zeros = 0;
 #pragma unroll
-    for (int e = 0; e < kSelPer; ++e) ties += live(e) && key[e] == prefix;
-    auto excl_scan = [&](int v) {                    // exclusive prefix over the workgroup
-        int incl = v;
+    for (int w = 0; w < WAVES; ++w) {
+        ones |= differ[w][0];
+        zeros |= differ[w][1];
+    }
+    ones = __builtin_amdgcn_readfirstlane(ones);
+    const uint32_t diff = ones & __builtin_amdgcn_readfirstlane(zeros);
+    int shift = diff ? 32 - __builtin_clz(diff) : 0;               // bits still to be decided
+    uint32_t himask = shift == 32 ? 0u : ~0u << shift, prefix = ones & himask;   // equal in every key
+    int k = n_keep;                                                // the k-th largest among the tokens matching `prefix`
+    for (int pass = 0; shift > 0; ++pass) {
+        shift = max(shift - 8, 0);
+        const uint32_t dmask = ~himask >> shift;                   // the digit: eight bits, or what is left
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int u = __shfl_up(incl, off);
-            if (lane >= off) incl += u;
-        }
-        __syncthreads();                             // wave_tot is reused between the two scans
-        if (lane == 63) wave_tot[wave] = incl;
+        for (int e = 0; e < PER; ++e)
+            if (live(e) && (key[e] & himask) == prefix) {
+                // the lanes that share the first one's digit add up together: many do where scores crowd at one end
+                const uint32_t digit = (key[e] >> shift) & dmask;
+                const bool same = digit == __builtin_amdgcn_readfirstlane(digit);
+                const uint64_t crowd = __ballot(same);
+                if (!same || lane == __builtin_ctzll(crowd)) atomicAdd(&hist[pass][digit], same ? __popcll(crowd) : 1);
+            }
         __syncthreads();
-        int base = 0;
-        for (int w = 0; w < wave; ++w) base += wave_tot[w];
-        return base + incl - v;
+        // lane l owns digits 255 - 4 l .. 252 - 4 l: sums over lanes run from the top digit down
+        const int4 c = *reinterpret_cast<const int4 *>(&hist[pass][252 - 4 * lane]);
+        const int mine = c.x + c.y + c.z + c.w, upto = wave_scan(mine), higher = upto - mine;
+        const uint64_t here = __ballot(higher < k && k <= upto);   // one lane: the k-th largest falls into its digits
+        const int rem = k - higher, s3 = c.w, s2 = s3 + c.z, s1 = s2 + c.y;
+        const int digit = 255 - 4 * lane - (rem > s3) - (rem > s2) - (rem > s1);
+        const int left = rem - (rem > s1 ? s1 : rem > s2 ? s2 : rem > s3 ? s3 : 0);
+        const int f = __builtin_ctzll(here);
+        prefix |= (uint32_t)__builtin_amdgcn_readlane(digit, f) << shift;
+        k = __builtin_amdgcn_readlane(left, f);
+        himask = shift ? ~0u << shift : ~0u;
+    }
+    // prefix = image of the n_keep-th largest score; k = number of tokens with exactly that score that survive
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+        const uint64_t ab = __ballot(live(e) && key[e] > prefix), eq = __ballot(live(e) && key[e] == prefix);
+        if (lane == 0) {
+            above_m[e * WAVES + wave] = ab;
+            equal_m[e * WAVES + wave] = eq;
+        }
+    }
+    __syncthreads();
+    // lane l: words 2 l and 2 l + 1
+    const ulonglong2 ab = *reinterpret_cast<const ulonglong2 *>(&above_m[2 * lane]), eq = *reinterpret_cast<const ulonglong2 *>(&equal_m[2 * lane]);
+    const int e0 = __popcll(eq.x), e1 = __popcll(eq.y);
+    const int ties = wave_scan(e0 + e1) - e0 - e1;                 // equal ones in front of this lane's
+    auto lowest = [](uint64_t m, int count, int n) {               // the n lowest of count set bits
+        if (n >= count) return m;
+        uint64_t rest = m;
+        for (; n > 0; --n) rest &= rest - 1;
+        return m ^ rest;
     };
-    int tie_ord = excl_scan(ties);
-    unsigned keepmask = 0;
-    int mine = 0;
+    const uint64_t k0 = ab.x | lowest(eq.x, e0, k - ties), k1 = ab.y | lowest(eq.y, e1, k - ties - e0);
+    const int n0 = __popcll(k0), n01 = n0 + __popcll(k1), end = wave_scan(n01);
+
+    const int per_row = WAVES / rows_per_wg;                   // wavefronts of a row
+    const int p = blockIdx.x * rows_per_wg + wave / per_row;
+    if (p >= n_keep) return;
+    const int f = __builtin_ctzll(__ballot(p < end));              // the first lane whose survivors reach past p
+    int r = p - __builtin_amdgcn_readlane(end - n01, f), at = 128 * f;
+    const int first = __builtin_amdgcn_readlane(n0, f);
+    const bool second = r >= first;
+    uint64_t word = second ? k1 : k0;
+    uint32_t lo = __builtin_amdgcn_readlane((uint32_t)word, f), hi = __builtin_amdgcn_readlane((uint32_t)(word >> 32), f);
+    if (second) {
+        r -= first;
+        at += 64;
+    }
+    word = ((uint64_t)hi << 32) | lo;
 #pragma unroll
-    for (int e = 0; e < kSelPer; ++e) {
-        if (!live(e)) continue;
-        bool keep = key[e] > prefix;
-        if (key[e] == prefix) keep = tie_ord++ < k;
-        if (keep) {
-            keepmask |= 1u << e;
-            ++mine;
+    for (int w = 32; w > 0; w >>= 1) {                             // the r-th set bit
+        const int n = __popcll(word & ((1ull << w) - 1));
+        if (r >= n) {
+            r -= n;
+            at += w;
+            word >>= w;
         }
     }
-    int pos = excl_scan(mine);
-#pragma unroll
-    for (int e = 0; e < kSelPer; ++e)
-        if (keepmask >> e & 1) idx_out[pos++] = lo + e;
-}
-
-__global__ __launch_bounds__(256) void gather_rows_kernel(const uint4 *__restrict__ x, const int32_t *__restrict__ idx,
-                                                           int64_t d8, uint4 *__restrict__ out) {
-    const int64_t src = idx[blockIdx.x];
-    for (int64_t c = threadIdx.x; c < d8; c += blockDim.x) out[(int64_t)blockIdx.x * d8 + c] = x[src * d8 + c];
-}
-
-// the same, and the rows' Eq.2 codes in the operand order of the tiled GEMM
-__global__ __launch_bounds__(256) void gather_codes_kernel(const uint4 *__restrict__ x, const int32_t *__restrict__ idx,
-                                                            int d8, uint4 *__restrict__ out, const AgqQuant q, char *__restrict__ tiles) {
-    const int r = blockIdx.x, src = idx[r];
-    for (int c = threadIdx.x; c < d8; c += 256) {
-        const uint4 v = x[(int64_t)src * d8 + c];
-        out[(int64_t)r * d8 + c] = v;
-        *reinterpret_cast<uint2 *>(tiles + agq_code_offset(r, c, d8 >> 4)) = agq_quant8<true>(v, q);
+    const int part = wave % per_row;
+    if (part == 0 && lane == 0) idx_out[p] = at;
+    const uint4 *const src = x + (int64_t)at * d8;
+    uint4 *const dst = out + (int64_t)p * d8;
+    const int stride = per_row * 64, last = d8 - 1;
+    for (int c = part * 64 + lane; c < d8; c += 4 * stride) {      // four loads under way at a time
+        const uint4 v0 = src[c], v1 = src[min(c + stride, last)], v2 = src[min(c + 2 * stride, last)], v3 = src[min(c + 3 * stride, last)];
+        auto put = [&](int at_c, const uint4 &v) {
+            if (at_c >= d8) return;
+            dst[at_c] = v;
+            if (CODES) *reinterpret_cast<uint2 *>(tiles + agq_code_offset(p, at_c, d8 >> 4)) = agq_quant8<true>(v, q);
+        };
+        put(c, v0);
+        put(c + stride, v1);
+        put(c + 2 * stride, v2);
+        put(c + 3 * stride, v3);
     }
 }
 
@@ -481,11 +535,19 @@ int agq_launch_log2_attn(const void *p, int64_t H, int64_t S, int64_t D, int cau
 int agq_launch_prune(const int32_t *score, int64_t S, int64_t n_keep, const void *x, int64_t d, int32_t *idx,
                      void *x_out, const AgqCodes &codes, void *stream) {
     hipStream_t st = (hipStream_t)stream;
-    prune_select_kernel<<<1, kSelThreads, 0, st>>>(score, (int)S, (int)n_keep, idx);
-    if (codes.tiles)
-        gather_codes_kernel<<<(unsigned)n_keep, 256, 0, st>>>((const uint4 *)x, idx, (int)(d / 8), (uint4 *)x_out,
-                                                              agq_make_quant_signed(codes.bits, codes.e, 0), (char *)codes.tiles);
-    else
-        gather_rows_kernel<<<(unsigned)n_keep, 256, 0, st>>>((const uint4 *)x, idx, d / 8, (uint4 *)x_out);
+    // Up to 512 tokens eight wavefronts and a row for each workgroup, else sixteen, and so many rows that 256 workgroups or
+    // so (one a CU) select: with two to four of them on a CU the selections wait for one another.
+    const int waves = S <= 512 ? 8 : 16;
+    int rows_per_wg = 1;
+    if (S > 512)
+        while (rows_per_wg < waves && n_keep > (int64_t)rows_per_wg * 256) rows_per_wg *= 2;
+    const unsigned grid = (unsigned)((n_keep + rows_per_wg - 1) / rows_per_wg);
+    const AgqQuant q = codes.tiles ? agq_make_quant_signed(codes.bits, codes.e, 0) : AgqQuant{};
+    auto launch = [&](auto kernel) {
+        kernel<<<grid, waves * 64, 0, st>>>(score, (int)S, (int)n_keep, rows_per_wg, (const uint4 *)x, (int)(d / 8), idx, (uint4 *)x_out, q, (char *)codes.tiles);
+    };
+    if (S <= 512) launch(codes.tiles ? prune_rows_kernel<8, 1, true> : prune_rows_kernel<8, 1, false>);
+    else if (S <= 2048) launch(codes.tiles ? prune_rows_kernel<16, 2, true> : prune_rows_kernel<16, 2, false>);
+    else launch(codes.tiles ? prune_rows_kernel<16, 8, true> : prune_rows_kernel<16, 8, false>);
     return (int)hipGetLastError();
 }

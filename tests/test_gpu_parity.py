@@ -759,6 +759,23 @@ def test_prune(agq, oracle, S, keep, d):
     assert np.array_equal(host(out).view(np.uint16), want_x.view(np.uint16))
 
 
+@pytest.mark.parametrize("S,keep,d", [(1, 1, 8), (64, 63, 8), (65, 1, 1032), (512, 512, 24), (513, 256, 520), (1024, 257, 2056), (2048, 2048, 8),
+                                      (2049, 513, 264), (4097, 1025, 16), (8192, 8192, 8), (8191, 4096, 40)])
+@pytest.mark.parametrize("low,high", [(0, 1), (0, 255), (-3, 300), (70000, 70000 + 2 ** 17), (-2 ** 31, 2 ** 31 - 1)])
+def test_prune_sizes_and_ranges(agq, oracle, S, keep, d, low, high):
+    """Both sides of every size at which the number of wavefronts, tokens per thread or rows per workgroup changes, and scores
+    that differ in one bit, in one digit, across a digit's edge, in the sign, and everywhere."""
+    rng = np.random.default_rng([S, keep, high & 0xFFFF])
+    score = rng.integers(low, high + 1, size=S, dtype=np.int64).astype(np.int32)
+    if high > 2 ** 16:
+        score[rng.random(S) < 0.6] = low                          # crowded at one end
+    x = rng.standard_normal((S, d)).astype(np.float16)
+    idx, out = agq.prune_tokens(dev(score), keep, dev(x))
+    want_idx, want_x = oracle.prune_tokens(score, keep, x)
+    assert np.array_equal(host(idx), want_idx)
+    assert np.array_equal(host(out).view(np.uint16), want_x.view(np.uint16))
+
+
 @pytest.mark.parametrize("kind", ["equal", "signed", "extremes", "max_size", "keep_none"])
 def test_prune_degenerate(agq, oracle, kind):
     """Score patterns that stress the threshold search: one value everywhere
