@@ -103,10 +103,18 @@ int site_gemm(int bits, const void *x, int64_t M, int64_t K, int e, int n_extra,
                      : agq_gemm_w4a4_trip_multi(x, M, K, K, e, 0, projs, count, n_extra, gws, gws_bytes, stream);
 }
 
+// Between two blocks of a stack the last addition of the one (its x1 + its down projection) is made by the first RMSNorm of
+// the other, which reads the sum anyway: one launch less, 4 to 5 us at a few hundred tokens.
+struct Joint {
+    const void *x1 = nullptr;     // of the block before: x is this plus `down`, and is written by the block that takes it up
+    const void *down = nullptr;
+    void *next_down = nullptr;    // leave the last addition to the block behind: the down projection goes here
+};
+
 // exps: the exponents to use, updated in place when `calibrate` is set
 int run(const agq_block *b, int *exps, bool calibrate, const void *x, const int32_t *pos, const float *cos_t,
         const float *sin_t, int64_t P, int64_t S, int64_t n_keep, void *x_out, int32_t *pos_out, void *workspace,
-        size_t workspace_bytes, void *stream) {
+        size_t workspace_bytes, void *stream, const Joint &joint = Joint()) {
     agq_block_layout L;
     AGQ_TRY(layout_of(b, S, n_keep, &L));
     if (!x || !pos || !cos_t || !sin_t || !x_out || !workspace || P < 1 || P > ((int64_t)1 << 30)) return AGQ_EINVAL;
@@ -163,8 +171,12 @@ int run(const agq_block *b, int *exps, bool calibrate, const void *x, const int3
                              {b->w_k, b->s_k, d, at(L.k), d, nullptr},
                              {b->w_v, b->s_v, d, at(L.v), d, nullptr}};
     const AgqCodes h1_codes = codes_for(8, E_ATTN_IN, b->trip_attn_in, S, d, qkv, 3);
-    AGQ_TRY_HIP(agq_launch_rmsnorm(x, nullptr, nullptr, b->g_attn_f16, nullptr, at(L.h1), S, d, b->rms_eps, nullptr, nullptr,
-                                   nullptr, h1_codes, stream));
+    if (joint.x1)
+        AGQ_TRY_HIP(agq_launch_rmsnorm(joint.down, joint.x1, nullptr, b->g_attn_f16, const_cast<void *>(x), at(L.h1), S, d, b->rms_eps,
+                                       nullptr, nullptr, nullptr, h1_codes, stream));
+    else
+        AGQ_TRY_HIP(agq_launch_rmsnorm(x, nullptr, nullptr, b->g_attn_f16, nullptr, at(L.h1), S, d, b->rms_eps, nullptr, nullptr,
+                                       nullptr, h1_codes, stream));
     AGQ_TRY(exp_for(E_ATTN_IN, at(L.h1), S, d, 8));
     AGQ_TRY(project(h1_codes, 8, at(L.h1), S, d, E_ATTN_IN, b->trip_attn_in, qkv, 3));
     if (calibrate) {
@@ -201,13 +213,13 @@ int run(const agq_block *b, int *exps, bool calibrate, const void *x, const int3
                                    b->rms_eps, pos, pos_out, pruned ? nullptr : idx, h2_codes, stream));
     AGQ_TRY(exp_for(E_MLP_IN, at(L.h2), n_keep, d, 8));
     AGQ_TRY(project(h2_codes, 8, at(L.h2), n_keep, d, E_MLP_IN, b->trip_mlp_in, gu, 2));
-    const agq_proj dp = {b->w_down, b->s_down, d, at(L.down), d, nullptr};
+    const agq_proj dp = {b->w_down, b->s_down, d, joint.next_down ? joint.next_down : at(L.down), d, nullptr};
     const AgqCodes act_codes = codes_for(8, E_MLP_ACT, b->trip_mlp_act, n_keep, F, &dp, 1);
     if (act_codes.tiles) AGQ_TRY_HIP(agq_launch_swiglu_rows(at(L.gate), at(L.up), at(L.act), n_keep, F, act_codes, stream));
     else AGQ_TRY_HIP(agq_launch_swiglu(at(L.gate), at(L.up), at(L.act), n_keep * F, stream));
     AGQ_TRY(exp_for(E_MLP_ACT, at(L.act), n_keep, F, 8));
     AGQ_TRY(project(act_codes, 8, at(L.act), n_keep, F, E_MLP_ACT, b->trip_mlp_act, &dp, 1));
-    AGQ_TRY_HIP(agq_launch_add(at(L.x1), at(L.down), x_out, n_keep * d, stream));
+    if (!joint.next_down) AGQ_TRY_HIP(agq_launch_add(at(L.x1), at(L.down), x_out, n_keep * d, stream));
     return AGQ_OK;
 }
 
@@ -291,7 +303,8 @@ int agq_block_calibrate(agq_block *blk, const void *x_f16, const int32_t *pos, c
 namespace {
 
 // layout of a stack's workspace: two token buffers and two position buffers (ping-pong between blocks), then
-// the largest block workspace
+// the largest block workspace.  Where the last addition of a block is left to the next one, the tokens lie in the first buffer
+// and the down projection in the second.
 struct StackLayout {
     size_t xa, xb, pa, pb, blk, total;
 };
@@ -350,18 +363,40 @@ int agq_stack_forward(const agq_block *blocks, int n_blocks, const int64_t *keep
         if (!x_f16 || !pos || !rope_cos || !rope_sin || !x_out_f16 || P < 1 || P > ((int64_t)1 << 30)) return AGQ_EINVAL;
         if (!aligned16(x_f16) || !aligned16(rope_cos) || !aligned16(rope_sin) || !aligned16(x_out_f16)) return AGQ_EINVAL;
     }
+    // Block l leaves its last addition to block l + 1 unless what that block's first launch writes (h1, and the codes in
+    // the GEMM scratch) would lie over x1 of block l.
+    auto joins = [&](int l, int64_t tokens) {
+        if (l + 1 >= n_blocks) return false;
+        agq_block_layout A, B;
+        if (layout_of(&blocks[l], tokens, keep[l], &A) != AGQ_OK || layout_of(&blocks[l + 1], keep[l], keep[l + 1], &B) != AGQ_OK) return false;
+        const size_t bytes = (size_t)keep[l] * (size_t)blocks[l].d * 2, codes = agq_codes_bytes(keep[l], blocks[l].d);
+        auto apart = [&](size_t from, size_t n) { return from + n <= A.x1 || A.x1 + bytes <= from; };
+        return apart(B.h1, bytes) && apart(B.gemm_ws, codes);
+    };
     const void *xin = x_f16;
     const int32_t *pin = pos;
     int64_t in = S;
+    Joint joint;
     for (int l = 0; l < n_blocks; ++l) {
         const bool last = l == n_blocks - 1;
-        void *xo = last ? x_out_f16 : static_cast<void *>(ws + ((l & 1) ? L.xb : L.xa));
+        const bool leave = joins(l, in);
+        // the buffer that does not hold x: x of this block when it takes up the sum itself lies in xa
+        void *const xo = last ? x_out_f16 : static_cast<void *>(ws + (xin == ws + L.xa ? L.xb : L.xa));
+        joint.next_down = leave ? ws + L.xb : nullptr;
         int32_t *po = last ? pos_out : reinterpret_cast<int32_t *>(ws + ((l & 1) ? L.pb : L.pa));
         int exps[7] = {blocks[l].e_attn_in, blocks[l].e_q, blocks[l].e_k, blocks[l].e_v, blocks[l].e_attn_out,
                        blocks[l].e_mlp_in, blocks[l].e_mlp_act};
         AGQ_TRY(run(&blocks[l], exps, false, xin, pin, rope_cos, rope_sin, P, in, keep[l], xo, po, ws + L.blk,
-                    L.total - L.blk, stream));
+                    L.total - L.blk, stream, joint));
+        joint = Joint();
         xin = xo;
+        if (leave) {
+            agq_block_layout A;
+            AGQ_TRY(layout_of(&blocks[l], in, keep[l], &A));
+            joint.x1 = ws + L.blk + A.x1;
+            joint.down = ws + L.xb;
+            xin = ws + L.xa;
+        }
         pin = po;
         in = keep[l];
     }
