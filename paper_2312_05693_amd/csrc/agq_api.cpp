@@ -322,7 +322,7 @@ int agq_qk_log2_softmax(const int8_t *q_q, const int8_t *k_q, int64_t H, int64_t
     if (!aligned16(q_q) || !aligned16(k_q) || !aligned16(v_q) || !aligned16(o_f16)) return AGQ_EINVAL;
     if (codes_out && !aligned16(codes_out)) return AGQ_EINVAL;
     return hip_status(agq_launch_qk_log2_attn(q_q, k_q, v_q, H, S, D, causal != 0, qmax, e_q, e_k, e_v, o_f16, codes_out,
-                                              score_out, stream));
+                                              score_out, AgqCodes(), stream));
 }
 
 int agq_prune_tokens(const int32_t *score, int64_t S, int64_t n_keep, const void *x_f16, int64_t d,

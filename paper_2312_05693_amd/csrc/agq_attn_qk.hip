@@ -40,6 +40,8 @@
 #include "agq_device.h"
 #include "agq_internal.h"
 
+AgqQuant agq_make_quant_signed(int bits, int e, int zp);   // agq_quant.hip
+
 #include <math.h>
 
 #include <type_traits>
@@ -66,6 +68,8 @@ struct QkArgs {
     float kappa;               // 2^(e_q+e_k) log2(e) / sqrt(D)
     float out_scale;           // 2^(e_v - qmax + 9)
     int ncu;
+    char *tiles;               // where Eq.2's codes of o go as well, in the operand order of the tiled GEMM, or null
+    AgqQuant quant;
 };
 
 template <int N>
@@ -86,7 +90,8 @@ __device__ __forceinline__ void meet() {
 }
 
 // DT = D / 32: int8 MFMA steps per score tile and 32-channel blocks of the output
-template <int DT, bool CODES>
+// CODES: the code map goes out as well; TILES: Eq.2's codes of o (a.tiles)
+template <int DT, bool CODES, bool TILES>
 __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
     constexpr int D = DT * 32;
     constexpr int kKTile = kKeys * D;                            // bytes of a K tile
@@ -571,13 +576,23 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
             uint32_t *const dst = reinterpret_cast<uint32_t *>(a.o + (int64_t)orow * ((int64_t)H * D) + (int64_t)h * D + NB * c);
             if constexpr (NB == 4) *reinterpret_cast<uint2 *>(dst) = make_uint2(hv[0], hv[1]);
             else *dst = hv[0];
+            if constexpr (TILES) {
+                uint32_t code[NB];
+#pragma unroll
+                for (int n = 0; n < NB; ++n)
+                    code[n] = agq_quant1(__half2float(__ushort_as_half((unsigned short)(hv[n / 2] >> (16 * (n & 1))))), a.quant);
+                const int ch = h * D + NB * c;
+                char *const at = a.tiles + agq_code_offset(orow, ch >> 3, H * D >> 7) + (ch & 7);
+                if constexpr (NB == 4) *reinterpret_cast<uint32_t *>(at) = agq_pack4(code[0], code[1], code[2], code[3]);
+                else *reinterpret_cast<uint16_t *>(at) = (uint16_t)((code[0] & 255u) | (code[1] << 8));
+            }
         }
 }
 
 }  // namespace
 
 int agq_launch_qk_log2_attn(const int8_t *q, const int8_t *k, const int8_t *v, int64_t H, int64_t S, int64_t D, int causal,
-                            int qmax, int e_q, int e_k, int e_v, void *o, void *codes, int32_t *score, void *stream) {
+                            int qmax, int e_q, int e_k, int e_v, void *o, void *codes, int32_t *score, const AgqCodes &o_codes, void *stream) {
     QkArgs a;
     a.q = q;
     a.k = k;
@@ -591,6 +606,8 @@ int agq_launch_qk_log2_attn(const int8_t *q, const int8_t *k, const int8_t *v, i
     a.qmax = qmax;
     a.kappa = (float)(ldexp(1.0, e_q + e_k) * 1.4426950408889634 / sqrt((double)D));
     a.out_scale = ldexpf(1.0f, e_v - qmax + 9);
+    a.tiles = (char *)o_codes.tiles;
+    a.quant = o_codes.tiles ? agq_make_quant_signed(o_codes.bits, o_codes.e, 0) : AgqQuant{};
     static int ncu_of[64] = {0};
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) return (int)hipGetLastError();
@@ -602,12 +619,8 @@ int agq_launch_qk_log2_attn(const int8_t *q, const int8_t *k, const int8_t *v, i
     a.ncu = ncu;
     hipStream_t st = (hipStream_t)stream;
     const unsigned grid = (unsigned)((S / kQRows) * H);
-    if (D == 128) {
-        if (codes) qk_log2_attn_kernel<4, true><<<grid, 256, 0, st>>>(a);
-        else qk_log2_attn_kernel<4, false><<<grid, 256, 0, st>>>(a);
-    } else {
-        if (codes) qk_log2_attn_kernel<2, true><<<grid, 256, 0, st>>>(a);
-        else qk_log2_attn_kernel<2, false><<<grid, 256, 0, st>>>(a);
-    }
+    auto launch = [&](auto kernel) { kernel<<<grid, 256, 0, st>>>(a); };
+    if (D == 128) launch(codes ? qk_log2_attn_kernel<4, true, false> : a.tiles ? qk_log2_attn_kernel<4, false, true> : qk_log2_attn_kernel<4, false, false>);
+    else launch(codes ? qk_log2_attn_kernel<2, true, false> : a.tiles ? qk_log2_attn_kernel<2, false, true> : qk_log2_attn_kernel<2, false, false>);
     return (int)hipGetLastError();
 }

@@ -445,6 +445,14 @@ def test_block_with_codes_from_the_operators(agq, oracle, blk_oracle, gemm_route
     test_block_stage_by_stage(agq, oracle, blk_oracle, S, d, H, F, keep, qmax, bits_o)
 
 
+@pytest.mark.parametrize("S,d,H,F,qmax,bits_o", [(260, 256, 4, 640, 15, 8), (385, 384, 6, 512, 7, 4), (513, 128, 1, 384, 15, 4)])
+def test_block_with_codes_from_the_attention(agq, oracle, blk_oracle, gemm_route, S, d, H, F, qmax, bits_o):
+    """No pruning: the attention writes the codes for the o projection, heads of 64 and of 128 channels, one head and an odd
+    place of a head in a K step, both widths of the codes."""
+    assert gemm_route(S, d, [d]) != "stream"
+    test_block_stage_by_stage(agq, oracle, blk_oracle, S, d, H, F, S, qmax, bits_o)
+
+
 def test_block_with_codes_for_large_tiles_and_a_split(agq, oracle, blk_oracle, gemm_route):
     """The operators' codes read by 128-token tiles (gate/up) and by a K split (down)."""
     S, d, H, F, keep = 1100, 512, 4, 8192, 1050
