@@ -204,22 +204,29 @@ def _projections(M, projs, device):
     return ys, (_i64 * len(flat))(*flat)
 
 
-def _gemm(fn_name, x, x_kind, M, K, ldx, e, zp, w_packed, w_scale, N, y, acc_out, workspace):
+# One layer is one short launch: what the host does around it counts, so these two write out what the other calls leave to
+# _ptr, _stream and _ok (768 x 768 at 128 rows 6.1 -> 5.5 us a call, of which 3.7 are the launch in the runtime and 0.7
+# the conversion of the arguments).
+def _gemm(fn, fn_name, x, x_kind, M, K, ldx, e, zp, w_packed, w_scale, N, y, acc_out, workspace):
     if y is None:
         y = torch.empty((M, N), dtype=torch.float16, device=w_packed.device)
     if workspace is None:
         workspace = _scratch(gemm_workspace_bytes(M, N, K), w_packed.device)
-    fn = getattr(lib(), fn_name)
-    _ok(fn(_ptr(x), x_kind, M, K, ldx, e, zp, _ptr(w_packed), _ptr(w_scale), N, _ptr(y), y.stride(0) if M else N,
-           _ptr(acc_out), _ptr(workspace), 0 if workspace is None else workspace.nbytes, _stream()), fn_name)
+    status = fn(x.data_ptr(), x_kind, M, K, ldx, e, zp, None if w_packed is None else w_packed.data_ptr(),
+                None if w_scale is None else w_scale.data_ptr(), N, y.data_ptr(), y.stride(0) if M else N,
+                None if acc_out is None else acc_out.data_ptr(), None if workspace is None else workspace.data_ptr(),
+                0 if workspace is None else workspace.nbytes,
+                _stream() if _raw_stream is None else _raw_stream(torch.cuda.current_device()))
+    if status != AGQ_OK:
+        raise AgqError(status, fn_name)
     return y
 
 
 def gemm_w4a8(x, e, w_packed, w_scale, N, K, x_kind=AGQ_X_F16, y=None, acc_out=None, workspace=None, zp=0):
     """x: fp16 [M,K] (AGQ_X_F16) or int8 codes [M,K] (AGQ_X_Q)."""
     M = x.shape[0]
-    return _gemm("agq_gemm_w4a8", x, x_kind, M, K, x.stride(0) if M else K, e, zp, w_packed, w_scale, N, y, acc_out,
-                 workspace)
+    return _gemm(lib().agq_gemm_w4a8, "agq_gemm_w4a8", x, x_kind, M, K, x.stride(0) if M else K, e, zp, w_packed, w_scale, N, y,
+                 acc_out, workspace)
 
 
 def gemm_w4a8_static(x, e, w_packed, w_scale, N, K, y, x_kind=AGQ_X_F16, acc_out=None, zp=0):
@@ -234,7 +241,7 @@ def gemm_w4a4(x, e, w_packed, w_scale, N, K, x_kind=AGQ_X_F16, y=None, acc_out=N
     """x: fp16 [M,K] (AGQ_X_F16) or nibble codes [M,K/2] bytes (AGQ_X_Q)."""
     M = x.shape[0]
     ldx = (x.stride(0) if M else K) * (2 if x_kind == AGQ_X_Q else 1)
-    return _gemm("agq_gemm_w4a4", x, x_kind, M, K, ldx, e, zp, w_packed, w_scale, N, y, acc_out, workspace)
+    return _gemm(lib().agq_gemm_w4a4, "agq_gemm_w4a4", x, x_kind, M, K, ldx, e, zp, w_packed, w_scale, N, y, acc_out, workspace)
 
 
 def _gemm_multi(fn_name, x, x_kind, M, K, ldx, e, zp, projs, workspace):
