@@ -31,9 +31,9 @@
 // dealt out one MFMA at a time, the scores of the next sub-tile beside the arithmetic of this one; scores become floats
 // by a subtraction; a conversion to bytes rounds and packs the weights' exponents; V is widened by one
 // packed multiply-add.  Against a kernel with nothing dealt out and three workgroups on a CU (the same results bit for
-// bit): 40 x 2048 x 128 causal 67 -> 62 us, 40 x 2048 x 64 57 -> 43 (half of the output blocks were empty there),
-// 32 x 384 x 128 14.4 -> 13.4.  What is left of a large causal call is the chain of its longest row blocks (32 tiles
-// take 46 us alone on a CU).  Not kept: a reference score in place of the running maximum, with differences to it straight from
+// bit): 40 x 2048 x 128 causal 67.2 -> 61.8 us, 40 x 2048 x 64 57 -> 43 (half of the output blocks were empty there),
+// 32 x 384 x 128 14.4 -> 13.3.  What is left of a large causal call is the chain of its longest row blocks (32 tiles
+// take 45 us alone on a CU, 305 instructions a tile in pass 2).  Not kept: a reference score in place of the running maximum, with differences to it straight from
 // the accumulators (58 us, and three times fewer codes off, but other codes than before); one block on eight
 // wavefronts, the key tiles shared by two groups of four (72 us then: both wavefronts of a SIMD want the same unit at
 // the same time); V tiles straight into registers (no difference).
@@ -90,8 +90,10 @@ __device__ __forceinline__ void meet() {
 }
 
 // DT = D / 32: int8 MFMA steps per score tile and 32-channel blocks of the output
-// CODES: the code map goes out as well; TILES: Eq.2's codes of o (a.tiles)
-template <int DT, bool CODES, bool TILES>
+// CODES: the code map goes out as well; TILES: Eq.2's codes of o (a.tiles).
+// WIDE: kappa > 1, where the rounding of kappa s may carry an exponent past the largest weight's, so that it is cut off above
+// too.  (Up to there that rounding stays below 0.4: |s| <= 2^21.)
+template <int DT, bool CODES, bool TILES, bool WIDE>
 __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
     constexpr int D = DT * 32;
     constexpr int kKTile = kKeys * D;                            // bytes of a K tile
@@ -145,12 +147,14 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
     }
     const uint32_t wave_u = __builtin_amdgcn_readfirstlane((uint32_t)wave);
     const uint32_t k_lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t *)kt) + wave_u * (kKC * 1024);
-    auto copy_k = [&](int T) {                                   // past the end: the last tile again, into a slot nobody reads
-        const int t = T < nt ? T : min(T, 2 * nt - 1) - nt;
-        const int8_t *const src = kh + (int64_t)t * kKTile + wave_u * (kKC * 1024);
-        const uint32_t dst = k_lds + (uint32_t)(T & (kRing - 1)) * kKTile;
-        lds_dma16_s<0, 0>(k_src[0], src, dst);
-        if constexpr (kKC == 2) lds_dma16_s<0, 1024>(k_src[kKC - 1], src, dst);
+    const uint32_t kv_bytes = (uint32_t)nt * kKTile;             // of the block's keys: at most 4 MiB
+    uint32_t k_at = 0, k_slot = 0;
+    auto copy_k = [&] {                                          // the next tile of the sequence; past its end into a slot nobody reads
+        const int8_t *const src = kh + wave_u * (kKC * 1024) + k_at;
+        lds_dma16_s<0, 0>(k_src[0], src, k_lds + k_slot);
+        if constexpr (kKC == 2) lds_dma16_s<0, 1024>(k_src[kKC - 1], src, k_lds + k_slot);
+        k_at = k_at + kKTile == kv_bytes ? 0 : k_at + kKTile;
+        k_slot = (k_slot + kKTile) & (kRing * kKTile - 1);
     };
     uint32_t k_rd[DT];                                           // operand reads: sixteen d of k-group g of step s, key l & 31
     const int swz = kPieces == 8 ? (c >> 1) & 7 : (c >> 2) & 3;
@@ -172,11 +176,13 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
     // pieces.
     constexpr int NB = DT;
     const uint32_t vq_lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t *)vq) + wave_u * (kKC * 1024);
-    auto copy_v = [&](int t) {                                   // past the end: the last tile again
-        const int8_t *const src = vh + (int64_t)min(t, nt - 1) * kKTile + wave_u * (kKC * 1024);
-        const uint32_t dst = vq_lds + (uint32_t)(t & 1) * kKTile;
-        lds_dma16_s<0, 0>((uint32_t)lane * 16, src, dst);
-        if constexpr (kKC == 2) lds_dma16_s<0, 1024>((uint32_t)lane * 16, src, dst);
+    uint32_t v_at = 0, v_slot = 0;
+    auto copy_v = [&] {                                          // the next tile; past the last one nobody reads it
+        const int8_t *const src = vh + wave_u * (kKC * 1024) + v_at;
+        lds_dma16_s<0, 0>((uint32_t)lane * 16, src, vq_lds + v_slot);
+        if constexpr (kKC == 2) lds_dma16_s<0, 1024>((uint32_t)lane * 16, src, vq_lds + v_slot);
+        v_at = v_at + kKTile == kv_bytes ? 0 : v_at + kKTile;
+        v_slot ^= kKTile;
     };
     const int vu_c = threadIdx.x & 31, vu_ch = threadIdx.x >> 5;
     const uint8_t *const v_src = vq + (32 * (vu_ch >> 2) + 16 * ((vu_ch >> 1) & 1) + 4 * (vu_ch & 1)) * D + NB * vu_c;
@@ -202,12 +208,12 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
         *reinterpret_cast<agq_u4 *>(v_dst + (t & 1) * kVTile + bb * (32 * 128)) = out;
     };
 
-    copy_k(0);
-    copy_k(1);
+    copy_k();
+    copy_k();
     meet<0>();                                                   // K tiles 0 and 1 and Q have landed
-    copy_k(2);
-    copy_v(0);
-    copy_v(1);
+    copy_k();
+    copy_v();
+    copy_v();
 
     // The accumulators start at the bit pattern of 1.5 * 2^23: read as floats they are 1.5 * 2^23 + s, and a subtraction
     // makes that (float)s for half the time of a conversion.  As integers they order like the scores.
@@ -224,14 +230,20 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
     constexpr int kMasked = -(1 << 30);                          // stands for -infinity (|s| < 2^23)
     int run_m = kMasked;
     float run_s = 0.f;
+    auto tile_scores = [&](const uint8_t *tile, agq_v16i &s0, agq_v16i &s1) {   // both sub-tiles of a tile at once
+        agq_v4i k1[DT];
 #pragma unroll
-    for (int s = 0; s < DT; ++s) read_k(s, kt, 0);
+        for (int s = 0; s < DT; ++s) {
+            read_k(s, tile, 0);
+            k1[s] = *reinterpret_cast<const agq_v4i *>(tile + k_rd[s] + 32 * D);
+        }
 #pragma unroll
-    for (int s = 0; s < DT; ++s) mfma_s(s, acc0);
-#pragma unroll
-    for (int s = 0; s < DT; ++s) read_k(s, kt, 1);
-#pragma unroll
-    for (int s = 0; s < DT; ++s) mfma_s(s, acc1);
+        for (int s = 0; s < DT; ++s) {
+            mfma_s(s, s0);
+            s1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(k1[s], qf[s], s == 0 ? cinit : s1, 0, 0, 0);
+        }
+    };
+    tile_scores(kt, acc0, acc1);
     // a sub-tile at the diagonal
     auto stats = [&](const agq_v16i &acc, int sub, bool masked) {
         auto dead = [&](int r) { return masked && 32 * sub + 8 * (r >> 2) + 4 * g + (r & 3) > row; };   // keys past the query do not count
@@ -269,7 +281,7 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
     // through difference, product and exponential, and a slot later into the sums.
     auto pass1_tile = [&](int T, const agq_v16i &cur0, const agq_v16i &cur1, agq_v16i &nxt0, agq_v16i &nxt1) {
         const uint8_t *const ahead = kt + ((T + 1) & (kRing - 1)) * kKTile;
-        copy_k(T + 3);
+        copy_k();
 #pragma unroll
         for (int s = 0; s < DT; ++s) read_k(s, ahead, 0);
         int mx[4] = {run_m + kBias, cur0[0], cur1[0], cur0[1]};
@@ -327,19 +339,11 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
         }
     };
     if (a.causal) {                                              // the two tiles at the diagonal
-        const uint8_t *const ahead = kt + ((T + 1) & (kRing - 1)) * kKTile;
-        copy_k(T + 3);
-#pragma unroll
-        for (int s = 0; s < DT; ++s) read_k(s, ahead, 0);
-#pragma unroll
-        for (int s = 0; s < DT; ++s) mfma_s(s, acc2);
-#pragma unroll
-        for (int s = 0; s < DT; ++s) read_k(s, ahead, 1);
-#pragma unroll
-        for (int s = 0; s < DT; ++s) mfma_s(s, acc3);
+        copy_k();
+        tile_scores(kt + ((T + 1) & (kRing - 1)) * kKTile, acc2, acc3);
         last_tile(T, acc0, acc1);
         meet<kKC>();
-        copy_k(T + 4);
+        copy_k();
         last_tile(T + 1, acc2, acc3);
         meet<kKC>();
     }
@@ -352,11 +356,10 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
                       os * __builtin_amdgcn_exp2f(kappa * (float)(om - M));
     // -log2 p = t = kappa (M - s) + log2(tot).  The weight 2^(qmax - c) has the fp16 exponent field
     // 15 + qmax - c = round(15 + qmax - t) clamped to [15, 15 + qmax]: one fused multiply-add gives 15 + qmax - t, and
-    // after the clamp a conversion to a byte rounds it (to even: a tie has measure zero and lies inside the
-    // evaluation error anyway).
+    // a conversion to a byte rounds it (to even: a tie has measure zero and lies inside the evaluation error anyway) and cuts
+    // it off at 0; the lower bound of 15 follows on the weights' patterns, two at a time.
     const float c2 = (float)(15 + a.qmax) - __builtin_amdgcn_logf(tot) - kappa * (float)M;   // v_log_f32: base 2
-    float elo = 15.0f, ehi = (float)(15 + a.qmax);
-    asm("" : "+v"(elo), "+v"(ehi));
+    auto cut = [&](float x) { return WIDE ? __builtin_amdgcn_fmed3f(x, 0.0f, (float)(15 + a.qmax)) : x; };
 
     // ---- pass 2: codes, weights, product with V
     agq_v16f acc_o[NB];
@@ -373,25 +376,25 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
     uint32_t f0 = 0, f1 = 0;                                     // exponents of a half sub-tile's eight weights, a byte each
     agq_u4 w;
 
-    read_v(0);
-    store_v(0, Int<0>{});
-    store_v(0, Int<1>{});
-    if constexpr (NB == 4) {
-        store_v(0, Int<2>{});
-        store_v(0, Int<3>{});
-    }
     {
         const uint8_t *const first = kt + (nt & (kRing - 1)) * kKTile;
 #pragma unroll
         for (int s = 0; s < DT; ++s) read_k(s, first, 0);
+        read_v(0);
 #pragma unroll
         for (int s = 0; s < DT; ++s) mfma_s(s, acc0);
 #pragma unroll
         for (int s = 0; s < DT; ++s) read_k(s, first, 1);
+        store_v(0, Int<0>{});
+        store_v(0, Int<1>{});
+        if constexpr (NB == 4) {
+            store_v(0, Int<2>{});
+            store_v(0, Int<3>{});
+        }
     }
     // importance on the quantized map: the weight of the first key (always live)
     if (a.score && g == 0)
-        atomicAdd(&a.score[row], 1 << (__builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(fmaf(kappa, score_of(acc0[0]), c2), elo, ehi), 0, 0) - 15));
+        atomicAdd(&a.score[row], 1 << (max(__builtin_amdgcn_cvt_pk_u8_f32(cut(fmaf(kappa, score_of(acc0[0]), c2)), 0, 0), 15u) - 15u));
     meet<63>();                                                  // V tile 0 is in LDS
 
     // the weights of half sub-tile `hs` (keys 16 hs ..) from their exponents
@@ -401,10 +404,14 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
     };
     auto weights = [&](int hs, auto masked_tag) {
         constexpr bool MASKED = decltype(masked_tag)::value;
-        w[0] = __builtin_amdgcn_perm(f0, f0, 0x010C000Cu);
-        w[1] = __builtin_amdgcn_perm(f0, f0, 0x030C020Cu);
-        w[2] = __builtin_amdgcn_perm(f1, f1, 0x010C000Cu);
-        w[3] = __builtin_amdgcn_perm(f1, f1, 0x030C020Cu);
+        auto two = [](uint32_t f, uint32_t sel) {                // two bytes as upper bytes of two patterns, not below 2^0
+            typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+            return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(us2, __builtin_amdgcn_perm(f, f, sel)), us2{0x3C00, 0x3C00}));
+        };
+        w[0] = two(f0, 0x010C000Cu);
+        w[1] = two(f0, 0x030C020Cu);
+        w[2] = two(f1, 0x010C000Cu);
+        w[3] = two(f1, 0x030C020Cu);
         if (MASKED) {
             const int left = row - (16 * hs + 4 * g);            // key i of a lane's four is live if i <= left
 #pragma unroll
@@ -419,7 +426,7 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
         uint32_t cw = 0;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            cw |= ((decltype(masked_tag)::value && key + r > row) ? (uint32_t)a.qmax : 15u + (uint32_t)a.qmax - ((f >> (8 * r)) & 255u)) << (4 * r);
+            cw |= ((decltype(masked_tag)::value && key + r > row) ? (uint32_t)a.qmax : 15u + (uint32_t)a.qmax - max((f >> (8 * r)) & 255u, 15u)) << (4 * r);
         *reinterpret_cast<uint16_t *>(a.codes + ((int64_t)h * S + row) * (S >> 1) + (key >> 1)) = (uint16_t)cw;
     };
     // Half a sub-tile (16 keys: registers 8 u .. 8 u + 7 of the scores): the exponents of its weights, the product of the half
@@ -443,8 +450,8 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
         };
         auto rnd = [&](auto i_tag) {
             constexpr int i = decltype(i_tag)::value;
-            n0 = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(x[i], elo, ehi), i, n0);
-            n1 = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(x[i + 4], elo, ehi), i, n1);
+            n0 = __builtin_amdgcn_cvt_pk_u8_f32(cut(x[i]), i, n0);
+            n1 = __builtin_amdgcn_cvt_pk_u8_f32(cut(x[i + 4]), i, n1);
         };
         auto pv = [&](auto n_tag) {
             constexpr int n = decltype(n_tag)::value;
@@ -515,8 +522,8 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
 #define AGQ_STAGE(P)                                                     \
     [&](auto k) {                                                        \
         if constexpr (decltype(k)::value == kAt) stage(Int<P>{});        \
-        if constexpr (decltype(k)::value == 1 && P == 1) copy_v(t + 2);  \
-        if constexpr (decltype(k)::value == 1 && P == 2) copy_k(nt + t + 3); \
+        if constexpr (decltype(k)::value == 1 && P == 1) copy_v();  \
+        if constexpr (decltype(k)::value == 1 && P == 2) copy_k(); \
     }
         read_v(t + 1);
         if constexpr (!MASKED) {
@@ -525,8 +532,8 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
             half(acc1, acc0, 2 * t + 1, Int<0>{}, vtile, ahead, masked_tag, AGQ_STAGE(2));
             half(acc1, acc0, 2 * t + 1, Int<1>{}, vtile, ahead, masked_tag, AGQ_STAGE(3));
         } else {
-            copy_v(t + 2);
-            copy_k(nt + t + 3);
+            copy_v();
+            copy_k();
             stage(Int<0>{});
             stage(Int<1>{});
             stage(Int<2>{});
@@ -620,7 +627,14 @@ int agq_launch_qk_log2_attn(const int8_t *q, const int8_t *k, const int8_t *v, i
     hipStream_t st = (hipStream_t)stream;
     const unsigned grid = (unsigned)((S / kQRows) * H);
     auto launch = [&](auto kernel) { kernel<<<grid, 256, 0, st>>>(a); };
-    if (D == 128) launch(codes ? qk_log2_attn_kernel<4, true, false> : a.tiles ? qk_log2_attn_kernel<4, false, true> : qk_log2_attn_kernel<4, false, false>);
-    else launch(codes ? qk_log2_attn_kernel<2, true, false> : a.tiles ? qk_log2_attn_kernel<2, false, true> : qk_log2_attn_kernel<2, false, false>);
+    auto pick = [&](auto dt_tag, auto wide_tag) {
+        constexpr int DT = decltype(dt_tag)::value;
+        constexpr bool WIDE = decltype(wide_tag)::value;
+        if (codes) launch(qk_log2_attn_kernel<DT, true, false, true>);
+        else if (a.tiles) launch(qk_log2_attn_kernel<DT, false, true, WIDE>);
+        else launch(qk_log2_attn_kernel<DT, false, false, WIDE>);
+    };
+    if (D == 128) a.kappa > 1.0f ? pick(Int<4>{}, std::true_type{}) : pick(Int<4>{}, std::false_type{});
+    else a.kappa > 1.0f ? pick(Int<2>{}, std::true_type{}) : pick(Int<2>{}, std::false_type{});
     return (int)hipGetLastError();
 }
