@@ -453,44 +453,44 @@ __global__ __launch_bounds__(WAVES * 64) void prune_rows_kernel(const int32_t *_
     const int n0 = __popcll(k0), n01 = n0 + __popcll(k1), end = wave_scan(n01);
 
     const int per_row = WAVES / rows_per_wg;                   // wavefronts of a row
-    const int p = blockIdx.x * rows_per_wg + wave / per_row;
-    if (p >= n_keep) return;
-    const int f = __builtin_ctzll(__ballot(p < end));              // the first lane whose survivors reach past p
-    int r = p - __builtin_amdgcn_readlane(end - n01, f), at = 128 * f;
-    const int first = __builtin_amdgcn_readlane(n0, f);
-    const bool second = r >= first;
-    uint64_t word = second ? k1 : k0;
-    uint32_t lo = __builtin_amdgcn_readlane((uint32_t)word, f), hi = __builtin_amdgcn_readlane((uint32_t)(word >> 32), f);
-    if (second) {
-        r -= first;
-        at += 64;
-    }
-    word = ((uint64_t)hi << 32) | lo;
-#pragma unroll
-    for (int w = 32; w > 0; w >>= 1) {                             // the r-th set bit
-        const int n = __popcll(word & ((1ull << w) - 1));
-        if (r >= n) {
-            r -= n;
-            at += w;
-            word >>= w;
+    for (int p = blockIdx.x * rows_per_wg + wave / per_row; p < n_keep; p += gridDim.x * rows_per_wg) {
+        const int f = __builtin_ctzll(__ballot(p < end));              // the first lane whose survivors reach past p
+        int r = p - __builtin_amdgcn_readlane(end - n01, f), at = 128 * f;
+        const int first = __builtin_amdgcn_readlane(n0, f);
+        const bool second = r >= first;
+        uint64_t word = second ? k1 : k0;
+        uint32_t lo = __builtin_amdgcn_readlane((uint32_t)word, f), hi = __builtin_amdgcn_readlane((uint32_t)(word >> 32), f);
+        if (second) {
+            r -= first;
+            at += 64;
         }
-    }
-    const int part = wave % per_row;
-    if (part == 0 && lane == 0) idx_out[p] = at;
-    const uint4 *const src = x + (int64_t)at * d8;
-    uint4 *const dst = out + (int64_t)p * d8;
-    const int stride = per_row * 64, last = d8 - 1;
-    for (int c = part * 64 + lane; c < d8; c += 4 * stride) {      // four loads under way at a time
-        const uint4 v0 = src[c], v1 = src[min(c + stride, last)], v2 = src[min(c + 2 * stride, last)], v3 = src[min(c + 3 * stride, last)];
-        auto put = [&](int at_c, const uint4 &v) {
-            if (at_c >= d8) return;
-            dst[at_c] = v;
-            if (CODES) *reinterpret_cast<uint2 *>(tiles + agq_code_offset(p, at_c, d8 >> 4)) = agq_quant8<true>(v, q);
-        };
-        put(c, v0);
-        put(c + stride, v1);
-        put(c + 2 * stride, v2);
-        put(c + 3 * stride, v3);
+        word = ((uint64_t)hi << 32) | lo;
+#pragma unroll
+        for (int w = 32; w > 0; w >>= 1) {                             // the r-th set bit
+            const int n = __popcll(word & ((1ull << w) - 1));
+            if (r >= n) {
+                r -= n;
+                at += w;
+                word >>= w;
+            }
+        }
+        const int part = wave % per_row;
+        if (part == 0 && lane == 0) idx_out[p] = at;
+        const uint4 *const src = x + (int64_t)at * d8;
+        uint4 *const dst = out + (int64_t)p * d8;
+        const int stride = per_row * 64, last = d8 - 1;
+        for (int c = part * 64 + lane; c < d8; c += 4 * stride) {      // four loads under way at a time
+            const uint4 v0 = src[c], v1 = src[min(c + stride, last)], v2 = src[min(c + 2 * stride, last)], v3 = src[min(c + 3 * stride, last)];
+            auto put = [&](int at_c, const uint4 &v) {
+                if (at_c >= d8) return;
+                dst[at_c] = v;
+                if (CODES) *reinterpret_cast<uint2 *>(tiles + agq_code_offset(p, at_c, d8 >> 4)) = agq_quant8<true>(v, q);
+            };
+            put(c, v0);
+            put(c + stride, v1);
+            put(c + 2 * stride, v2);
+            put(c + 3 * stride, v3);
+        }
     }
 }
 
@@ -541,7 +541,13 @@ int agq_launch_prune(const int32_t *score, int64_t S, int64_t n_keep, const void
     int rows_per_wg = 1;
     if (S > 512)
         while (rows_per_wg < waves && n_keep > (int64_t)rows_per_wg * 256) rows_per_wg *= 2;
-    const unsigned grid = (unsigned)((n_keep + rows_per_wg - 1) / rows_per_wg);
+    unsigned grid = (unsigned)((n_keep + rows_per_wg - 1) / rows_per_wg);
+    // A result that lies over the scores is written by one workgroup, after its barriers: with more, some would still read them.
+    auto over_scores = [&](const void *out, int64_t bytes) {
+        const uintptr_t o = (uintptr_t)out, s = (uintptr_t)score;
+        return o < s + (size_t)S * 4 && s < o + (size_t)bytes;
+    };
+    if (over_scores(idx, n_keep * 4) || over_scores(x_out, n_keep * d * 2)) grid = 1;
     const AgqQuant q = codes.tiles ? agq_make_quant_signed(codes.bits, codes.e, 0) : AgqQuant{};
     auto launch = [&](auto kernel) {
         kernel<<<grid, waves * 64, 0, st>>>(score, (int)S, (int)n_keep, rows_per_wg, (const uint4 *)x, (int)(d / 8), idx, (uint4 *)x_out, q, (char *)codes.tiles);

@@ -776,6 +776,24 @@ def test_prune_sizes_and_ranges(agq, oracle, S, keep, d, low, high):
     assert np.array_equal(host(out).view(np.uint16), want_x.view(np.uint16))
 
 
+@pytest.mark.parametrize("over", ["idx", "rows"])
+@pytest.mark.parametrize("S,keep,d", [(300, 213, 264), (2048, 1024, 520), (8192, 8192, 8)])
+def test_prune_into_the_scores(agq, oracle, S, keep, d, over):
+    """The indices, or the rows, written over the scores: every token has been ranked by then."""
+    rng = np.random.default_rng(S)
+    score = rng.integers(-1000, 1000, size=S).astype(np.int32)
+    x = rng.standard_normal((S, d)).astype(np.float16)
+    buf = torch.zeros(max(S * 4, keep * d * 2), dtype=torch.uint8, device="cuda")
+    buf.view(torch.int32)[:S] = dev(score)
+    idx = buf.view(torch.int32)[:keep] if over == "idx" else torch.empty(keep, dtype=torch.int32, device="cuda")
+    out = buf.view(torch.float16)[:keep * d].view(keep, d) if over == "rows" else torch.empty((keep, d), dtype=torch.float16, device="cuda")
+    xd = dev(x)
+    assert agq.lib().agq_prune_tokens(agq._ptr(buf), S, keep, agq._ptr(xd), d, agq._ptr(idx), agq._ptr(out), agq._stream()) == 0
+    want_idx, want_x = oracle.prune_tokens(score, keep, x)
+    assert np.array_equal(host(idx), want_idx)
+    assert np.array_equal(host(out).view(np.uint16), want_x.view(np.uint16))
+
+
 @pytest.mark.parametrize("kind", ["equal", "signed", "extremes", "max_size", "keep_none"])
 def test_prune_degenerate(agq, oracle, kind):
     """Score patterns that stress the threshold search: one value everywhere
