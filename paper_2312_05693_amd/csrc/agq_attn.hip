@@ -348,6 +348,25 @@ __device__ __forceinline__ int wave_scan(int x) {                  // inclusive 
     return (int)v;
 }
 
+// Output row p from src, the chunks c, c + stride, ...; with CODES the row's Eq.2 codes as well.
+template <bool CODES>
+__device__ __forceinline__ void copy_row(const uint4 *__restrict__ src, uint4 *__restrict__ dst, int p, int d8, int c, int stride,
+                                         const AgqQuant &q, char *__restrict__ tiles) {
+    const int last = d8 - 1;
+    for (; c < d8; c += 4 * stride) {                              // four loads under way at a time
+        const uint4 v0 = src[c], v1 = src[min(c + stride, last)], v2 = src[min(c + 2 * stride, last)], v3 = src[min(c + 3 * stride, last)];
+        auto put = [&](int at_c, const uint4 &v) {
+            if (at_c >= d8) return;
+            dst[at_c] = v;
+            if (CODES) *reinterpret_cast<uint2 *>(tiles + agq_code_offset(p, at_c, d8 >> 4)) = agq_quant8<true>(v, q);
+        };
+        put(c, v0);
+        put(c + stride, v1);
+        put(c + 2 * stride, v2);
+        put(c + 3 * stride, v3);
+    }
+}
+
 // Survivors of Eq.4, the n_keep tokens with the largest score, equal scores to the lower index, in ascending order, and
 // their rows: out[p] = x[idx[p]], with CODES also the rows' Eq.2 codes in the operand order of the tiled GEMM.
 //
@@ -364,10 +383,11 @@ __device__ __forceinline__ int wave_scan(int x) {                  // inclusive 
 // kept, rows of 5120 11.8 -> 8.4 us (14.0 -> 8.8 where scores crowd at one end), 300 tokens, 213 rows of 4096 8.7 -> 4.6,
 // 8192 tokens, 4096 rows of 4096 24.0 -> 22.4.  What is left of it: about 2.5 us of latency from the scores to the rows,
 // more where a wavefront holds more tokens (code for sixteen tokens a thread alone took 2 us), and the rows.
-// WAVES: wavefronts of a workgroup; PER: tokens per thread, in registers
-template <int WAVES, int PER, bool CODES>
-__global__ __launch_bounds__(WAVES * 64) void prune_rows_kernel(const int32_t *__restrict__ score, int S, int n_keep, int rows_per_wg,
-                                                                 const uint4 *__restrict__ x, int d8, int32_t *__restrict__ idx_out,
+// WAVES: wavefronts of a workgroup; PER: tokens per thread, in registers.  ROWS: as above; without, one workgroup writes the
+// indices alone, which may lie over the scores: every thread holds its own in registers by then.
+template <int WAVES, int PER, bool CODES, bool ROWS>
+__global__ __launch_bounds__(WAVES * 64) void prune_rows_kernel(const int32_t *score, int S, int n_keep, int rows_per_wg,
+                                                                 const uint4 *__restrict__ x, int d8, int32_t *idx_out,
                                                                  uint4 *__restrict__ out, const AgqQuant q, char *__restrict__ tiles) {
     constexpr int kThreads = WAVES * 64;
     __shared__ __align__(16) int hist[4][256];
@@ -452,6 +472,18 @@ __global__ __launch_bounds__(WAVES * 64) void prune_rows_kernel(const int32_t *_
     const uint64_t k0 = ab.x | lowest(eq.x, e0, k - ties), k1 = ab.y | lowest(eq.y, e1, k - ties - e0);
     const int n0 = __popcll(k0), n01 = n0 + __popcll(k1), end = wave_scan(n01);
 
+    if constexpr (!ROWS) {
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+            const int w = e * WAVES + wave, l = w >> 1;            // this wavefront's word lies with lane l
+            const uint64_t word = (w & 1) ? k1 : k0;
+            const uint64_t kept = ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(word >> 32), l) << 32) | (uint32_t)__builtin_amdgcn_readlane((uint32_t)word, l);
+            const int before = __builtin_amdgcn_readlane(end - n01, l) + ((w & 1) ? __builtin_amdgcn_readlane(n0, l) : 0);
+            if (kept >> lane & 1) idx_out[before + __popcll(kept & ((1ull << lane) - 1))] = 64 * w + lane;
+        }
+        return;
+    }
+
     const int per_row = WAVES / rows_per_wg;                   // wavefronts of a row
     for (int p = blockIdx.x * rows_per_wg + wave / per_row; p < n_keep; p += gridDim.x * rows_per_wg) {
         const int f = __builtin_ctzll(__ballot(p < end));              // the first lane whose survivors reach past p
@@ -476,22 +508,16 @@ __global__ __launch_bounds__(WAVES * 64) void prune_rows_kernel(const int32_t *_
         }
         const int part = wave % per_row;
         if (part == 0 && lane == 0) idx_out[p] = at;
-        const uint4 *const src = x + (int64_t)at * d8;
-        uint4 *const dst = out + (int64_t)p * d8;
-        const int stride = per_row * 64, last = d8 - 1;
-        for (int c = part * 64 + lane; c < d8; c += 4 * stride) {      // four loads under way at a time
-            const uint4 v0 = src[c], v1 = src[min(c + stride, last)], v2 = src[min(c + 2 * stride, last)], v3 = src[min(c + 3 * stride, last)];
-            auto put = [&](int at_c, const uint4 &v) {
-                if (at_c >= d8) return;
-                dst[at_c] = v;
-                if (CODES) *reinterpret_cast<uint2 *>(tiles + agq_code_offset(p, at_c, d8 >> 4)) = agq_quant8<true>(v, q);
-            };
-            put(c, v0);
-            put(c + stride, v1);
-            put(c + 2 * stride, v2);
-            put(c + 3 * stride, v3);
-        }
+        copy_row<CODES>(x + (int64_t)at * d8, out + (int64_t)p * d8, p, d8, part * 64 + lane, per_row * 64, q, tiles);
     }
+}
+
+// The rows by themselves, behind a selection that wrote the indices alone.
+template <bool CODES>
+__global__ __launch_bounds__(256) void gather_rows_kernel(const uint4 *__restrict__ x, const int32_t *__restrict__ idx, int d8,
+                                                           uint4 *__restrict__ out, const AgqQuant q, char *__restrict__ tiles) {
+    const int p = blockIdx.x;
+    copy_row<CODES>(x + (int64_t)idx[p] * d8, out + (int64_t)p * d8, p, d8, threadIdx.x, 256, q, tiles);
 }
 
 }  // namespace
@@ -541,19 +567,26 @@ int agq_launch_prune(const int32_t *score, int64_t S, int64_t n_keep, const void
     int rows_per_wg = 1;
     if (S > 512)
         while (rows_per_wg < waves && n_keep > (int64_t)rows_per_wg * 256) rows_per_wg *= 2;
-    unsigned grid = (unsigned)((n_keep + rows_per_wg - 1) / rows_per_wg);
-    // A result that lies over the scores is written by one workgroup, after its barriers: with more, some would still read them.
+    const unsigned grid = (unsigned)((n_keep + rows_per_wg - 1) / rows_per_wg);
+    const AgqQuant q = codes.tiles ? agq_make_quant_signed(codes.bits, codes.e, 0) : AgqQuant{};
+    auto launch = [&](unsigned workgroups, auto kernel) {
+        kernel<<<workgroups, waves * 64, 0, st>>>(score, (int)S, (int)n_keep, rows_per_wg, (const uint4 *)x, (int)(d / 8), idx, (uint4 *)x_out, q, (char *)codes.tiles);
+    };
+    // Results that lie over the scores: with every workgroup selecting for itself some would still read scores when others
+    // write there, so one workgroup writes the indices and a launch behind it the rows: 2048 tokens, 1024 kept, rows of
+    // 5120 9.8 us, 300 tokens, 213 rows of 4096 5.6 (one workgroup for the rows too: 286 and 128).
     auto over_scores = [&](const void *out, int64_t bytes) {
         const uintptr_t o = (uintptr_t)out, s = (uintptr_t)score;
         return o < s + (size_t)S * 4 && s < o + (size_t)bytes;
     };
-    if (over_scores(idx, n_keep * 4) || over_scores(x_out, n_keep * d * 2)) grid = 1;
-    const AgqQuant q = codes.tiles ? agq_make_quant_signed(codes.bits, codes.e, 0) : AgqQuant{};
-    auto launch = [&](auto kernel) {
-        kernel<<<grid, waves * 64, 0, st>>>(score, (int)S, (int)n_keep, rows_per_wg, (const uint4 *)x, (int)(d / 8), idx, (uint4 *)x_out, q, (char *)codes.tiles);
-    };
-    if (S <= 512) launch(codes.tiles ? prune_rows_kernel<8, 1, true> : prune_rows_kernel<8, 1, false>);
-    else if (S <= 2048) launch(codes.tiles ? prune_rows_kernel<16, 2, true> : prune_rows_kernel<16, 2, false>);
-    else launch(codes.tiles ? prune_rows_kernel<16, 8, true> : prune_rows_kernel<16, 8, false>);
+    if (over_scores(idx, n_keep * 4) || over_scores(x_out, n_keep * d * 2)) {
+        if (S <= 512) launch(1, prune_rows_kernel<8, 1, false, false>);
+        else if (S <= 2048) launch(1, prune_rows_kernel<16, 2, false, false>);
+        else launch(1, prune_rows_kernel<16, 8, false, false>);
+        (codes.tiles ? gather_rows_kernel<true> : gather_rows_kernel<false>)<<<(unsigned)n_keep, 256, 0, st>>>(
+            (const uint4 *)x, idx, (int)(d / 8), (uint4 *)x_out, q, (char *)codes.tiles);
+    } else if (S <= 512) launch(grid, codes.tiles ? prune_rows_kernel<8, 1, true, true> : prune_rows_kernel<8, 1, false, true>);
+    else if (S <= 2048) launch(grid, codes.tiles ? prune_rows_kernel<16, 2, true, true> : prune_rows_kernel<16, 2, false, true>);
+    else launch(grid, codes.tiles ? prune_rows_kernel<16, 8, true, true> : prune_rows_kernel<16, 8, false, true>);
     return (int)hipGetLastError();
 }

@@ -794,6 +794,31 @@ def test_prune_into_the_scores(agq, oracle, S, keep, d, over):
     assert np.array_equal(host(out).view(np.uint16), want_x.view(np.uint16))
 
 
+@pytest.mark.parametrize("over", ["idx", "rows"])
+def test_prune_into_the_scores_copies_with_the_whole_chip(agq, over):
+    """10 MB of rows take a few microseconds on all compute units and some 300 on one; with the results over the scores the
+    call may cost a launch more, not the chip.  (9.8 against 8.6 us in a graph; the bound leaves a factor of four and the host's share.)"""
+    S, keep, d = 2048, 1024, 5120
+    buf = torch.randint(0, 1 << 30, (keep * d // 2,), dtype=torch.int32, device="cuda")
+    x = torch.randn((S, d), device="cuda").half()
+    rows, idx = torch.empty((keep, d), dtype=torch.float16, device="cuda"), torch.empty(keep, dtype=torch.int32, device="cuda")
+
+    def us(idx_out, x_out):
+        calls, best = 40, float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            a.record()
+            for _ in range(calls):
+                assert agq.lib().agq_prune_tokens(agq._ptr(buf), S, keep, agq._ptr(x), d, agq._ptr(idx_out), agq._ptr(x_out), agq._stream()) == 0
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 1000 / calls)
+        return best
+    apart = us(idx, rows)
+    assert us(buf if over == "idx" else idx, buf if over == "rows" else rows) < 4 * apart + 5
+
+
 @pytest.mark.parametrize("kind", ["equal", "signed", "extremes", "max_size", "keep_none"])
 def test_prune_degenerate(agq, oracle, kind):
     """Score patterns that stress the threshold search: one value everywhere
