@@ -31,8 +31,8 @@
 // dealt out one MFMA at a time, the scores of the next sub-tile beside the arithmetic of this one; scores become floats
 // by a subtraction; a conversion to bytes rounds and packs the weights' exponents; V is widened by one
 // packed multiply-add.  Against a kernel with nothing dealt out and three workgroups on a CU (the same results bit for
-// bit): 40 x 2048 x 128 causal 67.2 -> 61.8 us, 40 x 2048 x 64 57 -> 43 (half of the output blocks were empty there),
-// 32 x 384 x 128 14.4 -> 13.3.  What is left of a large causal call is the chain of its longest row blocks (32 tiles
+// bit): 40 x 2048 x 128 causal 67.2 -> 59.6 us, 40 x 2048 x 64 55 -> 40 (half of the output blocks were empty there),
+// 32 x 384 x 128 14.7 -> 12.6, one head of 128 tokens 7.03 -> 6.85 (without causality 6.18 -> 6.30).  What is left of a large causal call is the chain of its longest row blocks (32 tiles
 // take 45 us alone on a CU, 305 instructions a tile in pass 2).  Not kept: a reference score in place of the running maximum, with differences to it straight from
 // the accumulators (58 us, and three times fewer codes off, but other codes than before); one block on eight
 // wavefronts, the key tiles shared by two groups of four (72 us then: both wavefronts of a SIMD want the same unit at
@@ -244,17 +244,21 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
         }
     };
     tile_scores(kt, acc0, acc1);
-    // a sub-tile at the diagonal
+    // A sub-tile at the diagonal; keys past the query do not count.  Alone on its SIMD a wavefront pays for every instruction: one
+    // comparison and a select per score, and the difference to the maximum in one subtraction of floats (one head of 128
+    // tokens 7.97 -> 7.22 us against integers and a conversion).
     auto stats = [&](const agq_v16i &acc, int sub, bool masked) {
-        auto dead = [&](int r) { return masked && 32 * sub + 8 * (r >> 2) + 4 * g + (r & 3) > row; };   // keys past the query do not count
-        int mx = kMasked;
+        const int left = masked ? row - (32 * sub + 4 * g) : 32;
+        auto dead = [&](int r) { return 8 * (r >> 2) + (r & 3) > left; };
+        int mx = run_m + kBias;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mx = max(mx, dead(r) ? kMasked : acc[r] - kBias);
-        const int nm = max(run_m, mx);
+        for (int r = 0; r < 16; ++r) mx = max(mx, dead(r) ? kMasked + kBias : acc[r]);
+        const int nm = mx - kBias;
+        const float ref = AGQ_MAGIC + (float)nm;                 // exact where a score counts, and so is the difference
         float add = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const float term = __builtin_amdgcn_exp2f(kappa * (float)(acc[r] - kBias - nm));
+            const float term = __builtin_amdgcn_exp2f(kappa * (__int_as_float(acc[r]) - ref));
             add += dead(r) ? 0.f : term;
         }
         // nothing counted so far (run_m == kMasked) means run_s == 0: the factor does not matter
@@ -436,6 +440,8 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
     auto half = [&](const agq_v16i &cur, agq_v16i &nxt, int sub, auto u_tag, const uint8_t *vtile, const uint8_t *ahead, auto masked_tag, auto other) {
         constexpr int u = decltype(u_tag)::value;
         const int vi = 2 * (sub & 1) + u, hs = 2 * sub + u;
+        // of a sub-tile with dead keys no other follows, so the half before this one has some only if it is the same sub-tile's
+        const std::integral_constant<bool, decltype(masked_tag)::value && u == 1> before_tag{};
         float x[8];
         uint32_t n0 = 0, n1 = 0;
         auto cvt = [&](auto i_tag) {                             // pair i: registers i and i + 4
@@ -473,7 +479,7 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (NB == 4) {
             qk(Int<2 * u>{});
-            exponents(); cvt(i0); weights(hs - 1, masked_tag);
+            exponents(); cvt(i0); weights(hs - 1, before_tag);
             end_slot(i0);
             pv(i0);
             cvt(i1); mul(i0);
@@ -492,7 +498,7 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
             end_slot(i5);
         } else {
             qk(Int<u>{});
-            exponents(); cvt(i0); cvt(i1); weights(hs - 1, masked_tag);
+            exponents(); cvt(i0); cvt(i1); weights(hs - 1, before_tag);
             end_slot(i0);
             pv(i0);
             cvt(i2); cvt(i3); mul(i0); mul(i1); rnd(i0);
@@ -525,19 +531,19 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
         if constexpr (decltype(k)::value == 1 && P == 1) copy_v();  \
         if constexpr (decltype(k)::value == 1 && P == 2) copy_k(); \
     }
-        read_v(t + 1);
+        if (!MASKED || t + 1 < nt) read_v(t + 1);
         if constexpr (!MASKED) {
             half(acc0, acc1, 2 * t, Int<0>{}, vtile, ahead, masked_tag, AGQ_STAGE(0));
             half(acc0, acc1, 2 * t, Int<1>{}, vtile, ahead, masked_tag, AGQ_STAGE(1));
             half(acc1, acc0, 2 * t + 1, Int<0>{}, vtile, ahead, masked_tag, AGQ_STAGE(2));
             half(acc1, acc0, 2 * t + 1, Int<1>{}, vtile, ahead, masked_tag, AGQ_STAGE(3));
         } else {
-            copy_v();
-            copy_k();
-            stage(Int<0>{});
-            stage(Int<1>{});
-            stage(Int<2>{});
-            stage(Int<3>{});
+            if (t + 1 < nt) {
+                stage(Int<0>{});
+                stage(Int<1>{});
+                stage(Int<2>{});
+                stage(Int<3>{});
+            }
             if (2 * t <= last_sub) {
                 half(acc0, acc1, 2 * t, Int<0>{}, vtile, ahead, masked_tag, none);
                 half(acc0, acc1, 2 * t, Int<1>{}, vtile, ahead, masked_tag, none);
@@ -548,7 +554,8 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
             }
         }
 #undef AGQ_STAGE
-        meet<kKC>();                                             // V tile t + 2 and K tile nt + t + 2 have landed
+        if constexpr (!MASKED) meet<kKC>();                      // V tile t + 2 and K tile nt + t + 2 have landed
+        else if (t + 1 < nt) meet<63>();                         // the last V tile is in LDS; no more are copied (nor waited for: 7.22 -> 6.85)
     };
     int t = 0;
     for (; t < n_main; ++t) pass2_tile(t, std::false_type{});
@@ -559,14 +566,14 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
 #pragma unroll
     for (int n = 0; n < NB; ++n) acc_o[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(agq_v8h, w), vf[n], acc_o[n], 0, 0, 0);
 
+    __builtin_amdgcn_s_waitcnt(0x70);                            // the last copies into LDS have landed before it is given back
+
     // code map right of the last sub-tile this wavefront multiplied: all qmax
     if (CODES && a.causal) {
         const uint32_t fill = 0x11111111u * (uint32_t)a.qmax;
         uint8_t *dst = a.codes + ((int64_t)h * S + row) * (S >> 1);
         for (int k = (last_sub + 1) * 32 + g * 8; k < S; k += 16) *reinterpret_cast<uint32_t *>(dst + (k >> 1)) = fill;
     }
-
-    __builtin_amdgcn_s_waitcnt(0x70);                            // the last copies into LDS have landed before it is given back
 
     // accumulator register 4 q + r holds query row 8 q + 4 g + r of the wavefront,
     // channel NB c + n in block n: NB consecutive channels per lane and row

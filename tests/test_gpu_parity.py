@@ -1271,6 +1271,41 @@ def test_qk_attention_whole_code_range(agq, oracle, D, e_q, causal, qmax):
     assert np.array_equal(host(score).astype(np.int64), oracle.start_token_score_codes(got_c, qmax))
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("want_codes", [False, True])
+def test_qk_attention_short_causal_call_costs_no_more_than_its_tiles(agq, D, want_codes):
+    """One head of 128 tokens: the causal call has fewer tiles than the other, and what its diagonal adds may not make up for it
+    (6 to 12 % of the time in replayed graphs; it was 26 to 30 when the diagonal converted every score and waited for
+    copies that nobody reads)."""
+    S = 128
+    q, k, v = [dev(t) for t in synth.make_qkv_int8(1, S, D, seed=6)]
+    o = torch.empty((S, D), dtype=torch.float16, device="cuda")
+    codes = torch.empty((1, S, S // 2), dtype=torch.uint8, device="cuda") if want_codes else None
+    score = torch.zeros(S, dtype=torch.int32, device="cuda")
+    graphs = []
+    for causal in (1, 0):
+        def call():
+            assert agq.lib().agq_qk_log2_softmax(agq._ptr(q), agq._ptr(k), 1, S, D, causal, 15, -5, -5, agq._ptr(v), -4, agq._ptr(o),
+                                                 agq._ptr(codes), agq._ptr(score), agq._stream()) == 0
+        call()
+        torch.cuda.synchronize()
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            for _ in range(50):
+                call()
+    best = [float("inf")] * 2
+    for _ in range(10):
+        for i, g in enumerate(graphs):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            g.replay()
+            a.record()
+            g.replay()
+            b.record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], a.elapsed_time(b))
+    assert best[0] < 1.2 * best[1], best
+
+
 def test_qk_attention_llama13b_full_size(agq, oracle):
     """The benchmark's configuration (H = 40, S = 2048, D = 128, causal); the oracle checks two
     whole heads, and the exact integer relations behind the codes are checked for every head."""
