@@ -344,10 +344,12 @@ int agq_log2_quant_softmax(const void *p_f16, int64_t H, int64_t S, int64_t D,
  *   c[h,i,j]  = CLIP(round(-log2 p[h,i,j]), 0, qmax)
  *   o[i,h*D+d]= fp16( 2^(e_v-qmax) * sum_j 2^(qmax-c[h,i,j]) * v_q[h,j,d] )
  *   score[i] += sum_h 2^(qmax - c[h,i,0])
- * -log2 p is evaluated in fp32 as log2(sum_j 2^(kappa s_j)) - kappa s with the
- * hardware's exp2 / log2: a code may differ from an exact evaluation where
- * -log2 p lies within about 1e-5 of a rounding boundary; o and score follow
- * exactly from the codes.
+ * -log2 p is evaluated in fp32 as log2(sum_j 2^(kappa s_j)) - kappa s, kappa =
+ * 2^(e_q+e_k) log2(e) / sqrt(D), with the hardware's exp2 / log2: a code may differ
+ * from an exact evaluation where -log2 p lies within about 1e-5 of a rounding
+ * boundary, to which 2^-22 times the row's largest |kappa s| is added for kappa
+ * <= 1 (6e-5 at 256; beyond kappa = 1 differences of scores are scaled instead);
+ * o and score follow exactly from the codes.
  * q_q, k_q, v_q : int8 [H,S,D] on the signed grid of Eq.2 with scales 2^e_q,
  *           2^e_k, 2^e_v.  D = 64 or 128; S % 128 == 0, S <= 32768.
  * qmax    : 15 or 7.   o_f16: fp16 [S, H*D].

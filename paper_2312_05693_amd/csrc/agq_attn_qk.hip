@@ -13,8 +13,9 @@
 // Two passes over the key tiles of a 128-row block: the first keeps a running
 // maximum and sum per row (L), the second recomputes the scores, turns them
 // into the weights 2^(qmax-c) and multiplies.  L and t are evaluated in fp32
-// (hardware exp2 / log2), so a code can differ from a float64 evaluation where t
-// lies within ~1e-5 of a rounding boundary; everything after the codes is exact.
+// (hardware exp2 / log2), so a code can differ from a float64 evaluation where t lies within the evaluation's error of a
+// rounding boundary: about 1e-5 where kappa > 1, 1e-5 + 2^-22 max |kappa s| up to there (see WIDE); everything after the
+// codes is exact.
 //
 // Scores are computed transposed, S^T = K Q^T, with the 32x32x32 int8 MFMA: a lane
 // then holds, for its query (column l & 31), the keys 8 q + 4 g + r (g = l >> 5,
@@ -91,8 +92,11 @@ __device__ __forceinline__ void meet() {
 
 // DT = D / 32: int8 MFMA steps per score tile and 32-channel blocks of the output
 // CODES: the code map goes out as well; TILES: Eq.2's codes of o (a.tiles).
-// WIDE: kappa > 1, where the rounding of kappa s may carry an exponent past the largest weight's, so that it is cut off above
-// too.  (Up to there that rounding stays below 0.4: |s| <= 2^21.)
+// WIDE: kappa > 1.  Up to there kappa times the row's maximum M is rounded by itself, once in pass 1 and once in pass 2 with
+// the constant it goes into: t is off by up to three roundings of kappa M, about 2^-14 where |kappa s| reaches 2^8, as it does for
+// activations, and below 0.4 at most (|s| <= 2^21), so that no exponent passes the largest weight's.  Beyond, those roundings
+// have no bound, and the difference to the maximum, exact in fp32, is taken before the product: the same number of
+// instructions, and nothing to cut off, as no difference is above 0.
 template <int DT, bool CODES, bool TILES, bool WIDE>
 __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
     constexpr int D = DT * 32;
@@ -222,11 +226,9 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
     for (int r = 0; r < 16; ++r) cinit[r] = kBias;
     float kappa = a.kappa;                                       // in a vector register: a product of three of those is the faster one
     asm("" : "+v"(kappa));
-    auto score_of = [&](int bits) { return __int_as_float(bits) - AGQ_MAGIC; };
+    auto scaled = [&](float s, float plus) { return WIDE ? kappa * s : fmaf(kappa, s, plus); };   // WIDE: s is a difference to the maximum
 
-    // ---- pass 1: per row the maximum score M (an integer) and sum_j 2^(kappa (s_j - M)).
-    // Differences of scores are exact integers, so the only roundings are the product
-    // with kappa and the exponential.
+    // ---- pass 1: per row the maximum score M (an integer) and sum_j 2^(kappa (s_j - M))
     constexpr int kMasked = -(1 << 30);                          // stands for -infinity (|s| < 2^23)
     int run_m = kMasked;
     float run_s = 0.f;
@@ -270,12 +272,12 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = max(mx, max(cur0[r], cur1[r]));
         const int nm = mx - kBias;
-        const float nmf = -kappa * (float)nm;
+        const float ref = WIDE ? AGQ_MAGIC + (float)nm : AGQ_MAGIC, nmf = WIDE ? 0.f : -kappa * (float)nm;
         float add0 = 0.f, add1 = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            add0 += __builtin_amdgcn_exp2f(fmaf(kappa, score_of(cur0[r]), nmf));
-            add1 += __builtin_amdgcn_exp2f(fmaf(kappa, score_of(cur1[r]), nmf));
+            add0 += __builtin_amdgcn_exp2f(scaled(__int_as_float(cur0[r]) - ref, nmf));
+            add1 += __builtin_amdgcn_exp2f(scaled(__int_as_float(cur1[r]) - ref, nmf));
         }
         run_s = run_s * __builtin_amdgcn_exp2f(kappa * (float)(run_m - nm)) + (add0 + add1);
         run_m = nm;
@@ -292,9 +294,8 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx[r & 3] = max(mx[r & 3], max(cur0[r], cur1[r]));
         const int nm = max(max(mx[0], mx[1]), max(mx[2], mx[3])) - kBias;
-        // kappa s - kappa M with one rounding of the product (|kappa s| stays far below 2^10,
-        // so the difference is good to ~1e-5: enough for a sum of 2^x)
-        const float nmf = -kappa * (float)nm;
+        // kappa s - kappa M with one rounding, that of kappa M, or kappa (s - M) (WIDE)
+        const float ref = WIDE ? AGQ_MAGIC + (float)nm : AGQ_MAGIC, nmf = WIDE ? 0.f : -kappa * (float)nm;
         const float keep = __builtin_amdgcn_exp2f(kappa * (float)(run_m - nm));
         float add0 = 0.f, add1 = 0.f;
         constexpr int R = 16 / DT;                               // scores of a slot: R / 2 of either sub-tile
@@ -307,14 +308,14 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
                 if constexpr (k < DT) read_k(s, ahead, 1);
                 float x[R];
 #pragma unroll
-                for (int r = 0; r < R; ++r) x[r] = score_of(r & 1 ? cur1[k * (R / 2) + r / 2] : cur0[k * (R / 2) + r / 2]);
+                for (int r = 0; r < R; ++r) x[r] = __int_as_float(r & 1 ? cur1[k * (R / 2) + r / 2] : cur0[k * (R / 2) + r / 2]) - ref;
                 __builtin_amdgcn_sched_barrier(0);
                 if (k > 0) {
 #pragma unroll
                     for (int r = 0; r < R; ++r) (r & 1 ? add1 : add0) += e[r];
                 }
 #pragma unroll
-                for (int r = 0; r < R; ++r) x[r] = fmaf(kappa, x[r], nmf);
+                for (int r = 0; r < R; ++r) x[r] = scaled(x[r], nmf);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int r = 0; r < R; ++r) e[r] = __builtin_amdgcn_exp2f(x[r]);
@@ -361,9 +362,12 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
     // -log2 p = t = kappa (M - s) + log2(tot).  The weight 2^(qmax - c) has the fp16 exponent field
     // 15 + qmax - c = round(15 + qmax - t) clamped to [15, 15 + qmax]: one fused multiply-add gives 15 + qmax - t, and
     // a conversion to a byte rounds it (to even: a tie has measure zero and lies inside the evaluation error anyway) and cuts
-    // it off at 0; the lower bound of 15 follows on the weights' patterns, two at a time.
-    const float c2 = (float)(15 + a.qmax) - __builtin_amdgcn_logf(tot) - kappa * (float)M;   // v_log_f32: base 2
-    auto cut = [&](float x) { return WIDE ? __builtin_amdgcn_fmed3f(x, 0.0f, (float)(15 + a.qmax)) : x; };
+    // it off at 0; the lower bound of 15 follows on the weights' patterns, two at a time.  (A dead key's byte may exceed
+    // 15 + qmax; what it shifts into the next byte stays among dead keys, whose weights and codes are masked.)
+    const float c1 = (float)(15 + a.qmax) - __builtin_amdgcn_logf(tot);                       // v_log_f32: base 2
+    const float c2 = WIDE ? c1 : c1 - kappa * (float)M;
+    const float zero = WIDE ? AGQ_MAGIC + (float)M : AGQ_MAGIC;
+    auto score_of = [&](int bits) { return __int_as_float(bits) - zero; };                    // WIDE: its difference to M
 
     // ---- pass 2: codes, weights, product with V
     agq_v16f acc_o[NB];
@@ -398,7 +402,7 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
     }
     // importance on the quantized map: the weight of the first key (always live)
     if (a.score && g == 0)
-        atomicAdd(&a.score[row], 1 << (max(__builtin_amdgcn_cvt_pk_u8_f32(cut(fmaf(kappa, score_of(acc0[0]), c2)), 0, 0), 15u) - 15u));
+        atomicAdd(&a.score[row], 1 << (max(__builtin_amdgcn_cvt_pk_u8_f32(fmaf(kappa, score_of(acc0[0]), c2), 0, 0), 15u) - 15u));
     meet<63>();                                                  // V tile 0 is in LDS
 
     // the weights of half sub-tile `hs` (keys 16 hs ..) from their exponents
@@ -456,8 +460,8 @@ __global__ __launch_bounds__(256, 2) void qk_log2_attn_kernel(const QkArgs a) {
         };
         auto rnd = [&](auto i_tag) {
             constexpr int i = decltype(i_tag)::value;
-            n0 = __builtin_amdgcn_cvt_pk_u8_f32(cut(x[i]), i, n0);
-            n1 = __builtin_amdgcn_cvt_pk_u8_f32(cut(x[i + 4]), i, n1);
+            n0 = __builtin_amdgcn_cvt_pk_u8_f32(x[i], i, n0);
+            n1 = __builtin_amdgcn_cvt_pk_u8_f32(x[i + 4], i, n1);
         };
         auto pv = [&](auto n_tag) {
             constexpr int n = decltype(n_tag)::value;
@@ -637,7 +641,7 @@ int agq_launch_qk_log2_attn(const int8_t *q, const int8_t *k, const int8_t *v, i
     auto pick = [&](auto dt_tag, auto wide_tag) {
         constexpr int DT = decltype(dt_tag)::value;
         constexpr bool WIDE = decltype(wide_tag)::value;
-        if (codes) launch(qk_log2_attn_kernel<DT, true, false, true>);
+        if (codes) launch(qk_log2_attn_kernel<DT, true, false, WIDE>);
         else if (a.tiles) launch(qk_log2_attn_kernel<DT, false, true, WIDE>);
         else launch(qk_log2_attn_kernel<DT, false, false, WIDE>);
     };

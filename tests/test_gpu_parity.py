@@ -1272,6 +1272,41 @@ def test_qk_attention_whole_code_range(agq, oracle, D, e_q, causal, qmax):
 
 
 @pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("e_q,e_k", [(1, 1), (2, 1), (5, 5), (20, 20), (40, 40)])
+@pytest.mark.parametrize("causal,qmax", [(True, 15), (False, 7)])
+def test_qk_attention_large_exponents(agq, oracle, D, e_q, e_k, causal, qmax):
+    """kappa = 2^(e_q+e_k) log2(e) / sqrt(D) just below 1, just above it, and up to the largest exponents that the call accepts:
+    scores over the whole int8 range, keys that occur many times, so that a row's maximum is shared, and small scores.
+    Reference: float64 on the exact differences of scores to the row's maximum.  Up to kappa = 1 the kernel rounds kappa times the
+    maximum (three roundings of 2^-24); with it -log2 p is good to CODE_MARGIN beyond."""
+    H, S, e_v = 3, 384, -4
+    rng = np.random.default_rng([78, D, e_q])
+    qq = rng.integers(-128, 128, (H, S, D)).astype(np.int8)
+    kq = rng.integers(-128, 128, (H, S, D)).astype(np.int8)
+    kq[1] = kq[1, rng.integers(0, 24, S)]
+    qq[2], kq[2] = rng.integers(-1, 2, (2, S, D))
+    vq = rng.integers(-128, 128, (H, S, D)).astype(np.int8)
+    kappa = 2.0 ** (e_q + e_k) * np.log2(np.e) / np.sqrt(D)
+    score = oracle.qk_scores(qq, kq).astype(np.float64)
+    live = np.tril(np.ones((S, S), dtype=bool))[None] if causal else np.ones((1, S, S), dtype=bool)
+    z = (score - np.where(live, score, -np.inf).max(axis=2, keepdims=True)) * kappa
+    t = np.where(live, np.log2(np.where(live, np.exp2(np.where(live, z, 0)), 0).sum(axis=2, keepdims=True)) - z, np.inf)
+    want_c = np.clip(np.rint(t), 0, qmax).astype(np.int32)
+    margin = np.abs(np.minimum(t, qmax) - np.floor(np.minimum(t, qmax)) - 0.5)
+    margin = np.where(t < qmax, margin, 0.5 + np.minimum(t, 2 * qmax) - qmax)
+    error = CODE_MARGIN + (0 if kappa > 1 else 2.0 ** -22 * kappa * np.abs(np.where(live, score, 0)).max(axis=2, keepdims=True))
+    o, codes, got_s = agq.qk_log2_softmax(dev(qq), dev(kq), dev(vq), e_q, e_k, e_v, qmax=qmax, causal=causal, want_codes=True)
+    got_c = unpack_codes(host(codes), S)
+    sure = margin > error
+    assert np.array_equal(got_c[sure], want_c[sure]) and np.abs(got_c - want_c).max() <= 1 and sure.mean() > 0.9
+    _, want_o = oracle.attn_v_from_codes(got_c, vq, e_v, qmax, causal)
+    assert np.array_equal(host(o).view(np.uint16), want_o.view(np.uint16))
+    assert np.array_equal(host(got_s).astype(np.int64), oracle.start_token_score_codes(got_c, qmax))
+    plain_o, _, plain_s = agq.qk_log2_softmax(dev(qq), dev(kq), dev(vq), e_q, e_k, e_v, qmax=qmax, causal=causal)
+    assert np.array_equal(host(plain_o).view(np.uint16), want_o.view(np.uint16)) and np.array_equal(host(plain_s), host(got_s))
+
+
+@pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("want_codes", [False, True])
 def test_qk_attention_short_causal_call_costs_no_more_than_its_tiles(agq, D, want_codes):
     """One head of 128 tokens: the causal call has fewer tiles than the other, and what its diagonal adds may not make up for it
