@@ -263,6 +263,42 @@ def test_stack_with_cascade_equals_block_by_block(agq, oracle, blk_oracle):
         agq.stack_forward(blocks[:1] + [other], keep[:2], xd, pd, cd, sd)
 
 
+def additions_left(agq, blocks, S, keep):
+    """For every block but the last, whether agq_stack_forward leaves its last addition to the next one: unless what that block
+    writes first (h1, the codes in the GEMM scratch) lies over this one's x1."""
+    left, s_in = [], S
+    for l in range(len(blocks) - 1):
+        A, B = agq.block_layout(blocks[l], s_in, keep[l]), agq.block_layout(blocks[l + 1], keep[l], keep[l + 1])
+        d, rows = blocks[l].d, keep[l]
+        written = ((B.h1, rows * d * 2), (B.gemm_ws, (rows + 127) // 128 * 128 * d))
+        left.append(all(at + n <= A.x1 or A.x1 + rows * d * 2 <= at for at, n in written))
+        s_in = keep[l]
+    return left
+
+
+@pytest.mark.parametrize("keep,left", [([150, 75], "n"), ([150, 75, 75, 75], "nyy"), ([300, 150, 75, 75], "yny"),
+                                       ([300, 150, 75, 52, 36], "ynny"), ([150, 75, 52, 18, 18], "nnyy"), ([150, 75, 27, 13, 4], "nynn")])
+def test_stack_whose_blocks_do_and_do_not_leave_their_addition(agq, keep, left):
+    """Schedules that make a block add its own down projection, in front of, between and behind blocks that leave the addition to
+    the next one: the tokens then lie in either of the two buffers.  Bit for bit the blocks run one by one, in a dirty
+    workspace."""
+    S, d, H, F = 300, 256, 2, 640
+    x, pos, cos, sin, _ = make_inputs(S, d, H, F, seed=43)
+    xd, pd, cd, sd = dev(x), dev(pos), dev(cos), dev(sin)
+    blocks, xg, pg = [], xd, pd
+    for layer, n_keep in enumerate(keep):
+        blk = agq.make_block(d, H, F, upload_weights(agq, synth.make_block_weights(d, H, F, 80 + layer)), rms_eps=EPS)
+        agq.block_forward(blk, xg, pg, cd, sd, n_keep=n_keep, calibrate=True)
+        xg, pg, _, _ = agq.block_forward(blk, xg, pg, cd, sd, n_keep=n_keep)
+        blocks.append(blk)
+    assert "".join("y" if l else "n" for l in additions_left(agq, blocks, S, keep)) == left
+    x_st, p_st, ws = agq.stack_forward(blocks, keep, xd, pd, cd, sd)
+    assert same(host(x_st), host(xg)) and np.array_equal(host(p_st), host(pg))
+    ws.fill_(0xA5)
+    x_st, p_st, _ = agq.stack_forward(blocks, keep, xd, pd, cd, sd, workspace=ws)
+    assert same(host(x_st), host(xg)) and np.array_equal(host(p_st), host(pg))
+
+
 def test_block_graph_replay(agq, oracle, blk_oracle):
     """agq_block_forward enqueues kernels only (no memset nodes, no allocation): captured into a HIP graph after an
     eager call, every replay reproduces the eager result bit for bit, with eager work in between."""
@@ -323,6 +359,24 @@ def test_swiglu_on_every_gate_value(agq, blk_oracle, n):
     got = host(agq.swiglu(dev(gate), dev(up)))
     nan = np.isnan(want)
     assert np.array_equal(nan, np.isnan(got)) and same(got[~nan], want[~nan])
+
+
+def test_swiglu_in_fp32_first_equals_float64_on_every_gate_and_mantissa(agq):
+    """Every finite gate with every mantissa of one binade of up, which puts products next to every rounding boundary: calls that
+    evaluate in fp32 first (256 * 256 * 8 values) against the same values in calls below that line (float64 throughout).  Tens of
+    thousands of the 65 million results lie within 2^-22 of a boundary, so an interval too narrow for some gates does not pass."""
+    line = 256 * 256 * 8
+    up = torch.arange(0x3C00, 0x4000, dtype=torch.int16, device="cuda").view(torch.float16).repeat(line // 1024)
+    gates = torch.arange(65536, dtype=torch.int32, device="cuda").to(torch.int16).view(torch.float16)
+    gates = gates[torch.isfinite(gates)]
+    assert gates.numel() % (line // 1024) == 0
+    differ = torch.zeros((), dtype=torch.int64, device="cuda")
+    for part in gates.view(-1, line // 1024):
+        gate = part.repeat_interleave(1024)
+        fast = agq.swiglu(gate, up)
+        exact = torch.cat([agq.swiglu(gate[h::2].contiguous(), up[h::2].contiguous()) for h in (0, 1)])
+        differ += (torch.cat([fast[0::2], fast[1::2]]).view(torch.int16) != exact.view(torch.int16)).sum()
+    assert int(differ) == 0
 
 
 @pytest.mark.parametrize("rows,d", [(5, 8), (3, 128), (7, 5120), (2, 8200), (2, 16384)])
@@ -451,6 +505,21 @@ def test_block_with_codes_from_the_attention(agq, oracle, blk_oracle, gemm_route
     place of a head in a K step, both widths of the codes."""
     assert gemm_route(S, d, [d]) != "stream"
     test_block_stage_by_stage(agq, oracle, blk_oracle, S, d, H, F, S, qmax, bits_o)
+
+
+@pytest.mark.parametrize("S,d,H,F,e_q,e_k", [(260, 256, 4, 640, 1, 2), (385, 512, 4, 512, 2, 2)])
+def test_block_with_codes_from_the_attention_at_large_exponents(agq, oracle, blk_oracle, gemm_route, S, d, H, F, e_q, e_k):
+    """The same with 2^(e_q+e_k) log2(e) / sqrt(D) > 1, where the attention scales differences of scores."""
+    assert gemm_route(S, d, [d]) != "stream" and 2.0 ** (e_q + e_k) * np.log2(np.e) / np.sqrt(d // H) > 1
+    x, pos, cos, sin, w = make_inputs(S, d, H, F, seed=200 + S)
+    for n in ("s_q", "s_k"):
+        w[n] = (w[n].astype(np.float32) * 8).astype(np.float16)
+    ref = blk_oracle.block_forward(x, pos, cos, sin, w, H, 15, EPS, S, bits_attn_out=8)
+    exps = dict(ref["exps"], e_q=e_q, e_k=e_k)
+    blk = agq.make_block(d, H, F, upload_weights(agq, w), bits_attn_out=8, rms_eps=EPS, exps=exps)
+    x_out, pos_out, ws, L = agq.block_forward(blk, dev(x), dev(pos), dev(cos), dev(sin))
+    g = gpu_tensors(agq, blk, L, ws, S, S)
+    check_stages(agq, oracle, blk_oracle, w, H, 15, 8, x, pos, cos, sin, S, exps, g, host(x_out), host(pos_out))
 
 
 def test_block_with_codes_for_large_tiles_and_a_split(agq, oracle, blk_oracle, gemm_route):

@@ -1222,6 +1222,9 @@ def run_qk_attention(agq, oracle, H, S, D, qmax, causal, seed, e_q=-5, e_k=-5, e
     for h in range(H):
         r = np.flatnonzero(rows_sure[h])
         assert np.array_equal(host(o)[r, h * D:(h + 1) * D].view(np.uint16), oracle_o[r, h * D:(h + 1) * D].view(np.uint16))
+    # without the code map the call is another instantiation of the kernel, the one that programs run
+    plain_o, _, plain_s = agq.qk_log2_softmax(dev(qq), dev(kq), dev(vq), e_q, e_k, e_v, qmax=qmax, causal=causal)
+    assert np.array_equal(host(plain_o).view(np.uint16), want_o.view(np.uint16)) and np.array_equal(host(plain_s), host(score))
     return float(sure.mean())
 
 
@@ -1269,6 +1272,8 @@ def test_qk_attention_whole_code_range(agq, oracle, D, e_q, causal, qmax):
     _, want_o = oracle.attn_v_from_codes(got_c, vq, e_v, qmax, causal)
     assert np.array_equal(host(o).view(np.uint16), want_o.view(np.uint16))
     assert np.array_equal(host(score).astype(np.int64), oracle.start_token_score_codes(got_c, qmax))
+    plain_o, _, plain_s = agq.qk_log2_softmax(dev(qq), dev(kq), dev(vq), e_q, e_k, e_v, qmax=qmax, causal=causal)
+    assert np.array_equal(host(plain_o).view(np.uint16), want_o.view(np.uint16)) and np.array_equal(host(plain_s), host(score))
 
 
 @pytest.mark.parametrize("D", [64, 128])
