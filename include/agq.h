@@ -388,8 +388,8 @@ int agq_prune_tokens(const int32_t *score, int64_t S, int64_t n_keep,
  *   x_out     = x1 + W4A8(a)                            (step 2^e_mlp_act)
  * RMSNorm: y = x g / sqrt(mean(x^2) + rms_eps).  rope: inside a head of width D the
  * pair (i, i + D/2) is rotated by the angle whose cosine and sine are
- * rope_cos[pos, i], rope_sin[pos, i].  Every fp16 operator computes in float64 and
- * rounds once to fp16.  All activation grids are signed (zp = 0).
+ * rope_cos[pos, i], rope_sin[pos, i].  Every fp16 operator returns what float64
+ * arithmetic gives, rounded once to fp16.  All activation grids are signed (zp = 0).
  *
  * d = H*D with D = 64 or 128; d % 128 == 0, F % 128 == 0; 1 <= n_keep <= S
  * (n_keep == S: nothing is pruned); S <= 8192 when tokens are pruned, else
@@ -432,7 +432,8 @@ int agq_block_layout_of(const agq_block *blk, int64_t S, int64_t n_keep, agq_blo
 
 /* The fp16 operators of the block as calls of their own (Section 4.2 keeps them in
  * fp16; other block shapes can be wired from these and the products above).  Each
- * computes in float64 and rounds once to fp16.  fp16 tensors are contiguous
+ * returns what float64 arithmetic gives, rounded once to fp16 (values for which fewer
+ * bits tell that are computed in fewer).  fp16 tensors are contiguous
  * (leading dimension = row width) and 16-byte aligned.
  *
  * agq_rmsnorm: y[r,:] = t[r,:] * g / sqrt(mean(t[r,:]^2) + eps).  res_f16 == NULL:

@@ -33,7 +33,8 @@
 // by a subtraction; a conversion to bytes rounds and packs the weights' exponents; V is widened by one
 // packed multiply-add.  Against a kernel with nothing dealt out and three workgroups on a CU (the same results bit for
 // bit): 40 x 2048 x 128 causal 67.2 -> 59.6 us, 40 x 2048 x 64 55 -> 40 (half of the output blocks were empty there),
-// 32 x 384 x 128 14.7 -> 12.6, one head of 128 tokens 7.03 -> 6.85 (without causality 6.18 -> 6.30).  What is left of a large causal call is the chain of its longest row blocks (32 tiles
+// 32 x 384 x 128 14.7 -> 12.6, one head of 128 tokens 7.03 -> 6.85 (without causality 6.18 -> 6.30, the one call that is slower);
+// with the code map 107 -> 100, 99 -> 92, 19.3 -> 15.6 and 8.50 -> 7.77.  What is left of a large causal call is the chain of its longest row blocks (32 tiles
 // take 45 us alone on a CU, 305 instructions a tile in pass 2).  Not kept: a reference score in place of the running maximum, with differences to it straight from
 // the accumulators (58 us, and three times fewer codes off, but other codes than before); one block on eight
 // wavefronts, the key tiles shared by two groups of four (72 us then: both wavefronts of a SIMD want the same unit at
@@ -79,7 +80,8 @@ struct Int {
 };
 
 // Between two tiles: at most VM of this wavefront's loads may still fly (they return in order), its LDS reads and writes
-// are done; then meet the others.
+// are done; then meet the others.  (Stores of the code map count as well and come behind the copies: with them a tile waits for
+// the copy it has just requested, too.)
 template <int VM>
 __device__ __forceinline__ void meet() {
     asm volatile("" ::: "memory");

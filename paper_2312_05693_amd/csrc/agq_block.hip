@@ -6,8 +6,8 @@
 // rounding to fp16 at the end, so that a result does not depend on the order of a
 // reduction or on the exponential's implementation beyond the last bit of a double.
 // SwiGLU's float64 exponential, quotient and rounding take longer than its bytes (1024 x 13824: 28 us for 85 MB).  Most values
-// do not need them: an fp32 evaluation with a proven error bound tells the fp16 result wherever both ends of its interval
-// round to the same one, and only the others, one in several hundred, take the float64 path; the results are float64's in
+// do not need them: an fp32 evaluation whose error is known for every fp16 gate tells the fp16 result wherever both ends of its
+// interval round to the same one, and only the others, one in several hundred, take the float64 path; the results are float64's in
 // every case (17.7 us; 300 x 11008 8.8 -> 6.6).  The others stream their operands once: they are bound by HBM, or by
 // latency where rows are few.  (The same for RMSNorm's and the rotary embedding's results, a product and a rounding
 // there: 5-20 % slower than float64.)
@@ -91,8 +91,10 @@ __device__ __forceinline__ uint4 Ends8::values() const {      // the low halves
 }
 
 // silu(z) u in eight values, rounded once.  In fp32: e = 2^(-z log2 e) with the exponent in two parts, 1 + e and its
-// reciprocal: off by 2^-22.8 at most, over all fp16 z (all of them compared with float64); the product z u is exact.  With the
-// rounding of an end itself (2^-24) that is 2^-22.3: the interval is 2^-22 to either side.
+// reciprocal: off by 2^-22.8 at most, measured over all fp16 z against float64 (the instructions' nominal errors alone would
+// allow a little more than the interval has, so it is this measurement that holds it, and a test of every gate with
+// every mantissa of a factor); the product z u is exact.  With the rounding of an end itself (2^-24) that is 2^-22.3: the
+// interval is 2^-22 to either side.
 __device__ __forceinline__ uint16_t swiglu1(uint16_t g, uint16_t u) {
     const double z = h2d(g);
     return d2h(z / (1.0 + exp(-z)) * h2d(u));

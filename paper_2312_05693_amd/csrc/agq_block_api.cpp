@@ -11,13 +11,16 @@ namespace {
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 constexpr int64_t kMaxTokens = 8192;        // agq_prune_tokens' limit (calls that prune)
-// Up to this many rows the operator in front of a projection (RMSNorm, SwiGLU, the gather of the surviving rows) writes the
-// tiled GEMM's codes itself and the pre-pass, a launch of 3 to 5 us at these sizes, is left out.  Two blocks of 512 tokens
-// 357 -> 347 us, four of 300 tokens 564 -> 540, four narrow ones of 212 tokens 277 -> 257, one of 1024 tokens 284 -> 280.  What
-// the operators' scattered 8-byte stores cost grows with rows times width, so the line is where the widest layers break even
-// (unpruned blocks, 1024 / 1280 / 1408 / 1536 tokens; F = 13824: 449 -> 443, 529 -> 520, 573 -> 570, 613 -> 610; F = 11008:
-// 313 -> 305, 390 -> 384, 425 -> 423, 448 -> 448; F = 2816: 106 -> 102 .. 140 -> 135); at 2048 tokens of F = 13824 they lose
-// (750 -> 758).  Narrow layers gain up to the line, and would beyond it.
+// Up to this many rows the operator in front of a projection (RMSNorm, SwiGLU, the row copies of the surviving tokens, the
+// attention where every token survives) writes the tiled GEMM's codes itself and the pre-pass, a launch of 3 to 5 us at
+// these sizes, is left out.  Two blocks of 512 tokens 357 -> 347 us, four of 300 tokens 564 -> 540, four narrow ones of 212
+// tokens 277 -> 257, one of 1024 tokens 284 -> 280.  What the operators' scattered 8-byte stores cost grows with rows times
+// width, so the line is where the widest layers break even (unpruned blocks, 1024 / 1280 / 1408 / 1536 tokens; F = 13824:
+// 449 -> 443, 529 -> 520, 573 -> 570, 613 -> 610; F = 11008: 313 -> 305, 390 -> 384, 425 -> 423, 448 -> 448; F = 2816: 106 ->
+// 102 .. 140 -> 135); at 2048 tokens of F = 13824 they lose (750 -> 758).  Narrow layers gain up to the line, and would beyond
+// it.  The attention's stores of four bytes (two where heads are 64 wide) gain at the line too (unpruned blocks without and
+// with them; 40 heads of 128, F = 13824, 1280 / 1536 tokens 487.0 -> 484.4, 560.8 -> 558.9; 32 heads of 64, F = 8192, 173.6 ->
+// 171.0, 198.8 -> 195.0; 12 heads of 64, F = 3072, 512 / 1536 tokens 64.7 -> 62.9, 107.7 -> 104.1).
 constexpr int64_t kFuseRows = 1536;
 constexpr int64_t kMaxAttnTokens = 32768;   // the attention call's limit (calls that keep every token)
 constexpr int64_t kMaxWidth = 65536;   // the GEMMs' limit on K
