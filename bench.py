@@ -46,8 +46,8 @@ PREFILL_M = 2048
 #   name: (bytes per launch, profiles/ file, source file, first 12 hex digits of the source's sha256)
 MEASURED_TRAFFIC = {
     "decode": (26.3e6, "profiles/gemm_decode_llama7b_sweep.md", "agq_gemm_decode.hip", "b749db6894b5"),
-    "attn": (252.6e6, "profiles/log2_attn_llama13b_block.md", "agq_attn.hip", "93d0e33be0e8"),
-    "tiled": (187.5e6, "profiles/gemm_decode_llama7b_sweep.md", "agq_gemm_tiled.hip", "2708e00109c9"),
+    "attn": (252.6e6, "profiles/log2_attn_llama13b_block.md", "agq_attn.hip", "e21c65f1ff1e"),
+    "tiled": (187.8e6, "profiles/gemm_decode_llama7b_sweep.md", "agq_gemm_tiled.hip", "4103ab608e9b"),
 }
 
 
