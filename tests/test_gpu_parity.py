@@ -1315,7 +1315,7 @@ def test_qk_attention_large_exponents(agq, oracle, D, e_q, e_k, causal, qmax):
 @pytest.mark.parametrize("want_codes", [False, True])
 def test_qk_attention_short_causal_call_costs_no_more_than_its_tiles(agq, D, want_codes):
     """One head of 128 tokens: the causal call has fewer tiles than the other, and what its diagonal adds may not make up for it
-    (6 to 12 % of the time in replayed graphs; it was 26 to 30 when the diagonal converted every score and waited for
+    (5 to 13 % of the time in replayed graphs; it was 26 to 30 when the diagonal converted every score and waited for
     copies that nobody reads)."""
     S = 128
     q, k, v = [dev(t) for t in synth.make_qkv_int8(1, S, D, seed=6)]
