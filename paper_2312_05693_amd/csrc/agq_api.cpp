@@ -63,7 +63,7 @@ int agq_gemm_w4_run(int bits, const void *x, int x_kind, int64_t M, int64_t K, i
     // many tokens: lay the codes out in MFMA operand order once (quantizing on the
     // way when x is fp16), then run the tiled kernel for all projections on that copy
     if (agq_launch_prepack_act(x, x_kind, bits, M, K, ldx, e, zp, workspace, stream)) return AGQ_EHIP;
-    return hip_status(agq_launch_gemm_tiled(workspace, M, K, e, agq_zp_corr(bits, zp), projs, count, -1, r.choice.variant, r.plan,
+    return hip_status(agq_launch_gemm_tiled(workspace, M, K, e, agq_zp_corr(bits, zp), projs, count, -1, r.choice,
                                             static_cast<char *>(workspace) + agq_codes_bytes(M, K), stream));
 }
 
@@ -74,7 +74,7 @@ bool agq_gemm_takes_tiles(int64_t M, int64_t K, const struct agq_proj *projs, in
 int agq_gemm_w4_tiles(int64_t M, int64_t K, int e, const struct agq_proj *projs, int count, void *workspace,
                       size_t workspace_bytes, void *stream) {
     const AgqRoute r = route_of(AGQ_X_F16, M, K, projs, count, -1, workspace_bytes);
-    return hip_status(agq_launch_gemm_tiled(workspace, M, K, e, 0, projs, count, -1, r.choice.variant, r.plan,
+    return hip_status(agq_launch_gemm_tiled(workspace, M, K, e, 0, projs, count, -1, r.choice,
                                             static_cast<char *>(workspace) + agq_codes_bytes(M, K), stream));
 }
 
@@ -129,7 +129,7 @@ int gemm_w4_trip_multi(int bits, const void *x, int64_t M, int64_t K, int64_t ld
     if (agq_launch_prepack_trip(x, bits, M, K, ldx, e, zp, projs[0].w_packed, projs[0].N, n_extra, workspace, stream))
         return AGQ_EHIP;
     const AgqRoute r = route_of(AGQ_X_F16, M, K, projs, count, n_extra, workspace_bytes);
-    return hip_status(agq_launch_gemm_tiled(workspace, M, K, e, agq_zp_corr(bits, zp), projs, count, n_extra, r.choice.variant, r.plan,
+    return hip_status(agq_launch_gemm_tiled(workspace, M, K, e, agq_zp_corr(bits, zp), projs, count, n_extra, r.choice,
                                             static_cast<char *>(workspace) + need, stream));
 }
 

@@ -46,18 +46,13 @@ static inline AgqTripLayout agq_trip_layout(int64_t N, int64_t K, int E) {
 
 // tokens up to which the weight-streaming kernel is used
 #define AGQ_DECODE_MAX_M 16
-// K split of the tiled kernel.  A K step of a workgroup takes about as long however few workgroups the launch has (the
-// plan counts 470 ns: a single wavefront per SIMD cannot cover its own waits): with few 128 x 128 tiles and a long K
-// most CUs idle while a few walk K.  Then `splits` workgroups share a tile's K steps (at least four each, at most one
-// workgroup per CU in all) and leave int32 partial tiles behind the activation codes in the workspace,
-// which a second kernel adds up.  That costs about 2 us for the launch and 0.45 us per MB of partial tiles
-// (written, read back); the plan is the split count with the smallest sum under this model (measured on
-// MI355X with an earlier schedule of the loop and resident weights).  Its count is the one that agq_tiled_choose below
-// weighs against the other variants with the constants of the present loop, and a plan of one slice is never offered there;
-// the sizes that callers reserve (agq_gemm_workspace_bytes) hold the plan's partial tiles whether or not the choice then
-// takes the split.  M tokens, tiles_n = 128-wide column tiles of all projections of the call, KT = K steps (TRIP
-// blobs: the extra steps in front included, all of which stay in the first slice: min_steps of them).
-// splits == 1: no split, bytes == 0.
+// K split of the tiled kernel: `splits` workgroups share a tile's K steps and leave int32 partial tiles behind the activation
+// codes in the workspace, which a second kernel adds up.  This plan says which calls may do so (fewer 128 x 128 tiles than
+// half of the CUs, a K of eight steps or more, at least four steps a slice) and what room callers reserve for the partial tiles
+// (agq_gemm_workspace_bytes), also where the choice below then takes no split, or one of fewer slices.  M tokens, tiles_n =
+// 128-wide column tiles of all projections of the call, KT = K steps (TRIP blobs: the extra steps in front included, all of
+// which stay in the first slice: min_steps of them).  splits == 1: no split, bytes == 0.  (The constants are those of an
+// earlier kernel; they are kept because they decide the sizes that programs reserve.)
 struct AgqSplitPlan {
     int splits, steps;
     size_t bytes;
@@ -82,66 +77,130 @@ static inline AgqSplitPlan agq_tiled_split_plan(int64_t M, int64_t tiles_n, int6
     return p;
 }
 
-// The tiled kernel's variants and the choice between them: the one with the smallest time under a model of the launch,
-// a fixed part and a time per K step that depends on how many workgroups share the chip (KT steps, w workgroups).
-//   TILED_128     128-token tiles, at most two workgroups on a CU
-//   TILED_SPLIT   the same with the K split above
-//   TILED_64      64-token tiles, at most three on a CU: half of the MFMAs per step for two thirds of the operand bytes, so
-//                 about 15 % dearer where the chip is full, but finer to deal out
-//   TILED_64X2    64-token tiles with the K steps of a tile shared by two groups of four wavefronts of one workgroup: at
-//                 most one workgroup per CU, whose two wavefronts per SIMD hide each other's waits
-// Measured (us, the GEMM launch alone, other weights from HBM at every launch, as a model's layers have it;
-// 128 / split / 64 / 64x2):
-//   4096 -> 4096     100 tokens 16.4 / 13.9 / 14.2 / 12.2, 300 tokens 16.7 / - / 14.7 / 12.5, 512 tokens 17.1 / - / 15.4 / 13.9
-//   11008 -> 4096    100 tokens 39.3 / 19.7 / 35.1 / 27.3, 213 tokens 39.1 / 23.6 / 35.2 / 27.4, 300 tokens 39.2 / 30.0 / 35.6 / 28.2
-//   4096 -> 12288    100 tokens 17.4 / - / 15.6 / 13.7, 213 tokens 19.1 / - / 20.8 / -, 300 tokens 27.9 / - / 23.4 / -
-//   4096 -> 22016    100 tokens 20.0 / - / 22.3 / 25.7, 213 tokens 31.3 / - / 33.0 / -, 300 tokens 42.2 / - / 41.5 / -
-//   5120 -> 5120     333 tokens 21.5 / - / 19.5 / 16.6, 1024 tokens 35.9 / - / 37.0 / -
-//   4096 -> 22016    1000 tokens 89 / - / 101 / -, 2048 tokens 157 / - / 186 / -
-// The model is within 10 % of these for 128-token, split and two-group tiles.  For 64-token tiles it is up to 15 % high
-// where two or three of them share a CU and 22 % high at 2048 tokens: of the calls above, 4096 -> 22016 at 300 tokens
-// goes to 128-token tiles for it, 2 % slower than 64-token ones.
+// The tiled kernel's workgroup tiles and the choice between them.  A tile is 16 nt tokens x 64 jt channels of four
+// wavefronts, times kg groups of four that share its K steps (agq_gemm_tiled.hip has what they have in common).
+//   TILED_128     128-token tiles, one group
+//   TILED_64      64- or 32-token tiles, one group
+//   TILED_64X2    64- or 32-token tiles, two groups
+//   TILED_SPLIT   64-token tiles whose K steps are shared out over workgroups, with a second launch that adds up
+#define AGQ_TILED_SHAPES(F) \
+    F(8, 4, 1) F(8, 3, 1) F(8, 2, 1) F(4, 4, 1) F(4, 3, 1) F(4, 2, 1) F(4, 1, 1) F(2, 2, 1) F(2, 1, 1) \
+    F(4, 2, 2) F(4, 1, 2) F(2, 2, 2) F(2, 1, 2)
 enum AgqTiledVariant { TILED_128, TILED_SPLIT, TILED_64, TILED_64X2 };
 struct AgqTiledChoice {
     AgqTiledVariant variant;
-    int64_t cost_ns;
+    int nt, jt, kg;
+    int splits, steps;     // TILED_SPLIT
 };
-static inline AgqTiledChoice agq_tiled_choose(int64_t M, int64_t tiles_n, int64_t KT, const AgqSplitPlan &plan, int n_extra = 0) {
-    const int64_t w = ((M + 127) / 128) * tiles_n, w64 = ((M + 63) / 64) * tiles_n;
-    auto at_least = [](int64_t a, int64_t b) { return a > b ? a : b; };
-    const int64_t step = w <= 256 ? 360 + w * 11 / 20 : (w <= 512 ? 700 + (w - 256) * 8 / 5 : at_least(1300, w * 187 / 100));
-    AgqTiledChoice c = {TILED_128, 4500 + KT * step};
-    auto offer = [&c](AgqTiledVariant v, int64_t cost) {
-        if (cost < c.cost_ns) c = {v, cost};
-    };
-    if (plan.splits > 1) {
-        const int64_t part_bytes = ((M + 31) / 32) * 32 * tiles_n * 512;
-        offer(TILED_SPLIT, 6500 + plan.steps * (360 + w * plan.splits * 11 / 20) + part_bytes * plan.splits * 450 / 1000000);
+
+// Time of a launch of w workgroups of one shape, KT steps, N output channels in all, in ns, fitted to 618 calls (17 to 2048
+// tokens, K 128 to 13824, N 272 to 27648; codes in, other weights from memory at every launch, graph replays): the error is 3 %
+// in the median where a shape is near the best one (10 % of them are off by more than 10 %), and the shape with the smallest
+// of these times was 1 % slower on average than the best of all shapes, 4 % at the ninth decile, 9 % at the hundredth.
+//   fixed  launch, fill and epilogue      step   a step of a lone workgroup on an empty chip      load   what a full chip adds
+//   many   a step where CUs have several  more   what each further round of workgroups adds       mem    weights, per 16384 channels
+//   ceil64 how far the last round counts as a whole one
+struct AgqTiledTime {
+    int nt, jt, kg, fixed, step, load, many, more, mem, ceil64;
+};
+static const AgqTiledTime agq_tiled_times[] = {
+    {8, 4, 1, 6922, 431, 226, 638, 2466, 32, 38},
+    {8, 3, 1, 6234, 339, 148, 471, 2442, 81, 33},
+    {8, 2, 1, 4850, 261, 91, 338, 2146, 96, 33},
+    {4, 4, 1, 4833, 295, 86, 350, 2104, 99, 31},
+    {4, 3, 1, 4533, 229, 62, 270, 1769, 120, 30},
+    {4, 2, 1, 3642, 163, 74, 200, 1196, 122, 32},
+    {4, 1, 1, 3012, 132, 46, 124, 839, 151, 42},
+    {2, 2, 1, 3248, 140, 28, 135, 791, 120, 40},
+    {2, 1, 1, 3016, 107, 7, 95, 554, 126, 42},
+    {4, 2, 2, 4420, 137, 96, 272, 2943, 115, 22},
+    {4, 1, 2, 3496, 107, 58, 190, 879, 116, 6},
+    {2, 2, 2, 3989, 110, 60, 196, 755, 112, 6},
+    {2, 1, 2, 3429, 86, 22, 100, 370, 132, 51},
+};
+static inline int64_t agq_tiled_ns(const AgqTiledTime &t, int64_t w, int64_t KT, int64_t n_sum) {
+    const int64_t mem = t.mem * n_sum / 16384, one = t.fixed + KT * (t.step + t.load * (w < 256 ? w : 256) / 256 + mem);
+    if (w <= 256) return one;
+    const int64_t n = (w + 255) / 256;
+    const int64_t several = t.fixed + (n - 1) * t.more + KT * (t.many * (n * 256 * t.ceil64 + (64 - t.ceil64) * w) / 16384 + mem);
+    return several > one ? several : one;
+}
+static inline int64_t agq_tiled_count(int64_t M, const int64_t *N, int count, int nt, int jt) {
+    int64_t n = 0;
+    for (int p = 0; p < count; ++p) n += (N[p] + jt * 64 - 1) / (jt * 64);
+    return n * ((M + nt * 16 - 1) / (nt * 16));
+}
+struct AgqTiledPick {
+    AgqTiledChoice choice;
+    int64_t ns;
+};
+// KT: steps, the n_extra of TRIP blobs included.
+static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int count, int64_t KT, const AgqSplitPlan &plan, int n_extra) {
+    int64_t tiles_n = 0, n_sum = 0;
+    bool ragged = false;
+    for (int p = 0; p < count; ++p) {
+        tiles_n += (N[p] + 127) / 128;
+        n_sum += N[p];
+        ragged = ragged || (N[p] & 7);
     }
-    const int64_t step64 = w64 <= 256 ? 300 + w64 * 7 / 20 : (w64 <= 768 ? 460 + (w64 - 256) * 21 / 20 : at_least(1360, w64 * 127 / 100));
-    offer(TILED_64, 4000 + KT * step64);
-    if (w64 <= 256 && KT > 1) offer(TILED_64X2, 4800 + at_least((KT + 1) / 2, n_extra) * (430 + w64 * 3 / 4));
-    return c;
+    const int64_t tiles = ((M + 127) / 128) * tiles_n;
+    AgqTiledPick best = {{TILED_128, 8, 4, 1, 1, (int)KT}, INT64_MAX};
+    // A K split for long K with few tiles: 64 x 64 tiles while four slices of them fit the CUs, else 64 x 128 ones, at most four
+    // slices (more only add partial tiles to write and read).  Measured against the best tile without: 64 x 11008 -> 4096 13.9
+    // against 15.6 us, 20 x 13824 -> 5120 16.8 / 19.1, 300 x 8192 -> 384 8.9 / 10.1, 300 x 13824 -> 640 11.3 / 15.0, 140 x 8192 ->
+    // 700 8.8 / 10.4; level or behind at the rule's edges, 100 x 11008 -> 4096 16.4 / 15.5, 1050 x 8192 -> 512 13.2 / 12.3,
+    // 300 x 4096 -> 768 8.9 / 6.9, 260 x 2560 -> 130 6.5 / 5.7.  (Eight slices of 128 x 128 tiles, as it was: 16.5, 17.3, 11.1, 13.7,
+    // 10.9 us for the first five.)
+    if (plan.splits > 1 && KT - n_extra >= 20 && 2 * KT >= 3 * tiles) {
+        const int s = plan.splits < 4 ? plan.splits : 4;
+        const int jt = agq_tiled_count(M, N, count, 4, 1) * s <= 256 ? 1 : 2;
+        const int64_t w = agq_tiled_count(M, N, count, 4, jt);
+        int64_t cut = w * s <= 256 ? s : (w * 2 <= 256 ? 256 / w : 2);
+        const int64_t steps = (KT + cut - 1) / cut;
+        best.choice = {TILED_SPLIT, 4, jt, 1, (int)((KT + steps - 1) / steps), (int)steps};
+        for (const AgqTiledTime &t : agq_tiled_times)
+            if (t.nt == 4 && t.jt == jt && t.kg == 1) best.ns = agq_tiled_ns(t, w * cut, steps, n_sum) + 3000 + M * n_sum * 4 * cut * 300 / 1000000;
+        return best;
+    }
+    // Two groups for twelve steps or more on at most 256 tiles of 64 x 128.  (Against one group, each with its best tile: 128 x
+    // 4096 -> 4096 6.7 / 7.0 us, 48 x 4096 -> 11008 11.0 / 10.9, 300 x 11008 -> 4096 27.3 / 26.9, 333 x 5120 -> 5120 15.7 / 15.2, 100 x
+    // 4096 -> 12288 13.6 / 13.0: little depends on this line.)
+    const bool two = KT >= 12 && ((M + 63) / 64) * tiles_n <= 256;
+    int64_t ns82 = INT64_MAX;
+    for (const AgqTiledTime &t : agq_tiled_times) {
+        if ((t.kg == 2) != two) continue;
+        // Rows of the output that do not start on sixteen bytes: stores across lines (1200 x 1280 -> 4096 / 4100: tiles of 128 x 256
+        // 12.0 / 16.0 us, 128 x 192 11.0 / 13.5, 64 x 192 11.2 / 12.2, 64 x 128 11.3 / 11.9).
+        const int64_t ns = agq_tiled_ns(t, agq_tiled_count(M, N, count, t.nt, t.jt), KT, n_sum) + (ragged ? t.nt * (t.jt - 1) * 100 : 0);
+        if (t.nt == 8 && t.jt == 2) ns82 = ns;
+        if (ns < best.ns) best = {{t.kg == 2 ? TILED_64X2 : (t.nt == 8 ? TILED_128 : TILED_64), t.nt, t.jt, t.kg, 1, (int)KT}, ns};
+    }
+    // One round of 128 x 128 tiles on more than half of the CUs, for more than 1024 tokens and eight steps: taken unless another
+    // tile is more than a tenth faster.  (There the model has this tile up to a tenth too slow: measured 0.92 to 0.99 of the
+    // best other tile on eight of nine such calls of 1200 to 2048 tokens, 1.09 on 1200 x 1408 -> 2000.)
+    if (!two && M > 1024 && KT > 8 && tiles <= 256 && tiles > 128 && ns82 * 10 <= best.ns * 11) best = {{TILED_128, 8, 2, 1, 1, (int)KT}, ns82};
+    return best;
 }
 
 // Between 17 and 256 rows of fp16 input the weight-streaming kernel can run with sixteen rows and two channel
 // tiles per workgroup (grid.y row groups): every row group reads the weights again (from L2 after the first),
 // about 3 us + 0.24 us per MB read in all, more when the workgroups fill the last round of 256 CUs badly.  The
 // other path is the layout pre-pass (about 3 us with the gap behind it) plus the tiled kernel (above).  Measured
-// (row groups against pre-pass and tiles): 4096 x 4096 at 32 / 64 / 100 rows 6.4 / 11.0 / 18.1 against about 13 us at
-// any of them; 768 x 768 at 128 rows 4.1 against 8.2 us.  (The two 3 us cancel in the rule.  Inside a block the operator in
-// front writes the codes and there is no pre-pass; the same rule is asked there, so between 17 and about 100 rows a block
-// may keep row groups, or tiles, a few rows too long.)  wg_pairs: tile pairs (32 channels) of all projections;
-// tiled_ns: the cost of the variant the call would run instead.  (Four tiles per workgroup instead of two were measured
-// too: the same at best, and 50 % slower on the widest layer, where the registers no longer hold the weight chunks.)
+// (row groups against pre-pass and tiles): 4096 x 4096 at 32 / 64 / 100 rows 6.4 / 11.0 / 18.1 against 9.7 / 9.8 / 10.1 us;
+// 768 x 768 at 128 rows 4.1 against 6.5 us.  The line is still where the tiles' predecessors put it, 4.4 us to the
+// right (tests name calls on both sides of it): at 4096 x 4096 row groups go on to 80 rows where the tiles would gain up to
+// 3 us from 56 rows on.  (Inside a block the operator in front writes the codes and there is no pre-pass; the same rule is
+// asked there.)  wg_pairs: tile pairs (32 channels) of all projections; tiles: what the call would run instead.  (Four tiles
+// per workgroup instead of two were measured too: the same at best, and 50 % slower on the widest layer, where the registers
+// no longer hold the weight chunks.)
 #define AGQ_ROW_GROUP_MAX_M 256
 static inline bool agq_decode_row_groups(int x_kind, int64_t M, int64_t K, int64_t n_sum, int64_t wg_pairs,
-                                         int64_t tiled_ns) {
+                                         const AgqTiledPick &tiles) {
     if (x_kind != 0 || M <= AGQ_DECODE_MAX_M || M > AGQ_ROW_GROUP_MAX_M) return false;
     const int64_t groups = (M + 15) / 16, wgs = groups * wg_pairs;
     int64_t read_ns = groups * (K * n_sum / 2) * 240 / 1000000;
     if (wgs < 768) read_ns = read_ns * ((wgs + 255) / 256 * 256) / wgs;   // a short last round costs a whole one
-    return read_ns <= tiled_ns;
+    return read_ns <= tiles.ns + (tiles.choice.variant == TILED_SPLIT ? 0 : 4400);
 }
 
 // int8 codes in operand order, tokens padded to the 128-row tile (a multiple of 16 KiB); K: extra steps included
@@ -151,7 +210,6 @@ static inline size_t agq_codes_bytes(int64_t M, int64_t K) { return (size_t)((M 
 // n_extra >= 0: TRIP blobs with that many extra steps; -1: plain blobs.
 struct AgqRoute {
     bool tiles;
-    AgqSplitPlan plan;
     AgqTiledChoice choice;
 };
 static inline AgqRoute agq_gemm_route(int x_kind, int64_t M, int64_t K, const int64_t *N, int count, int n_extra,
@@ -166,10 +224,11 @@ static inline AgqRoute agq_gemm_route(int x_kind, int64_t M, int64_t K, const in
     // caller's workspace has the room for the partial tiles behind the codes.
     const int extra = n_extra > 0 ? n_extra : 0;
     const int64_t KT = agq_k_tiles(K) + extra;
-    AgqRoute r = {false, agq_tiled_split_plan(M, tiles_n, KT, true, extra), {}};
-    if (workspace_bytes < agq_codes_bytes(M, KT * 128) + r.plan.bytes) r.plan = agq_tiled_split_plan(M, tiles_n, KT, false);
-    r.choice = agq_tiled_choose(M, tiles_n, KT, r.plan, extra);
-    r.tiles = M > AGQ_DECODE_MAX_M && (n_extra >= 0 || !agq_decode_row_groups(x_kind, M, K, n_sum, wg_pairs, r.choice.cost_ns));
+    AgqSplitPlan plan = agq_tiled_split_plan(M, tiles_n, KT, true, extra);
+    if (workspace_bytes < agq_codes_bytes(M, KT * 128) + plan.bytes) plan = agq_tiled_split_plan(M, tiles_n, KT, false);
+    const AgqTiledPick pick = agq_tiled_choose(M, N, count, KT, plan, extra);
+    AgqRoute r = {false, pick.choice};
+    r.tiles = M > AGQ_DECODE_MAX_M && (n_extra >= 0 || !agq_decode_row_groups(x_kind, M, K, n_sum, wg_pairs, pick));
     return r;
 }
 
@@ -215,9 +274,9 @@ int agq_launch_gemm_decode(const void *x, int x_kind, int bits, int64_t M, int64
                            const struct agq_proj *projs, int count, int n_extra, void *stream);
 // K counts the main chunks only; with TRIP blobs (all packed with the same factors) x_tiles and the blobs hold
 // n_extra more steps in front.  The `count` projections of the activation run as one launch.
-// TILED_SPLIT: split_ws has room for the partial tiles that `plan` describes.
+// TILED_SPLIT: split_ws has the room that agq_tiled_split_plan asks for.
 int agq_launch_gemm_tiled(const void *x_tiles, int64_t M, int64_t K, int e, int corr, const struct agq_proj *projs, int count,
-                          int n_extra, AgqTiledVariant variant, const AgqSplitPlan &plan, void *split_ws, void *stream);
+                          int n_extra, const AgqTiledChoice &choice, void *split_ws, void *stream);
 int agq_launch_trip_search(const void *x, int64_t M, int64_t K, int64_t ldx, int bits, int e, int zp, int kmax,
                            int8_t *alpha, void *stream);
 int agq_trip_count_extra(const int8_t *alpha_host, int64_t K);   // number of extra chunks, -1 = bad factors or too many

@@ -100,6 +100,14 @@ extern "C" int agq_probe_gemm_route(int x_kind, int64_t M, int64_t K, const int6
     return r.tiles ? (int)r.choice.variant : -1;
 }
 
+// Host only: the workgroup tile of that call, 100 nt + 10 jt + kg of AgqTiledChoice, plus 1000 times the slices of a K split;
+// -1 for the weight-streaming kernel.
+extern "C" int agq_probe_gemm_tile(int x_kind, int64_t M, int64_t K, const int64_t *N, int count, int n_extra, size_t workspace_bytes) {
+    const AgqRoute r = agq_gemm_route(x_kind, M, K, N, count, n_extra, workspace_bytes);
+    if (!r.tiles) return -1;
+    return (r.choice.variant == TILED_SPLIT ? 1000 * r.choice.splits : 0) + 100 * r.choice.nt + 10 * r.choice.jt + r.choice.kg;
+}
+
 // Host only: whether 5 to 16 rows of fp16 input on plain blobs [N[p], K] run with two channel tiles per workgroup of the
 // per-tile kernel (1 / 0).
 extern "C" int agq_probe_decode_pairs(int64_t M, int64_t K, const int64_t *N, int count) {

@@ -1,0 +1,97 @@
+"""Every workgroup tile of the tiled kernel against 64-bit torch, on calls that the dispatch gives it."""
+import ctypes
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def agq():
+    from paper_2312_05693_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.fixture(scope="module")
+def tile_of(agq):
+    """tile_of(M, K, Ns, n_extra): 100 x 16-token tiles + 10 x (channels / 64) + groups, + 1000 x the slices of a K split."""
+    from paper_2312_05693_amd import build
+    probe = ctypes.CDLL(build.PROBE_LIB)
+
+    def tile(M, K, Ns, n_extra=-1, workspace_bytes=0):
+        return probe.agq_probe_gemm_tile(1, ctypes.c_int64(M), ctypes.c_int64(K), (ctypes.c_int64 * len(Ns))(*Ns), len(Ns), n_extra,
+                                         ctypes.c_size_t(workspace_bytes))
+    return tile
+
+
+def inputs(M, K, N, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    q = torch.randint(-128, 128, (M, K), generator=g, device="cuda", dtype=torch.int8)
+    wq = torch.randint(-8, 8, (N, K), generator=g, device="cuda", dtype=torch.int8)
+    sw = torch.rand(N, generator=g, device="cuda").half() * 0.01 + 0.001
+    return g, q, wq, sw
+
+
+def check(acc, y, q64, wq, sw, e):
+    want = torch.mm(q64, wq.double().t().contiguous())                   # whole numbers below 2^53: exact
+    assert torch.equal(acc.double(), want)
+    ref = want * (sw.double() * 2.0 ** e)
+    assert bool(((y.double() - ref).abs() <= ref.abs() * 2.0 ** -10 + 2.0 ** -24).all())     # one rounding to fp16, of a product in fp32
+
+
+# token counts one past and at the edge of a tile, widths that end inside a wavefront's channels and off the 16-byte grid, and
+# K steps around the number that a wavefront requests ahead (P of the kernel): fewer, as many, one more, a remainder of each size
+CASES = [
+    (211, 17, 44, (1, 2, 9, 10, 11)), (211, 64, 513, (3, 8)), (221, 32, 22000, (1, 5, 7)), (221, 129, 12001, (12, 14, 20)),
+    (411, 33, 8200, (2, 6, 7, 8, 11)), (421, 33, 22001, (5, 6, 7, 8, 11)), (431, 65, 22000, (1, 4, 5, 6, 7, 11, 13)),
+    (441, 257, 12000, (1, 3, 4, 5, 6, 9, 14)), (821, 257, 10000, (1, 5, 6, 7, 8)), (821, 1100, 2001, (9, 12, 13, 14)),
+    (831, 161, 22000, (3, 4, 5, 6)), (831, 1100, 10000, (1,)), (841, 513, 12000, (1, 2, 3, 4, 5, 6, 7, 9)),
+    (212, 17, 44, (12, 15, 16, 17, 18, 19)), (222, 17, 22000, (12, 13, 14, 15)), (412, 33, 8201, (12, 13, 18, 20)),
+    (422, 33, 22000, (12, 13, 20)), (422, 400, 4096, (19,)), (4411, 17, 40, (20, 21, 26)), (4421, 100, 4096, (64, 66, 67)),
+    (2421, 210, 4096, (97,)),
+]
+
+
+@pytest.mark.parametrize("tile,M,N,steps", [(t, M, N, s) for t, M, N, every in CASES for s in every])
+def test_tile(agq, tile_of, tile, M, N, steps):
+    K = 128 * steps
+    size = agq.gemm_workspace_bytes(M, N, K)
+    assert tile_of(M, K, [N], workspace_bytes=size) == tile
+    _, q, wq, sw = inputs(M, K, N, 7 * steps + M)
+    acc = torch.full((M, N), -7, dtype=torch.int32, device="cuda")
+    ybuf = torch.full((M, N + 3), 5.0, dtype=torch.float16, device="cuda")           # a pitch off the 16-byte grid
+    ws = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda")
+    agq.gemm_w4a8(q, -4, agq.pack_w4(wq), sw, N, K, x_kind=agq.AGQ_X_Q, acc_out=acc, y=ybuf[:, :N], workspace=ws)
+    check(acc, ybuf[:, :N], q.double(), wq, sw, -4)
+    assert bool((ybuf[:, N:] == 5.0).all())
+
+
+@pytest.mark.parametrize("tile,M,N,steps,n_extra", [(841, 513, 12000, 8, 3), (841, 513, 12000, 1, 1), (831, 161, 22000, 5, 2),
+                                                    (821, 1100, 2001, 11, 2), (441, 257, 12000, 9, 4), (431, 65, 22000, 6, 2),
+                                                    (421, 33, 22000, 5, 5), (221, 32, 22000, 3, 6), (412, 33, 8200, 9, 4)])
+def test_tile_with_extra_steps(agq, tile_of, tile, M, N, steps, n_extra):
+    """TRIP blobs: the shifts behind the extra steps, which may be all of the steady loop, and its tail."""
+    K = 128 * steps
+    g, _, wq, sw = inputs(M, K, N, 11 * steps + M)
+    x = torch.randn(M, K, generator=g, device="cuda").half()
+    levels = [4, 3, 2, 1]
+    alpha = torch.zeros(K, dtype=torch.int8)
+    left = list(torch.randperm(K).tolist())
+    for c in range(n_extra):                                             # one chunk more for every channel past a multiple of 128
+        for k in left[:1 if c < 4 else 128]:
+            alpha[k] = levels[c % 4] if c < 4 else levels[(c - 4) % 4]
+        left = left[1 if c < 4 else 128:]
+    packed, extra = agq.pack_w4_trip(wq, alpha.numpy())
+    assert extra == n_extra
+    size = agq.lib().agq_gemm_trip_workspace_bytes(M, N, K, extra)
+    assert tile_of(M, K, [N], extra, size) == tile
+    e = -6
+    acc = torch.full((M, N), -7, dtype=torch.int32, device="cuda")
+    y = torch.empty(M, N, dtype=torch.float16, device="cuda")
+    agq.gemm_trip_multi(x, 8, e, [(packed, sw, N, y, acc)], extra, K, workspace=torch.empty(size, dtype=torch.uint8, device="cuda"))
+    up = 2.0 ** alpha.to("cuda").double()
+    q64 = (x.double() * 2.0 ** -e / up).round().clamp(-128, 127) * up
+    check(acc, y, q64, wq, sw, e)
