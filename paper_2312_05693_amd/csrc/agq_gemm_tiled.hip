@@ -53,6 +53,7 @@ struct TiledArgs {
     const agq_u4 *xt;    // activation codes in operand order (pre-pass output)
     int M, K, KT;
     int tiles_m, band;      // token tiles, and how many of them the tile walk takes together
+    int turn;               // two groups: K steps by which a token tile starts further on than the one before it
     float scale_e;
     int corr;               // unsigned activation grid: acc += corr * wsum[n]; 0 on the signed grid
     // TRIP blob: the first n_extra steps are the extra chunks of the channels with a factor;
@@ -195,7 +196,7 @@ __global__ __launch_bounds__(kThreads * KG, 2) void gemm_tiled_kernel(const Tile
     // Activation: the token tiles of the workgroup are 2 NT KiB in a row of every 16 KiB stage of the pre-pass, a quarter of
     // them per wavefront.  (The pre-pass pads the tokens to 128.)
     const uint32_t voff = (uint32_t)lane * 16;
-    const char *ap = reinterpret_cast<const char *>(a.xt) + ((int64_t)(m0 >> 7) * KTfull + kbeg) * 16384 + (m0 & 127) * 128 + wave * (NC * 1024);
+    const char *const ap = reinterpret_cast<const char *>(a.xt) + ((int64_t)(m0 >> 7) * KTfull + kbeg) * 16384 + (m0 & 127) * 128 + wave * (NC * 1024);
     const __attribute__((address_space(1))) char *bp[JT];
     const int nt_last = ((pN + 255) >> 8) * 16 - 1;      // channel tiles of the blob
 #pragma unroll
@@ -216,18 +217,25 @@ __global__ __launch_bounds__(kThreads * KG, 2) void gemm_tiled_kernel(const Tile
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[i][j][r] = 0;
 
+    auto load_w = [&](agq_u4 (&d)[JT], int j) { d[j] = *(const __attribute__((address_space(1))) agq_u4 *)(bp[j] + wvoff); };
+    // Requests past the end repeat the last step.  Two groups: a token tile takes its steps from the `turn`-th of the one
+    // before it on (see the launcher); request `jump` is then the last step of K, the one behind it the first.
+    const int last = KT - 1;
+    constexpr bool TURN = KG == 2 && !TRIP;
+    const int first_step = TURN ? a.turn * tm : 0, jump = first_step > 0 ? last - first_step : -1;
+    wvoff += first_step * 1024;
+    uint32_t avoff = voff + first_step * 16384;
+    auto ahead = [&](int k) { return TURN && k == jump ? -last : (k < last ? 1 : 0); };      // from request k to the next, in steps
+    auto next_w = [&](int k) { wvoff += ahead(k) * 1024; };
+    auto next_a = [&](int k) { avoff += ahead(k) * 16384; };
     auto copy_stage = [&](uint32_t st) {
         unroll<NC>([&](auto p_tag) {
             constexpr int p = decltype(p_tag)::value;
             const uint32_t at = lds_dma_base(lds_base + st);
             asm volatile("s_nop 0");
-            lds_dma16_at<p * 1024>(at, voff, ap);
+            lds_dma16_at<p * 1024>(at, avoff, ap);
         });
     };
-    auto load_w = [&](agq_u4 (&d)[JT], int j) { d[j] = *(const __attribute__((address_space(1))) agq_u4 *)(bp[j] + wvoff); };
-    const int last = KT - 1;                             // requests past the end repeat the last step
-    auto next_w = [&](int k) { wvoff += k < last ? 1024 : 0; };
-    auto next_a = [&](int k) { ap += k < last ? 16384 : 0; };
     constexpr int V = P > Q ? P : Q;
     unroll<V>([&](auto v_tag) {                          // what steps -V .. -1 would have requested
         constexpr int v = decltype(v_tag)::value - V;
@@ -308,9 +316,9 @@ __global__ __launch_bounds__(kThreads * KG, 2) void gemm_tiled_kernel(const Tile
                 static_assert(n >= NC + 1 || n >= 2, "room for the copies");
                 if constexpr (COPY && sl == first) m0r = lds_dma_base(lds_base + rd);
                 if constexpr (COPY && n >= NC + 1) {
-                    if constexpr (sl > first && (sl - first) % by == 0 && (sl - first) / by <= NC) lds_dma16_at<((sl - first) / by - 1) * 1024>(m0r, voff, ap);
+                    if constexpr (sl > first && (sl - first) % by == 0 && (sl - first) / by <= NC) lds_dma16_at<((sl - first) / by - 1) * 1024>(m0r, avoff, ap);
                 } else if constexpr (COPY && sl == SLOTS - 1) {
-                    unroll<NC>([&](auto p_tag) { lds_dma16_at<decltype(p_tag)::value * 1024>(m0r, voff, ap); });
+                    unroll<NC>([&](auto p_tag) { lds_dma16_at<decltype(p_tag)::value * 1024>(m0r, avoff, ap); });
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -546,9 +554,12 @@ int agq_launch_gemm_tiled(const void *x_tiles, int64_t M, int64_t K, int e, int 
     a.KT = (int)agq_k_tiles(K);
     a.tiles_m = (int)((M + tile_m - 1) / tile_m);
     // The walk takes up to 1024 tokens as one band, so that the weights come from memory once (300 tokens in a band of four
-    // 64-token tiles and one of one: 4096 -> 22016 33 -> 31 us); beyond, 512 at a time, a compact rectangle for every XCD.
+    // 64-token tiles and one of one: 4096 -> 22016 33 -> 31 us); beyond, and from six 128-token tiles on, five at a time, a compact
+    // rectangle for every XCD.  (Four, or eight: strides that are powers of two meet in fewer memory channels; 2048 x 4096 ->
+    // 22016 130.7 and 128 -> 126 us, 2048 x 5120 -> 15360 113 and 114 -> 108, level at 1000 tokens.)
     const int most = 1024 / tile_m;
     a.band = a.tiles_m <= most ? a.tiles_m : most / 2;
+    if (choice.nt == 8 && a.tiles_m > 5) a.band = 5;
     a.scale_e = ldexpf(1.0f, e);
     a.corr = corr;
     int tiles = 0;
@@ -573,6 +584,20 @@ int agq_launch_gemm_tiled(const void *x_tiles, int64_t M, int64_t K, int e, int 
         a.KT = (int)L.KTall;
         a.n_extra = n_extra;
         a.trip_shift = (const int32_t *)((const char *)projs[0].w_packed + L.meta_off) + 16;
+    }
+    if (choice.kg == 2 && !trip && a.tiles_m > 1) {
+        // Workgroups that need the same weights (the token tiles of a column) would request them in the same moment, five at a
+        // time with a fifth of the weights in flight.  Started apart in K, each brings in what the others read later: as far
+        // apart as the steps go round, as long as what is in between (64 bytes per channel, step and group, an eighth of it
+        // per XCD) stays in an XCD's L2.  300 x 11008 -> 4096 27.5 -> 22.2 us, 213 tokens 20.6 -> 18.1, 100 tokens 16.2 -> 14.8, 333 x 5120 -> 5120
+        // 15.8 -> 14.3, 333 x 13824 -> 5120 33.3 -> 31; level where K is 4096.  (One group gains less, 128-token tiles lose: more than
+        // five of them, and L2 does not hold what lies between; 1024 x 13824 -> 5120 56.5 -> 58.2.)
+        int64_t n_sum = 0;
+        for (int p = 0; p < count; ++p) n_sum += projs[p].N;
+        const int64_t steps = a.KT / 2, apart = a.tiles_m - 1;
+        int64_t turn = steps / a.tiles_m;
+        if (turn > 2500000 / (16 * n_sum * apart)) turn = 2500000 / (16 * n_sum * apart);
+        a.turn = (int)turn;
     }
     unsigned grid = (unsigned)tiles;
     if (split) {

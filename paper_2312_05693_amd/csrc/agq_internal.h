@@ -93,10 +93,10 @@ struct AgqTiledChoice {
     int splits, steps;     // TILED_SPLIT
 };
 
-// Time of a launch of w workgroups of one shape, KT steps, N output channels in all, in ns, fitted to 618 calls (17 to 2048
-// tokens, K 128 to 13824, N 272 to 27648; codes in, other weights from memory at every launch, graph replays): the error is 3 %
-// in the median where a shape is near the best one (10 % of them are off by more than 10 %), and the shape with the smallest
-// of these times was 1 % slower on average than the best of all shapes, 4 % at the ninth decile, 9 % at the hundredth.
+// Time of a launch of w workgroups of one shape, KT steps, N output channels in all, in ns, fitted to 600 calls (17 to 2048
+// tokens, K 128 to 13824, N 512 to 27648; codes in, other weights from memory at every launch, graph replays): the error is 4 %
+// in the median where a shape is near the best one (10 % of them are off by more than 10 %), and the choice below was 1.2 %
+// slower on average than the best of all shapes, 4 % at the ninth decile, 17 % at most.
 //   fixed  launch, fill and epilogue      step   a step of a lone workgroup on an empty chip      load   what a full chip adds
 //   many   a step where CUs have several  more   what each further round of workgroups adds       mem    weights, per 16384 channels
 //   ceil64 how far the last round counts as a whole one
@@ -104,19 +104,19 @@ struct AgqTiledTime {
     int nt, jt, kg, fixed, step, load, many, more, mem, ceil64;
 };
 static const AgqTiledTime agq_tiled_times[] = {
-    {8, 4, 1, 6922, 431, 226, 638, 2466, 32, 38},
-    {8, 3, 1, 6234, 339, 148, 471, 2442, 81, 33},
-    {8, 2, 1, 4850, 261, 91, 338, 2146, 96, 33},
-    {4, 4, 1, 4833, 295, 86, 350, 2104, 99, 31},
-    {4, 3, 1, 4533, 229, 62, 270, 1769, 120, 30},
-    {4, 2, 1, 3642, 163, 74, 200, 1196, 122, 32},
-    {4, 1, 1, 3012, 132, 46, 124, 839, 151, 42},
-    {2, 2, 1, 3248, 140, 28, 135, 791, 120, 40},
-    {2, 1, 1, 3016, 107, 7, 95, 554, 126, 42},
-    {4, 2, 2, 4420, 137, 96, 272, 2943, 115, 22},
-    {4, 1, 2, 3496, 107, 58, 190, 879, 116, 6},
-    {2, 2, 2, 3989, 110, 60, 196, 755, 112, 6},
-    {2, 1, 2, 3429, 86, 22, 100, 370, 132, 51},
+    {8, 4, 1, 6851, 427, 232, 637, 2355, 23, 38},
+    {8, 3, 1, 6080, 346, 127, 460, 2382, 80, 39},
+    {8, 2, 1, 4768, 265, 78, 334, 2130, 95, 32},
+    {4, 4, 1, 4817, 299, 81, 352, 2083, 94, 30},
+    {4, 3, 1, 4508, 210, 68, 269, 1710, 122, 28},
+    {4, 2, 1, 3701, 158, 73, 200, 1168, 118, 30},
+    {4, 1, 1, 3034, 130, 37, 119, 830, 153, 34},
+    {2, 2, 1, 3187, 153, 18, 136, 786, 115, 40},
+    {2, 1, 1, 3010, 97, 13, 84, 618, 140, 40},
+    {4, 2, 2, 4643, 136, 55, 200, 3172, 128, 37},
+    {4, 1, 2, 3554, 100, 34, 132, 1033, 141, 37},
+    {2, 2, 2, 4165, 104, 29, 150, 555, 125, 33},
+    {2, 1, 2, 3628, 73, 10, 84, 576, 138, 64},
 };
 static inline int64_t agq_tiled_ns(const AgqTiledTime &t, int64_t w, int64_t KT, int64_t n_sum) {
     const int64_t mem = t.mem * n_sum / 16384, one = t.fixed + KT * (t.step + t.load * (w < 256 ? w : 256) / 256 + mem);
@@ -145,13 +145,13 @@ static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int cou
     }
     const int64_t tiles = ((M + 127) / 128) * tiles_n;
     AgqTiledPick best = {{TILED_128, 8, 4, 1, 1, (int)KT}, INT64_MAX};
-    // A K split for long K with few tiles: 64 x 64 tiles while four slices of them fit the CUs, else 64 x 128 ones, at most four
-    // slices (more only add partial tiles to write and read).  Measured against the best tile without: 64 x 11008 -> 4096 13.9
-    // against 15.6 us, 20 x 13824 -> 5120 16.8 / 19.1, 300 x 8192 -> 384 8.9 / 10.1, 300 x 13824 -> 640 11.3 / 15.0, 140 x 8192 ->
-    // 700 8.8 / 10.4; level or behind at the rule's edges, 100 x 11008 -> 4096 16.4 / 15.5, 1050 x 8192 -> 512 13.2 / 12.3,
-    // 300 x 4096 -> 768 8.9 / 6.9, 260 x 2560 -> 130 6.5 / 5.7.  (Eight slices of 128 x 128 tiles, as it was: 16.5, 17.3, 11.1, 13.7,
-    // 10.9 us for the first five.)
-    if (plan.splits > 1 && KT - n_extra >= 20 && 2 * KT >= 3 * tiles) {
+    // A K split for long K with few tiles: 64 x 64 tiles while four slices of them fit the CUs, else (narrow layers alone) 64 x 128
+    // ones, at most four slices (more only add partial tiles to write and read).  Measured against the best tile without: 20 x 11008
+    // -> 4096 12.8 against 15.8 us, 64 x 11008 -> 4096 13.7 / 13.9, 300 x 13824 -> 640 11.1 / 13.2; behind at the rule's edges, 300 x
+    // 8192 -> 384 8.8 / 8.3, 1050 x 8192 -> 512 13.2 / 12.3, 300 x 4096 -> 768 8.9 / 6.9, 260 x 2560 -> 130 6.5 / 5.7.  100 x 11008 ->
+    // 4096, whose slices do not fit, 16.2 / 13.7.  (Eight slices of 128 x 128 tiles: 15.1, 17.3, 13.7, 10.9 us for the first four.)
+    if (plan.splits > 1 && KT - n_extra >= 20 && 2 * KT >= 3 * tiles &&
+        (n_sum <= 1024 || agq_tiled_count(M, N, count, 4, 1) * (plan.splits < 4 ? plan.splits : 4) <= 256)) {
         const int s = plan.splits < 4 ? plan.splits : 4;
         const int jt = agq_tiled_count(M, N, count, 4, 1) * s <= 256 ? 1 : 2;
         const int64_t w = agq_tiled_count(M, N, count, 4, jt);
@@ -162,9 +162,10 @@ static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int cou
             if (t.nt == 4 && t.jt == jt && t.kg == 1) best.ns = agq_tiled_ns(t, w * cut, steps, n_sum) + 3000 + M * n_sum * 4 * cut * 300 / 1000000;
         return best;
     }
-    // Two groups for twelve steps or more on at most 256 tiles of 64 x 128.  (Against one group, each with its best tile: 128 x
-    // 4096 -> 4096 6.7 / 7.0 us, 48 x 4096 -> 11008 11.0 / 10.9, 300 x 11008 -> 4096 27.3 / 26.9, 333 x 5120 -> 5120 15.7 / 15.2, 100 x
-    // 4096 -> 12288 13.6 / 13.0: little depends on this line.)
+    // Two groups for twelve steps or more on at most 256 tiles of 64 x 128: token tiles that start apart in K bring in weights
+    // for each other (agq_gemm_tiled.hip).  Against one group, each with its best tile: 100 x 11008 -> 4096 13.7 / 15.5 us, 213 tokens
+    // 17.2 / 21.1, 300 tokens 21.5 / 26.9, 333 x 13824 -> 5120 30.0 / 33.2, 333 x 5120 -> 5120 14.8 / 15.3, 100 x 4096 -> 12288 12.7 / 13.0; behind
+    // where K is short and the CUs are full, 512 x 4096 -> 4096 11.6 / 10.3, 256 x 2560 -> 6912 9.5 / 8.1.
     const bool two = KT >= 12 && ((M + 63) / 64) * tiles_n <= 256;
     int64_t ns82 = INT64_MAX;
     for (const AgqTiledTime &t : agq_tiled_times) {
@@ -187,7 +188,7 @@ static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int cou
 // about 3 us + 0.24 us per MB read in all, more when the workgroups fill the last round of 256 CUs badly.  The
 // other path is the layout pre-pass (about 3 us with the gap behind it) plus the tiled kernel (above).  Measured
 // (row groups against pre-pass and tiles): 4096 x 4096 at 32 / 64 / 100 rows 6.4 / 11.0 / 18.1 against 9.7 / 9.8 / 10.1 us;
-// 768 x 768 at 128 rows 4.1 against 6.5 us.  The line is still where the tiles' predecessors put it, 4.4 us to the
+// 768 x 768 at 128 rows 4.1 against 6.5 us.  The line is still where the tiles' predecessors put it, 4.9 us to the
 // right (tests name calls on both sides of it): at 4096 x 4096 row groups go on to 80 rows where the tiles would gain up to
 // 3 us from 56 rows on.  (Inside a block the operator in front writes the codes and there is no pre-pass; the same rule is
 // asked there.)  wg_pairs: tile pairs (32 channels) of all projections; tiles: what the call would run instead.  (Four tiles
@@ -200,7 +201,7 @@ static inline bool agq_decode_row_groups(int x_kind, int64_t M, int64_t K, int64
     const int64_t groups = (M + 15) / 16, wgs = groups * wg_pairs;
     int64_t read_ns = groups * (K * n_sum / 2) * 240 / 1000000;
     if (wgs < 768) read_ns = read_ns * ((wgs + 255) / 256 * 256) / wgs;   // a short last round costs a whole one
-    return read_ns <= tiles.ns + (tiles.choice.variant == TILED_SPLIT ? 0 : 4400);
+    return read_ns <= tiles.ns + (tiles.choice.variant == TILED_SPLIT ? 0 : 4900);
 }
 
 // int8 codes in operand order, tokens padded to the 128-row tile (a multiple of 16 KiB); K: extra steps included

@@ -46,12 +46,14 @@ def check(acc, y, q64, wq, sw, e):
 # K steps around the number that a wavefront requests ahead (P of the kernel): fewer, as many, one more, a remainder of each size
 CASES = [
     (211, 17, 44, (1, 2, 9, 10, 11)), (211, 64, 513, (3, 8)), (221, 32, 22000, (1, 5, 7)), (221, 129, 12001, (12, 14, 20)),
-    (411, 33, 8200, (2, 6, 7, 8, 11)), (421, 33, 22001, (5, 6, 7, 8, 11)), (431, 65, 22000, (1, 4, 5, 6, 7, 11, 13)),
+    (411, 33, 8200, (2, 6, 7, 8, 11)), (421, 33, 22001, (6, 7, 8, 11)), (431, 65, 22000, (1, 4, 5, 6, 7, 11, 13)),
     (441, 257, 12000, (1, 3, 4, 5, 6, 9, 14)), (821, 257, 10000, (1, 5, 6, 7, 8)), (821, 1100, 2001, (9, 12, 13, 14)),
     (831, 161, 22000, (3, 4, 5, 6)), (831, 1100, 10000, (1,)), (841, 513, 12000, (1, 2, 3, 4, 5, 6, 7, 9)),
     (212, 17, 44, (12, 15, 16, 17, 18, 19)), (222, 17, 22000, (12, 13, 14, 15)), (412, 33, 8201, (12, 13, 18, 20)),
-    (422, 33, 22000, (12, 13, 20)), (422, 400, 4096, (19,)), (4411, 17, 40, (20, 21, 26)), (4421, 100, 4096, (64, 66, 67)),
-    (2421, 210, 4096, (97,)),
+    (422, 33, 22000, (12, 13, 20)), (422, 400, 4096, (19,)), (4411, 17, 40, (20, 21, 26)), (4421, 1100, 300, (64, 66, 67)),
+    (3421, 1050, 512, (64,)),
+    # token tiles that start apart in K: the first and the last of a group's steps, odd and even counts of them, a short second group
+    (212, 100, 4096, (85, 86)), (222, 213, 4096, (85, 86)), (422, 300, 4096, (24, 85, 86)), (422, 100, 8201, (41, 42)),
 ]
 
 
