@@ -53,6 +53,7 @@ struct TiledArgs {
     const agq_u4 *xt;    // activation codes in operand order (pre-pass output)
     int M, K, KT;
     int tiles_m, band;      // token tiles, and how many of them the tile walk takes together
+    int whole;              // tiles from here on are dealt out as halves (a multiple of 8)
     int turn;               // two groups: K steps by which a token tile starts further on than the one before it
     float scale_e;
     int corr;               // unsigned activation grid: acc += corr * wsum[n]; 0 on the signed grid
@@ -139,14 +140,16 @@ constexpr int fragment_ring(int NT, int JT) { return NT == 8 && JT == 4 ? 4 : (N
 // counts below: in front of group B every wavefront has read all of this step's stage, which the copies of the step Q ahead
 // then fill, and the codes of the step two ahead have arrived.  The last steps (at most P of them) are code of their own that
 // requests no weights: the compiler would drop those loads, which nobody reads, and with them the counts would be wrong.
-template <bool TRIP, bool SPLIT, int NT, int JT, int KG>
-__global__ __launch_bounds__(kThreads * KG, 2) void gemm_tiled_kernel(const TiledArgs a) {
+// GJT: the grid's column tiles are 64 GJT channels wide, and this workgroup takes the half `part_n` of tile `bid` where JT is
+// half of GJT, else all of it (part_n 0).
+template <bool TRIP, bool SPLIT, int NT, int JT, int KG, int GJT>
+__device__ __forceinline__ void tiled_tile(const TiledArgs &a, unsigned char *const lds, int bid, int part_n) {
     constexpr int P = weights_ahead(NT, JT, KG) - (TRIP && NT == 8);   // (the shifts take registers)
     constexpr int SETS = P + 1;                          // register sets of weights
     constexpr int Q = code_stages(NT, KG), R = fragment_ring(NT, JT);
     constexpr int B = 2 * NT - R / 2;                    // group of MFMAs in front of which the wavefronts meet
     constexpr int NC = NT / 2;                           // activation copies of a wavefront per step
-    constexpr int BMT = NT * 16, BNT = JT * 64;
+    constexpr int BMT = NT * 16, BNT = GJT * 64;
     constexpr int kStageT = NT * 2048;
     constexpr int kRow = JT * 32 + 16;                   // bytes per row of a wavefront's output in LDS
     constexpr int kPass = NT / KG < 4 ? NT / KG : 4;     // 16-token tiles per pass of the epilogue
@@ -154,18 +157,11 @@ __global__ __launch_bounds__(kThreads * KG, 2) void gemm_tiled_kernel(const Tile
     static_assert(SETS >= 3 && P >= Q - 2 && Q >= 3, "the counts of the waits below");
     static_assert(kGroupLds >= 4 * kPass * 16 * kRow, "the epilogue's rows fit the stages");
     static_assert(KG == 1 || NT * JT * 4 * kThreads * 4 <= KG * kGroupLds, "the sums that change hands fit");
-    __shared__ __align__(16) unsigned char lds[KG * kGroupLds];
     const int lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);
     const int grp = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
     const int tid = threadIdx.x & (kThreads - 1);
 
-    // XCD-aware tile order.  Consecutive workgroup ids land on different XCDs (round-robin over 8), each with its own L2, so
-    // first give every XCD a contiguous run of logical tile ids (the first nblk % 8 of them one more); then walk the tile grid
-    // in bands of token tiles, column by column, so that a run re-reads as little of either operand as possible.
-    const int nblk = gridDim.x;
-    int bid = blockIdx.x;
-    bid = (bid & 7) * (nblk >> 3) + min(bid & 7, nblk & 7) + (bid >> 3);
     // SPLIT: workgroups with the same K slice are neighbours (they share activation stages)
     const int split = SPLIT ? bid / a.tiles_all : 0;
     if (SPLIT) bid -= split * a.tiles_all;
@@ -183,7 +179,7 @@ __global__ __launch_bounds__(kThreads * KG, 2) void gemm_tiled_kernel(const Tile
     const int rows = min(a.band, a.tiles_m - band * a.band);
     const int within = bid - band * a.band * ptiles_n;
     const int tn = within / rows, tm = band * a.band + within - tn * rows;
-    const int m0 = tm * BMT, n0 = tn * BNT + (int)wave * (JT * 16);      // channels of this wavefront
+    const int m0 = tm * BMT, n0 = tn * BNT + part_n * (JT * 64) + (int)wave * (JT * 16);      // channels of this wavefront
     const int KTfull = a.KT;
     const int kwg = SPLIT ? split * a.steps_per_split : 0;
     const int KTwg = SPLIT ? min(a.steps_per_split, KTfull - kwg) : KTfull;  // steps of this workgroup
@@ -483,6 +479,28 @@ __global__ __launch_bounds__(kThreads * KG, 2) void gemm_tiled_kernel(const Tile
 }
 
 
+// HALVES: the tiles from a.whole on, a last round that fills at most half of the CUs, are dealt out as halves (half of the
+// channels each) to twice as many workgroups; see agq_tiled_halves.
+template <bool TRIP, bool SPLIT, int NT, int JT, int KG, bool HALVES>
+__global__ __launch_bounds__(kThreads * KG, 2) void gemm_tiled_kernel(const TiledArgs a) {
+    __shared__ __align__(16) unsigned char lds[KG * code_stages(NT, KG) * NT * 2048];
+    // XCD-aware tile order.  Consecutive workgroup ids land on different XCDs (round-robin over 8), each with its own L2, so
+    // first give every XCD a contiguous run of logical tile ids (the first nblk % 8 of them one more); then walk the tile grid
+    // in bands of token tiles, column by column, so that a run re-reads as little of either operand as possible.
+    const int whole = HALVES ? a.whole : (int)gridDim.x;
+    const bool half = HALVES && (int)blockIdx.x >= whole;
+    const int nblk = half ? (int)gridDim.x - whole : whole;
+    int bid = half ? (int)blockIdx.x - whole : (int)blockIdx.x;
+    bid = (bid & 7) * (nblk >> 3) + min(bid & 7, nblk & 7) + (bid >> 3);
+    if constexpr (HALVES) {
+        if (half) {
+            tiled_tile<TRIP, SPLIT, NT, JT / 2, KG, JT>(a, lds, whole + (bid >> 1), bid & 1);
+            return;
+        }
+    }
+    tiled_tile<TRIP, SPLIT, NT, JT, KG, JT>(a, lds, bid, 0);
+}
+
 // Second kernel of a K split: workgroup (tile, piece c) adds the `splits` partial copies of accumulator piece c of
 // every thread of the tile's workgroups (same thread numbering, same tile walk as above) and runs the same
 // epilogue arithmetic on the sums; a thread owns four consecutive channels of one token.
@@ -614,8 +632,17 @@ int agq_launch_gemm_tiled(const void *x_tiles, int64_t M, int64_t K, int e, int 
         constexpr bool SPLIT = decltype(sp)::value != 0;
         if (found || split != SPLIT || choice.nt != NT || choice.jt != JT || choice.kg != KG) return;
         found = true;
-        if (trip) gemm_tiled_kernel<true, SPLIT, NT, JT, KG><<<grid, kThreads * KG, 0, st>>>(a);
-        else gemm_tiled_kernel<false, SPLIT, NT, JT, KG><<<grid, kThreads * KG, 0, st>>>(a);
+        if constexpr (NT == 8 && JT == 4) {
+            a.whole = tiles - (int)agq_tiled_halves(tiles);
+            if (a.whole < tiles) {
+                const unsigned more = grid + (unsigned)(tiles - a.whole);
+                if (trip) gemm_tiled_kernel<true, SPLIT, NT, JT, KG, true><<<more, kThreads * KG, 0, st>>>(a);
+                else gemm_tiled_kernel<false, SPLIT, NT, JT, KG, true><<<more, kThreads * KG, 0, st>>>(a);
+                return;
+            }
+        }
+        if (trip) gemm_tiled_kernel<true, SPLIT, NT, JT, KG, false><<<grid, kThreads * KG, 0, st>>>(a);
+        else gemm_tiled_kernel<false, SPLIT, NT, JT, KG, false><<<grid, kThreads * KG, 0, st>>>(a);
     };
 #define AGQ_SHAPE(NT, JT, KG) launch(Int<NT>{}, Int<JT>{}, Int<KG>{}, Int<0>{});
     AGQ_TILED_SHAPES(AGQ_SHAPE)

@@ -118,11 +118,14 @@ static const AgqTiledTime agq_tiled_times[] = {
     {2, 2, 2, 4165, 104, 29, 150, 555, 125, 33},
     {2, 1, 2, 3628, 73, 10, 84, 576, 138, 64},
 };
+// 128 x 256 tiles of a last round that fills at most half of the CUs are dealt out as halves, in the same launch: how many of w
+// (1000 x 4096 -> 12288 46.4 -> 40.7 us, 1024 x 5120 -> 27648 113 -> 104, 333 x 5120 -> 27648 54 -> 48, 2048 x 4096 -> 22016 134 -> 129).
+static inline int64_t agq_tiled_halves(int64_t w) { return w > 256 && w % 256 <= 128 ? w % 256 : 0; }
 static inline int64_t agq_tiled_ns(const AgqTiledTime &t, int64_t w, int64_t KT, int64_t n_sum) {
     const int64_t mem = t.mem * n_sum / 16384, one = t.fixed + KT * (t.step + t.load * (w < 256 ? w : 256) / 256 + mem);
     if (w <= 256) return one;
-    const int64_t n = (w + 255) / 256;
-    const int64_t several = t.fixed + (n - 1) * t.more + KT * (t.many * (n * 256 * t.ceil64 + (64 - t.ceil64) * w) / 16384 + mem);
+    const int64_t n = (w + 255) / 256, halves = 2 * n - (t.nt == 8 && t.jt == 4 && agq_tiled_halves(w) > 0);
+    const int64_t several = t.fixed + (n - 1) * t.more + KT * (t.many * (halves * 128 * t.ceil64 + (64 - t.ceil64) * w) / 16384 + mem);
     return several > one ? several : one;
 }
 static inline int64_t agq_tiled_count(int64_t M, const int64_t *N, int count, int nt, int jt) {

@@ -52,6 +52,8 @@ CASES = [
     (212, 17, 44, (12, 15, 16, 17, 18, 19)), (222, 17, 22000, (12, 13, 14, 15)), (412, 33, 8201, (12, 13, 18, 20)),
     (422, 33, 22000, (12, 13, 20)), (422, 400, 4096, (19,)), (4411, 17, 40, (20, 21, 26)), (4421, 1100, 300, (64, 66, 67)),
     (3421, 1050, 512, (64,)),
+    # a last round of 128 x 256 tiles that is dealt out as halves (some of them past the last channel)
+    (841, 1100, 17000, (2, 5, 8)), (841, 2000, 10003, (3,)),
     # token tiles that start apart in K: the first and the last of a group's steps, odd and even counts of them, a short second group
     (212, 100, 4096, (85, 86)), (222, 213, 4096, (85, 86)), (422, 300, 4096, (24, 85, 86)), (422, 100, 8201, (41, 42)),
 ]
@@ -71,7 +73,7 @@ def test_tile(agq, tile_of, tile, M, N, steps):
     assert bool((ybuf[:, N:] == 5.0).all())
 
 
-@pytest.mark.parametrize("tile,M,N,steps,n_extra", [(841, 513, 12000, 8, 3), (841, 513, 12000, 1, 1), (831, 161, 22000, 5, 2),
+@pytest.mark.parametrize("tile,M,N,steps,n_extra", [(841, 513, 12000, 8, 3), (841, 1100, 17000, 4, 2), (841, 513, 12000, 1, 1), (831, 161, 22000, 5, 2),
                                                     (821, 1100, 2001, 11, 2), (441, 257, 12000, 9, 4), (431, 65, 22000, 6, 2),
                                                     (421, 33, 22000, 5, 5), (221, 32, 22000, 3, 6), (412, 33, 8200, 9, 4)])
 def test_tile_with_extra_steps(agq, tile_of, tile, M, N, steps, n_extra):
