@@ -127,9 +127,9 @@ int agq_unpack_w4(const void *packed, int64_t N, int64_t K, int8_t *wq_out,
  * rows the weight-streaming kernel; 17..256 rows of fp16 input the same kernel with
  * sixteen rows (and two channel tiles) per workgroup while re-reading the weights per row group is cheaper
  * than the tiled path (a measured rule on the sizes); else the layout pre-pass and
- * the tiled kernel: with 128 x 128 tiles, with K split over workgroups (few tiles, a
- * long K, and the workspace has the room) or with 64-token tiles, K shared by one or
- * two groups of wavefronts, whichever a measured cost model puts first.
+ * the tiled kernel: with tiles of 32, 64 or 128 tokens x 64 to 256 channels, K shared
+ * by one or two groups of wavefronts, or with K split over workgroups (few tiles, a
+ * long K, and the workspace has the room), whichever a measured cost model puts first.
  * Graph capture: the calls enqueue kernels only and may be captured.  (The first
  * weight-streaming call on a device also raises the LDS limit of the library's
  * kernels there: a host-side setting, not a stream operation, made once per
