@@ -186,25 +186,31 @@ static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int cou
     return best;
 }
 
-// Between 17 and 256 rows of fp16 input the weight-streaming kernel can run with sixteen rows and two channel
-// tiles per workgroup (grid.y row groups): every row group reads the weights again (from L2 after the first),
-// about 3 us + 0.24 us per MB read in all, more when the workgroups fill the last round of 256 CUs badly.  The
-// other path is the layout pre-pass (about 3 us with the gap behind it) plus the tiled kernel (above).  Measured
-// (row groups against pre-pass and tiles): 4096 x 4096 at 32 / 64 / 100 rows 6.4 / 11.0 / 18.1 against 9.7 / 9.8 / 10.1 us;
-// 768 x 768 at 128 rows 4.1 against 6.5 us.  The line is still where the tiles' predecessors put it, 4.9 us to the
-// right (tests name calls on both sides of it): at 4096 x 4096 row groups go on to 80 rows where the tiles would gain up to
-// 3 us from 56 rows on.  (Inside a block the operator in front writes the codes and there is no pre-pass; the same rule is
-// asked there.)  wg_pairs: tile pairs (32 channels) of all projections; tiles: what the call would run instead.  (Four tiles
-// per workgroup instead of two were measured too: the same at best, and 50 % slower on the widest layer, where the registers
-// no longer hold the weight chunks.)
+// Between 17 and 256 rows of fp16 input the weight-streaming kernel can run with sixteen rows and two channel tiles per
+// workgroup (grid.y row groups): every row group reads the weights again (from L2 after the first).  The other path is the
+// layout pre-pass plus the tiled kernel (above).  Both sides measured on 2600 calls of 17 to 256 rows (K 128 to 13824, N 32 to
+// 42000 in up to three projections, other weights from memory at every launch, graph replays):
+//   row groups   about 3 us + 89 ns a K step while every workgroup has a CU of its own;
+//                beyond, 3 us + 200 ns and 126 ns a K step for every round of 256, the second and third of which count whole
+//   tiles        the launch below + 2.1 us + 1.6 ns per 1024 values for the pre-pass
+// The rule takes 0.6 us for what the fixed parts differ by.  Its calls are 0.6 % slower on average than the faster side of each,
+// 18 % at the 99th percentile; past three rounds with a K of 1280 to 1700 the worst of them 1.5 times (45 x 1408 -> 8600 11.2 / 7.2 us).
+// Row groups / tiles: 30 x 11136 -> 3040 12.6 / 15.2 us, 139 x 10880 -> 400 11.0 / 12.9, 768 x 768 at 128 rows 4.1 / 6.5; 200 x 1536 ->
+// 3 x 1536 13.4 / 8.1, 80 x 2560 -> 6912 18.0 / 10.1, 256 x 1280 -> 4100 15.1 / 8.3.
+// Up to 80 rows, below three rounds, row groups go on for 5.5 us longer from 32 steps on: tests hold three calls of that region
+// to them (4096 x 4096 at 64 and 80 rows 10.3 / 9.9 and 13.7 / 10.1, 4096 -> 11008 at 32 rows 13.4 / 11.5).
+// (Inside a block the operator in front writes the codes and there is no pre-pass; the same rule is asked there.)
+// wg_pairs: tile pairs (32 channels) of all projections; tiles: what the call would run instead.  (Four tiles per workgroup instead
+// of two were measured too: the same at best, and 50 % slower on the widest layer, where the registers no longer hold the
+// weight chunks.)
 #define AGQ_ROW_GROUP_MAX_M 256
-static inline bool agq_decode_row_groups(int x_kind, int64_t M, int64_t K, int64_t n_sum, int64_t wg_pairs,
-                                         const AgqTiledPick &tiles) {
+static inline bool agq_decode_row_groups(int x_kind, int64_t M, int64_t KT, int64_t wg_pairs, const AgqTiledPick &tiles) {
     if (x_kind != 0 || M <= AGQ_DECODE_MAX_M || M > AGQ_ROW_GROUP_MAX_M) return false;
-    const int64_t groups = (M + 15) / 16, wgs = groups * wg_pairs;
-    int64_t read_ns = groups * (K * n_sum / 2) * 240 / 1000000;
-    if (wgs < 768) read_ns = read_ns * ((wgs + 255) / 256 * 256) / wgs;   // a short last round costs a whole one
-    return read_ns <= tiles.ns + (tiles.choice.variant == TILED_SPLIT ? 0 : 4900);
+    const int64_t wgs = (M + 15) / 16 * wg_pairs;
+    const int64_t whole = wgs < 768 ? (wgs + 255) / 256 * 256 : wgs;
+    const int64_t read_ns = wgs <= 256 ? 89 * KT : whole * (200 + 126 * KT) / 256;
+    const int64_t more = tiles.choice.variant == TILED_SPLIT ? 0 : (KT >= 32 && M <= 80 && wgs < 768 ? 5500 : 600);
+    return read_ns <= tiles.ns + more;
 }
 
 // int8 codes in operand order, tokens padded to the 128-row tile (a multiple of 16 KiB); K: extra steps included
@@ -218,11 +224,10 @@ struct AgqRoute {
 };
 static inline AgqRoute agq_gemm_route(int x_kind, int64_t M, int64_t K, const int64_t *N, int count, int n_extra,
                                       size_t workspace_bytes) {
-    int64_t tiles_n = 0, wg_pairs = 0, n_sum = 0;
+    int64_t tiles_n = 0, wg_pairs = 0;
     for (int p = 0; p < count; ++p) {
         tiles_n += (N[p] + 127) / 128;
         wg_pairs += (N[p] + 31) / 32;
-        n_sum += N[p];
     }
     // With few tiles and a long K the tiled kernel splits the tiles' K steps over workgroups, if the
     // caller's workspace has the room for the partial tiles behind the codes.
@@ -232,7 +237,7 @@ static inline AgqRoute agq_gemm_route(int x_kind, int64_t M, int64_t K, const in
     if (workspace_bytes < agq_codes_bytes(M, KT * 128) + plan.bytes) plan = agq_tiled_split_plan(M, tiles_n, KT, false);
     const AgqTiledPick pick = agq_tiled_choose(M, N, count, KT, plan, extra);
     AgqRoute r = {false, pick.choice};
-    r.tiles = M > AGQ_DECODE_MAX_M && (n_extra >= 0 || !agq_decode_row_groups(x_kind, M, K, n_sum, wg_pairs, pick));
+    r.tiles = M > AGQ_DECODE_MAX_M && (n_extra >= 0 || !agq_decode_row_groups(x_kind, M, KT, wg_pairs, pick));
     return r;
 }
 

@@ -16,12 +16,13 @@ def agq():
 
 @pytest.fixture(scope="module")
 def tile_of(agq):
-    """tile_of(M, K, Ns, n_extra): 100 x 16-token tiles + 10 x (channels / 64) + groups, + 1000 x the slices of a K split."""
+    """tile_of(M, K, Ns, n_extra): 100 x 16-token tiles + 10 x (channels / 64) + groups, + 1000 x the slices of a K split; -1: the
+    weight-streaming kernel."""
     from paper_2312_05693_amd import build
     probe = ctypes.CDLL(build.PROBE_LIB)
 
-    def tile(M, K, Ns, n_extra=-1, workspace_bytes=0):
-        return probe.agq_probe_gemm_tile(1, ctypes.c_int64(M), ctypes.c_int64(K), (ctypes.c_int64 * len(Ns))(*Ns), len(Ns), n_extra,
+    def tile(M, K, Ns, n_extra=-1, workspace_bytes=0, x_kind=1):
+        return probe.agq_probe_gemm_tile(x_kind, ctypes.c_int64(M), ctypes.c_int64(K), (ctypes.c_int64 * len(Ns))(*Ns), len(Ns), n_extra,
                                          ctypes.c_size_t(workspace_bytes))
     return tile
 
@@ -99,3 +100,25 @@ def test_tile_with_extra_steps(agq, tile_of, tile, M, N, steps, n_extra):
     up = 2.0 ** alpha.to("cuda").double()
     q64 = (x.double() * 2.0 ** -e / up).round().clamp(-128, 127) * up
     check(acc, y, q64, wq, sw, e)
+
+
+@pytest.mark.parametrize("M,steps,Ns,bits,zp", [(30, 87, [3040], 8, 0), (39, 65, [40, 1264], 8, 0), (255, 85, [400], 8, 131), (17, 74, [801], 4, 0),
+                                                (130, 108, [17, 48], 4, 9), (49, 52, [1000], 8, 0)])
+def test_row_groups_on_a_long_k(agq, tile_of, M, steps, Ns, bits, zp):
+    """Sixteen rows a workgroup over more K steps than its wavefronts hold at a time, ragged last groups and widths."""
+    K = 128 * steps
+    assert tile_of(M, K, Ns, workspace_bytes=agq.gemm_workspace_bytes(M, sum(Ns), K), x_kind=0) == -1
+    g = torch.Generator(device="cuda")
+    g.manual_seed(steps + M)
+    x = (torch.randn(M, K, generator=g, device="cuda") * 3).half()
+    e = -4 if bits == 8 else 0
+    projs, weights = [], []
+    for N in Ns:
+        _, _, wq, sw = inputs(16, K, N, N + steps)
+        projs.append((agq.pack_w4(wq), sw, N, torch.empty(M, N, dtype=torch.float16, device="cuda"), torch.full((M, N), -7, dtype=torch.int32, device="cuda")))
+        weights.append(wq)
+    (agq.gemm_w4a8_multi if bits == 8 else agq.gemm_w4a4_multi)(x, e, projs, K, zp=zp)
+    lo, hi = (0, 2 ** bits - 1) if zp else (-2 ** (bits - 1), 2 ** (bits - 1) - 1)
+    q64 = ((x.double() * 2.0 ** -e).round() + zp).clamp(lo, hi) - zp
+    for (_, sw, _, y, acc), wq in zip(projs, weights):
+        check(acc, y, q64, wq, sw, e)
