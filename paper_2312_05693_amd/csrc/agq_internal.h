@@ -103,7 +103,7 @@ struct AgqTiledChoice {
 struct AgqTiledTime {
     int nt, jt, kg, fixed, step, load, many, more, mem, ceil64;
 };
-static const AgqTiledTime agq_tiled_times[] = {
+static constexpr AgqTiledTime agq_tiled_times[] = {
     {8, 4, 1, 6851, 427, 232, 637, 2355, 23, 38},
     {8, 3, 1, 6080, 346, 127, 460, 2382, 80, 39},
     {8, 2, 1, 4768, 265, 78, 334, 2130, 95, 32},
@@ -122,16 +122,34 @@ static const AgqTiledTime agq_tiled_times[] = {
 // (1000 x 4096 -> 12288 46.4 -> 40.7 us, 1024 x 5120 -> 27648 113 -> 104, 333 x 5120 -> 27648 54 -> 48, 2048 x 4096 -> 22016 134 -> 129).
 static inline int64_t agq_tiled_halves(int64_t w) { return w > 256 && w % 256 <= 128 ? w % 256 : 0; }
 static inline int64_t agq_tiled_ns(const AgqTiledTime &t, int64_t w, int64_t KT, int64_t n_sum) {
-    const int64_t mem = t.mem * n_sum / 16384, one = t.fixed + KT * (t.step + t.load * (w < 256 ? w : 256) / 256 + mem);
+    const int64_t mem = t.mem * n_sum >> 14, one = t.fixed + KT * (t.step + (t.load * (w < 256 ? w : 256) >> 8) + mem);
     if (w <= 256) return one;
-    const int64_t n = (w + 255) / 256, halves = 2 * n - (t.nt == 8 && t.jt == 4 && agq_tiled_halves(w) > 0);
-    const int64_t several = t.fixed + (n - 1) * t.more + KT * (t.many * (halves * 128 * t.ceil64 + (64 - t.ceil64) * w) / 16384 + mem);
+    const int64_t n = (w + 255) >> 8, halves = 2 * n - (t.nt == 8 && t.jt == 4 && agq_tiled_halves(w) > 0);
+    const int64_t several = t.fixed + (n - 1) * t.more + KT * ((t.many * (halves * 128 * t.ceil64 + (64 - t.ceil64) * w) >> 14) + mem);
     return several > one ? several : one;
 }
-static inline int64_t agq_tiled_count(int64_t M, const int64_t *N, int count, int nt, int jt) {
-    int64_t n = 0;
-    for (int p = 0; p < count; ++p) n += (N[p] + jt * 64 - 1) / (jt * 64);
-    return n * ((M + nt * 16 - 1) / (nt * 16));
+static constexpr int agq_tiled_least_ns() {
+    int least = agq_tiled_times[0].fixed;
+    for (const AgqTiledTime &t : agq_tiled_times)
+        if (t.fixed < least) least = t.fixed;
+    return least;
+}
+// Workgroups of a call for every tile, counted once for the table: divisions for every shape and projection were half of the host's time.
+struct AgqTileCounts {
+    int64_t m[9], n[5];    // token tiles of 16 nt (nt 2, 4, 8), column tiles of 64 jt (jt 1 to 4)
+    int64_t operator()(int nt, int jt) const { return m[nt] * n[jt]; }
+};
+static inline AgqTileCounts agq_tile_counts(int64_t M, const int64_t *N, int count) {
+    AgqTileCounts c = {};
+    for (int nt = 2; nt <= 8; nt *= 2) c.m[nt] = (M + nt * 16 - 1) / (nt * 16);
+    for (int p = 0; p < count; ++p) {
+        const int64_t n64 = (N[p] + 63) / 64;
+        c.n[1] += n64;
+        c.n[2] += (n64 + 1) / 2;
+        c.n[3] += (n64 + 2) / 3;
+        c.n[4] += (n64 + 3) / 4;
+    }
+    return c;
 }
 struct AgqTiledPick {
     AgqTiledChoice choice;
@@ -139,14 +157,14 @@ struct AgqTiledPick {
 };
 // KT: steps, the n_extra of TRIP blobs included.
 static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int count, int64_t KT, const AgqSplitPlan &plan, int n_extra) {
-    int64_t tiles_n = 0, n_sum = 0;
+    int64_t n_sum = 0;
     bool ragged = false;
     for (int p = 0; p < count; ++p) {
-        tiles_n += (N[p] + 127) / 128;
         n_sum += N[p];
         ragged = ragged || (N[p] & 7);
     }
-    const int64_t tiles = ((M + 127) / 128) * tiles_n;
+    const AgqTileCounts workgroups = agq_tile_counts(M, N, count);
+    const int64_t tiles = workgroups(8, 2);
     AgqTiledPick best = {{TILED_128, 8, 4, 1, 1, (int)KT}, INT64_MAX};
     // A K split for long K with few tiles: 64 x 64 tiles while four slices of them fit the CUs, else (narrow layers alone) 64 x 128
     // ones, at most four slices (more only add partial tiles to write and read).  Measured against the best tile without: 20 x 11008
@@ -154,10 +172,10 @@ static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int cou
     // 8192 -> 384 8.8 / 8.3, 1050 x 8192 -> 512 13.2 / 12.3, 300 x 4096 -> 768 8.9 / 6.9, 260 x 2560 -> 130 6.5 / 5.7.  100 x 11008 ->
     // 4096, whose slices do not fit, 16.2 / 13.7.  (Eight slices of 128 x 128 tiles: 15.1, 17.3, 13.7, 10.9 us for the first four.)
     if (plan.splits > 1 && KT - n_extra >= 20 && 2 * KT >= 3 * tiles &&
-        (n_sum <= 1024 || agq_tiled_count(M, N, count, 4, 1) * (plan.splits < 4 ? plan.splits : 4) <= 256)) {
+        (n_sum <= 1024 || workgroups(4, 1) * (plan.splits < 4 ? plan.splits : 4) <= 256)) {
         const int s = plan.splits < 4 ? plan.splits : 4;
-        const int jt = agq_tiled_count(M, N, count, 4, 1) * s <= 256 ? 1 : 2;
-        const int64_t w = agq_tiled_count(M, N, count, 4, jt);
+        const int jt = workgroups(4, 1) * s <= 256 ? 1 : 2;
+        const int64_t w = workgroups(4, jt);
         int64_t cut = w * s <= 256 ? s : (w * 2 <= 256 ? 256 / w : 2);
         const int64_t steps = (KT + cut - 1) / cut;
         best.choice = {TILED_SPLIT, 4, jt, 1, (int)((KT + steps - 1) / steps), (int)steps};
@@ -169,13 +187,13 @@ static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int cou
     // for each other (agq_gemm_tiled.hip).  Against one group, each with its best tile: 100 x 11008 -> 4096 13.7 / 15.5 us, 213 tokens
     // 17.2 / 21.1, 300 tokens 21.5 / 26.9, 333 x 13824 -> 5120 30.0 / 33.2, 333 x 5120 -> 5120 14.8 / 15.3, 100 x 4096 -> 12288 12.7 / 13.0; behind
     // where K is short and the CUs are full, 512 x 4096 -> 4096 11.6 / 10.3, 256 x 2560 -> 6912 9.5 / 8.1.
-    const bool two = KT >= 12 && ((M + 63) / 64) * tiles_n <= 256;
+    const bool two = KT >= 12 && workgroups(4, 2) <= 256;
     int64_t ns82 = INT64_MAX;
     for (const AgqTiledTime &t : agq_tiled_times) {
         if ((t.kg == 2) != two) continue;
         // Rows of the output that do not start on sixteen bytes: stores across lines (1200 x 1280 -> 4096 / 4100: tiles of 128 x 256
         // 12.0 / 16.0 us, 128 x 192 11.0 / 13.5, 64 x 192 11.2 / 12.2, 64 x 128 11.3 / 11.9).
-        const int64_t ns = agq_tiled_ns(t, agq_tiled_count(M, N, count, t.nt, t.jt), KT, n_sum) + (ragged ? t.nt * (t.jt - 1) * 100 : 0);
+        const int64_t ns = agq_tiled_ns(t, workgroups(t.nt, t.jt), KT, n_sum) + (ragged ? t.nt * (t.jt - 1) * 100 : 0);
         if (t.nt == 8 && t.jt == 2) ns82 = ns;
         if (ns < best.ns) best = {{t.kg == 2 ? TILED_64X2 : (t.nt == 8 ? TILED_128 : TILED_64), t.nt, t.jt, t.kg, 1, (int)KT}, ns};
     }
@@ -200,17 +218,17 @@ static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int cou
 // Up to 80 rows, below three rounds, row groups go on for 5.5 us longer from 32 steps on: tests hold three calls of that region
 // to them (4096 x 4096 at 64 and 80 rows 10.3 / 9.9 and 13.7 / 10.1, 4096 -> 11008 at 32 rows 13.4 / 11.5).
 // (Inside a block the operator in front writes the codes and there is no pre-pass; the same rule is asked there.)
-// wg_pairs: tile pairs (32 channels) of all projections; tiles: what the call would run instead.  (Four tiles per workgroup instead
+// wgs: groups of sixteen rows times tile pairs (32 channels) of all projections; tiles: what the call would run instead.  (Four tiles per workgroup instead
 // of two were measured too: the same at best, and 50 % slower on the widest layer, where the registers no longer hold the
 // weight chunks.)
 #define AGQ_ROW_GROUP_MAX_M 256
-static inline bool agq_decode_row_groups(int x_kind, int64_t M, int64_t KT, int64_t wg_pairs, const AgqTiledPick &tiles) {
-    if (x_kind != 0 || M <= AGQ_DECODE_MAX_M || M > AGQ_ROW_GROUP_MAX_M) return false;
-    const int64_t wgs = (M + 15) / 16 * wg_pairs;
+static inline int64_t agq_row_groups_ns(int64_t wgs, int64_t KT) {
     const int64_t whole = wgs < 768 ? (wgs + 255) / 256 * 256 : wgs;
-    const int64_t read_ns = wgs <= 256 ? 89 * KT : whole * (200 + 126 * KT) / 256;
+    return wgs <= 256 ? 89 * KT : whole * (200 + 126 * KT) / 256;
+}
+static inline bool agq_decode_row_groups(int64_t M, int64_t KT, int64_t wgs, const AgqTiledPick &tiles) {
     const int64_t more = tiles.choice.variant == TILED_SPLIT ? 0 : (KT >= 32 && M <= 80 && wgs < 768 ? 5500 : 600);
-    return read_ns <= tiles.ns + more;
+    return agq_row_groups_ns(wgs, KT) <= tiles.ns + more;
 }
 
 // int8 codes in operand order, tokens padded to the 128-row tile (a multiple of 16 KiB); K: extra steps included
@@ -224,21 +242,26 @@ struct AgqRoute {
 };
 static inline AgqRoute agq_gemm_route(int x_kind, int64_t M, int64_t K, const int64_t *N, int count, int n_extra,
                                       size_t workspace_bytes) {
-    int64_t tiles_n = 0, wg_pairs = 0;
+    // The calls whose launches are shortest do not look at the tiles: up to sixteen rows have no other kernel, and row groups that
+    // take no longer than the shortest launch of any tile (which the split's second launch is on top of) need no comparison.
+    // The host's time for a choice: 1 x 4096 -> 4096 62 -> 2 ns, 128 x 768 -> 768 66 -> 4, 2048 x 4096 -> 3 x 4096 112 -> 65.
+    if (M <= AGQ_DECODE_MAX_M) return {false, {}};
+    const bool may_stream = x_kind == 0 && n_extra < 0 && M <= AGQ_ROW_GROUP_MAX_M;
+    int64_t tiles_n = 0, wgs = 0;
     for (int p = 0; p < count; ++p) {
         tiles_n += (N[p] + 127) / 128;
-        wg_pairs += (N[p] + 31) / 32;
+        wgs += (N[p] + 31) / 32;
     }
-    // With few tiles and a long K the tiled kernel splits the tiles' K steps over workgroups, if the
-    // caller's workspace has the room for the partial tiles behind the codes.
+    wgs *= (M + 15) / 16;
     const int extra = n_extra > 0 ? n_extra : 0;
     const int64_t KT = agq_k_tiles(K) + extra;
+    if (may_stream && agq_row_groups_ns(wgs, KT) <= agq_tiled_least_ns() + 600) return {false, {}};
+    // With few tiles and a long K the tiled kernel splits the tiles' K steps over workgroups, if the
+    // caller's workspace has the room for the partial tiles behind the codes.
     AgqSplitPlan plan = agq_tiled_split_plan(M, tiles_n, KT, true, extra);
     if (workspace_bytes < agq_codes_bytes(M, KT * 128) + plan.bytes) plan = agq_tiled_split_plan(M, tiles_n, KT, false);
     const AgqTiledPick pick = agq_tiled_choose(M, N, count, KT, plan, extra);
-    AgqRoute r = {false, pick.choice};
-    r.tiles = M > AGQ_DECODE_MAX_M && (n_extra >= 0 || !agq_decode_row_groups(x_kind, M, KT, wg_pairs, pick));
-    return r;
+    return {!(may_stream && agq_decode_row_groups(M, KT, wgs, pick)), pick.choice};
 }
 
 // K steps up to which a launch of five to sixteen rows with several channel tiles per CU takes the K-sliced kernel

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <chrono>
+
 #include "agq_internal.h"
 
 namespace {
@@ -106,6 +108,14 @@ extern "C" int agq_probe_gemm_tile(int x_kind, int64_t M, int64_t K, const int64
     const AgqRoute r = agq_gemm_route(x_kind, M, K, N, count, n_extra, workspace_bytes);
     if (!r.tiles) return -1;
     return (r.choice.variant == TILED_SPLIT ? 1000 * r.choice.splits : 0) + 100 * r.choice.nt + 10 * r.choice.jt + r.choice.kg;
+}
+
+// Host only: nanoseconds that the host takes for that choice, fp16 input on plain blobs, on average over `reps` of them.
+extern "C" double agq_probe_gemm_route_ns(int64_t M, int64_t K, const int64_t *N, int count, size_t workspace_bytes, int reps) {
+    const auto t0 = std::chrono::steady_clock::now();
+    volatile int64_t rows = M, taken = 0;                // (read and written every time, so that no choice is left out)
+    for (int i = 0; i < reps; ++i) taken = taken + agq_gemm_route(0, rows, K, N, count, -1, workspace_bytes).tiles;
+    return std::chrono::duration<double, std::nano>(std::chrono::steady_clock::now() - t0).count() / reps;
 }
 
 // Host only: whether 5 to 16 rows of fp16 input on plain blobs [N[p], K] run with two channel tiles per workgroup of the

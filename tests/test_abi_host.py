@@ -378,6 +378,20 @@ def test_line_between_row_groups_and_tiles(gemm_route, M, K, Ns, stream):
     assert (gemm_route(M, K, Ns) == "stream") == stream
 
 
+def test_the_shortest_calls_choose_without_the_table(probe):
+    """One row and a small layer have the shortest launches: the host's choice for them does not evaluate the tiled kernel's shapes
+    (2 and 4 ns against 65 for a call that does; 62 and 66 against 112 when all calls did)."""
+    probe.agq_probe_gemm_route_ns.restype = ctypes.c_double
+
+    def ns(M, K, Ns):
+        widths = (ctypes.c_int64 * len(Ns))(*Ns)
+        return min(probe.agq_probe_gemm_route_ns(ctypes.c_int64(M), ctypes.c_int64(K), widths, len(Ns), ctypes.c_size_t(1 << 28), 5000)
+                   for _ in range(10))
+    full = ns(2048, 4096, [4096] * 3)
+    for M, K, Ns in ((1, 4096, [4096]), (16, 4096, [4096] * 3), (128, 768, [768])):
+        assert ns(M, K, Ns) < full / 4, (M, K, Ns)
+
+
 def test_two_groups_have_a_step_each(gemm_route):
     """The kernel whose two wavefront groups share a tile's K steps is never chosen for a tile of a single step."""
     for M in (17, 64, 100, 257, 300, 700, 2000):
