@@ -1488,7 +1488,7 @@ def test_qk_attention_longest_sequence(agq, oracle):
 @pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 6, 7, 8, 11])
 @pytest.mark.parametrize("M,N,variant", [(300, 40, "64"), (1100, 2000, "64"), (1000, 12000, "128")])
 def test_tiled_every_pipeline_tail(agq, oracle, gemm_route, M, N, variant, steps):
-    """The tiled kernel's K loop: fewer steps than its three stages, and every number of steps behind the steady loop."""
+    """The tiled kernel's K loop: fewer steps than a wavefront requests ahead, and every number of steps behind the steady loop."""
     if (N, steps) == (2000, 11):
         variant = "128"                                  # the longest of these takes the larger tiles
     assert gemm_route(M, 128 * steps, [N]) == variant
@@ -1503,7 +1503,8 @@ def test_tiled_every_pipeline_tail(agq, oracle, gemm_route, M, N, variant, steps
 
 
 def test_trip_split_slice_of_extra_steps_only(agq, oracle, gemm_route):
-    """A K split whose first slice is the 16 extra steps and nothing else: its last step is followed by a shift."""
+    """A K split whose first slice is the 16 extra steps and steps of the main weights behind them.  (Slices that are the extra steps to
+    the step: test_gpu_tiles.py, test_split_whose_first_slice_is_the_extra_steps.)"""
     M, N, K = 100, 300, 10240
     full = agq.lib().agq_gemm_trip_workspace_bytes(M, N, K, 16)
     assert gemm_route(M, K, [N], n_extra=16, workspace_bytes=full) == "split"

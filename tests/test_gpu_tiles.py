@@ -40,7 +40,8 @@ def check(acc, y, q64, wq, sw, e):
     want = torch.mm(q64, wq.double().t().contiguous())                   # whole numbers below 2^53: exact
     assert torch.equal(acc.double(), want)
     ref = want * (sw.double() * 2.0 ** e)
-    assert bool(((y.double() - ref).abs() <= ref.abs() * 2.0 ** -10 + 2.0 ** -24).all())     # one rounding to fp16, of a product in fp32
+    # one rounding to fp16 (2^-11, or half of the smallest subnormal), of an fp32 product of two factors that are rounded to fp32 (3 x 2^-24)
+    assert bool(((y.double() - ref).abs() <= ref.abs() * (2.0 ** -11 + 2.0 ** -22) + 2.0 ** -25).all())
 
 
 # token counts one past and at the edge of a tile, widths that end inside a wavefront's channels and off the 16-byte grid, and
@@ -76,7 +77,8 @@ def test_tile(agq, tile_of, tile, M, N, steps):
 
 @pytest.mark.parametrize("tile,M,N,steps,n_extra", [(841, 513, 12000, 8, 3), (841, 1100, 17000, 4, 2), (841, 513, 12000, 1, 1), (831, 161, 22000, 5, 2),
                                                     (821, 1100, 2001, 11, 2), (441, 257, 12000, 9, 4), (431, 65, 22000, 6, 2),
-                                                    (421, 33, 22000, 5, 5), (221, 32, 22000, 3, 6), (412, 33, 8200, 9, 4)])
+                                                    (421, 33, 22000, 5, 5), (221, 32, 22000, 3, 6), (412, 33, 8200, 9, 4),
+                                                    (212, 17, 44, 14, 3), (222, 17, 22000, 13, 4), (422, 300, 4096, 14, 3)])
 def test_tile_with_extra_steps(agq, tile_of, tile, M, N, steps, n_extra):
     """TRIP blobs: the shifts behind the extra steps, which may be all of the steady loop, and its tail."""
     K = 128 * steps
@@ -84,7 +86,9 @@ def test_tile_with_extra_steps(agq, tile_of, tile, M, N, steps, n_extra):
     x = torch.randn(M, K, generator=g, device="cuda").half()
     levels = [4, 3, 2, 1]
     alpha = torch.zeros(K, dtype=torch.int8)
-    left = list(torch.randperm(K).tolist())
+    order = torch.Generator()
+    order.manual_seed(13 * steps + M)
+    left = list(torch.randperm(K, generator=order).tolist())
     for c in range(n_extra):                                             # one chunk more for every channel past a multiple of 128
         for k in left[:1 if c < 4 else 128]:
             alpha[k] = levels[c % 4] if c < 4 else levels[(c - 4) % 4]
@@ -100,6 +104,76 @@ def test_tile_with_extra_steps(agq, tile_of, tile, M, N, steps, n_extra):
     up = 2.0 ** alpha.to("cuda").double()
     q64 = (x.double() * 2.0 ** -e / up).round().clamp(-128, 127) * up
     check(acc, y, q64, wq, sw, e)
+
+
+@pytest.mark.parametrize("tile,M,Ns,steps,bits,zp,n_extra", [
+    # the last round of 128 x 256 tiles, dealt out as halves: its first tile is another projection's than the last whole one, or
+    # lies inside a projection, and the projections behind it start among the halves
+    (841, 1000, [8101, 8104, 3001, 130], 4, 8, 131, None), (841, 1023, [16300, 4001], 5, 4, 9, None), (841, 1000, [13801, 13825], 2, 8, 7, None),
+    (841, 1000, [16301, 3000, 520], 3, 8, 0, 3), (841, 1020, [8100, 8101, 4001], 2, 4, 5, 2),
+    # the unsigned grid on the tiles of 32 tokens, and on two groups
+    (211, 17, [44, 301], 3, 8, 77, None), (221, 213, [4096, 300], 5, 4, 15, None), (212, 17, [513, 130], 14, 8, 200, None),
+    (222, 213, [4096, 300], 20, 4, 1, None), (422, 300, [4096, 300], 14, 8, 128, None), (412, 100, [4096, 300], 14, 8, 3, 3)])
+def test_tile_of_several_projections(agq, tile_of, tile, M, Ns, steps, bits, zp, n_extra):
+    K = 128 * steps
+    g = torch.Generator(device="cuda")
+    g.manual_seed(17 * steps + M)
+    x = (torch.randn(M, K, generator=g, device="cuda") * 3).half()
+    e = -6 if bits == 8 else -1
+    alpha = torch.zeros(K, dtype=torch.int8)
+    for c in range(n_extra or 0):                                        # as many chunks, of factors 2 and 1 or 3, 2 and 1
+        alpha[5 * c + 1::97] = n_extra - c
+    projs, weights = [], []
+    for i, N in enumerate(Ns):
+        _, _, wq, sw = inputs(16, K, N, N + steps + i)
+        blob = agq.pack_w4(wq) if n_extra is None else agq.pack_w4_trip(wq, alpha.numpy())
+        if n_extra is not None:
+            assert blob[1] == n_extra
+            blob = blob[0]
+        projs.append((blob, sw, N, torch.empty(M, N, dtype=torch.float16, device="cuda"), torch.full((M, N), -7, dtype=torch.int32, device="cuda")))
+        weights.append(wq)
+    if n_extra is None:
+        xq = agq.quantize_act(x, bits, e, zp)
+        size = agq.gemm_workspace_bytes(M, sum(Ns), K)
+        assert tile_of(M, K, Ns, workspace_bytes=size) == tile
+        multi = agq.gemm_w4a8_multi if bits == 8 else agq.gemm_w4a4_multi
+        multi(xq, e, projs, K, x_kind=agq.AGQ_X_Q, workspace=torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda"), zp=zp)
+    else:
+        size = agq.lib().agq_gemm_trip_workspace_bytes(M, sum(Ns), K, n_extra)
+        assert tile_of(M, K, Ns, n_extra, size) == tile
+        agq.gemm_trip_multi(x, bits, e, projs, n_extra, K, workspace=torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda"), zp=zp)
+    lo, hi = (0, 2 ** bits - 1) if zp else (-2 ** (bits - 1), 2 ** (bits - 1) - 1)
+    up = 2.0 ** alpha.to("cuda").double()
+    q64 = (((x.double() * 2.0 ** -e / up).round() + zp).clamp(lo, hi) - zp) * up
+    for (_, sw, _, y, acc), wq in zip(projs, weights):
+        check(acc, y, q64, wq, sw, e)
+
+
+@pytest.mark.parametrize("K,slices", [(4096, 3), (6144, 4)])
+def test_split_whose_first_slice_is_the_extra_steps(agq, tile_of, K, slices):
+    """Sixteen extra steps, the first slice of the K split to the step: its last step is followed by a shift, and no step of the
+    main weights is."""
+    M, N, n_extra = 100, 300, 16
+    size = agq.lib().agq_gemm_trip_workspace_bytes(M, N, K, n_extra)
+    tile = tile_of(M, K, [N], n_extra, size, x_kind=0)
+    assert tile // 1000 == slices and -(-(K // 128 + n_extra) // slices) == n_extra          # steps a slice, as the choice divides them
+    g, _, wq, sw = inputs(16, K, N, K)
+    x = torch.randn(M, K, generator=g, device="cuda").half()
+    for counts in ((2048, 0, 0, 0), (700, 600, 300, 256)):               # channels of factor 4, 3, 2, 1: one level, four of them
+        alpha = torch.zeros(K, dtype=torch.int8)
+        order = torch.Generator()
+        order.manual_seed(K)
+        left = torch.randperm(K, generator=order)
+        for level, n in zip((4, 3, 2, 1), counts):
+            alpha[left[:n]] = level
+            left = left[n:]
+        packed, extra = agq.pack_w4_trip(wq, alpha.numpy())
+        assert extra == n_extra
+        acc = torch.full((M, N), -7, dtype=torch.int32, device="cuda")
+        y = torch.empty(M, N, dtype=torch.float16, device="cuda")
+        agq.gemm_trip_multi(x, 8, -7, [(packed, sw, N, y, acc)], extra, K, workspace=torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda"))
+        up = 2.0 ** alpha.to("cuda").double()
+        check(acc, y, (x.double() * 2.0 ** 7 / up).round().clamp(-128, 127) * up, wq, sw, -7)
 
 
 @pytest.mark.parametrize("M,steps,Ns,bits,zp", [(30, 87, [3040], 8, 0), (39, 65, [40, 1264], 8, 0), (255, 85, [400], 8, 131), (17, 74, [801], 4, 0),
