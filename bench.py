@@ -492,15 +492,16 @@ def main():
             ent[label] = {"us": round(ms * 1e3, 2), "TOP/s": round(2.0 * PREFILL_M * N * K / (ms * 1e-3) / 1e12, 1)}
         ent["note"] = "same launch, same instruction stream and bytes; only the operand values differ"
         prefill["operand_values_w4a8_4096_to_11008"] = ent
-        # What the matrix cores sustain on this device for the kernel's instruction (32 x 32 x 32 int8 MFMA, two
-        # wavefronts per SIMD, four independent accumulators, no memory traffic): with all-zero operands, with
+        # What the matrix cores sustain on this device for the kernel's instruction (16 x 16 x 64 int8 MFMA, two
+        # wavefronts per SIMD, eight independent accumulators, no memory traffic): with all-zero operands, with
         # operand values taken from the workload (weights as the kernels feed them, 16 w, and the activation's
-        # 8-bit codes) and with uniformly random bytes.  The instruction stream is the same in all three.
+        # 8-bit codes) and with uniformly random bytes.  The instruction stream is the same in all three; the
+        # 32 x 32 x 32 form beside it.
         if not args.no_probe:
             import ctypes
             probe = ctypes.CDLL(os.path.join(ROOT, "paper_2312_05693_amd", "libagq_probe.so"))
             probe.agq_probe_mfma_i8.restype = ctypes.c_int
-            probe.agq_probe_mfma_i8.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int, ctypes.c_int,
+            probe.agq_probe_mfma_i8.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int,
                                                 ctypes.c_void_p, ctypes.c_void_p]
             gen_p = torch.Generator(device=dev)
             gen_p.manual_seed(11)
@@ -513,9 +514,11 @@ def main():
             wgs, reps_p = 512, 20000                     # two workgroups of four wavefronts per CU
             ops = 8.0 * 32 ** 3 * reps_p * wgs * 4
             mp = {}
-            for label, pa, pb in (("zero_operands", zero, zero), ("workload_operands", w16, codes),
-                                  ("uniform_random_bytes", rnd[:nb_p].contiguous(), rnd[nb_p:].contiguous())):
-                launch = lambda: probe.agq_probe_mfma_i8(pa.data_ptr(), pb.data_ptr(), wgs, reps_p, sink_p.data_ptr(),
+            r0, r1 = rnd[:nb_p].contiguous(), rnd[nb_p:].contiguous()
+            for label, pa, pb, wide in (("zero_operands", zero, zero, 0), ("workload_operands", w16, codes, 0),
+                                        ("uniform_random_bytes", r0, r1, 0), ("zero_operands_32x32x32", zero, zero, 1),
+                                        ("workload_operands_32x32x32", w16, codes, 1), ("uniform_random_bytes_32x32x32", r0, r1, 1)):
+                launch = lambda: probe.agq_probe_mfma_i8(pa.data_ptr(), pb.data_ptr(), wgs, reps_p, wide, sink_p.data_ptr(),
                                                          torch.cuda.current_stream().cuda_stream)
                 assert launch() == 0
                 torch.cuda.synchronize()

@@ -33,38 +33,46 @@ __global__ __launch_bounds__(kThreads) void probe_read_kernel(const probe_u4 *sr
 
 __global__ void probe_empty_kernel() {}
 
-// The int8 matrix instruction of the tiled kernel with no memory traffic at all: every lane loads four pairs of
-// operand registers once (4 x 16 bytes each from `a` and `b`, the same 16 KiB for every workgroup) and then issues
-// `reps` rounds of four independent 32 x 32 x 32 MFMAs, every one with another pair than the one before it, as in a
-// GEMM.  What this measures is the rate the matrix cores sustain for given operand VALUES (the instruction stream
-// is the same for all of them).
+// An int8 matrix instruction with no memory traffic at all: every lane loads four pairs of operand registers once (4 x 16 bytes
+// each from `a` and `b`, the same 16 KiB for every workgroup) and then issues MFMAs, every one with another pair than the one
+// before it, as in a GEMM: 16 x 16 x 64 (the tiled kernel's), eight independent ones a round, or 32 x 32 x 32 (WIDE), four of twice
+// the operations.  What this measures is the rate the matrix cores sustain for given operand VALUES (the instruction
+// stream is the same for all of them).
 typedef int probe_v4i __attribute__((ext_vector_type(4)));
-typedef int probe_v16i __attribute__((ext_vector_type(16)));
 
+template <bool WIDE>
 __global__ __launch_bounds__(256) void probe_mfma_kernel(const probe_v4i *a, const probe_v4i *b, int reps, uint32_t *sink) {
+    constexpr int kAcc = WIDE ? 4 : 8, kRegs = WIDE ? 16 : 4;
+    typedef int acc_t __attribute__((ext_vector_type(kRegs)));
     probe_v4i av[4], bv[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         av[j] = a[j * 256 + threadIdx.x];
         bv[j] = b[j * 256 + threadIdx.x];
     }
-    probe_v16i acc[4];
+    acc_t acc[kAcc];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < kAcc; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[j][r] = 0;
+        for (int r = 0; r < kRegs; ++r) acc[j][r] = 0;
     for (int it = 0; it < reps; it += 4) {
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(av[j], bv[(j + u) & 3], acc[j], 0, 0, 0);
+            for (int j = 0; j < kAcc; ++j) {
+                const probe_v4i x = av[j & 3], y = bv[(j + u + (j >> 2)) & 3];
+                // (as assembly: around the builtins the compiler copied the accumulators once a turn, a fifth of the rate of the small form)
+                if constexpr (WIDE) asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+v"(acc[j]) : "v"(x), "v"(y));
+                else asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+v"(acc[j]) : "v"(x), "v"(y));
+            }
     }
+#pragma unroll
+    for (int j = 0; j < kAcc; ++j) asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[j]));    // the last results, before they are read
     uint32_t x = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < kAcc; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) x ^= (uint32_t)acc[j][r];
+        for (int r = 0; r < kRegs; ++r) x ^= (uint32_t)acc[j][r];
     if (x == 0x9e3779b9u) sink[threadIdx.x & 63] = x;   // never, but the compiler cannot rule it out
 }
 
@@ -86,12 +94,12 @@ extern "C" int agq_probe_empty(void *stream) {
 }
 
 // `a`, `b`: 16 KiB each (4 x 256 lanes x 16 bytes of int8 operand values, device memory); `workgroups` of 256
-// threads (four wavefronts, one per SIMD of a CU); `reps` (a multiple of four) rounds of four MFMAs per wavefront
-// = 8 x 32^3 x reps operations each.
-extern "C" int agq_probe_mfma_i8(const void *a, const void *b, int workgroups, int reps, void *sink, void *stream) {
+// threads (four wavefronts, one per SIMD of a CU); `reps` (a multiple of four) rounds of 8 x 32^3 operations per wavefront;
+// wide: 32 x 32 x 32 instead of 16 x 16 x 64 MFMAs.
+extern "C" int agq_probe_mfma_i8(const void *a, const void *b, int workgroups, int reps, int wide, void *sink, void *stream) {
     if (!a || !b || !sink || workgroups < 1 || reps < 4 || (reps & 3)) return -1;
-    probe_mfma_kernel<<<(unsigned)workgroups, 256, 0, (hipStream_t)stream>>>((const probe_v4i *)a, (const probe_v4i *)b,
-                                                                            reps, (uint32_t *)sink);
+    const auto kernel = wide ? probe_mfma_kernel<true> : probe_mfma_kernel<false>;
+    kernel<<<(unsigned)workgroups, 256, 0, (hipStream_t)stream>>>((const probe_v4i *)a, (const probe_v4i *)b, reps, (uint32_t *)sink);
     return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
