@@ -41,7 +41,8 @@ int agq_gemm_w4_run(int bits, const void *x, int x_kind, int64_t M, int64_t K, i
         n_sum += projs[p].N;
     }
     if (tiles > kMaxDim) return AGQ_EINVAL;
-    // the tiled kernel's grid: 128 x 128 tiles of all projections
+    // the tiled kernel's grid, counted in 128 x 128 tiles (its tiles go down to 32 x 64: eight times as many at most, which stays
+    // below 2^31 for every output that fits this card's memory)
     if (((M + 127) / 128) * ((n_sum + 127) / 128 + count) > kMaxDim) return AGQ_EINVAL;
     if (M == 0) return AGQ_OK;
     if (!x || !aligned16(x)) return AGQ_EINVAL;

@@ -14,9 +14,9 @@
 //     (16 tokens x 64 k) reads token l & 15, k 16 (l >> 4): four runs of 256 bytes, every run over all banks, so the
 //     sixteen lanes that an LDS cycle serves meet every bank once as they would in one run of 1 KiB.
 //
-// Why this shape.  With all CUs multiplying the chip runs at its power limit, 1.6 to 1.9 GHz, so what counts is energy per
-// product.  16 x 16 x 64 MFMAs keep 4.4-4.7 POP/s on the codes and weights of a layer where 32 x 32 x 32 ones keep
-// 3.2-3.9 (nothing else in the loop; 16 accumulators are read and written per 64 k instead of per 32).  A wavefront that
+// Why this shape.  With all CUs multiplying the chip runs at its power limit, so what counts is energy per product.  Nothing but
+// 16 x 16 x 64 MFMAs on the codes and weights of a layer runs at 2.1 to 2.2 GHz, 4.4-4.6 POP/s, nothing but 32 x 32 x 32 ones at
+// 3.7-4.1 (accumulators are read and written once per 64 k instead of per 32; 4.9 both on zeros); this kernel's loop at 1.6 to 1.9 GHz.  A wavefront that
 // owns all tokens of the tile needs no weight twice, so weights skip LDS, are widened half as often (128 tokens) as by
 // wavefronts of 64 x 64, and a CU loads and reads from LDS a third less.  Against 128 x 128 tiles in 64 x 64 wavefronts with
 // both operands through LDS: 2048 x 11008 -> 4096 74 -> 64 us, 4096 -> 12288 89 -> 74, 4096 -> 22016 155 -> 140;
@@ -51,7 +51,7 @@ struct TiledProj {
 struct TiledArgs {
     TiledProj proj[kMaxProj];   // projections past the last one repeat it, with no tile left for them
     const agq_u4 *xt;    // activation codes in operand order (pre-pass output)
-    int M, K, KT;
+    int M, KT;
     int tiles_m, band;      // token tiles, and how many of them the tile walk takes together
     int whole;              // tiles from here on are dealt out as halves (a multiple of 8)
     int turn;               // two groups: K steps by which a token tile starts further on than the one before it
@@ -568,7 +568,6 @@ int agq_launch_gemm_tiled(const void *x_tiles, int64_t M, int64_t K, int e, int 
     TiledArgs a = {};
     a.xt = (const agq_u4 *)x_tiles;
     a.M = (int)M;
-    a.K = (int)K;
     a.KT = (int)agq_k_tiles(K);
     a.tiles_m = (int)((M + tile_m - 1) / tile_m);
     // The walk takes up to 1024 tokens as one band, so that the weights come from memory once (300 tokens in a band of four

@@ -54,12 +54,12 @@ static inline AgqTripLayout agq_trip_layout(int64_t N, int64_t K, int E) {
 // which stay in the first slice: min_steps of them).  splits == 1: no split, bytes == 0.  (The constants are those of an
 // earlier kernel; they are kept because they decide the sizes that programs reserve.)
 struct AgqSplitPlan {
-    int splits, steps;
+    int splits;
     size_t bytes;
 };
 static inline AgqSplitPlan agq_tiled_split_plan(int64_t M, int64_t tiles_n, int64_t KT, bool may_split, int min_steps = 0) {
     const int64_t tiles = ((M + 127) / 128) * tiles_n;
-    AgqSplitPlan p = {1, (int)KT, 0};
+    AgqSplitPlan p = {1, 0};
     if (!may_split || tiles < 1 || tiles * 2 > 256 || KT < 8) return p;
     const int64_t part_bytes = ((M + 31) / 32) * 32 * tiles_n * 512;   // per split: rows that hold tokens x columns x 4
     int64_t least = KT * 470;
@@ -70,7 +70,6 @@ static inline AgqSplitPlan agq_tiled_split_plan(int64_t M, int64_t tiles_n, int6
         if (cost < least) {
             least = cost;
             p.splits = (int)s;
-            p.steps = (int)steps;
         }
     }
     if (p.splits > 1) p.bytes = (size_t)tiles * p.splits * (128 * 128 * 4);
@@ -95,8 +94,9 @@ struct AgqTiledChoice {
 
 // Time of a launch of w workgroups of one shape, KT steps, N output channels in all, in ns, fitted to 600 calls (17 to 2048
 // tokens, K 128 to 13824, N 512 to 27648; codes in, other weights from memory at every launch, graph replays): the error is 4 %
-// in the median where a shape is near the best one (10 % of them are off by more than 10 %), and the choice below was 1.2 %
-// slower on average than the best of all shapes, 4 % at the ninth decile, 17 % at most.
+// in the median where a shape is near the best one (10 % of them are off by more than 10 %).  On 650 other calls of 128 to 2048
+// tokens, half of them with a K up to 1024, the choice below was 1.1 % slower than the best of all shapes on average, 4 % at the ninth
+// decile, 14 % at most; calls that take a K split are apart, see there.
 //   fixed  launch, fill and epilogue      step   a step of a lone workgroup on an empty chip      load   what a full chip adds
 //   many   a step where CUs have several  more   what each further round of workgroups adds       mem    weights, per 16384 channels
 //   ceil64 how far the last round counts as a whole one
@@ -168,9 +168,12 @@ static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int cou
     AgqTiledPick best = {{TILED_128, 8, 4, 1, 1, (int)KT}, INT64_MAX};
     // A K split for long K with few tiles: 64 x 64 tiles while four slices of them fit the CUs, else (narrow layers alone) 64 x 128
     // ones, at most four slices (more only add partial tiles to write and read).  Measured against the best tile without: 20 x 11008
-    // -> 4096 12.8 against 15.8 us, 64 x 11008 -> 4096 13.7 / 13.9, 300 x 13824 -> 640 11.1 / 13.2; behind at the rule's edges, 300 x
-    // 8192 -> 384 8.8 / 8.3, 1050 x 8192 -> 512 13.2 / 12.3, 300 x 4096 -> 768 8.9 / 6.9, 260 x 2560 -> 130 6.5 / 5.7.  100 x 11008 ->
-    // 4096, whose slices do not fit, 16.2 / 13.7.  (Eight slices of 128 x 128 tiles: 15.1, 17.3, 13.7, 10.9 us for the first four.)
+    // -> 4096 12.8 against 15.8 us, 64 x 11008 -> 4096 13.7 / 13.9, 300 x 13824 -> 640 11.1 / 13.2.  100 x 11008 -> 4096, whose slices do
+    // not fit, 16.2 / 13.7.  (Eight slices of 128 x 128 tiles: 15.1, 17.3, 13.7, 10.9 us for the first four.)
+    // The rule does not compare the two.  Over 68 calls that take the split it was level with the best tile on average, up to a fifth
+    // ahead for a K of 8192 and more, but a tenth to a quarter behind where the slices are short, a K of 2560 to 5120: 350 x 2560 -> 496
+    // 10.2 / 8.2; with the pre-pass 200 x 13824 -> 640 15.0 / 18.3, 333 x 4096 -> 768 12.9 / 10.4, 512 x 5120 -> 768 15.2 / 12.5, 512 x 8192 ->
+    // 1024 19.7 / 16.4.  (Tests hold some such calls to the split.)
     if (plan.splits > 1 && KT - n_extra >= 20 && 2 * KT >= 3 * tiles &&
         (n_sum <= 1024 || workgroups(4, 1) * (plan.splits < 4 ? plan.splits : 4) <= 256)) {
         const int s = plan.splits < 4 ? plan.splits : 4;
