@@ -211,26 +211,28 @@ static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int cou
 // workgroup (grid.y row groups): every row group reads the weights again (from L2 after the first).  The other path is the
 // layout pre-pass plus the tiled kernel (above).  Both sides measured on 2600 calls of 17 to 256 rows (K 128 to 13824, N 32 to
 // 42000 in up to three projections, other weights from memory at every launch, graph replays):
-//   row groups   about 3 us + 89 ns a K step while every workgroup has a CU of its own;
-//                beyond, 3 us + 200 ns and 126 ns a K step for every round of 256, the second and third of which count whole
+//   row groups   about 3 us + 89 ns a K step while every workgroup has a CU of its own; for each of two or three rounds of 256 112 ns
+//                a K step up to 32 of them, 3.5 us + 50 ns beyond (a wavefront then holds four chunks at a time); from
+//                three rounds on 200 ns + 126 ns a K step for every 256 workgroups
 //   tiles        the launch below + 2.1 us + 1.6 ns per 1024 values for the pre-pass
-// The rule takes 0.6 us for what the fixed parts differ by.  Its calls are 0.6 % slower on average than the faster side of each,
-// 18 % at the 99th percentile; past three rounds with a K of 1280 to 1700 the worst of them 1.5 times (45 x 1408 -> 8600 11.2 / 7.2 us).
+// The rule takes 0.3 us for what the fixed parts differ by.  Its calls are 0.6 % slower on average than the faster side of each,
+// 17 % at the 99th percentile; past three rounds with a K of 1280 to 1700 the worst of them 1.5 times (45 x 1408 -> 8600 11.2 / 7.2 us).
 // Row groups / tiles: 30 x 11136 -> 3040 12.6 / 15.2 us, 139 x 10880 -> 400 11.0 / 12.9, 768 x 768 at 128 rows 4.1 / 6.5; 200 x 1536 ->
-// 3 x 1536 13.4 / 8.1, 80 x 2560 -> 6912 18.0 / 10.1, 256 x 1280 -> 4100 15.1 / 8.3.
-// Up to 80 rows, below three rounds, row groups go on for 5.5 us longer from 32 steps on: tests hold three calls of that region
+// 3 x 1536 13.4 / 8.1, 80 x 2560 -> 6912 18.0 / 10.1, 256 x 1280 -> 4100 15.1 / 8.3; 256 x 4096 -> 768 9.4 / 10.6 (a K split).
+// Up to 80 rows, below three rounds, row groups go on for 3.6 us longer from 25 to 32 steps: tests hold three calls of that region
 // to them (4096 x 4096 at 64 and 80 rows 10.3 / 9.9 and 13.7 / 10.1, 4096 -> 11008 at 32 rows 13.4 / 11.5).
 // (Inside a block the operator in front writes the codes and there is no pre-pass; the same rule is asked there.)
-// wgs: groups of sixteen rows times tile pairs (32 channels) of all projections; tiles: what the call would run instead.  (Four tiles per workgroup instead
-// of two were measured too: the same at best, and 50 % slower on the widest layer, where the registers no longer hold the
-// weight chunks.)
+// wgs: groups of sixteen rows times tile pairs (32 channels) of all projections; tiles: what the call would run instead.
+// (Four tiles per workgroup instead of two were measured too: the same at best, and 50 % slower on the widest layer, where the
+// registers no longer hold the weight chunks.)
 #define AGQ_ROW_GROUP_MAX_M 256
 static inline int64_t agq_row_groups_ns(int64_t wgs, int64_t KT) {
-    const int64_t whole = wgs < 768 ? (wgs + 255) / 256 * 256 : wgs;
-    return wgs <= 256 ? 89 * KT : whole * (200 + 126 * KT) / 256;
+    if (wgs <= 256) return 89 * KT;
+    if (wgs < 768) return (wgs + 255) / 256 * (KT <= 32 ? 112 * KT : 3500 + 50 * KT);
+    return wgs * (200 + 126 * KT) / 256;
 }
 static inline bool agq_decode_row_groups(int64_t M, int64_t KT, int64_t wgs, const AgqTiledPick &tiles) {
-    const int64_t more = tiles.choice.variant == TILED_SPLIT ? 0 : (KT >= 32 && M <= 80 && wgs < 768 ? 5500 : 600);
+    const int64_t more = tiles.choice.variant == TILED_SPLIT ? 0 : (KT > 24 && KT <= 32 && M <= 80 && wgs < 768 ? 3600 : 300);
     return agq_row_groups_ns(wgs, KT) <= tiles.ns + more;
 }
 
@@ -258,7 +260,7 @@ static inline AgqRoute agq_gemm_route(int x_kind, int64_t M, int64_t K, const in
     wgs *= (M + 15) / 16;
     const int extra = n_extra > 0 ? n_extra : 0;
     const int64_t KT = agq_k_tiles(K) + extra;
-    if (may_stream && agq_row_groups_ns(wgs, KT) <= agq_tiled_least_ns() + 600) return {false, {}};
+    if (may_stream && agq_row_groups_ns(wgs, KT) <= agq_tiled_least_ns() + 300) return {false, {}};
     // With few tiles and a long K the tiled kernel splits the tiles' K steps over workgroups, if the
     // caller's workspace has the room for the partial tiles behind the codes.
     AgqSplitPlan plan = agq_tiled_split_plan(M, tiles_n, KT, true, extra);
