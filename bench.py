@@ -47,7 +47,7 @@ PREFILL_M = 2048
 MEASURED_TRAFFIC = {
     "decode": (26.3e6, "profiles/gemm_decode_llama7b_sweep.md", "agq_gemm_decode.hip", "b749db6894b5"),
     "attn": (252.6e6, "profiles/log2_attn_llama13b_block.md", "agq_attn.hip", "e21c65f1ff1e"),
-    "tiled": (186.2e6, "profiles/gemm_decode_llama7b_sweep.md", "agq_gemm_tiled.hip", "6400ab5116c3"),
+    "tiled": (186.2e6, "profiles/gemm_decode_llama7b_sweep.md", "agq_gemm_tiled.hip", "c80578732a47"),
 }
 
 

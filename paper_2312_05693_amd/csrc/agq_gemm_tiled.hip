@@ -570,13 +570,9 @@ int agq_launch_gemm_tiled(const void *x_tiles, int64_t M, int64_t K, int e, int 
     a.M = (int)M;
     a.KT = (int)agq_k_tiles(K);
     a.tiles_m = (int)((M + tile_m - 1) / tile_m);
-    // The walk takes up to 1024 tokens as one band, so that the weights come from memory once (300 tokens in a band of four
-    // 64-token tiles and one of one: 4096 -> 22016 33 -> 31 us); beyond, and from six 128-token tiles on, five at a time, a compact
-    // rectangle for every XCD.  (Four, or eight: strides that are powers of two meet in fewer memory channels; 2048 x 4096 ->
-    // 22016 130.7 and 128 -> 126 us, 2048 x 5120 -> 15360 113 and 114 -> 108, level at 1000 tokens.)
-    const int most = 1024 / tile_m;
-    a.band = a.tiles_m <= most ? a.tiles_m : most / 2;
-    if (choice.nt == 8 && a.tiles_m > 5) a.band = 5;
+    int64_t n_sum = 0;
+    for (int p = 0; p < count; ++p) n_sum += projs[p].N;
+    a.band = agq_tiled_band(M, n_sum, choice.nt, choice.kg);
     a.scale_e = ldexpf(1.0f, e);
     a.corr = corr;
     int tiles = 0;
@@ -609,8 +605,6 @@ int agq_launch_gemm_tiled(const void *x_tiles, int64_t M, int64_t K, int e, int 
         // per XCD) stays in an XCD's L2.  300 x 11008 -> 4096 27.5 -> 22.2 us, 213 tokens 20.6 -> 18.1, 100 tokens 16.2 -> 14.8, 333 x 5120 -> 5120
         // 15.8 -> 14.3, 333 x 13824 -> 5120 33.3 -> 31; level where K is 4096.  (One group gains less, 128-token tiles lose: more than
         // five of them, and L2 does not hold what lies between; 1024 x 13824 -> 5120 56.5 -> 58.2.)
-        int64_t n_sum = 0;
-        for (int p = 0; p < count; ++p) n_sum += projs[p].N;
         const int64_t steps = a.KT / 2, apart = a.tiles_m - 1;
         int64_t turn = steps / a.tiles_m;
         if (turn > 2500000 / (16 * n_sum * apart)) turn = 2500000 / (16 * n_sum * apart);

@@ -236,6 +236,25 @@ static inline bool agq_decode_row_groups(int64_t M, int64_t KT, int64_t wgs, con
     return agq_row_groups_ns(wgs, KT) <= tiles.ns + more;
 }
 
+// Token tiles that the tiled kernel's walk takes together, column by column (a band).  An XCD's run of the walk reads the codes of
+// its token tiles and the weights of its columns, so the band says which of the two all eight XCDs read.
+//   Tiles of 64 and 32 tokens: up to 1024 tokens in one band, so that the weights come from memory once (300 tokens in a band of four
+// tiles and one of one: 4096 -> 22016 33 -> 31 us); layers up to twice as wide as there are tokens tile by tile, and up to ten times as wide
+// (two groups: four) in pairs of tiles, so that the codes are read once.  One band for all of them, as it was, against one or two tiles (600
+// calls of 150 to 2048 tokens): two groups 7 % and 4 % slower on average, at most 17 %, one group 4 % and 1 %, a K split 3 % and 1 %; 800 x
+// 4096 -> 1000 14.5 -> 12.2 us, 986 x 3456 -> 1072 15.4 -> 13.0, 600 x 3072 -> 1536 11.7 -> 11.0.  Wider layers lose: tile by tile 5 %
+// from ten times on, two groups in pairs where their token tiles start apart in K for each other (512 x 11008 -> 4096 31.3 -> 35.6).
+//   Tiles of 128 tokens: five at a time from six on, a compact rectangle for every XCD.  (Four, or eight: strides that are powers of two
+// meet in fewer memory channels; 2048 x 4096 -> 22016 130.7 and 128 -> 126 us, 2048 x 5120 -> 15360 113 and 114 -> 108, level at
+// 1000 tokens.)
+static inline int agq_tiled_band(int64_t M, int64_t n_sum, int nt, int kg) {
+    const int64_t tiles_m = (M + nt * 16 - 1) / (nt * 16), most = 64 / nt;
+    if (nt == 8) return (int)(tiles_m > 5 ? 5 : tiles_m);
+    if (n_sum < 2 * M) return 1;
+    if (n_sum < (kg == 2 ? 4 : 10) * M) return 2;
+    return (int)(tiles_m <= most ? tiles_m : most / 2);
+}
+
 // int8 codes in operand order, tokens padded to the 128-row tile (a multiple of 16 KiB); K: extra steps included
 static inline size_t agq_codes_bytes(int64_t M, int64_t K) { return (size_t)((M + 127) / 128) * 128 * (size_t)K; }
 

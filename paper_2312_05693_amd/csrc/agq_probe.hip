@@ -118,6 +118,9 @@ extern "C" int agq_probe_gemm_tile(int x_kind, int64_t M, int64_t K, const int64
     return (r.choice.variant == TILED_SPLIT ? 1000 * r.choice.splits : 0) + 100 * r.choice.nt + 10 * r.choice.jt + r.choice.kg;
 }
 
+// Host only: token tiles that the walk over tiles of 16 nt tokens, kg groups, takes together, for M tokens and n_sum channels in all.
+extern "C" int agq_probe_tiled_band(int64_t M, int64_t n_sum, int nt, int kg) { return agq_tiled_band(M, n_sum, nt, kg); }
+
 // Host only: nanoseconds that the host takes for that choice, fp16 input on plain blobs, on average over `reps` of them.
 extern "C" double agq_probe_gemm_route_ns(int64_t M, int64_t K, const int64_t *N, int count, size_t workspace_bytes, int reps) {
     const auto t0 = std::chrono::steady_clock::now();
