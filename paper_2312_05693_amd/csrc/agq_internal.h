@@ -103,7 +103,7 @@ struct AgqTiledChoice {
 struct AgqTiledTime {
     int nt, jt, kg, fixed, step, load, many, more, mem, ceil64;
 };
-static constexpr AgqTiledTime agq_tiled_times[] = {
+static const AgqTiledTime agq_tiled_times[] = {
     {8, 4, 1, 6851, 427, 232, 637, 2355, 23, 38},
     {8, 3, 1, 6080, 346, 127, 460, 2382, 80, 39},
     {8, 2, 1, 4768, 265, 78, 334, 2130, 95, 32},
@@ -127,12 +127,6 @@ static inline int64_t agq_tiled_ns(const AgqTiledTime &t, int64_t w, int64_t KT,
     const int64_t n = (w + 255) >> 8, halves = 2 * n - (t.nt == 8 && t.jt == 4 && agq_tiled_halves(w) > 0);
     const int64_t several = t.fixed + (n - 1) * t.more + KT * ((t.many * (halves * 128 * t.ceil64 + (64 - t.ceil64) * w) >> 14) + mem);
     return several > one ? several : one;
-}
-static constexpr int agq_tiled_least_ns() {
-    int least = agq_tiled_times[0].fixed;
-    for (const AgqTiledTime &t : agq_tiled_times)
-        if (t.fixed < least) least = t.fixed;
-    return least;
 }
 // Workgroups of a call for every tile, counted once for the table: divisions for every shape and projection were half of the host's time.
 struct AgqTileCounts {
@@ -215,8 +209,10 @@ static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int cou
 //                a K step up to 32 of them, 3.5 us + 50 ns beyond (a wavefront then holds four chunks at a time); from
 //                three rounds on 200 ns + 126 ns a K step for every 256 workgroups
 //   tiles        the launch below + 2.1 us + 1.6 ns per 1024 values for the pre-pass
-// The rule takes 0.3 us for what the fixed parts differ by.  Its calls are 0.6 % slower on average than the faster side of each,
-// 17 % at the 99th percentile; past three rounds with a K of 1280 to 1700 the worst of them 1.5 times (45 x 1408 -> 8600 11.2 / 7.2 us).
+// A program that makes its calls one after the other waits for the host, 4.4 us for the one launch of row groups and 8.3 us for
+// the two of the tiles (graph replays do not), so row groups of up to 8.6 us are taken whatever the tiles would take.  The others are
+// compared.  In graph replays the rule's calls are 0.7 % slower on average than the faster side of each, 20 % at the 99th percentile; with the
+// host's share 0.3 %.  Past three rounds with a K of 1280 to 1700 the worst of them 1.5 times (45 x 1408 -> 8600 11.2 / 7.2 us).
 // Row groups / tiles: 30 x 11136 -> 3040 12.6 / 15.2 us, 139 x 10880 -> 400 11.0 / 12.9, 768 x 768 at 128 rows 4.1 / 6.5; 200 x 1536 ->
 // 3 x 1536 13.4 / 8.1, 80 x 2560 -> 6912 18.0 / 10.1, 256 x 1280 -> 4100 15.1 / 8.3; 256 x 4096 -> 768 9.4 / 10.6 (a K split).
 // Up to 80 rows, below three rounds, row groups go on for 3.6 us longer from 25 to 32 steps: tests hold three calls of that region
@@ -232,8 +228,8 @@ static inline int64_t agq_row_groups_ns(int64_t wgs, int64_t KT) {
     return wgs * (200 + 126 * KT) / 256;
 }
 static inline bool agq_decode_row_groups(int64_t M, int64_t KT, int64_t wgs, const AgqTiledPick &tiles) {
-    const int64_t more = tiles.choice.variant == TILED_SPLIT ? 0 : (KT > 24 && KT <= 32 && M <= 80 && wgs < 768 ? 3600 : 300);
-    return agq_row_groups_ns(wgs, KT) <= tiles.ns + more;
+    const bool on = KT > 24 && KT <= 32 && M <= 80 && wgs < 768 && tiles.choice.variant != TILED_SPLIT;
+    return agq_row_groups_ns(wgs, KT) <= tiles.ns + (on ? 3600 : 0);
 }
 
 // Token tiles that the tiled kernel's walk takes together, column by column (a band).  An XCD's run of the walk reads the codes of
@@ -266,8 +262,8 @@ struct AgqRoute {
 };
 static inline AgqRoute agq_gemm_route(int x_kind, int64_t M, int64_t K, const int64_t *N, int count, int n_extra,
                                       size_t workspace_bytes) {
-    // The calls whose launches are shortest do not look at the tiles: up to sixteen rows have no other kernel, and row groups that
-    // take no longer than the shortest launch of any tile (which the split's second launch is on top of) need no comparison.
+    // The calls whose launches are shortest do not look at the tiles: up to sixteen rows have no other kernel, and for row groups of
+    // up to 8.6 us (3 us besides the time below) the host's second launch decides.
     // The host's time for a choice: 1 x 4096 -> 4096 62 -> 2 ns, 128 x 768 -> 768 66 -> 4, 2048 x 4096 -> 3 x 4096 112 -> 65.
     if (M <= AGQ_DECODE_MAX_M) return {false, {}};
     const bool may_stream = x_kind == 0 && n_extra < 0 && M <= AGQ_ROW_GROUP_MAX_M;
@@ -279,7 +275,7 @@ static inline AgqRoute agq_gemm_route(int x_kind, int64_t M, int64_t K, const in
     wgs *= (M + 15) / 16;
     const int extra = n_extra > 0 ? n_extra : 0;
     const int64_t KT = agq_k_tiles(K) + extra;
-    if (may_stream && agq_row_groups_ns(wgs, KT) <= agq_tiled_least_ns() + 300) return {false, {}};
+    if (may_stream && agq_row_groups_ns(wgs, KT) <= 5600) return {false, {}};
     // With few tiles and a long K the tiled kernel splits the tiles' K steps over workgroups, if the
     // caller's workspace has the room for the partial tiles behind the codes.
     AgqSplitPlan plan = agq_tiled_split_plan(M, tiles_n, KT, true, extra);
