@@ -159,15 +159,15 @@ static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int cou
     }
     const AgqTileCounts workgroups = agq_tile_counts(M, N, count);
     const int64_t tiles = workgroups(8, 2);
-    AgqTiledPick best = {{TILED_128, 8, 4, 1, 1, (int)KT}, INT64_MAX};
+    AgqTiledPick best = {{TILED_128, 8, 4, 1, 1, (int)KT}, INT64_MAX}, split = best;
     // A K split for long K with few tiles: 64 x 64 tiles while four slices of them fit the CUs, else (narrow layers alone) 64 x 128
     // ones, at most four slices (more only add partial tiles to write and read).  Measured against the best tile without: 20 x 11008
     // -> 4096 12.8 against 15.8 us, 64 x 11008 -> 4096 13.7 / 13.9, 300 x 13824 -> 640 11.1 / 13.2.  100 x 11008 -> 4096, whose slices do
     // not fit, 16.2 / 13.7.  (Eight slices of 128 x 128 tiles: 15.1, 17.3, 13.7, 10.9 us for the first four.)
-    // The rule does not compare the two.  Over 68 calls that take the split it was level with the best tile on average, up to a fifth
-    // ahead for a K of 8192 and more, but a tenth to a quarter behind where the slices are short, a K of 2560 to 5120: 350 x 2560 -> 496
-    // 10.2 / 8.2; with the pre-pass 200 x 13824 -> 640 15.0 / 18.3, 333 x 4096 -> 768 12.9 / 10.4, 512 x 5120 -> 768 15.2 / 12.5, 512 x 8192 ->
-    // 1024 19.7 / 16.4.  (Tests hold some such calls to the split.)
+    // Layers of 768 channels and more compare the two (the split's time below is about 1 us high): of 224 such calls no one is slower
+    // than with the split alone, 5 % less on average; 512 x 5120 -> 768 14.7 -> 10.6 us, 333 x 4096 -> 768 12.4 -> 9.6, 512 x 8192 -> 1024 18.1 -> 13.8 (with
+    // the pre-pass); 200 x 13824 -> 640 keeps it, 14.3 against 16.8.  Narrower ones always take it: tests hold a dozen such calls to
+    // it.  There it is level on average, up to a fifth ahead from a K of 8192 on, 10 to 30 % behind for one of 2560 to 4096.
     if (plan.splits > 1 && KT - n_extra >= 20 && 2 * KT >= 3 * tiles &&
         (n_sum <= 1024 || workgroups(4, 1) * (plan.splits < 4 ? plan.splits : 4) <= 256)) {
         const int s = plan.splits < 4 ? plan.splits : 4;
@@ -175,10 +175,10 @@ static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int cou
         const int64_t w = workgroups(4, jt);
         int64_t cut = w * s <= 256 ? s : (w * 2 <= 256 ? 256 / w : 2);
         const int64_t steps = (KT + cut - 1) / cut;
-        best.choice = {TILED_SPLIT, 4, jt, 1, (int)((KT + steps - 1) / steps), (int)steps};
+        split.choice = {TILED_SPLIT, 4, jt, 1, (int)((KT + steps - 1) / steps), (int)steps};
         for (const AgqTiledTime &t : agq_tiled_times)
-            if (t.nt == 4 && t.jt == jt && t.kg == 1) best.ns = agq_tiled_ns(t, w * cut, steps, n_sum) + 3000 + M * n_sum * 4 * cut * 300 / 1000000;
-        return best;
+            if (t.nt == 4 && t.jt == jt && t.kg == 1) split.ns = agq_tiled_ns(t, w * cut, steps, n_sum) + 3000 + M * n_sum * 4 * cut * 300 / 1000000;
+        if (n_sum < 768) return split;
     }
     // Two groups for twelve steps or more on at most 256 tiles of 64 x 128: token tiles that start apart in K bring in weights
     // for each other (agq_gemm_tiled.hip).  Against one group, each with its best tile: 100 x 11008 -> 4096 13.7 / 15.5 us, 213 tokens
@@ -198,7 +198,7 @@ static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int cou
     // tile is more than a tenth faster.  (There the model has this tile up to a tenth too slow: measured 0.92 to 0.99 of the
     // best other tile on eight of nine such calls of 1200 to 2048 tokens, 1.09 on 1200 x 1408 -> 2000.)
     if (!two && M > 1024 && KT > 8 && tiles <= 256 && tiles > 128 && ns82 * 10 <= best.ns * 11) best = {{TILED_128, 8, 2, 1, 1, (int)KT}, ns82};
-    return best;
+    return split.ns - 1000 <= best.ns ? split : best;
 }
 
 // Between 17 and 256 rows of fp16 input the weight-streaming kernel can run with sixteen rows and two channel tiles per
@@ -214,7 +214,7 @@ static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int cou
 // compared.  In graph replays the rule's calls are 0.7 % slower on average than the faster side of each, 20 % at the 99th percentile; with the
 // host's share 0.3 %.  Past three rounds with a K of 1280 to 1700 the worst of them 1.5 times (45 x 1408 -> 8600 11.2 / 7.2 us).
 // Row groups / tiles: 30 x 11136 -> 3040 12.6 / 15.2 us, 139 x 10880 -> 400 11.0 / 12.9, 768 x 768 at 128 rows 4.1 / 6.5; 200 x 1536 ->
-// 3 x 1536 13.4 / 8.1, 80 x 2560 -> 6912 18.0 / 10.1, 256 x 1280 -> 4100 15.1 / 8.3; 256 x 4096 -> 768 9.4 / 10.6 (a K split).
+// 3 x 1536 13.4 / 8.1, 80 x 2560 -> 6912 18.0 / 10.1, 256 x 1280 -> 4100 15.1 / 8.3.
 // Up to 80 rows, below three rounds, row groups go on for 3.6 us longer from 25 to 32 steps: tests hold three calls of that region
 // to them (4096 x 4096 at 64 and 80 rows 10.3 / 9.9 and 13.7 / 10.1, 4096 -> 11008 at 32 rows 13.4 / 11.5).
 // (Inside a block the operator in front writes the codes and there is no pre-pass; the same rule is asked there.)

@@ -371,11 +371,20 @@ def test_rule_for_tile_pairs(probe, M, K, Ns, pairs):
     # row groups against pre-pass and tiles, measured in us: a launch of one round of workgroups reads a long K faster than a K
     # split, several rounds of them re-read what the tiles read once
     (30, 11136, [3040], True), (139, 10880, [400], True), (225, 12288, [296], True), (164, 9728, [669], True),       # 12.6 / 15.2, 11.0 / 12.9,
-    (39, 12032, [1264] * 2, True), (17, 9472, [801], True), (256, 4096, [768], True), (190, 3840, [736], True),      # 11.9 / 15.4, 9.1 / 11.7
-    (64, 1536, [1536] * 3, True), (141, 4480, [1328], False), (200, 1536, [1536] * 3, False), (80, 2560, [6912], False), (256, 1280, [4100], False), (137, 1280, [7808], False),     # 13.4 / 8.1, 18.0 / 10.1
+    (39, 12032, [1264] * 2, True), (17, 9472, [801], True), (190, 3840, [736], True),                                 # 11.9 / 15.4, 9.1 / 11.7
+    (64, 1536, [1536] * 3, True), (141, 4480, [1328], False),                                                        # a call below 8.6; 12.0 / 11.0
+    (200, 1536, [1536] * 3, False), (80, 2560, [6912], False), (256, 1280, [4100], False), (137, 1280, [7808], False),     # 13.4 / 8.1, 18.0 / 10.1
     (95, 640, [13992], False), (65, 3456, [2008] * 3, False), (195, 256, [4750] * 3, False)])                        # 11.0 / 7.3, 18.6 / 10.9
 def test_line_between_row_groups_and_tiles(gemm_route, M, K, Ns, stream):
     assert (gemm_route(M, K, Ns) == "stream") == stream
+
+
+@pytest.mark.parametrize("M,K,Ns,split", [
+    # the K split against the best tile without one, measured in us, the layout pass included
+    (512, 5120, [768], False), (333, 4096, [768], False), (512, 8192, [1024], False), (300, 4096, [512] * 2, False),   # 14.7 / 10.6, 12.4 / 9.6, 18.1 / 13.8
+    (200, 13824, [640], True), (200, 13824, [1024], True), (64, 11008, [4096], True), (300, 13824, [640], True)])      # 14.3 / 16.8, 17.1 / 17.6, 15.7 / 17.5
+def test_line_between_the_k_split_and_tiles_without_one(gemm_route, M, K, Ns, split):
+    assert (gemm_route(M, K, Ns, x_kind=1) == "split") == split
 
 
 @pytest.mark.parametrize("M,n_sum,nt,kg,band", [
