@@ -165,7 +165,7 @@ static inline AgqTiledPick agq_tiled_choose(int64_t M, const int64_t *N, int cou
     // -> 4096 12.8 against 15.8 us, 64 x 11008 -> 4096 13.7 / 13.9, 300 x 13824 -> 640 11.1 / 13.2.  100 x 11008 -> 4096, whose slices do
     // not fit, 16.2 / 13.7.  (Eight slices of 128 x 128 tiles: 15.1, 17.3, 13.7, 10.9 us for the first four.)
     // Layers of 768 channels and more compare the two (the split's time below is about 1 us high): of 224 such calls no one is slower
-    // than with the split alone, 5 % less on average; 512 x 5120 -> 768 14.7 -> 10.6 us, 333 x 4096 -> 768 12.4 -> 9.6, 512 x 8192 -> 1024 18.1 -> 13.8 (with
+    // than with the split alone, 4 % less on average; 512 x 5120 -> 768 14.7 -> 10.6 us, 333 x 4096 -> 768 12.4 -> 9.6, 512 x 8192 -> 1024 18.1 -> 13.8 (with
     // the pre-pass); 200 x 13824 -> 640 keeps it, 14.3 against 16.8.  Narrower ones always take it: tests hold a dozen such calls to
     // it.  There it is level on average, up to a fifth ahead from a K of 8192 on, 10 to 30 % behind for one of 2560 to 4096.
     if (plan.splits > 1 && KT - n_extra >= 20 && 2 * KT >= 3 * tiles &&
